@@ -511,8 +511,7 @@ struct Work {
   uint8_t* mark = nullptr;
   unsigned long long* rest_bits = nullptr;
   unsigned long long* sep_count = nullptr;   // separated pairs (ranking and score criteria)
-  unsigned long long* sort_key = nullptr;    // device-wide sort of the ranked list
-  int32_t* sort_ext = nullptr;
+  SortRecs sort[2] = {};                      // device-wide sort of the ranked list
   void* hot_part = nullptr;                  // two-pass walk step: per-row pass-1 sums
   RunScalars* sc = nullptr;
 };
@@ -884,7 +883,7 @@ int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T) {
 
 // small_m: the active set is known to hold at most kSmallActive nodes, so one
 // workgroup runs the whole of converged().
-int enqueue_select(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
+int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, bool small_m) {
   const int ts = T.start(T_SELECT, s);
   if (run.criterion == KATZ_SCORE) {
     KATZ_HIP(launch_score_check(sel_args(run, r), s));
@@ -916,8 +915,18 @@ int enqueue_select(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
   } else {
     const SelArgs sa = sel_args(run, r);
     const bool large = run.k > kMaxK;
-    KATZ_HIP(launch_select_iteration(sa, run.grid, s, large ? run.w->sort_key : nullptr,
-                                     large ? run.w->sort_ext : nullptr));
+    // Every node ranked (k = n): nothing to select, the list is every node.
+    if (!large || run.k < run.n) KATZ_HIP(launch_select_iteration(sa, run.grid, s, !large));
+    if (large) {
+      // The flag comes back before the sort's launches (10 and more, 5 to 13 us
+      // each at 5e5 records) are known to be needed: one read-back of about
+      // 20 us per iteration, where the last iteration or two need the sort.
+      KATZ_HIP(launch_large_test(sa, run.w->sort, s));
+      KATZ_HIP(hipMemcpyAsync(hs.sc, run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+      KATZ_HIP(hipStreamSynchronize(s));
+      if (!hs.sc->err && !hs.sc->done && hs.sc->need) KATZ_HIP(launch_large_sort(sa, run.w->sort, s));
+      KATZ_HIP(launch_large_finish(sa, s));
+    }
   }
   T.stop(ts, s);
   run.cur ^= 1;
@@ -941,11 +950,11 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
     const Range range("katz iteration", r);
     const bool small_m = m_known <= kSmallActive;
     if (pass == 0 && check_first) {
-      KATZ_TRY(enqueue_select(run, r - 1, s, T, false));
+      KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, false));
     } else if (r <= run.max_iter) {
       if (run.st) KATZ_TRY(ensure_levels(run.st, r));
       KATZ_TRY(enqueue_walk(run, r, s, T));
-      KATZ_TRY(enqueue_select(run, r, s, T, small_m));
+      KATZ_TRY(enqueue_select(run, hs, r, s, T, small_m));
       ++r;
     } else {
       break;
@@ -991,7 +1000,7 @@ int write_result(Run& run, HostSync& hs, katz_result* out, int32_t* stage_ids, d
   if (!ids || !lo || !up) return KATZ_E_INVALID_ARG;
   const int tr = T.start(T_RESULT, s);
   // Score criterion: the output is every node in ranking order.
-  if (run.criterion == KATZ_SCORE) KATZ_HIP(launch_score_output(fa, run.w->sort_key, run.w->sort_ext, s));
+  if (run.criterion == KATZ_SCORE) KATZ_HIP(launch_score_output(fa, run.w->sort, s));
   KATZ_HIP(hipMemsetAsync(run.w->mark, 0, (size_t)run.n, s));
   KATZ_HIP(hipMemsetAsync(run.w->rest_bits, 0, sizeof(unsigned long long), s));
   KATZ_HIP(launch_write_result(fa, run.w->mark, ids, lo, up, run.w->rest_bits, run.grid, s));
@@ -1124,8 +1133,9 @@ void layout(Arena& ar, const Plan& pl, Bins& b, Work& w, Staging& stg) {
     w.rest_bits = ar.take<unsigned long long>(1);
     w.sep_count = ar.take<unsigned long long>(1);
     if (pl.sort_n) {
-      w.sort_key = ar.take<unsigned long long>(pl.sort_n);
-      w.sort_ext = ar.take<int32_t>(pl.sort_n);
+      w.sort[0].key = ar.take<unsigned long long>(pl.sort_n);
+      w.sort[0].ext = ar.take<int32_t>(pl.sort_n);
+      w.sort[1] = SortRecs{w.cand_key[0], w.cand_v[0]};   // the selection's, which is over by then
     }
   }
   if (pl.solve_vectors) {

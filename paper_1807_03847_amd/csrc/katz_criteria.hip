@@ -14,15 +14,18 @@
 //     {w, v} with l(w) > u(v) or l(v) > u(w); with the lower bounds sorted
 //     descending, node v contributes the number of lower bounds above u(v).
 //
-// The device-wide sort is a bitonic network in its direction-free form: for
-// every block size s = 2, 4, ..., P (P the power of two >= count) first the
-// mirrored pairs (i, i ^ (s - 1)) and then the half-cleaner pairs (i, i + d),
-// d = s/4, ..., 1, each compare-exchange putting the smaller record at the
-// lower index.  Indices at or past `count` hold virtual +infinity records:
-// every pair that reaches one is already in order, so those pairs are skipped
-// and no padding is stored.  Pairs inside a 2048-record tile run in LDS (one
-// launch covers every stage up to s = 2048, and one launch the strides below
-// 2048 of each later stage); longer strides run one global pass each.
+// The device-wide sort is a merge sort on (key, caller id): 2048-record tiles
+// are sorted in LDS by one launch, then each launch merges pairs of sorted runs
+// (lk_merge).  What bounds it is launches, not bytes (12 B per record): a sort
+// of 5e5 records is 9 launches of 8 to 13 us, where a bitonic network took 45.
+//
+// The test comes before the sort.  A pair (x, y) of the list with l(x) >= l(y)
+// and u(y) - eps >= l(x) fails the test of converged() whether or not other
+// nodes lie between the two: y's predecessor p has l(p) <= l(x), so (p, y)
+// fails as well.  lk_test sorts each 2048-record tile of the (unsorted) list
+// and tests its adjacent pairs; while some tile fails, which is every iteration
+// but the last one or two (a renumbered list holds nodes of like degree side by
+// side), the device-wide sort is not launched.
 #include <climits>
 #include <cstdint>
 
@@ -44,7 +47,7 @@ __device__ __forceinline__ bool rec_less(unsigned long long ka, int ea, unsigned
   return ka < kb || (ka == kb && ea < eb);
 }
 
-__device__ __forceinline__ void cmp_swap(unsigned long long* key, int32_t* ext, long long i, long long j) {
+__device__ __forceinline__ void cmp_swap(unsigned long long* key, int32_t* ext, uint16_t* slot, int i, int j) {
   const unsigned long long ki = key[i], kj = key[j];
   const int ei = ext[i], ej = ext[j];
   if (rec_less(kj, ej, ki, ei)) {
@@ -52,46 +55,119 @@ __device__ __forceinline__ void cmp_swap(unsigned long long* key, int32_t* ext, 
     key[j] = ki;
     ext[i] = ej;
     ext[j] = ei;
-  }
-}
-
-// Whether the top list is sorted and tested in this iteration (the same rule
-// as the LDS check): when no node outside the top-k survived, or when the run
-// stops here for another reason and the sorted list is the output.
-__device__ __forceinline__ bool sort_needed(const SelArgs& a) {
-  const RunScalars* sc = a.sc;
-  const bool walk_zero = a.b.fp32 ? (a.xmax32[a.b.r] == 0u) : (a.xmax64[a.b.r] == 0ull);
-  return sc->kept_count == 0 || walk_zero || (a.b.fp32 && !sc->progress) || a.b.r >= a.max_iter;
-}
-
-// Sort records of the top list: key = ~bits(l), id = caller id.  list = null
-// takes the identity list 0..count-1 (every node, score criterion output).
-__global__ void __launch_bounds__(kWG) lk_fill(SelArgs a, const int32_t* list, long long count, int gate,
-                                               unsigned long long* key, int32_t* ext) {
-  if (gate) {
-    if (halted(a.sc)) return;
-    if (a.sc->top_count != a.k) {
-      // The selection must hand over exactly k top nodes; anything else is an
-      // internal inconsistency and stops the run before ids are used.
-      if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->err = 2;
-      return;
+    if (slot) {
+      const uint16_t s = slot[i];
+      slot[i] = slot[j];
+      slot[j] = s;
     }
-    if (!sort_needed(a)) return;
-  }
-  for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < count; i += (long long)gridDim.x * kWG) {
-    const int v = list ? list[i] : (int)i;
-    double lo, up;
-    bound_eval(a.b, v, lo, up);
-    key[i] = ~key_of(lo);
-    ext[i] = to_ext(a, v);
   }
 }
 
-// Tile pass in LDS.  full = 1: every stage s = 2 .. kTile; full = 0: the
-// half-cleaner strides kTile/2 .. 1 of a later stage.
-__global__ void __launch_bounds__(kFinishThreads) lk_tile(SelArgs a, long long count, int gate, int full,
+// Sorts a tile of kTile records in LDS: a bitonic network in its direction-free
+// form (stage s: the mirrored pairs (i, i ^ (s - 1)), then the half-cleaner
+// strides s/4 .. 1), one pair per thread and step.
+__device__ __forceinline__ void sort_tile(unsigned long long* key, int32_t* ext, uint16_t* slot) {
+  const int t = threadIdx.x;
+  for (int s = 2; s <= kTile; s <<= 1) {
+    const int h = s >> 1;
+    const int i0 = (t / h) * s + (t % h);
+    cmp_swap(key, ext, slot, i0, i0 ^ (s - 1));
+    __syncthreads();
+    for (int d = s >> 2; d >= 1; d >>= 1) {
+      const int i = (t / d) * 2 * d + (t % d);
+      cmp_swap(key, ext, slot, i, i + d);
+      __syncthreads();
+    }
+  }
+}
+
+// Bits of RunScalars::fail here: a tile's pair failed (lk_test), a pair of the
+// sorted list failed (lk_emit).
+constexpr int kTileFail = 2, kPairFail = 1;
+
+// Whether the run stops in this iteration whatever the test says, so that the
+// sorted list is the output.
+__device__ __forceinline__ bool stops_anyway(const SelArgs& a) {
+  const bool walk_zero = a.b.fp32 ? (a.xmax32[a.b.r] == 0u) : (a.xmax64[a.b.r] == 0ull);
+  return walk_zero || (a.b.fp32 && !a.sc->progress) || a.b.r >= a.max_iter;
+}
+
+// Whether the top list is sorted and tested device-wide in this iteration: no
+// node outside the top-k survived and no tile failed, or the run stops here.
+__device__ __forceinline__ bool sort_needed(const SelArgs& a) {
+  return (a.sc->kept_count == 0 && !(a.sc->fail & kTileFail)) || stops_anyway(a);
+}
+
+// The test of the list's tiles (see the head of this file), and the records
+// for the sort.  list = null takes the identity list 0..count-1 (k = n, where
+// there is no selection: every node is in the list, none is kept beside it).
+__global__ void __launch_bounds__(kFinishThreads) lk_test(SelArgs a, const int32_t* list, long long count,
                                                           unsigned long long* key, int32_t* ext) {
-  if (gate && (halted(a.sc) || !sort_needed(a))) return;
+  if (halted(a.sc)) return;
+  if (list && a.sc->top_count != a.k) {
+    // The selection must hand over exactly k top nodes; anything else is an
+    // internal inconsistency and stops the run before ids are used.
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->err = 2;
+    return;
+  }
+  __shared__ unsigned long long sk[kTile];
+  __shared__ int32_t se[kTile];
+  __shared__ uint16_t ss[kTile];
+  __shared__ double su[kTile];
+  const long long base = (long long)blockIdx.x * kTile;
+  bool prog = false;
+#pragma unroll
+  for (int u = 0; u < kTile / kFinishThreads; ++u) {
+    const int t = threadIdx.x + u * kFinishThreads;
+    const long long i = base + t;
+    sk[t] = ~0ull;
+    se[t] = INT_MAX;
+    ss[t] = (uint16_t)t;
+    if (i < count) {
+      const int v = list ? list[i] : (int)i;
+      double lo, up;
+      bound_eval(a.b, v, lo, up);
+      const int e = to_ext(a, v);
+      key[i] = sk[t] = ~key_of(lo);
+      ext[i] = se[t] = e;
+      su[t] = up;
+      prog = prog || (!list && can_progress(a.b, v));
+    }
+  }
+  __syncthreads();
+  sort_tile(sk, se, ss);
+  const int valid = (int)min((long long)kTile, count - base);
+  bool fail = false;
+#pragma unroll
+  for (int u = 0; u < kTile / kFinishThreads; ++u) {
+    const int t = threadIdx.x + u * kFinishThreads;
+    if (t > 0 && t < valid && su[ss[t]] - a.b.eps >= __longlong_as_double((long long)~sk[t - 1])) fail = true;
+  }
+  const unsigned long long bf = __ballot(fail), bp = __ballot(prog);
+  if (lane_id() == 0) {
+    if (bf && !(a.sc->fail & kTileFail)) atomicOr(&a.sc->fail, kTileFail);
+    if (bp && !a.sc->progress) atomicOr(&a.sc->progress, 1);
+  }
+}
+
+// sc->need: whether the host launches the sort of this iteration.
+__global__ void lk_decide(SelArgs a) {
+  if (!halted(a.sc)) a.sc->need = sort_needed(a) ? 1 : 0;
+}
+
+// Sort records of every node (score criterion output): key = ~bits(l), id =
+// caller id.
+__global__ void __launch_bounds__(kWG) lk_fill(SelArgs a, long long count, unsigned long long* key, int32_t* ext) {
+  for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < count; i += (long long)gridDim.x * kWG) {
+    double lo, up;
+    bound_eval(a.b, (int)i, lo, up);
+    key[i] = ~key_of(lo);
+    ext[i] = to_ext(a, (int)i);
+  }
+}
+
+// Sorts each tile of the records in place.
+__global__ void __launch_bounds__(kFinishThreads) lk_tile(long long count, unsigned long long* key, int32_t* ext) {
   __shared__ unsigned long long sk[kTile];
   __shared__ int32_t se[kTile];
   const long long base = (long long)blockIdx.x * kTile;
@@ -101,63 +177,96 @@ __global__ void __launch_bounds__(kFinishThreads) lk_tile(SelArgs a, long long c
     se[t] = i < count ? ext[i] : INT_MAX;
   }
   __syncthreads();
-  const int t = threadIdx.x;   // one pair per thread and step
-  if (full) {
-    for (int s = 2; s <= kTile; s <<= 1) {
-      {
-        const int h = s >> 1;
-        const int i = (t / h) * s + (t % h);
-        cmp_swap(sk, se, i, i ^ (s - 1));
-      }
-      __syncthreads();
-      for (int d = s >> 2; d >= 1; d >>= 1) {
-        const int i = (t / d) * 2 * d + (t % d);
-        cmp_swap(sk, se, i, i + d);
-        __syncthreads();
-      }
-    }
-  } else {
-    for (int d = kTile >> 1; d >= 1; d >>= 1) {
-      const int i = (t / d) * 2 * d + (t % d);
-      cmp_swap(sk, se, i, i + d);
-      __syncthreads();
-    }
-  }
-  for (int u = threadIdx.x; u < kTile; u += kFinishThreads) {
-    const long long i = base + u;
+  sort_tile(sk, se, nullptr);
+  for (int t = threadIdx.x; t < kTile; t += kFinishThreads) {
+    const long long i = base + t;
     if (i < count) {
-      key[i] = sk[u];
-      ext[i] = se[u];
+      key[i] = sk[t];
+      ext[i] = se[t];
     }
   }
 }
 
-// One global pass: mirror = 1 pairs (i, i ^ (s - 1)) of stage s; mirror = 0
-// pairs (i, i + d).
-__global__ void __launch_bounds__(kWG) lk_pass(SelArgs a, long long count, long long half_pairs, int gate,
-                                               int mirror, long long s, long long d, unsigned long long* key,
-                                               int32_t* ext) {
-  if (gate && (halted(a.sc) || !sort_needed(a))) return;
-  for (long long t = (long long)blockIdx.x * kWG + threadIdx.x; t < half_pairs;
-       t += (long long)gridDim.x * kWG) {
-    long long i, j;
-    if (mirror) {
-      const long long h = s >> 1;
-      i = (t / h) * s + (t % h);
-      j = i ^ (s - 1);
-    } else {
-      i = (t / d) * 2 * d + (t % d);
-      j = i + d;
+// How many of the first d records of the merge of a[0..na) and b[0..nb) come
+// from a.  One wave searches: every round its 64 lanes test 64 places of the
+// remaining range (3 rounds of dependent loads up to 2^18 records, where a
+// binary search takes 18).  Every lane of the wave must call it.
+__device__ __forceinline__ long long merge_split(const unsigned long long* ka, const int32_t* ea, long long na,
+                                                 const unsigned long long* kb, const int32_t* eb, long long nb,
+                                                 long long d) {
+  long long lo = max(0ll, d - nb), hi = min(d, na);   // the answer is in [lo, hi]
+  while (lo < hi) {
+    const long long step = (hi - lo + kWave - 1) / kWave;
+    const long long i = lo + lane_id() * step;       // is the answer above i?
+    bool above = false;
+    if (i < hi) {
+      // a[i] is among the first d when it orders before b[d - 1 - i].
+      const long long j = d - 1 - i;
+      above = j >= nb || rec_less(ka[i], ea[i], kb[j], eb[j]);
     }
-    if (j < count) cmp_swap(key, ext, i, j);
+    const int yes = __popcll(__ballot(above));        // true for a prefix of the lanes
+    if (yes == 0) return lo;
+    const long long last = lo + (yes - 1) * step;      // the answer is above this place
+    hi = min(hi, lo + yes * step);
+    lo = last + 1;
+  }
+  return lo;
+}
+
+// One merge pass: sorted runs of `run` records are merged in pairs; a workgroup
+// writes 2048 records of the output.  Its two waves of the split search find
+// where its share begins and ends in both runs; the share is staged in the LDS,
+// where a record's place is its own index plus its rank in the other run.
+__global__ void __launch_bounds__(kFinishThreads) lk_merge(long long count, long long run,
+                                                           const unsigned long long* key_in, const int32_t* ext_in,
+                                                           unsigned long long* key_out, int32_t* ext_out) {
+  __shared__ unsigned long long sk[kTile];
+  __shared__ int32_t se[kTile];
+  __shared__ long long split[2];
+  const long long out0 = (long long)blockIdx.x * kTile;
+  const long long pair0 = out0 / (2 * run) * (2 * run);
+  const long long na = min(run, count - pair0);
+  const long long nb = max(0ll, min(run, count - pair0 - run));
+  const unsigned long long* ka = key_in + pair0;
+  const int32_t* ea = ext_in + pair0;
+  const unsigned long long* kb = ka + na;
+  const int32_t* eb = ea + na;
+  const long long d0 = out0 - pair0, d1 = min(d0 + kTile, na + nb);
+  const int w = threadIdx.x / kWave;
+  if (w < 2) {
+    const long long s = merge_split(ka, ea, na, kb, eb, nb, w == 0 ? d0 : d1);
+    if (lane_id() == 0) split[w] = s;
+  }
+  __syncthreads();
+  const long long a0 = split[0], b0 = d0 - a0;
+  const int ca = (int)(split[1] - a0), cb = (int)(d1 - d0) - ca;   // records of the share from a and from b
+  for (int t = threadIdx.x; t < ca + cb; t += kFinishThreads) {
+    const bool from_a = t < ca;
+    sk[t] = from_a ? ka[a0 + t] : kb[b0 + t - ca];
+    se[t] = from_a ? ea[a0 + t] : eb[b0 + t - ca];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < ca + cb; t += kFinishThreads) {
+    const unsigned long long k = sk[t];
+    const int32_t e = se[t];
+    // Records of the other part that order before this one.
+    int lo = t < ca ? ca : 0, hi = t < ca ? ca + cb : ca;
+    const int first = lo;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (rec_less(sk[mid], se[mid], k, e)) lo = mid + 1;
+      else hi = mid;
+    }
+    const long long o = out0 + (t < ca ? t : t - ca) + (lo - first);
+    key_out[o] = k;
+    ext_out[o] = e;
   }
 }
 
 // The sorted list becomes the ranking output; with test = 1 every adjacent
 // pair is tested for eps-separation (the check of converged()).
-__global__ void __launch_bounds__(kWG) lk_emit(SelArgs a, long long count, int gate, int test,
+__global__ void __launch_bounds__(kWG) lk_emit(SelArgs a, long long count, int test,
                                                const unsigned long long* key, const int32_t* ext) {
-  if (gate && (halted(a.sc) || !sort_needed(a))) return;
   bool fail = false;
   for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < count; i += (long long)gridDim.x * kWG) {
     const int v = to_int(a, ext[i]);
@@ -168,7 +277,7 @@ __global__ void __launch_bounds__(kWG) lk_emit(SelArgs a, long long count, int g
     a.top_up[i] = up;
     if (test && i > 0 && up - a.b.eps >= __longlong_as_double((long long)~key[i - 1])) fail = true;
   }
-  if (test && __ballot(fail) && lane_id() == 0) atomicOr(&a.sc->fail, 1);
+  if (test && __ballot(fail) && lane_id() == 0) atomicOr(&a.sc->fail, kPairFail);
 }
 
 // converged(), decision: the same rule as the LDS check.
@@ -176,9 +285,8 @@ __global__ void lk_finish(SelArgs a) {
   RunScalars* sc = a.sc;
   if (halted(sc)) return;
   const bool walk_zero = a.b.fp32 ? (a.xmax32[a.b.r] == 0u) : (a.xmax64[a.b.r] == 0ull);
-  const bool sorted = sort_needed(a);
   const int kept = sc->kept_count;
-  const bool certified = kept == 0 && sorted && !sc->fail;
+  const bool certified = kept == 0 && !sc->fail;
   int status = -1;
   if (certified) status = KATZ_OK;
   else if (walk_zero) status = KATZ_W_EXACT_TIES;
@@ -297,32 +405,41 @@ unsigned grid_for(long long items, long long cap) {
   return (unsigned)std::max<long long>(1, std::min<long long>(g, cap));
 }
 
-// The whole sort of `count` records already filled into key / ext.
-void enqueue_sort(const SelArgs& a, long long count, int gate, unsigned long long* key, int32_t* ext,
-                  hipStream_t s) {
-  const long long tiles = (count + kTile - 1) / kTile;
-  hipLaunchKernelGGL(lk_tile, dim3((unsigned)tiles), dim3(kFinishThreads), 0, s, a, count, gate, 1, key, ext);
-  long long P = kTile;
-  while (P < count) P <<= 1;
-  const long long half = P / 2;
-  const unsigned g = grid_for(half, 1 << 16);
-  for (long long sz = 2 * (long long)kTile; sz <= P; sz <<= 1) {
-    hipLaunchKernelGGL(lk_pass, dim3(g), dim3(kWG), 0, s, a, count, half, gate, 1, sz, 0ll, key, ext);
-    for (long long d = sz >> 2; d >= kTile; d >>= 1)
-      hipLaunchKernelGGL(lk_pass, dim3(g), dim3(kWG), 0, s, a, count, half, gate, 0, 0ll, d, key, ext);
-    hipLaunchKernelGGL(lk_tile, dim3((unsigned)tiles), dim3(kFinishThreads), 0, s, a, count, gate, 0, key, ext);
+// Sorts the `count` records in rec[0]; the sorted records end in rec[*which].
+hipError_t enqueue_sort(long long count, const SortRecs rec[2], int* which, hipStream_t s) {
+  const unsigned tiles = (unsigned)((count + kTile - 1) / kTile);
+  hipLaunchKernelGGL(lk_tile, dim3(tiles), dim3(kFinishThreads), 0, s, count, rec[0].key, rec[0].ext);
+  int cur = 0;
+  for (long long run = kTile; run < count; run *= 2) {
+    hipLaunchKernelGGL(lk_merge, dim3(tiles), dim3(kFinishThreads), 0, s, count, run,
+                       (const unsigned long long*)rec[cur].key, (const int32_t*)rec[cur].ext, rec[cur ^ 1].key,
+                       rec[cur ^ 1].ext);
+    cur ^= 1;
   }
+  *which = cur;
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_large_check(const SelArgs& a, unsigned long long* key, int32_t* ext, hipStream_t s) {
+hipError_t launch_large_test(const SelArgs& a, const SortRecs rec[2], hipStream_t s) {
   const long long k = a.k;
-  const unsigned g = grid_for(k, 1 << 14);
-  hipLaunchKernelGGL(lk_fill, dim3(g), dim3(kWG), 0, s, a, (const int32_t*)a.act_out, k, 1, key, ext);
-  enqueue_sort(a, k, 1, key, ext, s);
-  hipLaunchKernelGGL(lk_emit, dim3(g), dim3(kWG), 0, s, a, k, 1, 1, (const unsigned long long*)key,
-                     (const int32_t*)ext);
+  hipLaunchKernelGGL(lk_test, dim3((unsigned)((k + kTile - 1) / kTile)), dim3(kFinishThreads), 0, s, a,
+                     k == a.n ? (const int32_t*)nullptr : (const int32_t*)a.act_out, k, rec[0].key, rec[0].ext);
+  hipLaunchKernelGGL(lk_decide, dim3(1), dim3(1), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_large_sort(const SelArgs& a, const SortRecs rec[2], hipStream_t s) {
+  int cur = 0;
+  const hipError_t e = enqueue_sort(a.k, rec, &cur, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lk_emit, dim3(grid_for(a.k, 1 << 14)), dim3(kWG), 0, s, a, (long long)a.k, 1,
+                     (const unsigned long long*)rec[cur].key, (const int32_t*)rec[cur].ext);
+  return hipGetLastError();
+}
+
+hipError_t launch_large_finish(const SelArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(lk_finish, dim3(1), dim3(1), 0, s, a);
   return hipGetLastError();
 }
@@ -333,13 +450,15 @@ hipError_t launch_score_check(const SelArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_score_output(const SelArgs& a, unsigned long long* key, int32_t* ext, hipStream_t s) {
+hipError_t launch_score_output(const SelArgs& a, const SortRecs rec[2], hipStream_t s) {
   const long long n = a.n;
   const unsigned g = grid_for(n, 1 << 14);
-  hipLaunchKernelGGL(lk_fill, dim3(g), dim3(kWG), 0, s, a, (const int32_t*)nullptr, n, 0, key, ext);
-  enqueue_sort(a, n, 0, key, ext, s);
-  hipLaunchKernelGGL(lk_emit, dim3(g), dim3(kWG), 0, s, a, n, 0, 0, (const unsigned long long*)key,
-                     (const int32_t*)ext);
+  hipLaunchKernelGGL(lk_fill, dim3(g), dim3(kWG), 0, s, a, n, rec[0].key, rec[0].ext);
+  int cur = 0;
+  const hipError_t e = enqueue_sort(n, rec, &cur, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lk_emit, dim3(g), dim3(kWG), 0, s, a, n, 0, (const unsigned long long*)rec[cur].key,
+                     (const int32_t*)rec[cur].ext);
   return hipGetLastError();
 }
 

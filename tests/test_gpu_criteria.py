@@ -97,6 +97,19 @@ def test_ranking_er(n, eps):
     assert abs(res.separated_fraction - OK.separated_fraction(orc.lower_all, orc.upper_all)) <= 1e-6
 
 
+@pytest.mark.parametrize("n,m,eps", [(4097, 4, 1e-9), (6144, 8, 1e-9), (6145, 8, 1e-7), (8192, 3, 0.0), (10241, 5, 1e-8)])
+def test_ranking_tile_edges(n, m, eps):
+    """Lists that end just before, at and just past a 2048-record tile and a
+    merged run: the tile test decides most iterations, the last ones go through
+    the sort; r and the order equal the oracle's (sparse graphs with m = 3..5
+    hold exact ties, which with eps = 0 run into the iteration limit)."""
+    say("ranking tile edges", n)
+    rp, col = sg.erdos_renyi(n, m * n, 11)
+    orc, res = run_both(rp, col, "ranking", eps=eps, max_iter=60)
+    ids, lo, up = check(orc, res)
+    assert sorted(ids.tolist()) == list(range(n))
+
+
 def test_ranking_rmat_ties_fp32():
     """R-MAT with isolated nodes (exact ties, separated only by eps) in the
     FP32 form: the widened intervals contain the oracle's."""
