@@ -55,6 +55,8 @@ struct HostSync {
   RunScalars* ring = nullptr;      // 2 slots: per-pass copies of the flags
   hipEvent_t ev[2] = {nullptr, nullptr};   // null: each pass synchronises the stream
   unsigned long long* bits = nullptr;   // 8 words of scalar read-backs
+  unsigned long long* flags = nullptr;   // 2 words that passes publish (null: the host copies the flags)
+  unsigned seq = 0;                // number of the last pass that publishes (wraps)
   bool borrowed = false;           // the mirrors are static host memory, not owned
 
   int init() {
@@ -62,6 +64,8 @@ struct HostSync {
     if (hipHostMalloc((void**)&sc, sizeof(RunScalars)) != hipSuccess) return KATZ_E_OOM;
     if (hipHostMalloc((void**)&ring, 2 * sizeof(RunScalars)) != hipSuccess) return KATZ_E_OOM;
     if (hipHostMalloc((void**)&bits, 8 * sizeof(unsigned long long)) != hipSuccess) return KATZ_E_OOM;
+    if (hipHostMalloc((void**)&flags, 2 * sizeof(unsigned long long)) != hipSuccess) return KATZ_E_OOM;
+    flags[0] = flags[1] = 0;
     for (hipEvent_t& e : ev)
       if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return KATZ_E_HIP;
     return KATZ_OK;
@@ -71,6 +75,7 @@ struct HostSync {
     if (sc) (void)hipHostFree(sc);
     if (ring) (void)hipHostFree(ring);
     if (bits) (void)hipHostFree(bits);
+    if (flags) (void)hipHostFree(flags);
     for (hipEvent_t e : ev)
       if (e) (void)hipEventDestroy(e);
   }
@@ -733,6 +738,11 @@ struct Run {
   const long long* coff = nullptr;
   const IdLen* pmap = nullptr;
   int32_t* ncol = nullptr;
+  WalkMax walk_max = {};       // maxima the next selection reduces (enqueue_walk)
+  Publish pub = {};            // where the next selection publishes its flags
+
+  // Whether one workgroup may run converged() (its LDS sort holds the top-k).
+  bool one_workgroup_select() const { return (criterion == KATZ_TOPK || criterion == KATZ_RANKING) && k <= kMaxK; }
 };
 
 void* x_at(const Run& run, int r) { return run.st ? run.st->X[r] : run.w->x[r & 1]; }
@@ -842,6 +852,7 @@ SelArgs sel_args(const Run& run, int r) {
   sa.k = run.k;
   sa.n = (int)run.n;
   sa.max_iter = run.max_iter;
+  sa.pub = run.pub;
   return sa;
 }
 
@@ -849,7 +860,9 @@ int ensure_levels(katz_state* st, int r);
 
 int refresh_bins(katz_state* st, hipStream_t s);
 
-int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T) {
+// small_m: the one-workgroup selection follows and reduces the step's maxima
+// itself when there are few (run.walk_max); else a launch of its own does.
+int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
   // A dynamic state re-bins its rows lazily, before the first whole-graph walk
   // after the updates that changed row lengths.
   if (run.st) KATZ_TRY(refresh_bins(run.st, s));
@@ -877,7 +890,9 @@ int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T) {
                               renum, renum ? 1 : run.walk_groups));
   T.stop(tw, s);
   const long long nb = r == 1 ? std::max<long long>(1, (run.bins->count + kWG - 1) / kWG) : grid;
-  KATZ_HIP(launch_reduce_blkmax(run.w->blkmax, nb, run.fp32, run.w->xmax32, run.w->xmax64, r, run.w->sc, s));
+  run.walk_max = WalkMax{nullptr, 0};
+  if (small_m && nb <= kFusedMaxSlots) run.walk_max = WalkMax{run.w->blkmax, (int)nb};
+  else KATZ_HIP(launch_reduce_blkmax(run.w->blkmax, nb, run.fp32, run.w->xmax32, run.w->xmax64, r, run.w->sc, s));
   return KATZ_OK;
 }
 
@@ -889,7 +904,7 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, b
     KATZ_HIP(launch_score_check(sel_args(run, r), s));
   } else if (run.criterion == KATZ_PAIR) {
     KATZ_HIP(launch_pair_check(sel_args(run, r), run.pair_u, run.pair_v, s));
-  } else if (small_m && run.k <= kMaxK) {
+  } else if (small_m) {
     GraphSel gs{};
     gs.b = bound_args(run, r);
     gs.act[0] = run.w->act[0];
@@ -911,7 +926,7 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, b
     gs.cur = run.cur;
     gs.ext_of = run.ext_of;
     gs.int_of = run.int_of;
-    KATZ_HIP(launch_select_wg_one(gs, s));
+    KATZ_HIP(launch_select_wg_one(gs, run.walk_max, run.pub, s));
   } else {
     const SelArgs sa = sel_args(run, r);
     const bool large = run.k > kMaxK;
@@ -934,45 +949,125 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, b
   return KATZ_OK;
 }
 
+// What the host learns of a finished pass.
+struct PassFlags {
+  int err = 0, status = -1, m = 0;   // status: -1 while the run goes on
+  bool stopped() const { return err || status >= 0; }
+};
+
+// Waits until pass `seq` has published its flags, polling their word; when the
+// stream has drained without them (an error made the pass return early), reads
+// the device flags.
+int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out, hipStream_t s) {
+  const unsigned long long* word = &hs.flags[seq & 1];
+  for (long long spins = 1;; ++spins) {
+    unsigned long long w = __atomic_load_n(word, __ATOMIC_RELAXED);
+    if (w >> 40 != (seq & 0xffffffu) && (spins & 0xfff) == 0) {
+      const hipError_t q = hipStreamQuery(s);
+      if (q == hipErrorNotReady) {
+        (void)hipGetLastError();
+        continue;
+      }
+      KATZ_HIP(q);
+      w = __atomic_load_n(word, __ATOMIC_RELAXED);
+      if (w >> 40 != (seq & 0xffffffu)) {
+        KATZ_HIP(hipMemcpyAsync(hs.sc, dev, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+        KATZ_HIP(hipStreamSynchronize(s));
+        *out = PassFlags{hs.sc->err, hs.sc->done ? hs.sc->status : -1, hs.sc->m};
+        return KATZ_OK;
+      }
+    }
+    if (w >> 40 == (seq & 0xffffffu)) {
+      *out = PassFlags{(int)(w >> 31 & 3), (int)(w >> 33 & 15) - 1, (int)(w & INT32_MAX)};
+      return KATZ_OK;
+    }
+    __builtin_ia32_pause();
+  }
+}
+
+// Graphs up to this many nodes and arcs take their flags by polling.  A pass
+// (walk step, selection) on them is 15 to 100 us, of which a copy of the flags
+// and its event took 15 to 20 us and the host's wake-up as much again; on larger
+// graphs the copy is below 2% of a pass, and the host sleeps through it.
+constexpr long long kPolledSize = 1ll << 24;
+// Without pinned memory (the allocation-free call) each read-back stalls the
+// stream for about 30 us, while a pass enqueued past the stop returns at once
+// (two launches, 8 us): small graphs read the flags every fourth pass.
+constexpr int kCopiedPasses = 4;
+
 // Iterates until the device stop flag: walk step r_next, selection,
 // converged(); then r_next + 1, ...  With check_first, the first pass is only a
 // selection at r_next - 1 (after a dynamic update).  Pass p is enqueued before
 // the host waits for the flags of pass p - 1; passes enqueued after the stop
-// return at once on the device.  On return hs.sc holds the final flags.
+// return at once on the device.  On return hs.sc holds the final flags (err,
+// status, iterations, m, cur).
 int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s, CallTimer& T) {
   bool stopped = false;
   int pass = 0;
   int r = r_next;
+  const bool small = run.n + run.nnz <= kPolledSize;
+  const bool polled = hs.flags && small && run.one_workgroup_select();
+  const int copy_every = !hs.ev[0] && small ? kCopiedPasses : 1;
+  PassFlags last;             // of the last pass waited for
+  struct PassAt {
+    int r, cur;               // the pass's iteration, the active list it wrote
+  } at[2] = {};
   // Upper bound of |M| from the latest flags read back; M never grows inside
   // this loop, so a bound read one pass behind stays valid.
-  long long m_known = check_first ? LLONG_MAX : run.n;
+  long long m_known = run.n;
   while (!stopped) {
     const Range range("katz iteration", r);
-    const bool small_m = m_known <= kSmallActive;
-    if (pass == 0 && check_first) {
+    const bool small_m = m_known <= kSmallActive && run.one_workgroup_select();
+    run.pub = polled ? Publish{&hs.flags[(hs.seq + 1) & 1], hs.seq + 1} : Publish{nullptr, 0};
+    const bool select_only = pass == 0 && check_first;
+    at[pass & 1] = PassAt{select_only ? r - 1 : r, run.cur ^ 1};
+    if (select_only) {
       KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, false));
     } else if (r <= run.max_iter) {
       if (run.st) KATZ_TRY(ensure_levels(run.st, r));
-      KATZ_TRY(enqueue_walk(run, r, s, T));
+      KATZ_TRY(enqueue_walk(run, r, s, T, small_m));
       KATZ_TRY(enqueue_select(run, hs, r, s, T, small_m));
       ++r;
     } else {
       break;
     }
-    KATZ_HIP(hipMemcpyAsync(&hs.ring[pass & 1], run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
-    if (hs.ev[0]) KATZ_HIP(hipEventRecord(hs.ev[pass & 1], s));
-    if (pass >= 1) {
-      if (hs.ev[0]) KATZ_HIP(hipEventSynchronize(hs.ev[(pass - 1) & 1]));
+    if (polled) {
+      ++hs.seq;
+      if (pass >= 1) {
+        KATZ_TRY(wait_flags(hs, hs.seq - 1, run.w->sc, &last, s));
+        stopped = last.stopped();
+        m_known = last.m;
+      }
+    } else if ((pass + 1) % copy_every == 0) {
+      KATZ_HIP(hipMemcpyAsync(&hs.ring[pass & 1], run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+      if (hs.ev[0]) KATZ_HIP(hipEventRecord(hs.ev[pass & 1], s));
       else KATZ_HIP(hipStreamSynchronize(s));
-      const RunScalars& prev = hs.ring[(pass - 1) & 1];
-      if (prev.err || prev.done) stopped = true;
-      m_known = prev.m;
+      const int seen = hs.ev[0] ? pass - 1 : pass;   // without events the copy just made is complete
+      if (seen >= 0) {
+        if (hs.ev[0]) KATZ_HIP(hipEventSynchronize(hs.ev[seen & 1]));
+        const RunScalars& prev = hs.ring[seen & 1];
+        if (prev.err || prev.done) stopped = true;
+        m_known = prev.m;
+      }
     }
     ++pass;
   }
-  KATZ_HIP(hipMemcpyAsync(hs.sc, run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
-  KATZ_HIP(hipStreamSynchronize(s));
-  if (hs.sc->err) return hs.sc->err == 2 ? KATZ_E_HIP : KATZ_E_CSR;
+  if (last.stopped()) {
+    const PassAt& a = at[pass & 1];   // the pass waited for is the one before the last enqueued
+    hs.sc->err = last.err;
+    hs.sc->done = 1;
+    hs.sc->status = last.status;
+    hs.sc->iterations = a.r;
+    hs.sc->m = last.m;
+    hs.sc->cur = a.cur;
+  } else {
+    KATZ_HIP(hipMemcpyAsync(hs.sc, run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+    KATZ_HIP(hipStreamSynchronize(s));
+  }
+  if (hs.sc->err) {
+    KATZ_HIP(hipStreamSynchronize(s));
+    return hs.sc->err == 2 ? KATZ_E_HIP : KATZ_E_CSR;
+  }
   return KATZ_OK;
 }
 
@@ -1517,7 +1612,7 @@ int bounds_on(const katz_csr* g, const katz_params* p, int r_target, double* low
   run.S = &S;
   CallTimer T;
   T.call_begin(s);
-  for (int r = 1; r <= r_target; ++r) KATZ_TRY(enqueue_walk(run, r, s, T));
+  for (int r = 1; r <= r_target; ++r) KATZ_TRY(enqueue_walk(run, r, s, T, false));
   if (!async) {
     KATZ_HIP(hipMemcpyAsync(ar.hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));
@@ -2122,7 +2217,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     for (int it = 0; it < kItersPerGraph && ce == hipSuccess; ++it) {
       ce = launch_batch_live_items(bw, total_blocks, items, n_items, cs);
       if (ce == hipSuccess) ce = launch_walk_batch(bw, total_blocks, walk_grid, n_huge, cs);
-      if (ce == hipSuccess) ce = launch_select_wg(gsel, count, r_dev, cs);
+      if (ce == hipSuccess) ce = launch_select_wg(gsel, count, r_dev, fp32, cs);
       if (ce == hipSuccess)
         ce = launch_batch_advance(r_dev, count, gsc, gxmax32, gsigma, gsigsum, gexp, galpha, gclog2, stride, fp32,
                                   ndone, n_items, cs);

@@ -381,14 +381,32 @@ __global__ void pair_test(SelArgs a, int ea, int eb) {
 }
 
 // Separated pairs: lo holds the n lower bounds in descending order, up the
-// upper bounds (any order); adds #{w : lo(w) > up(v)} over v to *count.
-__global__ void __launch_bounds__(kWG) separated_count(const double* lo, const double* up, long long n,
-                                                       unsigned long long* count) {
+// upper bounds (any order); adds #{w : lo(w) > up(v)} over v to *count.  Bound
+// by the chain of dependent loads of a search per node, so its first steps run
+// on every step-th bound, kept in the LDS: 8 dependent loads are left of 19 at
+// n = 5e5.
+constexpr int kSamples = 2048;
+
+__global__ void __launch_bounds__(kFinishThreads) separated_count(const double* lo, const double* up, long long n,
+                                                                  unsigned long long* count) {
+  __shared__ double s[kSamples];
+  const long long step = (n + kSamples - 1) / kSamples;
+  const int ns = (int)((n + step - 1) / step);
+  for (int i = threadIdx.x; i < ns; i += kFinishThreads) s[i] = lo[i * step];
+  __syncthreads();
   unsigned long long acc = 0;
-  for (long long v = (long long)blockIdx.x * kWG + threadIdx.x; v < n; v += (long long)gridDim.x * kWG) {
+  for (long long v = (long long)blockIdx.x * kFinishThreads + threadIdx.x; v < n;
+       v += (long long)gridDim.x * kFinishThreads) {
     const double u = up[v];
     // First position whose lower bound is not above u (lo is non-increasing).
-    long long a0 = 0, b0 = n;
+    int sa = 0, sb = ns;
+    while (sa < sb) {
+      const int mid = (sa + sb) >> 1;
+      if (s[mid] > u) sa = mid + 1;
+      else sb = mid;
+    }
+    // s[sa - 1] is above u, s[sa] is not.
+    long long a0 = sa == 0 ? 0 : (sa - 1) * step + 1, b0 = min(n, sa * step);
     while (a0 < b0) {
       const long long mid = a0 + ((b0 - a0) >> 1);
       if (lo[mid] > u) a0 = mid + 1;
@@ -469,7 +487,7 @@ hipError_t launch_pair_check(const SelArgs& a, int ea, int eb, hipStream_t s) {
 
 hipError_t launch_separated_count(const double* lo_desc, const double* up, long long n, unsigned long long* count,
                                   hipStream_t s) {
-  hipLaunchKernelGGL(separated_count, dim3(grid_for(n, 1 << 14)), dim3(kWG), 0, s, lo_desc, up, n, count);
+  hipLaunchKernelGGL(separated_count, dim3(grid_for((n + 3) / 4, 512)), dim3(kFinishThreads), 0, s, lo_desc, up, n, count);
   return hipGetLastError();
 }
 

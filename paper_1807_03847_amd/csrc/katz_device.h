@@ -71,9 +71,12 @@ __device__ __forceinline__ typename Prec<F32>::T ldx(const void* x, int32_t j) {
 //               by the per-node accumulator e and the global factors; the
 //               interval [lo, up] contains the exact l_r and u_r.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void bound_eval(const BoundArgs& b, int v, double& lo, double& up) {
+// The form is a template argument where several nodes are evaluated per thread:
+// a branch on b.fp32 around each would keep their loads from overlapping.
+template <bool F32>
+__device__ __forceinline__ void bound_eval_as(const BoundArgs& b, int v, double& lo, double& up) {
   const double cv = b.c[v];
-  if (!b.fp32) {
+  if constexpr (!F32) {
     const double s = reinterpret_cast<const double*>(b.x)[v];
     lo = b.undirected ? cv + b.alpha * s : cv;
     up = cv + b.beta * s;
@@ -86,10 +89,16 @@ __device__ __forceinline__ void bound_eval(const BoundArgs& b, int v, double& lo
   }
 }
 
+__device__ __forceinline__ void bound_eval(const BoundArgs& b, int v, double& lo, double& up) {
+  if (b.fp32) bound_eval_as<true>(b, v, lo, up);
+  else bound_eval_as<false>(b, v, lo, up);
+}
+
 // FP32 form: true while the part of the interval that further iterations
 // shrink still exceeds 1/16 of the part they cannot shrink (rounding margin).
-__device__ __forceinline__ bool can_progress(const BoundArgs& b, int v) {
-  if (!b.fp32) return true;
+template <bool F32>
+__device__ __forceinline__ bool can_progress_as(const BoundArgs& b, int v) {
+  if constexpr (!F32) return true;
   const double cv = b.c[v];
   const double s = b.sigma[b.r] * (double)reinterpret_cast<const float*>(b.x)[v];
   const double down = (double)b.e[v] * b.f_e + b.tau_coef * b.sigma_sum[b.r];
@@ -98,10 +107,22 @@ __device__ __forceinline__ bool can_progress(const BoundArgs& b, int v) {
   return intrinsic * 16.0 > margin;
 }
 
+__device__ __forceinline__ bool can_progress(const BoundArgs& b, int v) {
+  return b.fp32 ? can_progress_as<true>(b, v) : true;
+}
+
 __device__ __forceinline__ unsigned long long key_of(double lo) {
   return (unsigned long long)__double_as_longlong(lo);
 }
 
+
+// A finished pass's flags to pinned host memory: one 64-bit word, so that the
+// host, which polls it, needs no ordering with other stores.  status: -1 while
+// the run goes on.  One thread.
+__device__ __forceinline__ void publish(const Publish& p, int err, int status, int m) {
+  if (!p.to) return;
+  __hip_atomic_store(p.to, pass_word(p.seq, err, status, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Exclusive scan of a long long array of length len with one 1024-thread block.
 __device__ inline void block_exclusive_scan_ll(long long* a, long long len, long long* total_out) {

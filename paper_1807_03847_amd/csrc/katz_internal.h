@@ -128,13 +128,27 @@ struct RunScalars {
   // Walk step 2 of a renumbered run found a caller column id out of range.
   // Kept apart from err while that kernel runs: every wave of a walk kernel
   // reads err once to decide whether to skip its work, and the waves of one
-  // workgroup must decide alike (they meet at barriers).  fold_col_err copies
-  // it into err after the launch.
+  // workgroup must decide alike (they meet at barriers).  The kernel that
+  // reduces the step's maxima copies it into err.
   int col_err;
   // An FP32 state's re-walk wrote an entry above its limit (its stored scales
   // no longer fit the graph): the update re-runs the state from level 1.
   int rescale;
 };
+
+// Where a pass (walk step, selection) publishes its flags, a word of pinned host
+// memory (null: nowhere), and the number it goes by.
+struct Publish {
+  unsigned long long* to;
+  unsigned seq;
+};
+
+// The published word: |M| in bits 0..30, then err (2 bits), status + 1 (4 bits;
+// 0 while the run goes on) and the low 24 bits of the pass's number.
+__host__ __device__ inline unsigned long long pass_word(unsigned seq, int err, int status, int m) {
+  return (unsigned long long)(unsigned)m | (unsigned long long)err << 31 | (unsigned long long)(status + 1) << 33 |
+         (unsigned long long)(seq & 0xffffffu) << 40;
+}
 
 // Bound evaluation parameters of one iteration.
 struct BoundArgs {
@@ -222,6 +236,7 @@ struct SelArgs {
   int max_iter;
   int act_out_idx;               // which active-list buffer act_out is (recorded on completion)
   int pad;
+  Publish pub;
 };
 
 // One graph's view for the one-workgroup selection (select_wg): every array
@@ -314,9 +329,10 @@ long long batch_walk_resident(int fp32);
 // kWalkGroups for walk_step_grouped (not with renumber).
 hipError_t launch_walk_step(const IterArgs& a, int fp32, long long total_blocks, long long max_grid,
                             long long* grid_used, hipStream_t s, bool renumber = false, int groups = 1);
-// Reduces the per-workgroup maxima of walk iteration r into xmax32[r] / xmax64[r].
+// Reduces the per-workgroup maxima of walk iteration r into xmax32[r] / xmax64[r]; a
+// column id that walk step 2 found out of range becomes the run's error here.
 hipError_t launch_reduce_blkmax(const void* blkmax, long long nb, int fp32, unsigned* xmax32,
-                                unsigned long long* xmax64, int r, const RunScalars* sc, hipStream_t s);
+                                unsigned long long* xmax64, int r, RunScalars* sc, hipStream_t s);
 hipError_t launch_check_col_range(const int32_t* col, long long nnz, long long n, RunScalars* sc, hipStream_t s);
 // The selection and deactivation pass; with check, then the LDS sort and test
 // of the top-k (k <= kMaxK).
@@ -418,8 +434,16 @@ hipError_t launch_min_lower_active(const BoundArgs& b, const int32_t* act, const
 hipError_t launch_reactivate_all(const BoundArgs& b, long long n, const unsigned long long* min_bits,
                                  uint8_t* mark, int32_t* out, int* count, hipStream_t s);
 
-hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, hipStream_t s);
-hipError_t launch_select_wg_one(const GraphSel& one, hipStream_t s);
+hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, int fp32, hipStream_t s);
+// The workgroup maxima of the walk step before a single graph's selection, when
+// that launch reduces them itself (blkmax null: launch_reduce_blkmax did).
+struct WalkMax {
+  const void* blkmax;
+  int count;
+};
+hipError_t launch_select_wg_one(const GraphSel& one, const WalkMax& walk, const Publish& pub, hipStream_t s);
+// Workgroup maxima at or below which the one-workgroup selection reduces them.
+constexpr long long kFusedMaxSlots = 8192;
 constexpr int kSmallActive = 1 << 16;   // |M| at or below which one workgroup selects
 
 // ---- batched form (katz_batch.hip) --------------------------------------------

@@ -672,8 +672,13 @@ __global__ void __launch_bounds__(kWG) huge_combine(IterArgs a) {
 
 __global__ void __launch_bounds__(kWG) reduce_blkmax(const void* blkmax, long long nb, int fp32,
                                                      unsigned* xmax32, unsigned long long* xmax64, int r,
-                                                     const RunScalars* sc) {
+                                                     RunScalars* sc) {
   if (sc->err || sc->done) return;
+  // After walk step 2 of a renumbered run: a bad column id fails the run.
+  if (sc->col_err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->err = 1;
+    return;
+  }
   __shared__ double wm[kWG / kWave];
   double m = 0.0;
   for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < nb; i += (long long)gridDim.x * kWG)
@@ -991,7 +996,10 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
   if (a.sc->top_count != a.k) {
     // The selection must produce exactly k top nodes; anything else is an
     // internal inconsistency and stops the run before ids are dereferenced.
-    if (threadIdx.x == 0) a.sc->err = 2;
+    if (threadIdx.x == 0) {
+      a.sc->err = 2;
+      publish(a.pub, 2, -1, 0);
+    }
     return;
   }
   __shared__ unsigned long long skey[kMaxK];
@@ -1073,6 +1081,7 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
       sc->status = status;
       sc->done = 1;
     }
+    publish(a.pub, 0, status, k + kept);
   }
 }
 
@@ -1160,11 +1169,6 @@ __global__ void __launch_bounds__(kWG) relabel_ids(const RowDesc* desc, long lon
   pmap[d.row] = IdLen{(int32_t)i, d.len};
   len_ll[i] = d.len;
   len32[i] = d.len;
-}
-
-// After walk step 2 of a renumbered run: a bad column id fails the run.
-__global__ void fold_col_err(RunScalars* sc) {
-  if (sc->col_err) sc->err = 1;
 }
 
 __global__ void reset_flags(RunScalars* sc) {
@@ -1301,7 +1305,7 @@ hipError_t launch_check_col_range(const int32_t* col, long long nnz, long long n
 }
 
 hipError_t launch_reduce_blkmax(const void* blkmax, long long nb, int fp32, unsigned* xmax32,
-                                unsigned long long* xmax64, int r, const RunScalars* sc, hipStream_t s) {
+                                unsigned long long* xmax64, int r, RunScalars* sc, hipStream_t s) {
   const unsigned grid = (unsigned)std::min<long long>(64, std::max<long long>(1, (nb + kWG - 1) / kWG));
   hipLaunchKernelGGL(reduce_blkmax, dim3(grid), dim3(kWG), 0, s, blkmax, nb, fp32, xmax32, xmax64, r, sc);
   return hipGetLastError();
@@ -1405,7 +1409,6 @@ hipError_t launch_walk_step(const IterArgs& a, int fp32, long long total_blocks,
     else hipLaunchKernelGGL(huge_combine<false>, dim3((unsigned)cg), dim3(kWG), 0, s, c);
     used += cg;
   }
-  if (renumber) hipLaunchKernelGGL(fold_col_err, dim3(1), dim3(1), 0, s, a.sc);
   *blocks_used = used;
   return hipGetLastError();
 }

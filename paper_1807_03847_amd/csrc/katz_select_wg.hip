@@ -37,11 +37,417 @@ struct SortArea {
   int ext[kMaxK];
 };
 
+// One record per thread (select_small): the exchange of the sort's long
+// strides, and each node's id and upper bound by the slot its record carries.
+struct SmallArea {
+  unsigned long long key[kFinishThreads];
+  int ext[kFinishThreads];
+  int slot[kFinishThreads];
+  int v[kFinishThreads];   // node id, bit 31: can_progress
+  double up[kFinishThreads];
+};
+
+// The end of an iteration's converged(): the status, the size of M, the stop
+// flag.  One thread.
+template <bool F32>
+__device__ __forceinline__ void finish_iteration(RunScalars* sc, const Publish& pub, const BoundArgs& b, int cur, int k,
+                                                 int kept, bool failed, bool progress, bool walk_zero, int max_iter) {
+  int status = -1;
+  if (kept == 0 && !failed) status = KATZ_OK;
+  else if (walk_zero) status = KATZ_W_EXACT_TIES;
+  else if (F32 && !progress) status = KATZ_W_PRECISION_LIMIT;
+  else if (b.r >= max_iter) status = KATZ_W_ITER_LIMIT;
+  sc->iterations = b.r;
+  sc->cur = cur ^ 1;
+  sc->m = k + kept;
+  if (status >= 0) {
+    sc->status = status;
+    sc->done = 1;
+  }
+  publish(pub, 0, status, k + kept);
+}
+
+// Sorts m <= kFinishThreads records, one per thread (threads at and past m hold
+// padding: ~0, INT_MAX), ascending by (key, ext).  Strides below a wave are lane
+// exchanges, longer ones go through the LDS: m = 1024 takes 10 of them.  Every
+// thread of the workgroup must call it.
+__device__ __forceinline__ void sort_records(int m, unsigned long long& key, int& ext, int& slot, SmallArea& sm) {
+  const int t = threadIdx.x;
+  int P = kWave;
+  while (P < m) P <<= 1;
+  for (int size = 2; size <= P; size <<= 1) {
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      unsigned long long ok;
+      int oe, os;
+      if (stride >= kWave) {
+        sm.key[t] = key;
+        sm.ext[t] = ext;
+        sm.slot[t] = slot;
+        __syncthreads();
+        ok = sm.key[t ^ stride];
+        oe = sm.ext[t ^ stride];
+        os = sm.slot[t ^ stride];
+        __syncthreads();
+      } else {
+        ok = __shfl_xor(key, stride);
+        oe = __shfl_xor(ext, stride);
+        os = __shfl_xor(slot, stride);
+      }
+      const bool take_min = ((t & stride) == 0) == ((t & size) == 0);
+      const bool other_first = ok < key || (ok == key && oe < ext);
+      const bool same = ok == key && oe == ext;   // padding records
+      if (!same && other_first == take_min) {
+        key = ok;
+        ext = oe;
+        slot = os;
+      }
+    }
+  }
+}
+
+// converged() for an active set of at most one node per thread: the whole set
+// is sorted by (lower desc, id asc), one record per thread, which gives the
+// top-k, theta and the pair test at once.  Bound by latency: one round of loads, the sort, one round of stores.  The
+// radix digits that larger sets take (below) cost the same for 20 nodes as for
+// 20000: on 16 nodes of a graph of 2000, 20.4 -> 6.5 us a launch.
+template <bool F32>
+__device__ __forceinline__ void select_small(const GraphSel& gs, const Publish& pub, const BoundArgs& b, int cur,
+                                             bool identity, int m, bool walk_zero, SmallArea& sm) {
+  __shared__ unsigned long long s_theta;
+  __shared__ int s_kept, s_fail, s_prog;
+  const int32_t* act_in = cur ? gs.act[1] : gs.act[0];
+  int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
+  const int k = gs.k;
+  const int t = threadIdx.x;
+  unsigned long long key = ~0ull;   // complemented bits of the lower bound: ascending records
+  int ext = INT_MAX;
+  int slot = t;
+  if (t == 0) {
+    s_kept = 0;
+    s_fail = 0;
+    s_prog = 0;
+  }
+  if (t < m) {
+    const int v = identity ? gs.base + t : act_in[t];
+    double lo, up;
+    bound_eval_as<F32>(b, v, lo, up);
+    key = ~key_of(lo);
+    ext = gs.ext_of ? gs.ext_of[v] : v;
+    sm.v[t] = v | (can_progress_as<F32>(b, v) ? INT_MIN : 0);
+    sm.up[t] = up;
+  }
+  sort_records(m, key, ext, slot, sm);
+  if (t == k - 1) s_theta = ~key;
+  sm.key[t] = key;
+  __syncthreads();
+  if (t < m) {
+    const double theta = __longlong_as_double((long long)s_theta);
+    const int vp = sm.v[slot];
+    const int v = vp & INT_MAX;
+    const double up = sm.up[slot];
+    const bool top = t < k;
+    const bool keep = !top && !(up - b.eps < theta);   // nodes past position k leave M when u - eps < l(M[k])
+    if ((top || keep) && vp < 0) s_prog = 1;
+    if (top) {
+      act_out[t] = v;
+      gs.top_sorted[t] = v;
+      gs.top_lo[t] = __longlong_as_double((long long)~key);
+      gs.top_up[t] = up;
+      if (t > 0 && up - b.eps >= __longlong_as_double((long long)~sm.key[t - 1])) s_fail = 1;
+    } else if (keep) {
+      act_out[k + atomicAdd(&s_kept, 1)] = v;
+    }
+  }
+  __syncthreads();
+  if (t == 0) finish_iteration<F32>(gs.sc, pub, b, cur, k, s_kept, s_fail != 0, s_prog != 0, walk_zero, gs.max_iter);
+}
+
+// The largest new walk entry over the workgroup maxima of the walk step, into
+// xmax[r] (zero before).  Every thread of the workgroup must call it.
+template <bool F32>
+__device__ __forceinline__ void reduce_walk_max(const GraphSel& gs, const WalkMax& walk) {
+  __shared__ double wm[kFinishThreads / kWave];
+  double m = 0.0;
+  for (int i = threadIdx.x; i < walk.count; i += kFinishThreads)
+    m = fmax(m, F32 ? (double)reinterpret_cast<const float*>(walk.blkmax)[i]
+                          : reinterpret_cast<const double*>(walk.blkmax)[i]);
+  for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  if (lane_id() == 0) wm[threadIdx.x / kWave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < kFinishThreads / kWave; ++i) m = fmax(m, wm[i]);
+    if constexpr (F32) const_cast<unsigned*>(gs.xmax32)[gs.b.r] = __float_as_uint((float)m);
+    else const_cast<unsigned long long*>(gs.xmax64)[gs.b.r] = (unsigned long long)__double_as_longlong(m);
+  }
+  __syncthreads();
+}
+
+// converged() for up to 16384 nodes (FP32 form: 8192) with the top-k in one record per
+// thread: every thread keeps the keys of its nodes in registers, so the digits of the radix select read no memory, and once the
+// k-th key's bucket holds at most one record per thread its records are sorted
+// instead of taking further digits.  False, with nothing written, when a bucket
+// of more records than that carries one key (many ties): the general path
+// resolves those.  The general path reads and writes every key several times
+// from one workgroup: 16384 nodes take it 46 us, this 17 us.
+template <bool F32> constexpr int kMidPer = F32 ? 8 : 16;   // nodes per thread (FP32: more would spill)
+template <bool F32> constexpr int kMidActive = kMidPer<F32> * kFinishThreads;
+constexpr int kMidIlp = 8;   // nodes whose loads overlap
+constexpr int kFinishWaves = kFinishThreads / kWave;
+
+struct MidArea {
+  SmallArea rec;
+  unsigned h[kDigits];
+};
+
+template <bool F32>
+__device__ __forceinline__ bool select_mid(const GraphSel& gs, const Publish& pub, const BoundArgs& b, int cur,
+                                           bool identity, int m, bool walk_zero, MidArea& sm) {
+  __shared__ unsigned long long s_kmin, s_kmax, s_theta;
+  __shared__ unsigned s_place;
+  __shared__ int s_cnt, s_fail, s_prog, s_cut;
+  const int32_t* act_in = cur ? gs.act[1] : gs.act[0];
+  int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
+  const int32_t* const ext_of = gs.ext_of;
+  constexpr int kPer = kMidPer<F32>;
+  const int k = gs.k;
+  const int t = threadIdx.x;
+  if (t == 0) {
+    s_kmin = ~0ull;
+    s_kmax = 0ull;
+    s_cnt = 0;
+    s_place = 0;
+    s_fail = 0;
+    s_prog = 0;
+  }
+  __syncthreads();
+  unsigned long long key[kPer];
+  unsigned long long kmin = ~0ull, kmax = 0ull;
+  {
+    int node[kPer];   // slots past m hold a valid node that is dropped
+    if (identity) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) node[u] = gs.base + (u * kFinishThreads + t < m ? u * kFinishThreads + t : 0);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) node[u] = act_in[u * kFinishThreads + t < m ? u * kFinishThreads + t : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = u * kFinishThreads + t;
+      double lo, up;
+      bound_eval_as<F32>(b, node[u], lo, up);
+      key[u] = key_of(lo);
+      if (i < m) {
+        kmin = key[u] < kmin ? key[u] : kmin;
+        kmax = key[u] > kmax ? key[u] : kmax;
+      }
+      if (u % kMidIlp == kMidIlp - 1) __builtin_amdgcn_sched_barrier(0);   // loads in flight, within the registers
+    }
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    const unsigned long long a = __shfl_xor(kmin, o), c = __shfl_xor(kmax, o);
+    kmin = a < kmin ? a : kmin;
+    kmax = c > kmax ? c : kmax;
+  }
+  if (lane_id() == 0) {
+    atomicMin(&s_kmin, kmin);
+    atomicMax(&s_kmax, kmax);
+  }
+  __syncthreads();
+  const unsigned long long kdiff = s_kmin ^ s_kmax;
+  int rem = kdiff ? 64 - __clzll((long long)kdiff) : 0;   // low bits still to resolve
+  unsigned long long pre = s_kmin >> rem;                 // resolved high bits (keys are below 2^63: rem < 64)
+  int need = k, cnt = m;
+  while (cnt > kFinishThreads) {
+    if (rem == 0) return false;
+    const int w = min(kDigitBits, rem);
+    const int shift = rem - w;
+    for (int d = t; d < kDigits; d += kFinishThreads) sm.h[d] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      wave_hist_add(sm.h, (unsigned)((key[u] >> shift) & ((1u << w) - 1u)),
+                    u * kFinishThreads + t < m && (key[u] >> rem) == pre);
+    __syncthreads();
+    const Bucket bk = find_bucket(sm.h, 1 << w, need, true);
+    pre = (pre << w) | (unsigned)bk.b;
+    need = bk.need;
+    cnt = bk.count;
+    rem = shift;
+  }
+  // The bucket's records, sorted: the need-th is the last of the top-k.
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = u * kFinishThreads + t;
+    const bool in = i < m && (key[u] >> rem) == pre;
+    if (__ballot(in)) {
+      const int pos = wave_append(&s_cnt, in);
+      if (in) {
+        const int v = identity ? gs.base + i : act_in[i];
+        sm.rec.key[pos] = ~key[u];
+        sm.rec.ext[pos] = ext_of ? ext_of[v] : v;
+      }
+    }
+  }
+  __syncthreads();
+  {
+    unsigned long long rk = t < cnt ? sm.rec.key[t] : ~0ull;
+    int re = t < cnt ? sm.rec.ext[t] : INT_MAX, rs = 0;
+    __syncthreads();
+    sort_records(cnt, rk, re, rs, sm.rec);
+    if (t == need - 1) {
+      s_theta = ~rk;
+      s_cut = re;
+    }
+  }
+  __syncthreads();
+  const unsigned long long theta_key = s_theta;
+  const double theta = __longlong_as_double((long long)theta_key);
+  const int cut = s_cut;
+  // Deactivation, from a second evaluation (keeping the upper bounds as well
+  // would take more registers than a thread has): one bit per node of the
+  // thread for the top-k and one for the others that stay.
+  asm volatile("" ::: "memory");   // the bounds are read again, not kept
+  unsigned mt = 0, mk = 0;
+  bool any = false;
+  {
+    int node[kPer];
+    if (identity) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) node[u] = gs.base + (u * kFinishThreads + t < m ? u * kFinishThreads + t : 0);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) node[u] = act_in[u * kFinishThreads + t < m ? u * kFinishThreads + t : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const bool valid = u * kFinishThreads + t < m;
+      double lo, up;
+      bound_eval_as<F32>(b, node[u], lo, up);
+      const bool top = valid && key[u] > theta_key;
+      const bool keep = valid && !top && !(up - b.eps < theta);
+      mt |= (unsigned)top << u;
+      mk |= (unsigned)keep << u;
+      if constexpr (F32) any |= (top | keep) & can_progress_as<F32>(b, node[u]);
+      if (u % kMidIlp == kMidIlp - 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!F32) any = true;   // the FP64 form can always go on
+    // Nodes tied with the k-th key: the caller ids up to the cut are top.
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      if (u * kFinishThreads + t < m && key[u] == theta_key) {
+        const int e = ext_of ? ext_of[node[u]] : node[u];
+        if (e <= cut) {
+          mt |= 1u << u;
+          mk &= ~(1u << u);
+          if constexpr (F32) any = any || can_progress_as<F32>(b, node[u]);
+        }
+      }
+    }
+  }
+  // Places in the new list, in the order of this one: a list in ascending
+  // order is read line by line in the next pass, one in any other order takes
+  // a line per node (16384 nodes: 50 us a pass).  Counts per 64 nodes (top-k
+  // in the low half, others in the high half), scanned by one wave.
+  const int w = t / kWave;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const unsigned c = (unsigned)__popcll(__ballot(mt >> u & 1u)) | (unsigned)__popcll(__ballot(mk >> u & 1u)) << 16;
+    if (lane_id() == 0) sm.h[u * kFinishWaves + w] = c;
+  }
+  __syncthreads();
+  if (w == 0) {
+    constexpr int kEach = kPer * kFinishWaves / kWave;
+    unsigned c[kEach], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      c[j] = sum;
+      sum += sm.h[lane_id() * kEach + j];
+    }
+    unsigned inc = sum;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const unsigned y = __shfl_up(inc, o);
+      if (lane_id() >= o) inc += y;
+    }
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) sm.h[lane_id() * kEach + j] = inc - sum + c[j];
+    if (lane_id() == kWave - 1) s_place = inc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const bool top = mt >> u & 1u, keep = mk >> u & 1u;
+    const unsigned long long bt = __ballot(top), bk = __ballot(keep);
+    const unsigned base = sm.h[u * kFinishWaves + w];
+    const int i = u * kFinishThreads + t;
+    const int v = top || keep ? (identity ? gs.base + i : act_in[i]) : 0;
+    if (top) {
+      const int pt = (int)(base & 0xffffu) + __popcll(bt & lanemask_lt());
+      if (pt < k) {
+        double lo, up;
+        bound_eval_as<F32>(b, v, lo, up);
+        act_out[pt] = v;
+        sm.rec.key[pt] = ~key[u];
+        sm.rec.ext[pt] = ext_of ? ext_of[v] : v;
+        sm.rec.v[pt] = v;
+        sm.rec.up[pt] = up;
+      }
+    } else if (keep) {
+      const int pk = (int)(base >> 16) + __popcll(bk & lanemask_lt());
+      if (k + pk < gs.n) act_out[k + pk] = v;
+    }
+  }
+  if (any) s_prog = 1;
+  __syncthreads();
+  const int kept = (int)(s_place >> 16);
+  if ((int)(s_place & 0xffffu) != k) {
+    if (t == 0) {
+      gs.sc->err = 2;
+      publish(pub, 2, -1, 0);
+    }
+    return true;
+  }
+  const bool need_sort = kept == 0 || walk_zero || (F32 && !s_prog) || b.r >= gs.max_iter;
+  if (need_sort) {
+    unsigned long long rk = t < k ? sm.rec.key[t] : ~0ull;
+    int re = t < k ? sm.rec.ext[t] : INT_MAX, rs = t;
+    __syncthreads();
+    sort_records(k, rk, re, rs, sm.rec);
+    sm.rec.key[t] = rk;
+    __syncthreads();
+    if (t < k) {
+      const double upv = sm.rec.up[rs];
+      gs.top_sorted[t] = sm.rec.v[rs];
+      gs.top_lo[t] = __longlong_as_double((long long)~rk);
+      gs.top_up[t] = upv;
+      if (t > 0 && upv - b.eps >= __longlong_as_double((long long)~sm.rec.key[t - 1])) s_fail = 1;
+    }
+    __syncthreads();
+  }
+  if (t == 0) finish_iteration<F32>(gs.sc, pub, b, cur, k, kept, s_fail != 0, s_prog != 0, walk_zero, gs.max_iter);
+  return true;
+}
+
 // Two kernels share the body, so that each reads its GraphSel from one address
 // space (global memory or the kernel arguments) and needs no private copy.
-__device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_dev) {
+// walk: the maxima of the walk step just run, when this launch reduces them
+// itself (one graph); null: they are in xmax32 / xmax64.
+template <bool F32>
+__device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_dev, const WalkMax* walk,
+                                             const Publish& pub) {
   RunScalars* sc = gs.sc;
   if (sc->done || sc->err) return;
+  if (walk) {
+    // Walk step 2 of a renumbered run found a bad column id.
+    if (sc->col_err) {
+      if (threadIdx.x == 0) {
+        sc->err = 1;
+        publish(pub, 1, -1, 0);
+      }
+      return;
+    }
+    if (walk->blkmax) reduce_walk_max<F32>(gs, *walk);
+  }
   BoundArgs b = gs.b;
   if (r_dev) refresh_bounds(b, gs, *r_dev);
   const int cur = r_dev ? sc->cur : gs.cur;
@@ -49,6 +455,19 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
   int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
   const bool identity = r_dev ? (b.r == 1) : gs.identity_in;
   const int m = identity ? gs.n : sc->m;
+  const bool walk_zero = F32 ? (gs.xmax32[b.r] == 0u) : (gs.xmax64[b.r] == 0ull);
+  __shared__ union {
+    unsigned h[kDigits];
+    SortArea srt;
+    SmallArea small;
+    MidArea mid;
+  } sm;
+  if (m <= kFinishThreads) {
+    select_small<F32>(gs, pub, b, cur, identity, m, walk_zero, sm.small);
+    return;
+  }
+  if (walk && m <= kMidActive<F32> && gs.k <= kFinishThreads && select_mid<F32>(gs, pub, b, cur, identity, m, walk_zero, sm.mid))
+    return;
   const int k = gs.k;
   // The graph's arrays and sizes as locals: read from gs once, not again after
   // every store (gs may sit in global memory, which the stores could alias).
@@ -65,10 +484,6 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
   auto ext = [ext_of](int v) { return ext_of ? ext_of[v] : v; };
   const int t = threadIdx.x;
 
-  __shared__ union {
-    unsigned h[kDigits];
-    SortArea srt;
-  } sm;
   __shared__ unsigned long long s_prefix, s_kmin, s_kmax;
   __shared__ int s_need, s_count, s_cnt, s_top, s_kept, s_fail, s_prog, s_idpre, s_idneed;
 
@@ -98,7 +513,7 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
         const int i = b0 + u * kFinishThreads + t;
         const int v = i < m ? (identity ? base_id + i : act_in[i]) : base_id;
         double lo, up;
-        bound_eval(b, v, lo, up);
+        bound_eval_as<F32>(b, v, lo, up);
         kk[u] = key_of(lo);
       }
 #pragma unroll
@@ -260,10 +675,10 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
         const int v = valid ? (identity ? base_id + i : act_in[i]) : base_id;
         const unsigned long long key = valid ? keys[i] : 0ull;
         double lo, up;
-        bound_eval(b, v, lo, up);
+        bound_eval_as<F32>(b, v, lo, up);
         top[u] = valid && (key > theta_key || (key == theta_key && ext(v) <= cut));
         keep[u] = valid && !top[u] && !(up - b.eps < theta);
-        if ((top[u] || keep[u]) && can_progress(b, v)) prog = true;
+        if ((top[u] || keep[u]) && can_progress_as<F32>(b, v)) prog = true;
         vv[u] = v;
       }
 #pragma unroll
@@ -278,14 +693,16 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
   }
   __syncthreads();
   if (s_top != k) {
-    if (t == 0) sc->err = 2;
+    if (t == 0) {
+      sc->err = 2;
+      publish(pub, 2, -1, 0);
+    }
     return;
   }
   // Sort the top-k by (lower desc, id asc) and test adjacent pairs: needed when
   // no node outside the top-k survived, or as the output when the run stops
   // here for another reason.
-  const bool walk_zero = b.fp32 ? (gs.xmax32[b.r] == 0u) : (gs.xmax64[b.r] == 0ull);
-  const bool need_sort = s_kept == 0 || walk_zero || (b.fp32 && !s_prog) || b.r >= gs.max_iter;
+  const bool need_sort = s_kept == 0 || walk_zero || (F32 && !s_prog) || b.r >= gs.max_iter;
   int P = 1;
   while (P < k) P <<= 1;
   if (!need_sort) P = 0;
@@ -294,7 +711,7 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
     if (i < k) {
       const int v = act_out[i];
       double lo, up;
-      bound_eval(b, v, lo, up);
+      bound_eval_as<F32>(b, v, lo, up);
       sm.srt.key[i] = key_of(lo);
       sm.srt.ext[i] = ext(v);
     } else {
@@ -325,46 +742,39 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
   for (int i = t; i < (need_sort ? k : 0); i += kFinishThreads) {
     const int v = int_of ? int_of[sm.srt.ext[i]] : sm.srt.ext[i];
     double lo, up;
-    bound_eval(b, v, lo, up);
+    bound_eval_as<F32>(b, v, lo, up);
     top_sorted[i] = v;
     top_lo[i] = lo;
     top_up[i] = up;
     if (i > 0 && up - b.eps >= __longlong_as_double((long long)sm.srt.key[i - 1])) s_fail = 1;
   }
   __syncthreads();
-  if (t == 0) {
-    const int kept = s_kept;
-    const bool certified = kept == 0 && !s_fail;
-    int status = -1;
-    if (certified) status = KATZ_OK;
-    else if (walk_zero) status = KATZ_W_EXACT_TIES;
-    else if (b.fp32 && !s_prog) status = KATZ_W_PRECISION_LIMIT;
-    else if (b.r >= gs.max_iter) status = KATZ_W_ITER_LIMIT;
-    sc->iterations = b.r;
-    sc->cur = cur ^ 1;
-    sc->m = k + kept;
-    if (status >= 0) {
-      sc->status = status;
-      sc->done = 1;
-    }
-  }
+  if (t == 0) finish_iteration<F32>(sc, pub, b, cur, k, s_kept, s_fail != 0, s_prog != 0, walk_zero, gs.max_iter);
 }
 
+template <bool F32>
 __global__ void __launch_bounds__(kFinishThreads) select_wg(const GraphSel* gsel, const int* r_dev) {
-  select_graph(gsel[blockIdx.x], r_dev);
+  select_graph<F32>(gsel[blockIdx.x], r_dev, nullptr, Publish{nullptr, 0});
 }
 
-__global__ void __launch_bounds__(kFinishThreads) select_wg_one(GraphSel one) { select_graph(one, nullptr); }
+template <bool F32>
+__global__ void __launch_bounds__(kFinishThreads) select_wg_one(GraphSel one, WalkMax walk, Publish pub) {
+  select_graph<F32>(one, nullptr, &walk, pub);
+}
 
 }  // namespace
 
-hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, hipStream_t s) {
-  if (count > 0) hipLaunchKernelGGL(select_wg, dim3(count), dim3(kFinishThreads), 0, s, gsel, r_dev);
+hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, int fp32, hipStream_t s) {
+  if (count > 0) {
+    if (fp32) hipLaunchKernelGGL(select_wg<true>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r_dev);
+    else hipLaunchKernelGGL(select_wg<false>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r_dev);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_select_wg_one(const GraphSel& one, hipStream_t s) {
-  hipLaunchKernelGGL(select_wg_one, dim3(1), dim3(kFinishThreads), 0, s, one);
+hipError_t launch_select_wg_one(const GraphSel& one, const WalkMax& walk, const Publish& pub, hipStream_t s) {
+  if (one.b.fp32) hipLaunchKernelGGL(select_wg_one<true>, dim3(1), dim3(kFinishThreads), 0, s, one, walk, pub);
+  else hipLaunchKernelGGL(select_wg_one<false>, dim3(1), dim3(kFinishThreads), 0, s, one, walk, pub);
   return hipGetLastError();
 }
 

@@ -75,6 +75,34 @@ def test_er_fp32_margin(seed):
 
 
 # --------------------------------------------------------------------------------
+# The one-workgroup selection: one record per thread up to 1024 active nodes, keys
+# in registers up to 16384, radix digits over memory beyond (and for many ties).
+# --------------------------------------------------------------------------------
+@pytest.mark.parametrize("n,k", [(2, 1), (63, 63), (64, 9), (65, 64), (1023, 1023), (1024, 500), (1025, 1), (1025, 1025),
+                                 (2049, 1024), (5000, 1025), (16384, 1024), (16385, 1000), (16385, 1)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_selection_sizes(n, k, precision):
+    say("selection sizes", n, k, precision)
+    rp, col = sg.erdos_renyi(n, min(6 * n, n * (n - 1) // 2), 21) if n > 2 else sg.path_graph(2)
+    orc, res = run_both(rp, col, k, 1e-4, precision=precision, max_iter=40)
+    ids = check(orc, res, widened=precision == "fp32", status=precision == "fp64")
+    assert len(set(ids.tolist())) == k
+    if precision == "fp64":
+        assert res.iterations == orc.iterations and res.active_final == orc.active_final
+
+
+@pytest.mark.parametrize("n,k", [(1024, 10), (3000, 10), (16384, 700), (20000, 1024)])
+def test_selection_all_tied(n, k):
+    """Every node of a cycle has one lower bound: the ids alone decide, in
+    records (n = 1024) and in the general path that more tied keys fall back to."""
+    say("selection ties", n, k)
+    rp, col = sg.cycle_graph(n)
+    orc, res = run_both(rp, col, k, 0.0, max_iter=6)
+    assert res.status == orc.status == K().W_ITER_LIMIT and res.active_final == n
+    assert np.array_equal(res.topk.cpu().numpy(), np.arange(k))
+
+
+# --------------------------------------------------------------------------------
 # katz_bounds: the score surface at equal r.
 # --------------------------------------------------------------------------------
 def _bound_graphs():
