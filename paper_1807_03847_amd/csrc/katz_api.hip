@@ -464,10 +464,7 @@ struct Bins {
   RowDesc* desc = nullptr;
   SegDesc* segs = nullptr;
   HugeRow* huge = nullptr;
-  long long* blk = nullptr;
-  long long* scan_sums = nullptr;    // scratch of the device-wide scans
-  long long* scan_totals = nullptr;  // [2]
-  int nblocks = 0;
+  PrepTable tab = {};    // binning scratch
   long long seg_cap = 0, huge_cap = 0;
   long long count = 0;   // rows binned
   long long bin_count[NUM_BINS] = {};
@@ -486,8 +483,10 @@ struct Bins {
 };
 
 // Capacities for binning up to `rows` rows that hold at most `arcs` arcs.
+int prep_blocks(long long rows) { return (int)std::max<long long>(1, (rows + kPrepRows - 1) / kPrepRows); }
+
 void bins_caps(Bins& b, long long rows, long long arcs) {
-  b.nblocks = (int)std::max<long long>(1, (rows + kWG - 1) / kWG);
+  b.tab.nblocks = prep_blocks(rows);
   b.seg_cap = 2 * (arcs / kSeg) + 2;
   b.huge_cap = arcs / (kBlockRowMax + 1) + 1;
 }
@@ -1153,15 +1152,7 @@ struct Staging {
   const int32_t* col = nullptr;
   // Internal renumbering (Plan::reorder).
   int32_t* ncol = nullptr;
-  long long* noff = nullptr;
-  long long* len_ll = nullptr;
-  int* len32 = nullptr;
-  int32_t* ext_of = nullptr;
-  int32_t* int_of = nullptr;
-  long long* coff = nullptr;      // internal id -> caller row offset
-  IdLen* pmap = nullptr;          // caller id -> {internal id, length}
-  long long* sums = nullptr;
-  long long* total = nullptr;
+  RelabelOut relabel = {};
   long long* row_off = nullptr;   // strict symmetry check
   int* row_len = nullptr;
   int32_t* out_ids = nullptr;
@@ -1176,9 +1167,8 @@ void layout(Arena& ar, const Plan& pl, Bins& b, Work& w, Staging& stg) {
   ar.used = 0;
   bins_caps(b, n, nnz);
   w.sc = ar.take<RunScalars>(1);
-  b.blk = ar.take<long long>((size_t)(NUM_BINS + 2) * b.nblocks);
-  b.scan_sums = ar.take<long long>(scan_sums_capacity((long long)NUM_BINS * b.nblocks));
-  b.scan_totals = ar.take<long long>(2);
+  b.tab.blk = ar.take<long long>((size_t)prep_table_rows(pl.reorder ? kBinParts : 1) * b.tab.nblocks);
+  b.tab.totals = ar.take<long long>(kPrepTableRows);
   b.desc = ar.take<RowDesc>(n);
   b.segs = ar.take<SegDesc>(b.seg_cap);
   b.huge = ar.take<HugeRow>(b.huge_cap);
@@ -1190,15 +1180,10 @@ void layout(Arena& ar, const Plan& pl, Bins& b, Work& w, Staging& stg) {
   }
   if (pl.reorder) {
     stg.ncol = ar.take<int32_t>(std::max<long long>(nnz, 1));
-    stg.noff = ar.take<long long>(n);
-    stg.len_ll = ar.take<long long>(n);
-    stg.len32 = ar.take<int>(n);
-    stg.ext_of = ar.take<int32_t>(n);
-    stg.int_of = ar.take<int32_t>(n);
-    stg.coff = ar.take<long long>(n);
-    stg.pmap = ar.take<IdLen>(n);
-    stg.sums = ar.take<long long>(scan_sums_capacity(n));
-    stg.total = ar.take<long long>(1);
+    stg.relabel.ext_of = ar.take<int32_t>(n);
+    stg.relabel.int_of = ar.take<int32_t>(n);
+    stg.relabel.coff = ar.take<long long>(n);
+    stg.relabel.pmap = ar.take<IdLen>(n);
   }
   const size_t xs = pl.fp32 ? 4 : 8;
   w.x[0] = ar.take<char>(n * xs);
@@ -1282,10 +1267,12 @@ int prepare(HostSync& hs, const Plan& pl, Bins& b, Work& w, Staging& stg, hipStr
     stg.col = g->col;
   }
   KATZ_HIP(launch_init_run(w.sc, g->n, w.sigma, w.sigma_sum, w.xmax32, w.xmax64, pl.max_iter, w.hist, s));
-  KATZ_HIP(launch_prep_count(stg.row_ptr, g->row_ptr_64, g->n, g->nnz, b.blk, b.nblocks, w.sc, b.bb, s));
-  KATZ_HIP(launch_prep_scan(b.blk, b.nblocks, b.scan_sums, b.scan_totals, w.sc, s));
-  KATZ_HIP(launch_prep_scatter(stg.row_ptr, g->row_ptr_64, g->n, b.blk, b.nblocks, b.desc, b.segs, b.huge, w.sc, b.bb,
-                               s));
+  // The strict checks read the caller's rows (their descriptors too), before a
+  // renumbered graph's take their place.
+  const bool strict = pl.validate == KATZ_VALIDATE_STRICT;
+  const RelabelOut none{};
+  KATZ_HIP(launch_prep_csr(stg.row_ptr, g->row_ptr_64, g->n, g->nnz, b.tab, b.desc, b.segs, b.huge,
+                           strict ? none : stg.relabel, w.sc, b.bb, s));
   // Column ids are range-checked before any gather uses them: here, or, when
   // the graph is renumbered with basic validation, in walk step 2, which reads
   // every caller column id to rename it and never indexes with a bad one (no
@@ -1298,24 +1285,15 @@ int prepare(HostSync& hs, const Plan& pl, Bins& b, Work& w, Staging& stg, hipStr
   KATZ_HIP(hipStreamSynchronize(s));
   if (hs.sc->err) return KATZ_E_CSR;
   b.read_back(*hs.sc, g->n);
-  if (pl.validate == KATZ_VALIDATE_STRICT) {
+  if (strict) {
     KATZ_HIP(launch_validate_strict(b.desc, g->n, b.segs, b.seg_total, b.huge, stg.col, g->undirected, stg.row_off,
                                     stg.row_len, w.sc, s));
     KATZ_HIP(hipMemcpyAsync(hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));
     if (hs.sc->err) return KATZ_E_CSR;
-  }
-  if (pl.reorder) {
-    // Renumber by the binned order and rebuild the bins on the renumbered rows
-    // (now contiguous per bin).
-    KATZ_HIP(launch_relabel(b.desc, g->n, stg.ext_of, stg.int_of, stg.coff, stg.pmap, stg.len_ll, stg.len32,
-                            stg.noff, stg.sums, stg.total, s));
-    KATZ_HIP(launch_prep_rows(nullptr, g->n, stg.noff, stg.len32, b.blk, b.nblocks, b.scan_sums, b.scan_totals,
-                              b.desc, b.segs, b.huge, w.sc, b.bb, s));
-    KATZ_HIP(hipMemcpyAsync(hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
-    KATZ_HIP(hipStreamSynchronize(s));
-    if (hs.sc->err) return hs.sc->err == 1 ? KATZ_E_CSR : KATZ_E_HIP;
-    b.read_back(*hs.sc, g->n);
+    if (pl.reorder)
+      KATZ_HIP(launch_prep_csr(stg.row_ptr, g->row_ptr_64, g->n, g->nnz, b.tab, b.desc, b.segs, b.huge, stg.relabel,
+                               w.sc, b.bb, s));
   }
   return KATZ_OK;
 }
@@ -1384,12 +1362,12 @@ int rank_in_arena(Arena& ar, const katz_csr* g, const katz_params* p, katz_resul
   run.fp32 = pl.fp32;
   run.validate = KATZ_VALIDATE_NONE;   // columns are checked in prepare() or in walk step 2
   run.col = pl.reorder ? stg.ncol : stg.col;
-  run.ext_of = pl.reorder ? stg.ext_of : nullptr;
-  run.int_of = pl.reorder ? stg.int_of : nullptr;
+  run.ext_of = stg.relabel.ext_of;
+  run.int_of = stg.relabel.int_of;
   run.renumber = renumber_in_walk(pl);
   run.col_src = stg.col;
-  run.coff = stg.coff;
-  run.pmap = stg.pmap;
+  run.coff = stg.relabel.coff;
+  run.pmap = stg.relabel.pmap;
   run.ncol = stg.ncol;
   run.walk_grid = (long long)tu.blocks_per_cu * cu_count(dev);
   run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
@@ -1446,12 +1424,11 @@ int reverse_graphs(Arena& ar, int count, const katz_csr* g, const katz_params* p
   };
   std::vector<Place> pl(count);
   RunScalars* sc = nullptr;
-  long long* blk = nullptr;
   char* scratch = nullptr;
   auto place = [&]() {
     ar.used = 0;
     sc = ar.take<RunScalars>(1);
-    blk = ar.take<long long>((size_t)(NUM_BINS + 2) * tmp.nblocks);
+    tmp.tab.blk = ar.take<long long>((size_t)kPrepTableRows * tmp.tab.nblocks);
     scratch = ar.take<char>(transpose_scratch_bytes(n_max, nnz_max));
     for (int i = 0; i < count; ++i) {
       if (!wants_reverse(&g[i], &p[i])) continue;
@@ -1481,10 +1458,9 @@ int reverse_graphs(Arena& ar, int count, const katz_csr* g, const katz_params* p
       KATZ_HIP(hipMemcpyAsync(pl[i].col_dev, g[i].col, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
       col = pl[i].col_dev;
     }
-    Bins bi;
-    bins_caps(bi, n, nnz);
+    const PrepTable tab{tmp.tab.blk, nullptr, prep_blocks(n)};
     KATZ_HIP(launch_reset_flags(sc, s));
-    KATZ_HIP(launch_prep_count(rp, g[i].row_ptr_64, n, nnz, blk, bi.nblocks, sc, BinBounds{}, s));
+    KATZ_HIP(launch_prep_count(rp, g[i].row_ptr_64, n, nnz, tab, sc, BinBounds{}, s));
     KATZ_HIP(launch_check_col_range(col, nnz, n, sc, s));
     KATZ_HIP(hipMemcpyAsync(ar.hs.sc, sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));
@@ -1596,12 +1572,12 @@ int bounds_on(const katz_csr* g, const katz_params* p, int r_target, double* low
   run.fp32 = pl.fp32;
   run.validate = KATZ_VALIDATE_NONE;   // columns are checked in prepare() or in walk step 2
   run.col = pl.reorder ? stg.ncol : stg.col;
-  run.ext_of = pl.reorder ? stg.ext_of : nullptr;
-  run.int_of = pl.reorder ? stg.int_of : nullptr;
+  run.ext_of = stg.relabel.ext_of;
+  run.int_of = stg.relabel.int_of;
   run.renumber = renumber_in_walk(pl);
   run.col_src = stg.col;
-  run.coff = stg.coff;
-  run.pmap = stg.pmap;
+  run.coff = stg.relabel.coff;
+  run.pmap = stg.relabel.pmap;
   run.ncol = stg.ncol;
   run.walk_grid = (long long)tu.blocks_per_cu * cu_count(dev);
   run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
@@ -1923,9 +1899,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     o_ids = ar.take<int32_t*>(count);
     o_lo = ar.take<double*>(count);
     o_up = ar.take<double*>(count);
-    b.blk = ar.take<long long>((size_t)(NUM_BINS + 2) * b.nblocks);
-    b.scan_sums = ar.take<long long>(scan_sums_capacity((long long)NUM_BINS * b.nblocks));
-    b.scan_totals = ar.take<long long>(2);
+    b.tab.blk = ar.take<long long>((size_t)kPrepTableRows * b.tab.nblocks);
+    b.tab.totals = ar.take<long long>(kPrepTableRows);
     b.desc = ar.take<RowDesc>(total_n);
     b.segs = ar.take<SegDesc>(b.seg_cap);
     b.huge = ar.take<HugeRow>(b.huge_cap);
@@ -1991,8 +1966,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   KATZ_HIP(hipMemsetAsync(gdmax, 0, sizeof(int) * count, s));
   int validate = 0;
   for (int i = 0; i < count; ++i) validate = std::max(validate, p[i].validate);
-  KATZ_HIP(launch_batch_prep(gbase, grp, grp64, gnnz, gabase, gcol, count, total_n, total_nnz, gid_of, b.blk,
-                             b.nblocks, b.scan_sums, b.scan_totals, b.desc, b.segs, b.huge, w.sc, validate, b.bb, s));
+  KATZ_HIP(launch_batch_prep(gbase, grp, grp64, gnnz, gabase, gcol, count, total_n, total_nnz, gid_of, b.tab,
+                             b.desc, b.segs, b.huge, w.sc, validate, b.bb, s));
   KATZ_HIP(launch_batch_dmax(grp, grp64, gbase, count, total_n, gdmax, s));
   std::vector<int> h_dmax(count);
   KATZ_HIP(hipMemcpyAsync(h_dmax.data(), gdmax, sizeof(int) * count, hipMemcpyDeviceToHost, s));
@@ -2007,8 +1982,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     KATZ_HIP(hipMemsetAsync(run_last, 0xFF, sizeof(long long) * (size_t)count * NUM_BINS, s));
     KATZ_HIP(launch_batch_relabel(b.desc, total_n, gbase, count, w.sc, run_first, run_last, run_start, ext_of, int_of,
                                   coff, pmap, len_ll, len32, noff, rsums, rtot, s));
-    KATZ_HIP(launch_prep_rows(nullptr, total_n, noff, len32, b.blk, b.nblocks, b.scan_sums, b.scan_totals, b.desc,
-                              b.segs, b.huge, w.sc, b.bb, s));
+    KATZ_HIP(launch_prep_rows(nullptr, total_n, noff, len32, false, b.tab, b.desc, b.segs, b.huge, w.sc, b.bb, s));
     KATZ_HIP(hipMemcpyAsync(ar.hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));
     if (ar.hs.sc->err) return ar.hs.sc->err == 1 ? KATZ_E_CSR : KATZ_E_HIP;
@@ -2337,18 +2311,16 @@ int alloc_bins(katz_state* st, Bins& b) {
     dfree(st, b.desc);
     dfree(st, b.segs);
     dfree(st, b.huge);
-    dfree(st, b.blk);
-    dfree(st, b.scan_sums);
-    dfree(st, b.scan_totals);
+    dfree(st, b.tab.blk);
+    dfree(st, b.tab.totals);
   }
   bins_caps(b, st->n, st->pool_cap);
   b.desc = dalloc<RowDesc>(st, st->n);
   b.segs = dalloc<SegDesc>(st, b.seg_cap);
   b.huge = dalloc<HugeRow>(st, b.huge_cap);
-  b.blk = dalloc<long long>(st, (size_t)(NUM_BINS + 2) * b.nblocks);
-  b.scan_sums = dalloc<long long>(st, scan_sums_capacity((long long)NUM_BINS * b.nblocks));
-  b.scan_totals = dalloc<long long>(st, 2);
-  if (!b.desc || !b.segs || !b.huge || !b.blk || !b.scan_sums || !b.scan_totals) return KATZ_E_OOM;
+  b.tab.blk = dalloc<long long>(st, (size_t)kPrepTableRows * b.tab.nblocks);
+  b.tab.totals = dalloc<long long>(st, kPrepTableRows);
+  if (!b.desc || !b.segs || !b.huge || !b.tab.blk || !b.tab.totals) return KATZ_E_OOM;
   return KATZ_OK;
 }
 
@@ -2363,9 +2335,8 @@ int alloc_partial(katz_state* st) {
 // Bins the rows `ids[0..count)` (or every row when ids is null) of the slack CSR.
 int bin_rows(katz_state* st, Bins& b, RunScalars* sc, const int32_t* ids, long long count, hipStream_t s) {
   KATZ_HIP(launch_reset_flags(sc, s));
-  b.nblocks = (int)std::max<long long>(1, (count + kWG - 1) / kWG);
-  KATZ_HIP(launch_prep_rows(ids, count, st->row_off, st->row_len, b.blk, b.nblocks, b.scan_sums, b.scan_totals,
-                            b.desc, b.segs, b.huge, sc, b.bb, s));
+  b.tab.nblocks = prep_blocks(count);
+  KATZ_HIP(launch_prep_rows(ids, count, st->row_off, st->row_len, true, b.tab, b.desc, b.segs, b.huge, sc, b.bb, s));
   KATZ_HIP(hipMemcpyAsync(st->hs.sc, sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
   KATZ_HIP(hipStreamSynchronize(s));
   if (st->hs.sc->err) return KATZ_E_HIP;
@@ -2654,14 +2625,14 @@ int create_state(const katz_csr* g, const katz_params* p, katz_result* out, katz
   {
     Bins tmp;
     bins_caps(tmp, n, g->nnz);
-    long long* blk = dalloc<long long>(st, (size_t)(NUM_BINS + 2) * tmp.nblocks);
-    if (!blk) return KATZ_E_OOM;
+    tmp.tab.blk = dalloc<long long>(st, (size_t)kPrepTableRows * tmp.tab.nblocks);
+    if (!tmp.tab.blk) return KATZ_E_OOM;
     KATZ_HIP(launch_reset_flags(st->w.sc, s));
-    KATZ_HIP(launch_prep_count(rp, g->row_ptr_64, n, g->nnz, blk, tmp.nblocks, st->w.sc, BinBounds{}, s));
+    KATZ_HIP(launch_prep_count(rp, g->row_ptr_64, n, g->nnz, tmp.tab, st->w.sc, BinBounds{}, s));
     KATZ_HIP(launch_check_col_range(col, g->nnz, n, st->w.sc, s));
     KATZ_HIP(hipMemcpyAsync(st->hs.sc, st->w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));
-    dfree(st, blk);
+    dfree(st, tmp.tab.blk);
     if (st->hs.sc->err) return KATZ_E_CSR;
   }
 

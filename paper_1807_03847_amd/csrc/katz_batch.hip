@@ -766,8 +766,7 @@ void launch_rename_bin(const RowDesc* desc, long long first, long long cnt, cons
 // ---------------------------------------------------------------------------
 hipError_t launch_batch_prep(const long long* gbase, const void* const* grp, const int* grp64, const long long* gnnz,
                              const long long* gabase, const int32_t* const* gcol, int count, long long total_n,
-                             long long total_nnz, int* gid_of, long long* blk, int nblocks, long long* sums,
-                             long long* totals, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
+                             long long total_nnz, int* gid_of, const PrepTable& tab, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
                              int validate, const BinBounds& bb, hipStream_t s) {
   const unsigned nb = (unsigned)std::max<long long>(1, (total_n + kWG - 1) / kWG);
   hipLaunchKernelGGL(fill_gid, dim3(nb), dim3(kWG), 0, s, gbase, count, total_n, gid_of);
@@ -777,11 +776,14 @@ hipError_t launch_batch_prep(const long long* gbase, const void* const* grp, con
     hipLaunchKernelGGL(batch_col_range, dim3(gx), dim3(kWG), 0, s, gcol, gabase, gbase, count, sc);
   }
   const BatchRows rows{gid_of, gbase, grp, grp64, gnnz};
-  hipLaunchKernelGGL(prep_count<BatchRows>, dim3(nblocks), dim3(kWG), 0, s, rows, total_n, blk, nblocks, sc, bb);
-  hipError_t e = launch_prep_scan(blk, nblocks, sums, totals, sc, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prep_scatter<BatchRows>, dim3(nblocks), dim3(kWG), 0, s, rows, total_n, (const long long*)blk,
-                     nblocks, desc, segs, huge, sc, bb);
+  // Bins uncut by length: batch_runs takes a graph's rows of a bin as one run.
+  const PrepClasses pc = prep_classes(bb);
+  hipLaunchKernelGGL((prep_count<BatchRows, 1>), dim3(tab.nblocks), dim3(kWG), 0, s, rows, total_n, tab.blk,
+                     tab.nblocks, sc, pc);
+  hipLaunchKernelGGL(prep_scan, dim3(prep_table_rows(1)), dim3(kFinishThreads), 0, s, tab.blk, tab.nblocks, tab.totals);
+  hipLaunchKernelGGL((prep_place<BatchRows, 1, false>), dim3(tab.nblocks), dim3(kWG), 0, s, rows, total_n,
+                     (const long long*)tab.blk, tab.nblocks, (const long long*)tab.totals, desc, segs, huge, sc, pc,
+                     RelabelOut{});
   return hipGetLastError();
 }
 

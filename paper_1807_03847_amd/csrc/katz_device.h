@@ -262,97 +262,321 @@ __device__ inline int block_reserve(int* counter, unsigned mask) {
   return base + ex;
 }
 
-// Binning kernels, shared by every row source (header-only templates; each
-// kernel source instantiates its own copies).
+// ---------------------------------------------------------------------------
+// Binning, shared by every row source (header-only templates; each kernel source
+// instantiates its own copies): prep_count, prep_scan, prep_place.
+//
+// A workgroup takes kPrepRows rows.  prep_count writes its rows and arcs of each
+// class (a bin, or one of SUB parts of a bin by length), its segments of long
+// rows and its longest row into one column of a table; prep_scan, one workgroup
+// per table row, scans them; prep_place then knows every row's position (class by
+// class, rows in their order inside a class) and, from the arcs, where a
+// renumbered row starts.  Three launches and two reads of the offsets; bound by
+// launches on small graphs (23 launches and two read-backs before, 250 us of a
+// call on 2000 nodes) and by the tables written on large ones.
+//
+// Table rows (of nblocks entries): rows per class, arcs per class, segments,
+// longest row; totals holds each row's sum (longest row: maximum).
+// ---------------------------------------------------------------------------
 namespace {
-// ---------------------------------------------------------------------------
-// Prep: per-block bin counts, maximum degree, CSR checks.
-// blk layout: [NUM_BINS + 1][nblocks]; column NUM_BINS counts huge segments.
-// ---------------------------------------------------------------------------
-template <class Rows>
+
+template <int SUB>
+__device__ __forceinline__ int prep_class(long long len, const PrepClasses& pc) {
+  const int b = bin_of_len(len, pc.bb);
+  if constexpr (SUB == 1) return b;
+  int s = 0;
+#pragma unroll
+  for (int i = 0; i < SUB - 1; ++i) s += len <= pc.sub[b][i] ? 1 : 0;
+  return b * SUB + s;
+}
+
+template <class Rows, int SUB>
 __global__ void __launch_bounds__(kWG) prep_count(Rows rows, long long count, long long* blk, int nblocks,
-                                                  RunScalars* sc, BinBounds bb) {
-  __shared__ int cnt[NUM_BINS + 1];
-  if (threadIdx.x <= NUM_BINS) cnt[threadIdx.x] = 0;
+                                                  RunScalars* sc, PrepClasses pc) {
+  constexpr int C = NUM_BINS * SUB;
+  constexpr int kPer = kPrepRows / kWG;
+  __shared__ int cnt[C];
+  __shared__ unsigned long long arcs[C];
+  __shared__ int s_seg, s_max, s_rows;
+  for (int c = threadIdx.x; c < C; c += kWG) {
+    cnt[c] = 0;
+    arcs[c] = 0ull;
+  }
+  if (threadIdx.x == 0) {
+    s_seg = 0;
+    s_max = 0;
+    s_rows = 0;
+  }
   __syncthreads();
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  int dmax = 0;
+  const long long base = (long long)blockIdx.x * kPrepRows;
+  int dmax = 0, full = 0;   // rows with arcs (the empty ones are what is left)
   bool bad = false;
-  if (i < count) {
-    int row;
-    long long off, len;
-    if (!rows.get(i, row, off, len)) {
-      bad = true;
-    } else {
-      const int b = bin_of_len(len, bb);
-      atomicAdd(&cnt[b], 1);
-      if (b == BIN_HUGE) atomicAdd(&cnt[NUM_BINS], (int)((len + kSeg - 1) / kSeg));
-      dmax = (int)len;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const long long i = base + j * kWG + threadIdx.x;
+    if (i < count) {
+      int row;
+      long long off, len;
+      if (!rows.get(i, row, off, len)) {
+        bad = true;
+      } else if (len > 0) {
+        const int c = prep_class<SUB>(len, pc);
+        atomicAdd(&cnt[c], 1);
+        atomicAdd(&arcs[c], (unsigned long long)len);
+        if (c < SUB) atomicAdd(&s_seg, (int)((len + kSeg - 1) / kSeg));   // BIN_HUGE
+        dmax = max(dmax, (int)len);
+        ++full;
+      }
     }
   }
   if constexpr (Rows::kCsr) {
-    if (i == 0 && ((long long)rows.rp[0] != 0 || (long long)rows.rp[count] != rows.nnz)) bad = true;
+    if (base == 0 && threadIdx.x == 0 && ((long long)rows.rp[0] != 0 || (long long)rows.rp[count] != rows.nnz))
+      bad = true;
   }
-  __shared__ int wmax[kWG / kWave];
-  for (int o = 32; o >= 1; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o));
-  if (lane_id() == 0) wmax[threadIdx.x / kWave] = dmax;
+  for (int o = 32; o >= 1; o >>= 1) {
+    dmax = max(dmax, __shfl_xor(dmax, o));
+    full += __shfl_xor(full, o);
+  }
+  if (lane_id() == 0) {
+    atomicMax(&s_max, dmax);
+    atomicAdd(&s_rows, full);
+  }
   if (bad) atomicOr(&sc->err, 1);
   __syncthreads();
-  if (threadIdx.x <= NUM_BINS) blk[(long long)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
-  // Column NUM_BINS + 1: the block's longest row (reduced by prep_finalize).
-  if (threadIdx.x == 0)
-    blk[(long long)(NUM_BINS + 1) * nblocks + blockIdx.x] = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+  const int empty = (int)min((long long)kPrepRows, count - base) - s_rows;
+  for (int c = threadIdx.x; c < C; c += kWG) {
+    blk[(long long)c * nblocks + blockIdx.x] = c == BIN_EMPTY * SUB ? empty : cnt[c];
+    blk[(long long)(C + c) * nblocks + blockIdx.x] = (long long)arcs[c];
+  }
+  if (threadIdx.x == 0) {
+    blk[2ll * C * nblocks + blockIdx.x] = s_seg;
+    blk[(2ll * C + 1) * nblocks + blockIdx.x] = s_max;
+  }
 }
 
-template <class Rows>
-__global__ void __launch_bounds__(kWG) prep_scatter(Rows rows, long long count, const long long* blk,
-                                                    int nblocks, RowDesc* desc, SegDesc* segs,
-                                                    HugeRow* huge, RunScalars* sc, BinBounds bb) {
-  if (sc->err) return;
-  __shared__ int wcnt[NUM_BINS][kWG / kWave];
-  __shared__ int wseg[kWG / kWave];
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  const int lane = lane_id();
+// Workgroup i scans table row i (exclusive, in place) and writes its total; the
+// last row's is the maximum.  Eight entries per thread and round.
+__global__ void __launch_bounds__(kFinishThreads) prep_scan(long long* blk, int nblocks, long long* totals) {
+  constexpr int kPer = 8;
+  __shared__ long long wsum[kFinishThreads / kWave];
+  long long* a = blk + (long long)blockIdx.x * nblocks;
+  const bool maximum = blockIdx.x == gridDim.x - 1;
   const int w = threadIdx.x / kWave;
-  long long off = 0, len = 0;
-  int row = 0;
-  int bin = -1;
-  int nseg = 0;
-  if (i < count) {
-    rows.get(i, row, off, len);
-    bin = bin_of_len(len, bb);
-    if (bin == BIN_HUGE) nseg = (int)((len + kSeg - 1) / kSeg);
-  }
-  int rank_in_wave = 0;
-  for (int b = 0; b < NUM_BINS; ++b) {
-    const unsigned long long mask = __ballot(bin == b);
-    if (bin == b) rank_in_wave = __popcll(mask & lanemask_lt());
-    if (lane == 0) wcnt[b][w] = __popcll(mask);
-  }
-  // Segment offsets of huge rows inside the wave (inclusive scan of nseg).
-  int sinc = nseg;
-  for (int o = 1; o < kWave; o <<= 1) {
-    int y = __shfl_up(sinc, o);
-    if (lane >= o) sinc += y;
-  }
-  if (lane == kWave - 1) wseg[w] = sinc;
-  __syncthreads();
-  if (i < count) {
-    int before = 0;
-    for (int ww = 0; ww < w; ++ww) before += wcnt[bin][ww];
-    const long long pos = blk[(long long)bin * nblocks + blockIdx.x] + before + rank_in_wave;
-    desc[pos] = RowDesc{off, (int32_t)row, (int32_t)len};
-    if (bin == BIN_HUGE) {
-      int sbefore = 0;
-      for (int ww = 0; ww < w; ++ww) sbefore += wseg[ww];
-      const long long part0 = blk[(long long)NUM_BINS * nblocks + blockIdx.x] + sbefore + sinc - nseg;
-      const long long hidx = pos - sc->bin_base[BIN_HUGE];
-      huge[hidx] = HugeRow{(int32_t)row, (int32_t)len, nseg, (int32_t)part0};
-      for (int sg = 0; sg < nseg; ++sg) {
-        const int slen = (int)min((long long)kSeg, len - (long long)sg * kSeg);
-        segs[part0 + sg] = SegDesc{off + (long long)sg * kSeg, slen, (int32_t)(part0 + sg), (int32_t)hidx, 0};
+  long long carry = 0;
+  for (long long base = 0; base < nblocks; base += kPer * kFinishThreads) {
+    const long long i0 = base + (long long)threadIdx.x * kPer;
+    long long v[kPer], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      v[j] = i0 + j < nblocks ? a[i0 + j] : 0;
+      sum = maximum ? max(sum, v[j]) : sum + v[j];
+    }
+    long long inc = sum;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const long long y = __shfl_up(inc, o);
+      if (lane_id() >= o) inc = maximum ? max(inc, y) : inc + y;
+    }
+    __syncthreads();
+    if (lane_id() == kWave - 1) wsum[w] = inc;
+    __syncthreads();
+    long long before = 0, all = 0;
+    for (int q = 0; q < kFinishThreads / kWave; ++q) {
+      if (q == w) before = all;
+      all = maximum ? max(all, wsum[q]) : all + wsum[q];
+    }
+    if (!maximum) {
+      long long run = carry + before + inc - sum;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (i0 + j < nblocks) a[i0 + j] = run;
+        run += v[j];
       }
     }
+    carry = maximum ? max(carry, all) : carry + all;
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// Descriptors (and segments of long rows) in binned order.  Relabel: the row at
+// position p becomes row p of the renumbered graph, its arcs starting where the
+// rows before it end; also the tables of both directions.  The first workgroup
+// writes the bins' sizes to sc.
+template <class Rows, int SUB, bool Relabel>
+__global__ void __launch_bounds__(kWG) prep_place(Rows rows, long long count, const long long* blk, int nblocks,
+                                                  const long long* totals, RowDesc* desc, SegDesc* segs, HugeRow* huge,
+                                                  RunScalars* sc, PrepClasses pc, RelabelOut out) {
+  constexpr int C = NUM_BINS * SUB;
+  constexpr int kPer = kPrepRows / kWG;
+  constexpr int kWaves = kWG / kWave;
+  static_assert(C < kWave, "classes are matched by 6 ballots and scanned by one wave");
+  if (sc->err) return;
+  __shared__ int wcnt[kWaves][C];
+  __shared__ int lbase[C + 1];                 // first local place of each class
+  __shared__ long long gpos[C], garc[C];       // position and arc offset of the class's first local row
+  __shared__ int l_row[kPrepRows], l_len[kPrepRows];
+  __shared__ long long l_off[kPrepRows];       // offset in the source; Relabel: then the arcs before the place
+  __shared__ uint8_t l_cls[kPrepRows];
+  __shared__ long long wsum[kWaves];
+  const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+  if (blockIdx.x == 0 && t == 0) {
+    long long pos = 0;
+    for (int b = 0; b < NUM_BINS; ++b) {
+      long long n_b = 0;
+      for (int s = 0; s < SUB; ++s) n_b += totals[b * SUB + s];
+      sc->bin_base[b] = pos;
+      sc->bin_count[b] = n_b;
+      pos += n_b;
+    }
+    sc->seg_total = totals[2 * C];
+    sc->dmax = (int)totals[2 * C + 1];
+  }
+  for (int c = lane; c < C; c += kWave) wcnt[w][c] = 0;
+  __syncthreads();
+  if (w == 0) {
+    // Class bases: exclusive scans of the totals over the classes.
+    const long long tp = lane < C ? totals[lane] : 0, ta = lane < C ? totals[C + lane] : 0;
+    long long ip = tp, ia = ta;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const long long yp = __shfl_up(ip, o), ya = __shfl_up(ia, o);
+      if (lane >= o) {
+        ip += yp;
+        ia += ya;
+      }
+    }
+    if (lane < C) {
+      gpos[lane] = ip - tp + blk[(long long)lane * nblocks + blockIdx.x];
+      garc[lane] = ia - ta + blk[(long long)(C + lane) * nblocks + blockIdx.x];
+    }
+  }
+  // Each wave's rows (kPer chunks of 64 consecutive ones): the rank of every row
+  // among the wave's rows of its class.
+  const long long base = (long long)blockIdx.x * kPrepRows;
+  int row[kPer], rank[kPer], cls[kPer];
+  long long off[kPer], len[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const long long i = base + w * (kPer * kWave) + j * kWave + lane;
+    cls[j] = kWave - 1;   // none
+    row[j] = 0;
+    off[j] = len[j] = 0;
+    if (i < count) {
+      rows.get(i, row[j], off[j], len[j]);
+      cls[j] = prep_class<SUB>(len[j], pc);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    unsigned long long peers = ~0ull;
+#pragma unroll
+    for (int bit = 0; bit < 6; ++bit) {
+      const bool on = cls[j] >> bit & 1;
+      const unsigned long long m = __ballot(on);
+      peers &= on ? m : ~m;
+    }
+    const int leader = __ffsll((long long)peers) - 1;
+    int old = 0;
+    if (lane == leader && cls[j] < C) {
+      old = wcnt[w][cls[j]];
+      wcnt[w][cls[j]] = old + __popcll(peers);
+    }
+    rank[j] = __shfl(old, leader) + __popcll(peers & lanemask_lt());
+  }
+  __syncthreads();
+  if (w == 0) {
+    int tot = 0;
+    if (lane < C) {
+      for (int q = 0; q < kWaves; ++q) {
+        const int c = wcnt[q][lane];
+        wcnt[q][lane] = tot;
+        tot += c;
+      }
+    }
+    int inc = tot;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (lane < C) lbase[lane] = inc - tot;
+    if (lane == C) lbase[C] = inc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    if (cls[j] >= C) continue;
+    const int c = cls[j];
+    const int in_class = wcnt[w][c] + rank[j];
+    const int p = lbase[c] + in_class;
+    l_row[p] = row[j];
+    l_len[p] = (int)len[j];
+    l_off[p] = off[j];
+    l_cls[p] = (uint8_t)c;
+    if constexpr (Relabel) {
+      const int32_t pos = (int32_t)(gpos[c] + in_class);
+      out.int_of[row[j]] = pos;
+      out.pmap[row[j]] = IdLen{pos, (int32_t)len[j]};
+    }
+  }
+  __syncthreads();
+  const int valid = lbase[C];
+  // Arcs before each place (four consecutive places per thread).
+  long long before[kPer] = {};
+  if constexpr (Relabel) {
+    long long sum = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      before[j] = sum;
+      sum += t * kPer + j < valid ? l_len[t * kPer + j] : 0;
+    }
+    long long inc = sum;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const long long y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (lane == kWave - 1) wsum[w] = inc;
+    __syncthreads();
+    long long start = inc - sum;
+    for (int q = 0; q < w; ++q) start += wsum[q];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      // The source offsets leave by position first; then the places take the arcs.
+      const int p = q * kWG + t;
+      if (p < valid) {
+        const int c = l_cls[p];
+        const long long pos = gpos[c] + (p - lbase[c]);
+        out.ext_of[pos] = l_row[p];
+        out.coff[pos] = l_off[p];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) l_off[t * kPer + j] = start + before[j];
+    __syncthreads();
+  }
+  auto offset_of = [&](int p, int c) {
+    if constexpr (Relabel) return garc[c] + l_off[p] - l_off[lbase[c]];
+    else return l_off[p];
+  };
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int p = q * kWG + t;
+    if (p >= valid) break;
+    const int c = l_cls[p];
+    const long long pos = gpos[c] + (p - lbase[c]);
+    desc[pos] = RowDesc{offset_of(p, c), Relabel ? (int32_t)pos : l_row[p], l_len[p]};
+  }
+  // Rows of more than one segment (their classes come first).
+  const int n_huge = lbase[SUB];
+  long long part = blk[2ll * C * nblocks + blockIdx.x];
+  for (int p = 0; p < n_huge; ++p) {
+    const int c = l_cls[p];
+    const long long pos = gpos[c] + (p - lbase[c]);
+    const int n_p = l_len[p];
+    const int nseg = (n_p + kSeg - 1) / kSeg;
+    const long long o = offset_of(p, c);
+    if (t == 0) huge[pos] = HugeRow{Relabel ? (int32_t)pos : l_row[p], n_p, nseg, (int32_t)part};
+    for (int sg = t; sg < nseg; sg += kWG)
+      segs[part + sg] = SegDesc{o + (long long)sg * kSeg, min(kSeg, n_p - sg * kSeg), (int32_t)(part + sg), (int32_t)pos, 0};
+    part += nseg;
   }
 }
 

@@ -74,6 +74,18 @@ struct BinBounds {
   int g4 = 4, g8 = 8, g16 = 16, g32 = 32, w16 = kShortRowMax, w64 = kWaveRowMax;
 };
 
+// Binning (katz_device.h): rows per workgroup, parts that a bin is cut into by
+// length (in a renumbered graph this orders the nodes of a bin by length, longest
+// first), and the lengths at which they are cut.
+constexpr int kPrepRows = 1024;
+constexpr int kBinParts = 4;
+constexpr int prep_table_rows(int parts) { return 2 * NUM_BINS * parts + 2; }
+constexpr int kPrepTableRows = prep_table_rows(kBinParts);
+struct PrepClasses {
+  BinBounds bb;
+  int sub[NUM_BINS][kBinParts - 1];   // descending; part = how many of them a row's length does not exceed
+};
+
 struct RowDesc {
   int64_t off;
   int32_t row;
@@ -93,6 +105,14 @@ struct SegDesc {
 struct IdLen {
   int32_t id;
   int32_t len;
+};
+
+// The tables of a renumbered graph (ext_of null: the rows keep their order).
+struct RelabelOut {
+  int32_t* ext_of;       // internal -> caller id
+  int32_t* int_of;       // caller -> internal id
+  long long* coff;       // internal id -> offset of its row in the caller's columns
+  IdLen* pmap;           // caller id -> {internal id, row length}
 };
 
 struct HugeRow {
@@ -305,14 +325,23 @@ struct BatchWalk {
 };
 
 // ---- launchers (katz_kernels.hip) ----------------------------------------
-hipError_t launch_prep_count(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz,
-                             long long* blk, int nblocks, RunScalars* sc, const BinBounds& bb, hipStream_t s);
-hipError_t launch_prep_scan(long long* blk, int nblocks, long long* sums, long long* totals, RunScalars* sc,
-                            hipStream_t s);
-hipError_t launch_prep_scatter(const void* row_ptr, int row_ptr_64, int64_t n,
-                               const long long* blk, int nblocks, RowDesc* desc,
-                               SegDesc* segs, HugeRow* huge, RunScalars* sc, const BinBounds& bb,
-                               hipStream_t s);
+// Binning scratch: the per-workgroup table (prep_table_rows x nblocks entries;
+// kBinParts where a graph is renumbered or a state binned, else 1) and its row
+// totals.
+struct PrepTable {
+  long long* blk;
+  long long* totals;
+  int nblocks;           // ceil(rows / kPrepRows)
+};
+PrepClasses prep_classes(const BinBounds& bb);
+// Offsets checked (sc->err) and counted; no descriptors.
+hipError_t launch_prep_count(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz, const PrepTable& tab,
+                             RunScalars* sc, const BinBounds& bb, hipStream_t s);
+// Bins of a CSR (sizes, longest row and error flag in sc).  out.ext_of set: the
+// bins of the renumbered graph, and its tables.
+hipError_t launch_prep_csr(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz, const PrepTable& tab,
+                           RowDesc* desc, SegDesc* segs, HugeRow* huge, const RelabelOut& out, RunScalars* sc,
+                           const BinBounds& bb, hipStream_t s);
 // segs / nseg / huge: the bins' segments of rows longer than kBlockRowMax
 // (their symmetry is checked segment by segment).
 hipError_t launch_validate_strict(const RowDesc* desc, long long n, const SegDesc* segs, long long nseg,
@@ -363,9 +392,11 @@ hipError_t launch_init_run(RunScalars* sc, int64_t n, double* sigma, double* sig
                            unsigned* xmax32, unsigned long long* xmax64, int max_iter,
                            unsigned* hist, hipStream_t s);
 
-hipError_t launch_prep_rows(const int32_t* ids, long long count, const long long* off, const int* len,
-                            long long* blk, int nblocks, long long* sums, long long* totals, RowDesc* desc,
-                            SegDesc* segs, HugeRow* huge, RunScalars* sc, const BinBounds& bb, hipStream_t s);
+// Bins of rows of a slack CSR: of ids[0..count), or of all when ids is null
+// (parts: each bin ordered by length, then by row; else by row).
+hipError_t launch_prep_rows(const int32_t* ids, long long count, const long long* off, const int* len, bool parts,
+                            const PrepTable& tab, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
+                            const BinBounds& bb, hipStream_t s);
 
 // ---- dynamic update (katz_dynamic.hip) ----------------------------------------
 hipError_t launch_scan_ll(const long long* in, long long count, long long* out, long long* sums,
@@ -424,9 +455,6 @@ hipError_t launch_c_from_history_f32(const int32_t* rows, long long count, float
 hipError_t launch_max_of_vector_f32(const float* x, long long n, unsigned* out, hipStream_t s);
 
 hipError_t launch_reset_flags(RunScalars* sc, hipStream_t s);
-hipError_t launch_relabel(const RowDesc* desc, long long n, int32_t* ext_of, int32_t* int_of, long long* coff,
-                          IdLen* pmap, long long* len_ll, int* len32, long long* noff, long long* sums,
-                          long long* total, hipStream_t s);
 hipError_t launch_gather_int(const int32_t* rows, long long t, const int* src, int* out, hipStream_t s);
 hipError_t launch_gather_ll(const int32_t* rows, long long t, const long long* src, long long* out, hipStream_t s);
 hipError_t launch_min_lower_active(const BoundArgs& b, const int32_t* act, const int* m_ptr,
@@ -449,8 +477,7 @@ constexpr int kSmallActive = 1 << 16;   // |M| at or below which one workgroup s
 // ---- batched form (katz_batch.hip) --------------------------------------------
 hipError_t launch_batch_prep(const long long* gbase, const void* const* grp, const int* grp64, const long long* gnnz,
                              const long long* gabase, const int32_t* const* gcol, int count, long long total_n,
-                             long long total_nnz, int* gid_of, long long* blk, int nblocks, long long* sums,
-                             long long* totals, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
+                             long long total_nnz, int* gid_of, const PrepTable& tab, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
                              int validate, const BinBounds& bb, hipStream_t s);
 hipError_t launch_batch_dmax(const void* const* grp, const int* grp64, const long long* gbase, int count,
                              long long total_n, int* gdmax, hipStream_t s);

@@ -17,6 +17,7 @@
 // enqueue iterations ahead of reading the flag.
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdint>
 #include <map>
 #include <mutex>
@@ -74,31 +75,6 @@ struct ListRows {
     return true;
   }
 };
-
-// After the device-wide scans of the bin counts (bin-major) and of the segment
-// counts: bin bases, bin sizes, segment total and the longest row.
-__global__ void __launch_bounds__(kFinishThreads) prep_finalize(const long long* blk, int nblocks,
-                                                                const long long* totals, RunScalars* sc) {
-  if (sc->err) return;
-  long long dm = 0;
-  for (long long i = threadIdx.x; i < nblocks; i += kFinishThreads)
-    dm = max(dm, blk[(long long)(NUM_BINS + 1) * nblocks + i]);
-  for (int o = 32; o >= 1; o >>= 1) dm = max(dm, __shfl_xor(dm, o));
-  __shared__ long long wm[kFinishThreads / kWave];
-  if (lane_id() == 0) wm[threadIdx.x / kWave] = dm;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < kFinishThreads / kWave; ++i) dm = max(dm, wm[i]);
-    sc->dmax = (int)dm;
-    for (int b = 0; b < NUM_BINS; ++b) {
-      const long long lo = blk[(long long)b * nblocks];
-      const long long hi = b + 1 < NUM_BINS ? blk[(long long)(b + 1) * nblocks] : totals[0];
-      sc->bin_base[b] = lo;
-      sc->bin_count[b] = hi - lo;
-    }
-    sc->seg_total = totals[1];
-  }
-}
 
 // Strict CSR checks: rows strictly increasing (no duplicates), no self-loops.
 __global__ void __launch_bounds__(kWG) validate_strict(const RowDesc* desc, long long count,
@@ -1155,22 +1131,6 @@ __global__ void init_run(RunScalars* sc, long long n, double* sigma, double* sig
   for (long long i = t; i < 2 * kDigits; i += stride) hist[i] = 0u;
 }
 
-// Internal renumbering: new id i = position of the row in the binned order
-// (degree classes, longest first).  ext_of[i] is the caller's id of new node i.
-__global__ void __launch_bounds__(kWG) relabel_ids(const RowDesc* desc, long long n, int32_t* ext_of,
-                                                   int32_t* int_of, long long* coff, IdLen* pmap, long long* len_ll,
-                                                   int* len32) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i >= n) return;
-  const RowDesc d = desc[i];
-  ext_of[i] = d.row;
-  int_of[d.row] = (int32_t)i;
-  coff[i] = d.off;
-  pmap[d.row] = IdLen{(int32_t)i, d.len};
-  len_ll[i] = d.len;
-  len32[i] = d.len;
-}
-
 __global__ void reset_flags(RunScalars* sc) {
   sc->err = 0;
   sc->done = 0;
@@ -1187,18 +1147,6 @@ __global__ void reset_flags(RunScalars* sc) {
 
 }  // namespace
 
-// Renumbering: new id i = position of row i in the binned order, the tables
-// of both directions, and the offsets of the renumbered rows (noff, an
-// exclusive scan of the lengths).  The renamed column ids are written by walk
-// step 2 (walk_step<F32, true>), which reads every column id anyway.
-hipError_t launch_relabel(const RowDesc* desc, long long n, int32_t* ext_of, int32_t* int_of, long long* coff,
-                          IdLen* pmap, long long* len_ll, int* len32, long long* noff, long long* sums,
-                          long long* total, hipStream_t s) {
-  const unsigned nb = (unsigned)std::max<long long>(1, (n + kWG - 1) / kWG);
-  hipLaunchKernelGGL(relabel_ids, dim3(nb), dim3(kWG), 0, s, desc, n, ext_of, int_of, coff, pmap, len_ll, len32);
-  return launch_scan_ll(len_ll, n, noff, sums, total, s);
-}
-
 hipError_t launch_reset_flags(RunScalars* sc, hipStream_t s) {
   hipLaunchKernelGGL(reset_flags, dim3(1), dim3(1), 0, s, sc);
   return hipGetLastError();
@@ -1207,62 +1155,74 @@ hipError_t launch_reset_flags(RunScalars* sc, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-hipError_t launch_prep_count(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz, long long* blk,
-                             int nblocks, RunScalars* sc, const BinBounds& bb, hipStream_t s) {
-  if (row_ptr_64)
-    hipLaunchKernelGGL(prep_count<CsrRows<int64_t>>, dim3(nblocks), dim3(kWG), 0, s,
-                       CsrRows<int64_t>{(const int64_t*)row_ptr, (long long)nnz}, (long long)n, blk, nblocks, sc, bb);
-  else
-    hipLaunchKernelGGL(prep_count<CsrRows<int32_t>>, dim3(nblocks), dim3(kWG), 0, s,
-                       CsrRows<int32_t>{(const int32_t*)row_ptr, (long long)nnz}, (long long)n, blk, nblocks, sc, bb);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep_scan(long long* blk, int nblocks, long long* sums, long long* totals, RunScalars* sc,
-                            hipStream_t s) {
-  hipError_t e = launch_scan_ll(blk, (long long)NUM_BINS * nblocks, blk, sums, totals, s);
-  if (e != hipSuccess) return e;
-  e = launch_scan_ll(blk + (long long)NUM_BINS * nblocks, nblocks, blk + (long long)NUM_BINS * nblocks, sums,
-                     totals + 1, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prep_finalize, dim3(1), dim3(kFinishThreads), 0, s, (const long long*)blk, nblocks,
-                     (const long long*)totals, sc);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep_scatter(const void* row_ptr, int row_ptr_64, int64_t n, const long long* blk,
-                               int nblocks, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
-                               const BinBounds& bb, hipStream_t s) {
-  if (row_ptr_64)
-    hipLaunchKernelGGL(prep_scatter<CsrRows<int64_t>>, dim3(nblocks), dim3(kWG), 0, s,
-                       CsrRows<int64_t>{(const int64_t*)row_ptr, 0}, (long long)n, blk, nblocks, desc, segs, huge,
-                       sc, bb);
-  else
-    hipLaunchKernelGGL(prep_scatter<CsrRows<int32_t>>, dim3(nblocks), dim3(kWG), 0, s,
-                       CsrRows<int32_t>{(const int32_t*)row_ptr, 0}, (long long)n, blk, nblocks, desc, segs, huge,
-                       sc, bb);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep_rows(const int32_t* ids, long long count, const long long* off, const int* len,
-                            long long* blk, int nblocks, long long* sums, long long* totals, RowDesc* desc,
-                            SegDesc* segs, HugeRow* huge, RunScalars* sc, const BinBounds& bb, hipStream_t s) {
-  if (ids) {
-    const ListRows rows{ids, off, len};
-    hipLaunchKernelGGL(prep_count<ListRows>, dim3(nblocks), dim3(kWG), 0, s, rows, count, blk, nblocks, sc, bb);
-    const hipError_t e = launch_prep_scan(blk, nblocks, sums, totals, sc, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(prep_scatter<ListRows>, dim3(nblocks), dim3(kWG), 0, s, rows, count, (const long long*)blk,
-                       nblocks, desc, segs, huge, sc, bb);
-  } else {
-    const SlackRows rows{off, len};
-    hipLaunchKernelGGL(prep_count<SlackRows>, dim3(nblocks), dim3(kWG), 0, s, rows, count, blk, nblocks, sc, bb);
-    const hipError_t e = launch_prep_scan(blk, nblocks, sums, totals, sc, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(prep_scatter<SlackRows>, dim3(nblocks), dim3(kWG), 0, s, rows, count, (const long long*)blk,
-                       nblocks, desc, segs, huge, sc, bb);
+// A bin's parts: its range of lengths cut in equal ratios (the longest rows: at
+// 4, 16 and 64 segments).
+PrepClasses prep_classes(const BinBounds& bb) {
+  PrepClasses pc{};
+  pc.bb = bb;
+  const int hi[NUM_BINS] = {0, kBlockRowMax, bb.w64, bb.w16, bb.g32, bb.g16, bb.g8, bb.g4, 0};
+  for (int b = 0; b < NUM_BINS; ++b) {
+    const double top = b == BIN_HUGE ? 256.0 * kSeg : hi[b];
+    const double low = b == BIN_HUGE ? kSeg : b + 1 < NUM_BINS ? std::max(hi[b + 1], 1) : 1;
+    for (int i = 0; i < kBinParts - 1; ++i)
+      pc.sub[b][i] = b == BIN_EMPTY ? -1 : (int)(top * std::pow(low / top, (i + 1.0) / kBinParts));
   }
+  return pc;
+}
+
+namespace {
+
+template <class Rows, int SUB, bool Relabel>
+hipError_t bin_launches(const Rows& rows, long long count, const PrepTable& tab, RowDesc* desc, SegDesc* segs,
+                        HugeRow* huge, const RelabelOut& out, RunScalars* sc, const PrepClasses& pc, hipStream_t s) {
+  hipLaunchKernelGGL((prep_count<Rows, SUB>), dim3(tab.nblocks), dim3(kWG), 0, s, rows, count, tab.blk, tab.nblocks, sc,
+                     pc);
+  hipLaunchKernelGGL(prep_scan, dim3(prep_table_rows(SUB)), dim3(kFinishThreads), 0, s, tab.blk, tab.nblocks,
+                     tab.totals);
+  hipLaunchKernelGGL((prep_place<Rows, SUB, Relabel>), dim3(tab.nblocks), dim3(kWG), 0, s, rows, count,
+                     (const long long*)tab.blk, tab.nblocks, (const long long*)tab.totals, desc, segs, huge, sc, pc,
+                     out);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prep_count(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz, const PrepTable& tab,
+                             RunScalars* sc, const BinBounds& bb, hipStream_t s) {
+  const PrepClasses pc = prep_classes(bb);
+  if (row_ptr_64)
+    hipLaunchKernelGGL((prep_count<CsrRows<int64_t>, 1>), dim3(tab.nblocks), dim3(kWG), 0, s,
+                       CsrRows<int64_t>{(const int64_t*)row_ptr, (long long)nnz}, (long long)n, tab.blk, tab.nblocks, sc,
+                       pc);
+  else
+    hipLaunchKernelGGL((prep_count<CsrRows<int32_t>, 1>), dim3(tab.nblocks), dim3(kWG), 0, s,
+                       CsrRows<int32_t>{(const int32_t*)row_ptr, (long long)nnz}, (long long)n, tab.blk, tab.nblocks, sc,
+                       pc);
+  return hipGetLastError();
+}
+
+hipError_t launch_prep_csr(const void* row_ptr, int row_ptr_64, int64_t n, int64_t nnz, const PrepTable& tab,
+                           RowDesc* desc, SegDesc* segs, HugeRow* huge, const RelabelOut& out, RunScalars* sc,
+                           const BinBounds& bb, hipStream_t s) {
+  const PrepClasses pc = prep_classes(bb);
+  const CsrRows<int64_t> r64{(const int64_t*)row_ptr, (long long)nnz};
+  const CsrRows<int32_t> r32{(const int32_t*)row_ptr, (long long)nnz};
+  if (out.ext_of)
+    return row_ptr_64 ? bin_launches<CsrRows<int64_t>, kBinParts, true>(r64, n, tab, desc, segs, huge, out, sc, pc, s)
+                      : bin_launches<CsrRows<int32_t>, kBinParts, true>(r32, n, tab, desc, segs, huge, out, sc, pc, s);
+  return row_ptr_64 ? bin_launches<CsrRows<int64_t>, 1, false>(r64, n, tab, desc, segs, huge, out, sc, pc, s)
+                    : bin_launches<CsrRows<int32_t>, 1, false>(r32, n, tab, desc, segs, huge, out, sc, pc, s);
+}
+
+hipError_t launch_prep_rows(const int32_t* ids, long long count, const long long* off, const int* len, bool parts,
+                            const PrepTable& tab, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
+                            const BinBounds& bb, hipStream_t s) {
+  const PrepClasses pc = prep_classes(bb);
+  const RelabelOut none{};
+  if (ids) return bin_launches<ListRows, 1, false>(ListRows{ids, off, len}, count, tab, desc, segs, huge, none, sc, pc, s);
+  const SlackRows rows{off, len};
+  return parts ? bin_launches<SlackRows, kBinParts, false>(rows, count, tab, desc, segs, huge, none, sc, pc, s)
+               : bin_launches<SlackRows, 1, false>(rows, count, tab, desc, segs, huge, none, sc, pc, s);
 }
 
 hipError_t launch_validate_strict(const RowDesc* desc, long long n, const SegDesc* segs, long long nseg,

@@ -223,3 +223,35 @@ def test_state_strict_checks_across_runs_of_empty_rows(katz, undirected):
         with pytest.raises(katz.KatzError) as e:
             katz.create_state(*dev(rp, bad), 16, alpha=alpha, undirected=undirected)
         assert e.value.code == katz.E_CSR
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2049, 13000])
+@pytest.mark.parametrize("table", [None, [1, 2, 3, 5, 9, 17]])
+@pytest.mark.parametrize("rp64", [True, False])
+def test_binning_block_edges(katz, n, table, rp64):
+    """Rows around the 1024-row share of a binning workgroup, in every length
+    class: hubs of several segments (n = 13000: in different workgroups), equal
+    lengths, empty rows.  Bounds equal the oracle's, and the renumbered run is
+    bitwise the run in caller order."""
+    say("binning edges", n, table, rp64)
+    rng = np.random.default_rng(n)
+    src, dst = [], []
+    for hub in {0, n // 2, n - 1}:                        # up to n - 1 arcs each
+        leaves = rng.choice(n, size=(n * 3) // 4, replace=False)
+        src.append(np.full(leaves.size, hub))
+        dst.append(leaves)
+    body = rng.integers(0, n, size=(2, 3 * n))
+    keep = (body % 5 != 4).all(axis=0)                    # every fifth node stays near-empty
+    rp, col = sg.from_edges(n, np.concatenate(src + [body[0][keep]]), np.concatenate(dst + [body[1][keep]]))
+    alpha = 1.0 / (1 + sg.max_degree(rp))
+    katz.tuning_set(bin_bounds=table)
+    rp_t = torch.from_numpy(np.asarray(rp, dtype=np.int64 if rp64 else np.int32)).cuda()
+    col_t = torch.from_numpy(np.asarray(col, dtype=np.int32)).cuda()
+    for precision in ("fp64", "fp32"):
+        lo, up = katz.bounds(rp_t, col_t, 4, alpha=alpha, precision=precision)
+        lo2, up2 = katz.bounds(rp_t, col_t, 4, alpha=alpha, precision=precision, flags=katz.FLAG_NO_REORDER)
+        assert torch.equal(lo, lo2) and torch.equal(up, up2)
+        if precision == "fp64":
+            olo, oup = oracle.bounds(rp, col, alpha, 4)
+            np.testing.assert_allclose(lo.cpu().numpy(), olo, rtol=1e-12, atol=0)
+            np.testing.assert_allclose(up.cpu().numpy(), oup, rtol=1e-12, atol=0)
