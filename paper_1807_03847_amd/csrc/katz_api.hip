@@ -590,14 +590,18 @@ void fp32_tables(Scalars& S, long long dmax, int max_iter, const BinBounds& bb, 
 }  // namespace katz
 
 namespace katz {
-// Device scratch of one update batch; grows to the largest batch seen.
+// Device scratch of one update batch, and the pinned memory it is staged in; both
+// grow to the largest batch seen.
 struct UpdateBufs {
-  int32_t* pairs = nullptr; size_t pairs_cap = 0;       // a[...] then b[...]
-  int32_t* rows = nullptr; size_t rows_cap = 0;
-  long long* ll = nullptr; size_t ll_cap = 0;           // ins_off | del_off | new_len | sbase | dest_off
-  int* ints = nullptr; size_t ints_cap = 0;             // ins_cnt | del_cnt | delta | dest_cap | caps
-  int32_t* dst = nullptr; size_t dst_cap = 0;           // ins_dst | del_dst
-  int32_t* scratch = nullptr; size_t scratch_cap = 0;
+  char* dev = nullptr;
+  char* host = nullptr;       // pinned, same layout as dev
+  size_t cap = 0;
+  int32_t* scratch = nullptr; // merged rows
+  size_t scratch_cap = 0;
+  ~UpdateBufs() {
+    if (dev) (void)hipFree(dev);
+    if (host) (void)hipHostFree(host);
+  }
 };
 }  // namespace katz
 
@@ -651,21 +655,20 @@ struct katz_state {
   // Re-walk scratch.
   int* level_of = nullptr;
   int32_t* clist = nullptr;
-  int* counter = nullptr;
-  unsigned long long* frontier_arcs = nullptr;   // arcs of the last expansion's new frontier
+  int* counter = nullptr;          // nodes found by the reactivation test
+  katz::FrontierCount* fcount = nullptr;
   long long* foff = nullptr;       // frontier row offsets of an expansion (n), scan scratch, total
   long long* fsums = nullptr;
   long long* ftotal = nullptr;
   int* dmax_dev = nullptr;
-  int* err_dev = nullptr;
   unsigned long long* min_bits = nullptr;
   uint8_t* tmark = nullptr;        // touched rows
   katz::RunScalars* sc2 = nullptr;       // prep of one level
   int32_t* out_ids = nullptr;      // [k] staging for outputs in host memory
   double* out_lo = nullptr;
   double* out_up = nullptr;
-  katz::UpdateBufs ub;
-  katz::UpdateBufs rub;            // the same for the reverse graph of a directed state
+  katz::UpdateBufs ub[2];          // the staged batch; the merge's plan
+  bool bins_pending = false;       // the whole-graph bins are being rebuilt (their sizes on the way to hs.ring[1])
   int X_dev_synced = 0;            // entries of X already copied to X_dev
   katz::HostSync hs;
   std::vector<void*> owned;
@@ -739,6 +742,7 @@ struct Run {
   int32_t* ncol = nullptr;
   WalkMax walk_max = {};       // maxima the next selection reduces (enqueue_walk)
   Publish pub = {};            // where the next selection publishes its flags
+  long long m_known = -1;      // |M| before the first pass, if known
 
   // Whether one workgroup may run converged() (its LDS sort holds the top-k).
   bool one_workgroup_select() const { return (criterion == KATZ_TOPK || criterion == KATZ_RANKING) && k <= kMaxK; }
@@ -1013,7 +1017,20 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
   } at[2] = {};
   // Upper bound of |M| from the latest flags read back; M never grows inside
   // this loop, so a bound read one pass behind stays valid.
-  long long m_known = run.n;
+  long long m_known = run.m_known >= 0 ? run.m_known : run.n;
+  if (check_first && hs.flags && run.one_workgroup_select()) {
+    // A changed graph is usually certified at its r: the next pass is not
+    // enqueued before that is known.
+    const unsigned seq = ++hs.seq;
+    run.pub = Publish{&hs.flags[seq & 1], seq};
+    at[0] = PassAt{r - 1, run.cur ^ 1};
+    run.walk_max = WalkMax{nullptr, 0};
+    KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, m_known <= kSmallActive));
+    KATZ_TRY(wait_flags(hs, seq, run.w->sc, &last, s));
+    stopped = last.stopped();
+    m_known = last.m;
+    check_first = false;
+  }
   while (!stopped) {
     const Range range("katz iteration", r);
     const bool small_m = m_known <= kSmallActive && run.one_workgroup_select();
@@ -2345,11 +2362,28 @@ int bin_rows(katz_state* st, Bins& b, RunScalars* sc, const int32_t* ids, long l
 }
 
 // The whole-graph bins, rebuilt if an update changed row lengths since they
-// were built (the maximum row length is tracked by the updates themselves).
+// were built (the maximum row length is tracked by the updates themselves).  An
+// update starts this as soon as its rows are merged (begin_bins); the sizes are
+// then on the host by the time a whole-graph walk asks for them.
+int begin_bins(katz_state* st, hipStream_t s) {
+  Bins& b = st->bins;
+  KATZ_HIP(launch_reset_flags(st->sc2, s));
+  b.tab.nblocks = prep_blocks(st->n);
+  KATZ_HIP(launch_prep_rows(nullptr, st->n, st->row_off, st->row_len, true, b.tab, b.desc, b.segs, b.huge, st->sc2, b.bb,
+                            s));
+  KATZ_HIP(hipMemcpyAsync(&st->hs.ring[1], st->sc2, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+  st->bins_pending = true;
+  return KATZ_OK;
+}
+
 int refresh_bins(katz_state* st, hipStream_t s) {
   if (!st->bins_stale) return KATZ_OK;
+  if (!st->bins_pending) KATZ_TRY(begin_bins(st, s));
+  KATZ_HIP(hipStreamSynchronize(s));
+  st->bins_pending = false;
+  if (st->hs.ring[1].err) return KATZ_E_HIP;
   const int dmax = st->bins.dmax;
-  KATZ_TRY(bin_rows(st, st->bins, st->sc2, nullptr, st->n, s));
+  st->bins.read_back(st->hs.ring[1], st->n);
   st->bins.dmax = dmax;
   st->bins_stale = false;
   return KATZ_OK;
@@ -2542,12 +2576,11 @@ int alloc_run_buffers(katz_state* st, hipStream_t s) {
   st->level_of = dalloc<int>(st, n);
   st->clist = dalloc<int32_t>(st, n);
   st->counter = dalloc<int>(st, 1);
-  st->frontier_arcs = dalloc<unsigned long long>(st, 1);
+  st->fcount = dalloc<FrontierCount>(st, 1);
   st->foff = dalloc<long long>(st, n);
   st->fsums = dalloc<long long>(st, scan_sums_capacity(n));
   st->ftotal = dalloc<long long>(st, 1);
   st->dmax_dev = dalloc<int>(st, 1);
-  st->err_dev = dalloc<int>(st, 1);
   st->min_bits = dalloc<unsigned long long>(st, 1);
   st->tmark = dalloc<uint8_t>(st, n);
   st->out_ids = dalloc<int32_t>(st, st->k);
@@ -2561,9 +2594,9 @@ int alloc_run_buffers(katz_state* st, hipStream_t s) {
   }
   if (!w.c || !w.act[0] || !w.act[1] || !w.keys || !w.cand_key[0] || !w.cand_key[1] || !w.cand_v[0] ||
       !w.cand_v[1] || !w.hist || !w.xmax32 || !w.xmax64 || !w.sigma || !w.sigma_sum || !w.top_sorted ||
-      !w.top_lo || !w.top_up || !w.mark || !w.rest_bits || !st->level_of || !st->clist || !st->counter || !st->frontier_arcs ||
+      !w.top_lo || !w.top_up || !w.mark || !w.rest_bits || !st->level_of || !st->clist || !st->counter || !st->fcount ||
       !st->foff || !st->fsums || !st->ftotal ||
-      !st->dmax_dev || !st->err_dev || !st->min_bits || !st->tmark || !st->out_ids || !st->out_lo || !st->out_up)
+      !st->dmax_dev || !st->min_bits || !st->tmark || !st->out_ids || !st->out_lo || !st->out_up)
     return KATZ_E_OOM;
   KATZ_HIP(hipMemsetAsync(w.mark, 0, n, s));
   KATZ_HIP(hipMemsetAsync(st->tmark, 0, n, s));
@@ -2813,110 +2846,218 @@ int grow_pool(katz_state* st, SlackRef c, long long need, hipStream_t s) {
   return KATZ_OK;
 }
 
-// The touched rows of one slack CSR, read before anything changes.
-struct Touched {
-  long long t = 0;
-  std::vector<long long> new_len, offs;
-  std::vector<int> caps;
+// ---------------------------------------------------------------------------
+// The batch on its way through the device.  Everything it takes is laid out in one
+// block, staged in pinned memory and uploaded by one copy; what the device finds
+// comes back by one copy (before, 10 uploads and 4 read-backs from pageable
+// memory, each a stall of 10 to 30 us).
+// ---------------------------------------------------------------------------
+struct Blob {
+  UpdateBufs& b;
+  size_t used = 0;
+  bool measuring = true;
+
+  template <class T>
+  T* dev(T* host) const {
+    return reinterpret_cast<T*>(b.dev + (reinterpret_cast<char*>(host) - b.host));
+  }
+  template <class T>
+  T* take(size_t count) {
+    char* p = measuring ? nullptr : b.host + used;
+    used += (count * sizeof(T) + 15) & ~size_t(15);
+    return reinterpret_cast<T*>(p);
+  }
+  // Room for `used` bytes; what take() returns next is real.
+  int allocate() {
+    measuring = false;
+    const size_t need = used;
+    used = 0;
+    if (need <= b.cap) return KATZ_OK;
+    if (b.dev) (void)hipFree(b.dev);
+    if (b.host) (void)hipHostFree(b.host);
+    b.dev = b.host = nullptr;
+    b.cap = 0;
+    const size_t cap = need + need / 2 + 4096;
+    if (hipMalloc((void**)&b.dev, cap) != hipSuccess || hipHostMalloc((void**)&b.host, cap) != hipSuccess) {
+      (void)hipGetLastError();
+      if (b.dev) (void)hipFree(b.dev);
+      b.dev = b.host = nullptr;
+      return KATZ_E_OOM;
+    }
+    b.cap = cap;
+    return KATZ_OK;
+  }
 };
 
-// Uploads one set of row groups into ub (rows in internal ids) and reads back
-// each touched row's new length, capacity and offset.  The touched rows are
-// left marked in st->tmark.
-int stage_groups(katz_state* st, UpdateBufs& ub, SlackRef c, const RowGroups& g, Touched& tt, hipStream_t s) {
-  const long long t = (long long)g.rows.size();
-  tt.t = t;
-  if (t == 0) return KATZ_OK;
-  KATZ_TRY(grow_buf(st, ub.rows, ub.rows_cap, t));
-  KATZ_TRY(grow_buf(st, ub.ll, ub.ll_cap, 5 * t));
-  KATZ_TRY(grow_buf(st, ub.ints, ub.ints_cap, 5 * t));
-  KATZ_TRY(grow_buf(st, ub.dst, ub.dst_cap, g.ins_dst.size() + g.del_dst.size()));
-  long long* d_ins_off = ub.ll;
-  long long* d_del_off = ub.ll + t;
-  long long* d_new_len = ub.ll + 2 * t;
-  long long* d_offs = ub.ll + 4 * t;
-  int* d_ins_cnt = ub.ints;
-  int* d_del_cnt = ub.ints + t;
-  int* d_delta = ub.ints + 2 * t;
-  int* d_caps = ub.ints + 4 * t;
-  int32_t* d_ins_dst = ub.dst;
-  int32_t* d_del_dst = ub.dst + g.ins_dst.size();
-  KATZ_HIP(hipMemcpyAsync(ub.rows, g.rows.data(), sizeof(int32_t) * t, hipMemcpyHostToDevice, s));
-  if (st->int_of) KATZ_HIP(launch_map_ids(ub.rows, t, st->int_of, s));   // touched rows, internal ids
-  KATZ_HIP(hipMemcpyAsync(d_ins_off, g.ins_off.data(), sizeof(long long) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_del_off, g.del_off.data(), sizeof(long long) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_ins_cnt, g.ins_cnt.data(), sizeof(int) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_del_cnt, g.del_cnt.data(), sizeof(int) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_delta, g.delta.data(), sizeof(int) * t, hipMemcpyHostToDevice, s));
-  if (!g.ins_dst.empty())
-    KATZ_HIP(hipMemcpyAsync(d_ins_dst, g.ins_dst.data(), sizeof(int32_t) * g.ins_dst.size(), hipMemcpyHostToDevice,
-                            s));
-  if (!g.del_dst.empty())
-    KATZ_HIP(hipMemcpyAsync(d_del_dst, g.del_dst.data(), sizeof(int32_t) * g.del_dst.size(), hipMemcpyHostToDevice,
-                            s));
-  KATZ_HIP(launch_touched_lengths(ub.rows, t, d_delta, c.row_len, d_new_len, st->tmark, s));
-  KATZ_HIP(launch_gather_int(ub.rows, t, c.row_cap, d_caps, s));
-  KATZ_HIP(launch_gather_ll(ub.rows, t, c.row_off, d_offs, s));
-  tt.new_len.resize(t);
-  tt.caps.resize(t);
-  tt.offs.resize(t);
-  KATZ_HIP(hipMemcpyAsync(tt.new_len.data(), d_new_len, sizeof(long long) * t, hipMemcpyDeviceToHost, s));
-  KATZ_HIP(hipMemcpyAsync(tt.caps.data(), d_caps, sizeof(int) * t, hipMemcpyDeviceToHost, s));
-  KATZ_HIP(hipMemcpyAsync(tt.offs.data(), d_offs, sizeof(long long) * t, hipMemcpyDeviceToHost, s));
-  KATZ_HIP(hipStreamSynchronize(s));
-  return KATZ_OK;
-}
+// One slack CSR's share of a batch: host addresses (pinned), and the kernels'
+// view of them on the device.
+struct GroupStage {
+  const RowGroups* g = nullptr;
+  int32_t *rows_in, *ins_dst, *del_dst, *ins_grp, *del_grp;
+  long long *ins_off, *del_off;
+  // Report.
+  long long* offs;
+  int *caps, *new_len;
+  // Device only (their host bytes are unused).
+  int32_t *rows, *ins_pos, *del_pos;
+  UpdateRows dev{};
 
-// Pool entries the touched rows that outgrow their capacity will take.
-long long growth_need(const Touched& tt) {
-  long long need = 0;
-  for (long long i = 0; i < tt.t; ++i)
-    if (tt.new_len[i] > tt.caps[i]) need += slack_cap_host(tt.new_len[i]);
-  return need;
+  long long t() const { return (long long)g->rows.size(); }
+
+  void take_inputs(Blob& bl) {
+    const size_t n = g->rows.size();
+    ins_off = bl.take<long long>(n + 1);
+    del_off = bl.take<long long>(n + 1);
+    rows_in = bl.take<int32_t>(n);
+    ins_dst = bl.take<int32_t>(g->ins_dst.size());
+    del_dst = bl.take<int32_t>(g->del_dst.size());
+    ins_grp = bl.take<int32_t>(g->ins_dst.size());
+    del_grp = bl.take<int32_t>(g->del_dst.size());
+  }
+  void take_report(Blob& bl) {
+    const size_t n = g->rows.size();
+    offs = bl.take<long long>(n);
+    caps = bl.take<int>(n);
+    new_len = bl.take<int>(n);
+  }
+  void take_device(Blob& bl) {
+    rows = bl.take<int32_t>(g->rows.size());
+    ins_pos = bl.take<int32_t>(g->ins_dst.size());
+    del_pos = bl.take<int32_t>(g->del_dst.size());
+  }
+  void fill(const Blob& bl, int* err) {
+    auto put = [](auto* to, const auto& v) {
+      if (!v.empty()) std::memcpy(to, v.data(), sizeof(v[0]) * v.size());
+    };
+    put(ins_off, g->ins_off);
+    put(del_off, g->del_off);
+    put(rows_in, g->rows);
+    put(ins_dst, g->ins_dst);
+    put(del_dst, g->del_dst);
+    put(ins_grp, g->ins_grp);
+    put(del_grp, g->del_grp);
+    dev.t = t();
+    dev.ni = (long long)g->ins_dst.size();
+    dev.nd = (long long)g->del_dst.size();
+    dev.rows_in = bl.dev(rows_in);
+    dev.ins_off = bl.dev(ins_off);
+    dev.del_off = bl.dev(del_off);
+    dev.ins_dst = bl.dev(ins_dst);
+    dev.del_dst = bl.dev(del_dst);
+    dev.ins_grp = bl.dev(ins_grp);
+    dev.del_grp = bl.dev(del_grp);
+    dev.rows = bl.dev(rows);
+    dev.offs = bl.dev(offs);
+    dev.caps = bl.dev(caps);
+    dev.new_len = bl.dev(new_len);
+    dev.ins_pos = bl.dev(ins_pos);
+    dev.del_pos = bl.dev(del_pos);
+    dev.err = bl.dev(err);
+  }
+  long long delta(long long i) const {
+    return (g->ins_off[i + 1] - g->ins_off[i]) - (g->del_off[i + 1] - g->del_off[i]);
+  }
+  // Pool entries the rows that outgrow their capacity will take.
+  long long growth() const {
+    long long need = 0;
+    for (long long i = 0; i < t(); ++i)
+      if (new_len[i] > caps[i]) need += slack_cap_host(new_len[i]);
+    return need;
+  }
+};
+
+// Uploads the batch, checks it against the graph and reads back the touched rows
+// (stream synchronised).  gs: the graph's groups and, for a directed state, the
+// reverse graph's.
+int stage_batch(katz_state* st, GroupStage* gs, int count, hipStream_t s) {
+  Blob bl{st->ub[0]};
+  int* err = nullptr;
+  size_t up_end = 0, report0 = 0, report_end = 0;
+  auto lay = [&] {
+    for (int i = 0; i < count; ++i) gs[i].take_inputs(bl);
+    report0 = bl.used;
+    err = bl.take<int>(1);
+    up_end = bl.used;                     // err is uploaded as 0
+    for (int i = 0; i < count; ++i) gs[i].take_report(bl);
+    report_end = bl.used;
+    for (int i = 0; i < count; ++i) gs[i].take_device(bl);
+  };
+  lay();
+  KATZ_TRY(bl.allocate());
+  lay();
+  *err = 0;
+  for (int i = 0; i < count; ++i) gs[i].fill(bl, err);
+  KATZ_HIP(hipMemcpyAsync(st->ub[0].dev, st->ub[0].host, up_end, hipMemcpyHostToDevice, s));
+  KATZ_HIP(launch_update_stage(gs[0].dev, st->row_off, st->row_len, st->row_cap, st->pool, st->ext_of, st->int_of, s));
+  if (count > 1)
+    KATZ_HIP(launch_update_stage(gs[1].dev, st->rrow_off, st->rrow_len, st->rrow_cap, st->rpool, st->ext_of, st->int_of,
+                                 s));
+  KATZ_HIP(hipMemcpyAsync(st->ub[0].host + report0, st->ub[0].dev + report0, report_end - report0, hipMemcpyDeviceToHost,
+                          s));
+  KATZ_HIP(hipStreamSynchronize(s));
+  return *err ? KATZ_E_UPDATE : KATZ_OK;
 }
 
 // Merges every touched row (old row without the deletions, with the
 // insertions, in caller-id order) into scratch, then places it in place when
 // it fits its capacity, else in a fresh region at the pool's end (the pool
-// has grown already).  ub holds what stage_groups uploaded.
-int merge_groups(katz_state* st, UpdateBufs& ub, SlackRef c, const RowGroups& g, const Touched& tt, hipStream_t s) {
-  const long long t = tt.t;
-  if (t == 0) return KATZ_OK;
-  std::vector<long long> sbase(t), dest_off(t);
-  std::vector<int> dest_cap(t);
-  long long scratch_total = 0;
-  for (long long i = 0; i < t; ++i) {
-    sbase[i] = scratch_total;
-    scratch_total += tt.new_len[i];
-    if (tt.new_len[i] <= tt.caps[i]) {
-      dest_off[i] = tt.offs[i];
-      dest_cap[i] = tt.caps[i];
-    } else {
-      dest_cap[i] = (int)slack_cap_host(tt.new_len[i]);
-      dest_off[i] = c.pool_used;
-      c.pool_used += dest_cap[i];
+// has grown already).
+int merge_batch(katz_state* st, GroupStage* gs, int count, hipStream_t s) {
+  Blob bl{st->ub[1]};
+  struct Plan {
+    long long *sbase, *dest_off;
+    int *dest_cap, *chunk_row, *chunk_first;
+    long long chunks = 0, total = 0;
+  } pl[2];
+  for (int q = 0; q < count; ++q)
+    for (long long i = 0; i < gs[q].t(); ++i) {
+      const long long len = std::max<long long>(gs[q].new_len[i], gs[q].new_len[i] - gs[q].delta(i));
+      pl[q].chunks += std::max<long long>(1, (len + kMergeChunk - 1) / kMergeChunk);
+      pl[q].total += gs[q].new_len[i];
+    }
+  auto lay = [&] {
+    for (int q = 0; q < count; ++q) {
+      pl[q].sbase = bl.take<long long>(gs[q].t());
+      pl[q].dest_off = bl.take<long long>(gs[q].t());
+      pl[q].dest_cap = bl.take<int>(gs[q].t());
+      pl[q].chunk_row = bl.take<int>(pl[q].chunks);
+      pl[q].chunk_first = bl.take<int>(pl[q].chunks);
+    }
+  };
+  lay();
+  const size_t bytes = bl.used;
+  KATZ_TRY(bl.allocate());
+  lay();
+  KATZ_TRY(grow_buf(st, st->ub[0].scratch, st->ub[0].scratch_cap, (size_t)(pl[0].total + (count > 1 ? pl[1].total : 0))));
+  for (int q = 0; q < count; ++q) {
+    SlackRef c = q == 0 ? fwd_csr(st) : rev_csr(st);
+    long long base = q == 0 ? 0 : pl[0].total, k = 0;
+    for (long long i = 0; i < gs[q].t(); ++i) {
+      const int len = gs[q].new_len[i];
+      pl[q].sbase[i] = base;
+      base += len;
+      if (len <= gs[q].caps[i]) {
+        pl[q].dest_off[i] = gs[q].offs[i];
+        pl[q].dest_cap[i] = gs[q].caps[i];
+      } else {
+        pl[q].dest_cap[i] = (int)slack_cap_host(len);
+        pl[q].dest_off[i] = c.pool_used;
+        c.pool_used += pl[q].dest_cap[i];
+      }
+      const long long most = std::max<long long>(len, len - gs[q].delta(i));
+      for (long long f = 0; f == 0 || f < most; f += kMergeChunk) {
+        pl[q].chunk_row[k] = (int)i;
+        pl[q].chunk_first[k++] = (int)f;
+      }
     }
   }
-  KATZ_TRY(grow_buf(st, ub.scratch, ub.scratch_cap, (size_t)scratch_total));
-  long long* d_ins_off = ub.ll;
-  long long* d_del_off = ub.ll + t;
-  long long* d_new_len = ub.ll + 2 * t;
-  long long* d_sbase = ub.ll + 3 * t;
-  long long* d_dest_off = ub.ll + 4 * t;
-  int* d_ins_cnt = ub.ints;
-  int* d_del_cnt = ub.ints + t;
-  int* d_dest_cap = ub.ints + 3 * t;
-  int32_t* d_ins_dst = ub.dst;
-  int32_t* d_del_dst = ub.dst + g.ins_dst.size();
-  KATZ_HIP(hipMemcpyAsync(d_sbase, sbase.data(), sizeof(long long) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_dest_off, dest_off.data(), sizeof(long long) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(d_dest_cap, dest_cap.data(), sizeof(int) * t, hipMemcpyHostToDevice, s));
-  KATZ_HIP(launch_merge_rows(ub.rows, t, d_ins_off, d_ins_cnt, d_ins_dst, d_del_off, d_del_cnt, d_del_dst, d_sbase,
-                             c.row_off, c.row_len, c.pool, st->ext_of, st->int_of, ub.scratch, s));
-  KATZ_HIP(launch_copy_back_rows(ub.rows, t, d_sbase, d_new_len, d_dest_off, d_dest_cap, ub.scratch, c.row_off,
-                                 c.row_len, c.row_cap, c.pool, s));
-  // The host vectors above are read by the copies: wait before they go.
-  KATZ_HIP(hipStreamSynchronize(s));
+  KATZ_HIP(hipMemcpyAsync(st->ub[1].dev, st->ub[1].host, bytes, hipMemcpyHostToDevice, s));
+  for (int q = 0; q < count; ++q) {
+    const SlackRef c = q == 0 ? fwd_csr(st) : rev_csr(st);
+    const MergePlan mp{pl[q].chunks,           bl.dev(pl[q].sbase),     bl.dev(pl[q].dest_off),
+                       bl.dev(pl[q].dest_cap), bl.dev(pl[q].chunk_row), bl.dev(pl[q].chunk_first)};
+    KATZ_HIP(launch_merge_rows(gs[q].dev, mp, c.row_off, c.row_len, c.row_cap, c.pool, st->int_of, st->ub[0].scratch, s));
+  }
   return KATZ_OK;
 }
 
@@ -2930,21 +3071,23 @@ void group_arcs(std::vector<Arc>& ia, std::vector<Arc>& da, RowGroups& g) {
   std::sort(rows.begin(), rows.end());
   rows.erase(std::unique(rows.begin(), rows.end()), rows.end());
   const long long t = (long long)rows.size();
-  g.ins_off.assign(t, 0);
-  g.del_off.assign(t, 0);
-  g.ins_cnt.assign(t, 0);
-  g.del_cnt.assign(t, 0);
-  g.delta.assign(t, 0);
-  size_t pi = 0, pd = 0;
-  for (long long i = 0; i < t; ++i) {
-    g.ins_off[i] = (long long)g.ins_dst.size();
-    while (pi < ia.size() && ia[pi].src == rows[i]) g.ins_dst.push_back(ia[pi++].dst);
-    g.ins_cnt[i] = (int)(g.ins_dst.size() - g.ins_off[i]);
-    g.del_off[i] = (long long)g.del_dst.size();
-    while (pd < da.size() && da[pd].src == rows[i]) g.del_dst.push_back(da[pd++].dst);
-    g.del_cnt[i] = (int)(g.del_dst.size() - g.del_off[i]);
-    g.delta[i] = g.ins_cnt[i] - g.del_cnt[i];
-  }
+  auto fill = [&](const std::vector<Arc>& arcs, std::vector<long long>& off, std::vector<int32_t>& dst,
+                  std::vector<int32_t>& grp) {
+    off.reserve(t + 1);
+    dst.reserve(arcs.size());
+    grp.reserve(arcs.size());
+    size_t p = 0;
+    for (long long i = 0; i < t; ++i) {
+      off.push_back((long long)p);
+      for (; p < arcs.size() && arcs[p].src == rows[i]; ++p) {
+        dst.push_back(arcs[p].dst);
+        grp.push_back((int32_t)i);
+      }
+    }
+    off.push_back((long long)p);
+  };
+  fill(ia, g.ins_off, g.ins_dst, g.ins_grp);
+  fill(da, g.del_off, g.del_dst, g.del_grp);
 }
 
 }  // namespace
@@ -2999,18 +3142,6 @@ int prepare_batch(long long n, int mode, const int32_t* ins_u, const int32_t* in
     std::set_intersection(ki.begin(), ki.end(), kd.begin(), kd.end(), std::back_inserter(both));
     if (!both.empty()) return KATZ_E_UPDATE;
   }
-  // Arcs for the existence check: a-ends then b-ends, insertions first (an
-  // undirected edge is checked by one of its arcs).
-  const long long np = n_ins + n_del;
-  pb.pa.resize(2 * np);
-  for (long long j = 0; j < n_ins; ++j) {
-    pb.pa[j] = iu[j];
-    pb.pa[np + j] = iv[j];
-  }
-  for (long long j = 0; j < n_del; ++j) {
-    pb.pa[n_ins + j] = du[j];
-    pb.pa[np + n_ins + j] = dv[j];
-  }
   // Stored arcs by source row; a directed state also keeps the reverse arcs by
   // target row (its reverse graph).
   std::vector<Arc> ia, da, ra, rd;
@@ -3045,22 +3176,13 @@ int apply_batch(katz_state* st, const PreparedBatch& pb, katz_result* out, hipSt
   if (pb.n != st->n || pb.mode != state_pair_mode(st)) return KATZ_E_INVALID_ARG;
   const long long n = st->n;
   const long long n_ins = pb.n_ins, n_del = pb.n_del;
-  UpdateBufs& ub = st->ub;
-
-  // ---- existence checks against the graph (device) ----
-  const long long np = n_ins + n_del;
-  if (np > 0) {
-    KATZ_TRY(grow_buf(st, ub.pairs, ub.pairs_cap, 2 * np));
-    KATZ_HIP(hipMemcpyAsync(ub.pairs, pb.pa.data(), sizeof(int32_t) * 2 * np, hipMemcpyHostToDevice, s));
-    KATZ_HIP(hipMemsetAsync(st->err_dev, 0, sizeof(int), s));
-    KATZ_HIP(launch_batch_exist(ub.pairs, ub.pairs + np, n_ins, np, st->row_off, st->row_len, st->pool, st->ext_of,
-                                st->int_of, st->err_dev, s));
-    int err = 0;
-    KATZ_HIP(hipMemcpyAsync(&err, st->err_dev, sizeof(int), hipMemcpyDeviceToHost, s));
-    KATZ_HIP(hipStreamSynchronize(s));
-    if (err) return KATZ_E_UPDATE;
-  }
   const long long t = (long long)pb.fwd.rows.size();
+  GroupStage gs[2];
+  gs[0].g = &pb.fwd;
+  gs[1].g = &pb.rev;
+  const int csrs = st->directed ? 2 : 1;
+  // ---- existence checks against the graph, the touched rows (device) ----
+  if (t > 0) KATZ_TRY(stage_batch(st, gs, csrs, s));
 
   CallTimer T;
   T.call_begin(s);
@@ -3068,42 +3190,41 @@ int apply_batch(katz_state* st, const PreparedBatch& pb, katz_result* out, hipSt
   int new_dmax = st->bins.dmax;
   if (t > 0) {
     // ---- candidate degrees and the degree cap (Theorem 1 needs alpha d < 1) ----
-    Touched ft, rt;
-    KATZ_TRY(stage_groups(st, ub, fwd_csr(st), pb.fwd, ft, s));
     // The new deg_max: the old one raised by the touched rows, unless a row of
     // the old maximum length shrank, when every untouched row is scanned too.
+    const GroupStage& f = gs[0];
     bool shrank_max = false;
-    new_dmax = st->bins.dmax;
+    unsigned long long f_arcs = 0;   // arcs of the frontier about to be expanded (0: not known)
     for (long long i = 0; i < t; ++i) {
-      const long long old_len = ft.new_len[i] - pb.fwd.delta[i];
-      if (old_len == st->bins.dmax && ft.new_len[i] < old_len) shrank_max = true;
-      new_dmax = (int)std::max<long long>(new_dmax, ft.new_len[i]);
+      const long long old_len = f.new_len[i] - f.delta(i);
+      if (old_len == st->bins.dmax && f.new_len[i] < old_len) shrank_max = true;
+      new_dmax = std::max(new_dmax, f.new_len[i]);
+      if (!st->directed) f_arcs += (unsigned long long)f.new_len[i];
     }
     if (shrank_max) {
+      int* out = reinterpret_cast<int*>(st->hs.bits);
+      KATZ_HIP(launch_mark_rows(f.dev.rows, t, st->tmark, 1, s));
       KATZ_HIP(hipMemsetAsync(st->dmax_dev, 0, sizeof(int), s));
-      KATZ_HIP(launch_max_len_after(st->row_len, st->tmark, n, ub.ll + 2 * t, t, st->dmax_dev, s));
-      KATZ_HIP(hipMemcpyAsync(&new_dmax, st->dmax_dev, sizeof(int), hipMemcpyDeviceToHost, s));
+      KATZ_HIP(launch_max_len_after(st->row_len, st->tmark, n, f.dev.new_len, t, st->dmax_dev, s));
+      KATZ_HIP(launch_mark_rows(f.dev.rows, t, st->tmark, 0, s));
+      KATZ_HIP(hipMemcpyAsync(out, st->dmax_dev, sizeof(int), hipMemcpyDeviceToHost, s));
+      KATZ_HIP(hipStreamSynchronize(s));
+      new_dmax = *out;
     }
-    KATZ_HIP(launch_unmark_rows(ub.rows, t, st->tmark, s));
-    KATZ_HIP(hipStreamSynchronize(s));
     if (!(st->alpha * (double)new_dmax < 1.0) || new_dmax > st->degree_cap) return KATZ_E_DEGREE_CAP;
-    if (st->directed) {
-      KATZ_TRY(stage_groups(st, st->rub, rev_csr(st), pb.rev, rt, s));
-      if (rt.t) KATZ_HIP(launch_unmark_rows(st->rub.rows, rt.t, st->tmark, s));
-    }
 
     // ---- apply: pools grown first (a failed allocation leaves the state as
     // it was), then every touched row merged into scratch and placed ----
-    KATZ_TRY(grow_pool(st, fwd_csr(st), growth_need(ft), s));
-    if (st->directed) KATZ_TRY(grow_pool(st, rev_csr(st), growth_need(rt), s));
-    KATZ_TRY(merge_groups(st, ub, fwd_csr(st), pb.fwd, ft, s));
-    if (st->directed) KATZ_TRY(merge_groups(st, st->rub, rev_csr(st), pb.rev, rt, s));
+    KATZ_TRY(grow_pool(st, fwd_csr(st), gs[0].growth(), s));
+    if (st->directed) KATZ_TRY(grow_pool(st, rev_csr(st), gs[1].growth(), s));
+    KATZ_TRY(merge_batch(st, gs, csrs, s));
     st->nnz += (st->directed ? 1 : 2) * (n_ins - n_del);
 
-    // ---- bins of the new graph: rebuilt before the next whole-graph walk ----
+    // ---- bins of the new graph, for the next whole-graph walk ----
     run = state_run(st);
     st->bins_stale = true;
     st->bins.dmax = new_dmax;
+    KATZ_TRY(begin_bins(st, s));
 
     // ---- re-walk levels 1..r over the affected set (Algorithm 2) ----
     // The walk kernels return at once while the run's stop flag is set; the
@@ -3115,46 +3236,47 @@ int apply_batch(katz_state* st, const PreparedBatch& pb, katz_result* out, hipSt
     const long long dense_at = std::max<long long>(1, n / 4);
     const long long dense_frontier = std::max<long long>(4096, n / 64);
     const unsigned long long dense_arcs = std::max<unsigned long long>(1ull << 16, (unsigned long long)st->nnz / 16);
-    unsigned long long f_arcs = 0;   // arcs of the frontier about to be expanded (0: not known)
-    KATZ_HIP(hipMemcpyAsync(st->clist, ub.rows, sizeof(int32_t) * t, hipMemcpyDeviceToDevice, s));
-    KATZ_HIP(launch_set_levels(ub.rows, t, st->level_of, 1, s));
+    KATZ_HIP(launch_open_affected(f.dev.rows, t, st->row_off, st->row_len, st->level_of, st->clist, st->lbins.desc,
+                                  st->fcount, s));
     long long csize = t, fbeg = 0;
+    unsigned long long arcs_seen = 0;
     bool dense = csize > dense_at;
     for (int i = 1; i <= st->r; ++i) {
       if (i >= 2 && !dense && (csize - fbeg > dense_frontier || f_arcs > dense_arcs)) dense = true;
       if (i >= 2 && !dense) {
         // C_i = C_{i-1} u in-neighbours(F_{i-1}); F_{i-1} = C[fbeg .. csize).
-        KATZ_HIP(hipMemcpyAsync(st->counter, &csize, sizeof(int), hipMemcpyHostToDevice, s));
-        KATZ_HIP(hipMemsetAsync(st->frontier_arcs, 0, sizeof(unsigned long long), s));
         // In-neighbours: the reverse graph's rows (an undirected graph's own).
         const SlackRef in = st->directed ? rev_csr(st) : fwd_csr(st);
         KATZ_HIP(launch_frontier_expand(st->clist + fbeg, csize - fbeg, in.row_off, in.row_len, in.pool,
-                                        st->level_of, i, st->clist, st->counter, st->frontier_arcs, st->foff,
-                                        st->fsums, st->ftotal, f_arcs, s));
-        int c2 = 0;
-        KATZ_HIP(hipMemcpyAsync(&c2, st->counter, sizeof(int), hipMemcpyDeviceToHost, s));
-        KATZ_HIP(hipMemcpyAsync(&f_arcs, st->frontier_arcs, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+                                        st->level_of, i, st->clist, st->fcount, st->foff, st->fsums, st->ftotal,
+                                        f_arcs, s));
+        FrontierCount* fc = reinterpret_cast<FrontierCount*>(st->hs.bits);
+        KATZ_HIP(hipMemcpyAsync(fc, st->fcount, sizeof(FrontierCount), hipMemcpyDeviceToHost, s));
         KATZ_HIP(hipStreamSynchronize(s));
+        f_arcs = fc->arcs - arcs_seen;
+        arcs_seen = fc->arcs;
         fbeg = csize;
-        csize = c2;
+        csize = fc->nodes;
         if (csize > dense_at) dense = true;
       }
-      long long tb = 0;
-      if (dense) {
+      long long tb = 0, g_used = 0;
+      if (i == 1 && !dense) {
+        // x_1 of a row is its length: no bins.
+        st->lbins.count = t;
+        const IterArgs ia = iter_args(run, st->lbins, 1, true, tb);
+        KATZ_HIP(launch_walk_first(ia, run.fp32, n, st->nnz, 0, s));
+      } else if (dense) {
         // A whole-graph re-walk level: the tuned launch shape (LDS copy of the
         // hottest entries of x_{i-1} in a renumbered state).
         KATZ_TRY(refresh_bins(st, s));
-        IterArgs ia2 = iter_args(run, st->bins, i, true, tb);
-        ia2.hub_n = run.hub_n;
-        long long g_used = 0;
-        if (i == 1) KATZ_HIP(launch_walk_first(ia2, run.fp32, n, st->nnz, 0, s));
-        else KATZ_HIP(launch_walk_step(ia2, run.fp32, tb, run.walk_grid, &g_used, s, false, run.walk_groups));
+        IterArgs ia = iter_args(run, st->bins, i, true, tb);
+        ia.hub_n = run.hub_n;
+        if (i == 1) KATZ_HIP(launch_walk_first(ia, run.fp32, n, st->nnz, 0, s));
+        else KATZ_HIP(launch_walk_step(ia, run.fp32, tb, run.walk_grid, &g_used, s, false, run.walk_groups));
       } else {
         KATZ_TRY(bin_rows(st, st->lbins, st->sc2, st->clist, csize, s));
-        const IterArgs ia2 = iter_args(run, st->lbins, i, true, tb);
-        long long g_used = 0;
-        if (i == 1) KATZ_HIP(launch_walk_first(ia2, run.fp32, n, st->nnz, 0, s));
-        else KATZ_HIP(launch_walk_step(ia2, run.fp32, tb, 0, &g_used, s));
+        const IterArgs ia = iter_args(run, st->lbins, i, true, tb);
+        KATZ_HIP(launch_walk_step(ia, run.fp32, tb, 0, &g_used, s));
       }
     }
     // c_r(w) = sum_i x_i(w) for every recomputed w, in the static order (FP32
@@ -3184,21 +3306,24 @@ int apply_batch(katz_state* st, const PreparedBatch& pb, katz_result* out, hipSt
   // of the next level); the lower levels keep theirs, which fixed the scales
   // of the levels above them.
   set_gamma(st->S, new_dmax);
-  if (!st->fp32) {
-    KATZ_HIP(hipMemsetAsync(&st->w.xmax64[st->r], 0, sizeof(unsigned long long), s));
+  KATZ_HIP(launch_recheck_begin(st->w.sc, st->fp32 ? &st->w.xmax32[st->r] : nullptr,
+                                st->fp32 ? nullptr : &st->w.xmax64[st->r], st->min_bits, st->counter, s));
+  if (!st->fp32)
     KATZ_HIP(launch_max_of_vector(static_cast<const double*>(st->X[st->r]), n, &st->w.xmax64[st->r], s));
-  } else {
-    KATZ_HIP(hipMemsetAsync(&st->w.xmax32[st->r], 0, sizeof(unsigned), s));
+  else
     KATZ_HIP(launch_max_of_vector_f32(static_cast<const float*>(st->X[st->r]), n, &st->w.xmax32[st->r], s));
-  }
-  KATZ_HIP(launch_reset_flags(st->w.sc, s));
   run = state_run(st);
   const BoundArgs b = bound_args(run, st->r);
-  KATZ_HIP(hipMemsetAsync(st->min_bits, 0xff, sizeof(unsigned long long), s));
   KATZ_HIP(launch_min_lower_active(b, st->w.act[st->cur], &st->w.sc->m, st->min_bits, st->w.mark, n, s));
-  KATZ_HIP(hipMemsetAsync(&st->w.sc->m, 0, sizeof(int), s));
-  KATZ_HIP(launch_reactivate_all(b, n, st->min_bits, st->w.mark, st->w.act[st->cur ^ 1], &st->w.sc->m, s));
+  KATZ_HIP(launch_reactivate_all(b, n, st->min_bits, st->w.mark, st->w.act[st->cur ^ 1], st->counter, s));
   run.cur = st->cur ^ 1;
+  // The size of the new M decides how it is selected from; the host needs it
+  // anyway before the test that usually ends the update.
+  const unsigned seq = ++st->hs.seq;
+  KATZ_HIP(launch_recheck_end(st->w.sc, st->counter, Publish{&st->hs.flags[seq & 1], seq}, s));
+  PassFlags pf;
+  KATZ_TRY(wait_flags(st->hs, seq, st->w.sc, &pf, s));
+  run.m_known = pf.m;
   KATZ_TRY(iterate(run, st->hs, st->r + 1, true, s, T));
   st->r = st->hs.sc->iterations;
   st->cur = st->hs.sc->cur;

@@ -116,6 +116,21 @@ __device__ __forceinline__ unsigned long long key_of(double lo) {
 }
 
 
+// The flags of a run that starts or goes on (M's size and the results stay).
+__device__ __forceinline__ void clear_flags(RunScalars* sc) {
+  sc->err = 0;
+  sc->done = 0;
+  sc->status = KATZ_OK;
+  sc->top_count = 0;
+  sc->kept_count = 0;
+  sc->progress = 0;
+  sc->cand_count[0] = 0;
+  sc->cand_count[1] = 0;
+  sc->dmax = 0;
+  sc->col_err = 0;
+  sc->rescale = 0;
+}
+
 // A finished pass's flags to pinned host memory: one 64-bit word, so that the
 // host, which polls it, needs no ordering with other stores.  status: -1 while
 // the run goes on.  One thread.
@@ -416,6 +431,7 @@ __global__ void __launch_bounds__(kWG) prep_place(Rows rows, long long count, co
   __shared__ int l_row[kPrepRows], l_len[kPrepRows];
   __shared__ long long l_off[kPrepRows];       // offset in the source; Relabel: then the arcs before the place
   __shared__ uint8_t l_cls[kPrepRows];
+  __shared__ int l_seg[kPrepRows];
   __shared__ long long wsum[kWaves];
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
   if (blockIdx.x == 0 && t == 0) {
@@ -564,19 +580,43 @@ __global__ void __launch_bounds__(kWG) prep_place(Rows rows, long long count, co
     const long long pos = gpos[c] + (p - lbase[c]);
     desc[pos] = RowDesc{offset_of(p, c), Relabel ? (int32_t)pos : l_row[p], l_len[p]};
   }
-  // Rows of more than one segment (their classes come first).
+  // Rows of more than one segment (their classes come first): the segments
+  // before each of them, then one thread per row and one per segment.
   const int n_huge = lbase[SUB];
-  long long part = blk[2ll * C * nblocks + blockIdx.x];
-  for (int p = 0; p < n_huge; ++p) {
+  if (n_huge == 0) return;
+  __syncthreads();
+  int nseg[kPer], before_seg = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int p = t * kPer + j;
+    nseg[j] = p < n_huge ? (l_len[p] + kSeg - 1) / kSeg : 0;
+    before_seg += nseg[j];
+  }
+  int n_segs = 0;
+  int run = block_scan_256(before_seg, &n_segs);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    l_seg[t * kPer + j] = run;
+    run += nseg[j];
+  }
+  __syncthreads();
+  const int part0 = (int)blk[2ll * C * nblocks + blockIdx.x];
+  for (int p = t; p < n_huge; p += kWG) {
     const int c = l_cls[p];
     const long long pos = gpos[c] + (p - lbase[c]);
-    const int n_p = l_len[p];
-    const int nseg = (n_p + kSeg - 1) / kSeg;
-    const long long o = offset_of(p, c);
-    if (t == 0) huge[pos] = HugeRow{Relabel ? (int32_t)pos : l_row[p], n_p, nseg, (int32_t)part};
-    for (int sg = t; sg < nseg; sg += kWG)
-      segs[part + sg] = SegDesc{o + (long long)sg * kSeg, min(kSeg, n_p - sg * kSeg), (int32_t)(part + sg), (int32_t)pos, 0};
-    part += nseg;
+    huge[pos] = HugeRow{Relabel ? (int32_t)pos : l_row[p], l_len[p], (l_len[p] + kSeg - 1) / kSeg, part0 + l_seg[p]};
+  }
+  for (int q = t; q < n_segs; q += kWG) {
+    int lo = 0, hi = n_huge - 1;   // the last row whose segments start at or before q
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (l_seg[mid] <= q) lo = mid;
+      else hi = mid - 1;
+    }
+    const int c = l_cls[lo];
+    const int sg = q - l_seg[lo];
+    segs[part0 + q] = SegDesc{offset_of(lo, c) + (long long)sg * kSeg, min(kSeg, l_len[lo] - sg * kSeg), part0 + q,
+                              (int32_t)(gpos[c] + (lo - lbase[c])), 0};
   }
 }
 

@@ -210,18 +210,6 @@ __global__ void __launch_bounds__(kStrictThreads) check_rows_strict(const OffT* 
   }
   if (__ballot(bad) && lane_id() == 0) atomicOr(&sc->err, 1);
 }
-__device__ __forceinline__ long long lower_bound_i32(const int32_t* a, long long len, int32_t x) {
-  long long lo = 0, hi = len;
-  while (lo < hi) {
-    const long long mid = (lo + hi) >> 1;
-    if (a[mid] < x) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-// A renumbered state stores internal ids, each row sorted by the caller ids
-// of its entries (the static order of that row's sum).  ext_of / int_of map
-// internal <-> caller ids; null maps are the identity (a state in caller order).
 __device__ __forceinline__ int32_t ext_or_id(const int32_t* ext_of, int32_t x) { return ext_of ? ext_of[x] : x; }
 
 // First position in a row whose entry's caller id is not below e.
@@ -236,27 +224,36 @@ __device__ __forceinline__ long long lower_bound_ext(const int32_t* row, long lo
   return lo;
 }
 
-// Inserted arcs must be absent and deleted arcs present (Section 4: I n E = {},
-// D c E).  Pairs [0, n_ins) are insertions, [n_ins, n_ins + n_del) deletions,
-// in caller ids.
-__global__ void __launch_bounds__(kWG) batch_exist(const int32_t* a, const int32_t* b, long long n_ins,
-                                                   long long total, const long long* row_off, const int* row_len,
-                                                   const int32_t* pool, const int32_t* ext_of, const int32_t* int_of,
-                                                   int* err) {
+// The first half of an update's device work, over the batch's touched rows and
+// its arcs.  Thread i < t: touched row i (stored id, offset, capacity, new
+// length).  The others: an arc's place in its row (the first entry whose caller
+// id is not below the arc's); inserted arcs must be absent and deleted arcs
+// present (Section 4: I n E = {}, D c E).
+__global__ void __launch_bounds__(kWG) update_stage(UpdateRows u, const long long* row_off, const int* row_len,
+                                                    const int* row_cap, const int32_t* pool, const int32_t* ext_of,
+                                                    const int32_t* int_of) {
   const long long j = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (j >= total) return;
-  const int32_t u = int_of ? int_of[a[j]] : a[j], v = b[j];
-  const int32_t* row = pool + row_off[u];
-  const long long len = row_len[u];
-  const long long p = lower_bound_ext(row, len, v, ext_of);
-  const bool found = p < len && ext_or_id(ext_of, row[p]) == v;
-  if ((j < n_ins) == found) atomicOr(err, 1);
-}
-
-// Caller ids -> internal ids, in place.
-__global__ void __launch_bounds__(kWG) map_ids(int32_t* ids, long long count, const int32_t* int_of) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < count) ids[i] = int_of[ids[i]];
+  if (j < u.t) {
+    const int32_t r = int_of ? int_of[u.rows_in[j]] : u.rows_in[j];
+    u.rows[j] = r;
+    u.offs[j] = row_off[r];
+    u.caps[j] = row_cap[r];
+    u.new_len[j] = row_len[r] + (int)(u.ins_off[j + 1] - u.ins_off[j]) - (int)(u.del_off[j + 1] - u.del_off[j]);
+    return;
+  }
+  const long long a = j - u.t;
+  if (a >= u.ni + u.nd) return;
+  const bool ins = a < u.ni;
+  const long long q = ins ? a : a - u.ni;
+  const int32_t r0 = u.rows_in[ins ? u.ins_grp[q] : u.del_grp[q]];
+  const int32_t e = ins ? u.ins_dst[q] : u.del_dst[q];
+  const int32_t r = int_of ? int_of[r0] : r0;
+  const int32_t* row = pool + row_off[r];
+  const long long len = row_len[r];
+  const long long p = lower_bound_ext(row, len, e, ext_of);
+  const bool found = p < len && ext_or_id(ext_of, row[p]) == e;
+  (ins ? u.ins_pos : u.del_pos)[q] = (int32_t)p;
+  if (ins == found) atomicOr(u.err, 1);
 }
 
 // Renumbering of a new state: internal id i = position of the caller's row in
@@ -352,25 +349,15 @@ __global__ void __launch_bounds__(kRenameThreads) rename_slots(const long long* 
   for (int q = 0; q < kRenamePer; ++q)
     if (c[q] >= 0) pool_new[c0 + q * kRenameThreads + t] = int_of[c[q]];
 }
-// Candidate lengths of the touched rows; marks them.
-__global__ void __launch_bounds__(kWG) touched_lengths(const int32_t* rows, long long t, const int* delta,
-                                                       const int* row_len, long long* new_len, uint8_t* mark) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i >= t) return;
-  const int w = rows[i];
-  new_len[i] = (long long)row_len[w] + delta[i];
-  mark[w] = 1;
-}
-
 // Maximum row length after the batch: untouched rows as they are, touched rows
 // at their candidate length.
 __global__ void __launch_bounds__(kWG) max_len_after(const int* row_len, const uint8_t* mark, long long n,
-                                                     const long long* new_len, long long t, int* out) {
+                                                     const int* new_len, long long t, int* out) {
   int m = 0;
   for (long long v = (long long)blockIdx.x * kWG + threadIdx.x; v < n; v += (long long)gridDim.x * kWG)
     if (!mark[v]) m = max(m, row_len[v]);
   for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < t; i += (long long)gridDim.x * kWG)
-    m = max(m, (int)new_len[i]);
+    m = max(m, new_len[i]);
   __shared__ int wm[kWG / kWave];
   for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
   if (lane_id() == 0) wm[threadIdx.x / kWave] = m;
@@ -378,58 +365,74 @@ __global__ void __launch_bounds__(kWG) max_len_after(const int* row_len, const u
   if (threadIdx.x == 0) atomicMax(out, max(max(wm[0], wm[1]), max(wm[2], wm[3])));
 }
 
-__global__ void __launch_bounds__(kWG) unmark_rows(const int32_t* rows, long long t, uint8_t* mark) {
+__global__ void __launch_bounds__(kWG) mark_rows(const int32_t* rows, long long t, uint8_t* mark, int value) {
   const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < t) mark[rows[i]] = 0;
+  if (i < t) mark[rows[i]] = (uint8_t)value;
 }
 
-// One workgroup per touched row w: new row = (old row \ del) u ins, in caller-id
-// order, written to scratch[sbase[i] ..].  ins and del hold caller ids, sorted
-// per row; the row's entries are stored ids (internal in a renumbered state).
-__global__ void __launch_bounds__(kWG) merge_rows(const int32_t* rows, const long long* ins_off, const int* ins_cnt,
-                                                  const int32_t* ins_dst, const long long* del_off,
-                                                  const int* del_cnt, const int32_t* del_dst,
-                                                  const long long* sbase, const long long* row_off,
-                                                  const int* row_len, const int32_t* pool, const int32_t* ext_of,
-                                                  const int32_t* int_of, int32_t* scratch) {
-  const long long i = blockIdx.x;
-  const int w = rows[i];
+// Merged rows: new row = (old row \ del) u ins, in caller-id order, written to
+// scratch[sbase[i] ..].  A workgroup takes one chunk (at most kMergeChunk entries)
+// of one touched row.  The places of the row's inserted and deleted arcs are
+// known, so an entry moves by the number of insertions at or before it less the
+// deletions before it: two searches in lists of places, no look at the entries.
+// Bound by the copy.  (One workgroup per row, searching by caller id, left a hub's
+// 10^5 entries and their id lookups to four waves: 990 us for 4000 updates of
+// R-MAT 22, now 74 us.)
+__device__ __forceinline__ int count_below(const int32_t* a, int n, int x) {   // entries of sorted a below x
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (a[mid] < x) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+__global__ void __launch_bounds__(kWG) merge_rows(UpdateRows u, MergePlan m, const long long* row_off,
+                                                  const int* row_len, const int32_t* pool, const int32_t* int_of,
+                                                  int32_t* scratch) {
+  const int i = m.chunk_row[blockIdx.x];
+  const int first = m.chunk_first[blockIdx.x];
+  const int w = u.rows[i];
   const int32_t* old = pool + row_off[w];
-  const long long len = row_len[w];
-  const int32_t* ins = ins_dst + ins_off[i];
-  const int32_t* del = del_dst + del_off[i];
-  const int ni = ins_cnt[i], nd = del_cnt[i];
-  int32_t* out = scratch + sbase[i];
-  for (long long j = threadIdx.x; j < len; j += kWG) {
-    const int32_t x = old[j];
-    const int32_t e = ext_or_id(ext_of, x);
-    const long long pd = lower_bound_i32(del, nd, e);
-    if (pd < nd && del[pd] == e) continue;
-    const long long pi = lower_bound_i32(ins, ni, e);
-    out[j - pd + pi] = x;
+  const int last = min(first + kMergeChunk, row_len[w]);
+  const long long i0 = u.ins_off[i], d0 = u.del_off[i];
+  const int ni = (int)(u.ins_off[i + 1] - i0), nd = (int)(u.del_off[i + 1] - d0);
+  const int32_t* ip = u.ins_pos + i0;
+  const int32_t* dp = u.del_pos + d0;
+  int32_t* out = scratch + m.sbase[i];
+  // Only the places inside the chunk are searched per entry.
+  const int ia = count_below(ip, ni, first), ib = count_below(ip, ni, last);
+  const int da = count_below(dp, nd, first), db = count_below(dp, nd, last);
+  for (int j = first + (int)threadIdx.x; j < last; j += kWG) {
+    const int pd = da + count_below(dp + da, db - da, j);
+    if (pd < db && dp[pd] == j) continue;
+    const int pi = ia + count_below(ip + ia, ib - ia, j + 1);
+    out[j - pd + pi] = old[j];
   }
-  for (int j = threadIdx.x; j < ni; j += kWG) {
-    const int32_t e = ins[j];
-    const long long po = lower_bound_ext(old, len, e, ext_of);
-    const long long pd = lower_bound_i32(del, nd, e);
-    out[j + po - pd] = int_of ? int_of[e] : e;
+  if (first == 0) {
+    for (int j = threadIdx.x; j < ni; j += kWG) {
+      const int32_t e = u.ins_dst[i0 + j];
+      out[j + ip[j] - count_below(dp, nd, ip[j])] = int_of ? int_of[e] : e;
+    }
   }
 }
 
-__global__ void __launch_bounds__(kWG) copy_back_rows(const int32_t* rows, const long long* sbase,
-                                                      const long long* new_len, const long long* dest_off,
-                                                      const int* dest_cap, const int32_t* scratch,
-                                                      long long* row_off, int* row_len, int* row_cap,
-                                                      int32_t* pool) {
-  const long long i = blockIdx.x;
-  const int w = rows[i];
-  const long long len = new_len[i];
-  const long long dst = dest_off[i];
-  for (long long j = threadIdx.x; j < len; j += kWG) pool[dst + j] = scratch[sbase[i] + j];
-  if (threadIdx.x == 0) {
+// The merged rows to their places (the old one, or the pool's end).
+__global__ void __launch_bounds__(kWG) copy_back_rows(UpdateRows u, MergePlan m, const int32_t* scratch,
+                                                      long long* row_off, int* row_len, int* row_cap, int32_t* pool) {
+  const int i = m.chunk_row[blockIdx.x];
+  const int first = m.chunk_first[blockIdx.x];
+  const int len = u.new_len[i];
+  const int last = min(first + kMergeChunk, len);
+  const long long dst = m.dest_off[i];
+  const int32_t* src = scratch + m.sbase[i];
+  for (int j = first + (int)threadIdx.x; j < last; j += kWG) pool[dst + j] = src[j];
+  if (first == 0 && threadIdx.x == 0) {
+    const int w = u.rows[i];
     row_off[w] = dst;
-    row_len[w] = (int)len;
-    row_cap[w] = dest_cap[i];
+    row_len[w] = len;
+    row_cap[w] = m.dest_cap[i];
   }
 }
 
@@ -454,8 +457,7 @@ __global__ void __launch_bounds__(kWG) frontier_lengths(const int32_t* frontier,
 __global__ void __launch_bounds__(kWG) frontier_expand(const int32_t* frontier, long long f, const long long* foff,
                                                        const long long* total, const long long* row_off,
                                                        const int* row_len, const int32_t* pool, int* level_of,
-                                                       int level, int32_t* next, int* next_count,
-                                                       unsigned long long* next_arcs) {
+                                                       int level, int32_t* next, FrontierCount* fc) {
   __shared__ int s_cnt[kWG / kWave];
   __shared__ unsigned long long s_arcs[kWG / kWave];
   __shared__ int s_base;
@@ -513,9 +515,9 @@ __global__ void __launch_bounds__(kWG) frontier_expand(const int32_t* frontier, 
     __syncthreads();
     if (threadIdx.x == 0) {
       const int tot = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-      s_base = tot ? atomicAdd(next_count, tot) : 0;
+      s_base = tot ? atomicAdd(&fc->nodes, tot) : 0;
       const unsigned long long at = s_arcs[0] + s_arcs[1] + s_arcs[2] + s_arcs[3];
-      if (at) atomicAdd(next_arcs, at);
+      if (at) atomicAdd(&fc->arcs, at);
     }
     __syncthreads();
     int pos = s_base + inc - nf;
@@ -527,9 +529,35 @@ __global__ void __launch_bounds__(kWG) frontier_expand(const int32_t* frontier, 
   }
 }
 
-__global__ void __launch_bounds__(kWG) set_levels(const int32_t* rows, long long t, int* level_of, int level) {
+// The touched rows open the affected set C (level 1) and its list; descriptors for
+// their level-1 walk entries.
+__global__ void __launch_bounds__(kWG) open_affected(const int32_t* rows, long long t, const long long* row_off,
+                                                     const int* row_len, int* level_of, int32_t* list, RowDesc* desc,
+                                                     FrontierCount* fc) {
   const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < t) level_of[rows[i]] = level;
+  if (i == 0) *fc = FrontierCount{0ull, (int)t, 0};
+  if (i >= t) return;
+  const int32_t w = rows[i];
+  level_of[w] = 1;
+  list[i] = w;
+  desc[i] = RowDesc{row_off[w], w, row_len[w]};
+}
+
+// Before the bounds of a changed graph are tested: the run's flags (M's size
+// stays), the top level's maximum, the reactivation test's scalars.
+__global__ void recheck_begin(RunScalars* sc, unsigned* xmax32, unsigned long long* xmax64, unsigned long long* min_bits,
+                              int* count) {
+  clear_flags(sc);
+  if (xmax32) *xmax32 = 0u;
+  if (xmax64) *xmax64 = 0ull;
+  *min_bits = ~0ull;
+  *count = 0;
+}
+
+// The reactivated M: its size to the run's flags, and to the host.
+__global__ void recheck_end(RunScalars* sc, const int* count, Publish pub) {
+  sc->m = *count;
+  publish(pub, 0, -1, *count);
 }
 
 __global__ void __launch_bounds__(kWG) clear_levels(const int32_t* rows, long long t, int* level_of) {
@@ -645,17 +673,6 @@ __global__ void __launch_bounds__(kWG) reactivate(BoundArgs b, long long n, cons
   }
 }
 
-__global__ void __launch_bounds__(kWG) gather_int(const int32_t* rows, long long t, const int* src, int* out) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < t) out[i] = src[rows[i]];
-}
-
-__global__ void __launch_bounds__(kWG) gather_ll(const int32_t* rows, long long t, const long long* src,
-                                                 long long* out) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < t) out[i] = src[rows[i]];
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -713,11 +730,6 @@ hipError_t launch_check_rows_strict(const void* rp, int rp64, const int32_t* col
   return hipGetLastError();
 }
 
-hipError_t launch_map_ids(int32_t* ids, long long count, const int32_t* int_of, hipStream_t s) {
-  if (count > 0) hipLaunchKernelGGL(map_ids, dim3(blocks_for(count)), dim3(kWG), 0, s, ids, count, int_of);
-  return hipGetLastError();
-}
-
 hipError_t launch_state_relabel(const RowDesc* desc, long long n, const int* row_cap, int32_t* ext_of,
                                int32_t* int_of, long long* cap_ll, hipStream_t s) {
   hipLaunchKernelGGL(state_relabel, dim3(blocks_for(n)), dim3(kWG), 0, s, desc, n, row_cap, ext_of, int_of, cap_ll);
@@ -741,56 +753,40 @@ hipError_t launch_state_rename_rows(const int32_t* ext_of, const int32_t* int_of
   return hipGetLastError();
 }
 
-hipError_t launch_batch_exist(const int32_t* a, const int32_t* b, long long n_ins, long long total,
-                              const long long* row_off, const int* row_len, const int32_t* pool,
-                              const int32_t* ext_of, const int32_t* int_of, int* err, hipStream_t s) {
-  if (total > 0)
-    hipLaunchKernelGGL(batch_exist, dim3(blocks_for(total)), dim3(kWG), 0, s, a, b, n_ins, total, row_off, row_len,
-                       pool, ext_of, int_of, err);
+hipError_t launch_update_stage(const UpdateRows& u, const long long* row_off, const int* row_len, const int* row_cap,
+                               const int32_t* pool, const int32_t* ext_of, const int32_t* int_of, hipStream_t s) {
+  const long long items = u.t + u.ni + u.nd;
+  if (items > 0)
+    hipLaunchKernelGGL(update_stage, dim3(blocks_for(items)), dim3(kWG), 0, s, u, row_off, row_len, row_cap, pool,
+                       ext_of, int_of);
   return hipGetLastError();
 }
 
-hipError_t launch_touched_lengths(const int32_t* rows, long long t, const int* delta, const int* row_len,
-                                  long long* new_len, uint8_t* mark, hipStream_t s) {
-  hipLaunchKernelGGL(touched_lengths, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, delta, row_len, new_len, mark);
-  return hipGetLastError();
-}
-
-hipError_t launch_max_len_after(const int* row_len, const uint8_t* mark, long long n, const long long* new_len,
+hipError_t launch_max_len_after(const int* row_len, const uint8_t* mark, long long n, const int* new_len,
                                 long long t, int* out, hipStream_t s) {
   const unsigned nb = (unsigned)std::min<long long>(blocks_for(n), 512);
   hipLaunchKernelGGL(max_len_after, dim3(nb), dim3(kWG), 0, s, row_len, mark, n, new_len, t, out);
   return hipGetLastError();
 }
 
-hipError_t launch_unmark_rows(const int32_t* rows, long long t, uint8_t* mark, hipStream_t s) {
-  hipLaunchKernelGGL(unmark_rows, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, mark);
+hipError_t launch_mark_rows(const int32_t* rows, long long t, uint8_t* mark, int value, hipStream_t s) {
+  if (t > 0) hipLaunchKernelGGL(mark_rows, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, mark, value);
   return hipGetLastError();
 }
 
-hipError_t launch_merge_rows(const int32_t* rows, long long t, const long long* ins_off, const int* ins_cnt,
-                             const int32_t* ins_dst, const long long* del_off, const int* del_cnt,
-                             const int32_t* del_dst, const long long* sbase, const long long* row_off,
-                             const int* row_len, const int32_t* pool, const int32_t* ext_of, const int32_t* int_of,
-                             int32_t* scratch, hipStream_t s) {
-  if (t > 0)
-    hipLaunchKernelGGL(merge_rows, dim3((unsigned)t), dim3(kWG), 0, s, rows, ins_off, ins_cnt, ins_dst, del_off,
-                       del_cnt, del_dst, sbase, row_off, row_len, pool, ext_of, int_of, scratch);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_back_rows(const int32_t* rows, long long t, const long long* sbase, const long long* new_len,
-                                 const long long* dest_off, const int* dest_cap, const int32_t* scratch,
-                                 long long* row_off, int* row_len, int* row_cap, int32_t* pool, hipStream_t s) {
-  if (t > 0)
-    hipLaunchKernelGGL(copy_back_rows, dim3((unsigned)t), dim3(kWG), 0, s, rows, sbase, new_len, dest_off, dest_cap,
-                       scratch, row_off, row_len, row_cap, pool);
+hipError_t launch_merge_rows(const UpdateRows& u, const MergePlan& m, long long* row_off, int* row_len, int* row_cap,
+                             int32_t* pool, const int32_t* int_of, int32_t* scratch, hipStream_t s) {
+  if (m.chunks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(merge_rows, dim3((unsigned)m.chunks), dim3(kWG), 0, s, u, m, (const long long*)row_off,
+                     (const int*)row_len, (const int32_t*)pool, int_of, scratch);
+  hipLaunchKernelGGL(copy_back_rows, dim3((unsigned)m.chunks), dim3(kWG), 0, s, u, m, (const int32_t*)scratch, row_off,
+                     row_len, row_cap, pool);
   return hipGetLastError();
 }
 
 hipError_t launch_frontier_expand(const int32_t* frontier, long long f, const long long* row_off, const int* row_len,
-                                  const int32_t* pool, int* level_of, int level, int32_t* next, int* next_count,
-                                  unsigned long long* next_arcs, long long* foff, long long* sums, long long* total,
+                                  const int32_t* pool, int* level_of, int level, int32_t* next, FrontierCount* fc,
+                                  long long* foff, long long* sums, long long* total,
                                   unsigned long long arcs_hint, hipStream_t s) {
   if (f <= 0) return hipSuccess;
   hipLaunchKernelGGL(frontier_lengths, dim3(blocks_for(f)), dim3(kWG), 0, s, frontier, f, row_len, foff);
@@ -801,12 +797,26 @@ hipError_t launch_frontier_expand(const int32_t* frontier, long long f, const lo
   const long long est = arcs_hint ? (long long)arcs_hint : 2048 * kExpandChunk;
   const unsigned grid = (unsigned)std::max<long long>(1, std::min<long long>(2048, (est + kExpandChunk - 1) / kExpandChunk));
   hipLaunchKernelGGL(frontier_expand, dim3(grid), dim3(kWG), 0, s, frontier, f, (const long long*)foff,
-                     (const long long*)total, row_off, row_len, pool, level_of, level, next, next_count, next_arcs);
+                     (const long long*)total, row_off, row_len, pool, level_of, level, next, fc);
   return hipGetLastError();
 }
 
-hipError_t launch_set_levels(const int32_t* rows, long long t, int* level_of, int level, hipStream_t s) {
-  if (t > 0) hipLaunchKernelGGL(set_levels, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, level_of, level);
+hipError_t launch_open_affected(const int32_t* rows, long long t, const long long* row_off, const int* row_len,
+                                int* level_of, int32_t* list, RowDesc* desc, FrontierCount* fc, hipStream_t s) {
+  if (t > 0)
+    hipLaunchKernelGGL(open_affected, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, row_off, row_len, level_of, list,
+                       desc, fc);
+  return hipGetLastError();
+}
+
+hipError_t launch_recheck_begin(RunScalars* sc, unsigned* xmax32, unsigned long long* xmax64,
+                                unsigned long long* min_bits, int* count, hipStream_t s) {
+  hipLaunchKernelGGL(recheck_begin, dim3(1), dim3(1), 0, s, sc, xmax32, xmax64, min_bits, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_recheck_end(RunScalars* sc, const int* count, const Publish& pub, hipStream_t s) {
+  hipLaunchKernelGGL(recheck_end, dim3(1), dim3(1), 0, s, sc, count, pub);
   return hipGetLastError();
 }
 
@@ -852,16 +862,6 @@ hipError_t launch_reactivate_all(const BoundArgs& b, long long n, const unsigned
                                  uint8_t* mark, int32_t* out, int* count, hipStream_t s) {
   const unsigned nb = (unsigned)std::min<long long>(blocks_for(n), 2048);
   hipLaunchKernelGGL(reactivate, dim3(nb), dim3(kWG), 0, s, b, n, min_bits, mark, out, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_int(const int32_t* rows, long long t, const int* src, int* out, hipStream_t s) {
-  if (t > 0) hipLaunchKernelGGL(gather_int, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, src, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_ll(const int32_t* rows, long long t, const long long* src, long long* out, hipStream_t s) {
-  if (t > 0) hipLaunchKernelGGL(gather_ll, dim3(blocks_for(t)), dim3(kWG), 0, s, rows, t, src, out);
   return hipGetLastError();
 }
 

@@ -409,12 +409,38 @@ hipError_t launch_copy_rows_to_pool(const void* rp, int rp64, const int32_t* col
 // Column ids in range, no self-loop, rows strictly ascending (sc->err |= 1 otherwise).
 hipError_t launch_check_rows_strict(const void* rp, int rp64, const int32_t* col, long long n, long long nnz,
                                     RunScalars* sc, hipStream_t s);
+// One slack CSR's share of an update: the batch's arcs grouped by touched row
+// (caller ids), and what the device finds for them.
+struct UpdateRows {
+  long long t, ni, nd;                 // touched rows, inserted arcs, deleted arcs
+  const int32_t* rows_in;              // [t] caller ids, ascending
+  const long long *ins_off, *del_off;  // [t + 1] each row's first arc
+  const int32_t *ins_dst, *del_dst;    // entries (caller ids), ascending per row
+  const int32_t *ins_grp, *del_grp;    // each arc's touched row
+  int32_t* rows;                       // [t] stored ids
+  long long* offs;                     // [t] row offset, capacity, length after the batch
+  int *caps, *new_len;
+  int32_t *ins_pos, *del_pos;          // each arc's place in its row
+  int* err;                            // set: an inserted arc is present or a deleted one absent
+};
+// Where the merged rows go, and the chunks that the merge is cut into.
+constexpr int kMergeChunk = 4096;
+struct MergePlan {
+  long long chunks;
+  const long long *sbase, *dest_off;   // [t] first entry in scratch, in the pool
+  const int* dest_cap;                 // [t]
+  const int *chunk_row, *chunk_first;  // [chunks]
+};
+// Affected nodes found so far, and the arcs of those found by expansions.
+struct FrontierCount {
+  unsigned long long arcs;
+  int nodes;
+  int pad;
+};
 // ext_of / int_of: internal <-> caller id maps of a renumbered state (null:
-// the state is in caller order); batch pairs and per-row lists are caller ids.
-hipError_t launch_batch_exist(const int32_t* a, const int32_t* b, long long n_ins, long long total,
-                              const long long* row_off, const int* row_len, const int32_t* pool,
-                              const int32_t* ext_of, const int32_t* int_of, int* err, hipStream_t s);
-hipError_t launch_map_ids(int32_t* ids, long long count, const int32_t* int_of, hipStream_t s);
+// the state is in caller order).
+hipError_t launch_update_stage(const UpdateRows& u, const long long* row_off, const int* row_len, const int* row_cap,
+                               const int32_t* pool, const int32_t* ext_of, const int32_t* int_of, hipStream_t s);
 hipError_t launch_state_relabel(const RowDesc* desc, long long n, const int* row_cap, int32_t* ext_of,
                                int32_t* int_of, long long* cap_ll, hipStream_t s);
 // off_old: row offsets of the old rows by caller id, int64 (off64 = 1) or int32.
@@ -422,27 +448,23 @@ hipError_t launch_state_rename_rows(const int32_t* ext_of, const int32_t* int_of
                                    const void* off_old, int off64, const int* len_old, const int* cap_old,
                                    const int32_t* pool_old, const long long* off_new, long long used_new,
                                    int* len_new, int* cap_new, int32_t* pool_new, long long* src_of, hipStream_t s);
-hipError_t launch_touched_lengths(const int32_t* rows, long long t, const int* delta, const int* row_len,
-                                  long long* new_len, uint8_t* mark, hipStream_t s);
-hipError_t launch_max_len_after(const int* row_len, const uint8_t* mark, long long n, const long long* new_len,
+hipError_t launch_max_len_after(const int* row_len, const uint8_t* mark, long long n, const int* new_len,
                                 long long t, int* out, hipStream_t s);
-hipError_t launch_unmark_rows(const int32_t* rows, long long t, uint8_t* mark, hipStream_t s);
-hipError_t launch_merge_rows(const int32_t* rows, long long t, const long long* ins_off, const int* ins_cnt,
-                             const int32_t* ins_dst, const long long* del_off, const int* del_cnt,
-                             const int32_t* del_dst, const long long* sbase, const long long* row_off,
-                             const int* row_len, const int32_t* pool, const int32_t* ext_of, const int32_t* int_of,
-                             int32_t* scratch, hipStream_t s);
-hipError_t launch_copy_back_rows(const int32_t* rows, long long t, const long long* sbase, const long long* new_len,
-                                 const long long* dest_off, const int* dest_cap, const int32_t* scratch,
-                                 long long* row_off, int* row_len, int* row_cap, int32_t* pool, hipStream_t s);
+hipError_t launch_mark_rows(const int32_t* rows, long long t, uint8_t* mark, int value, hipStream_t s);
+hipError_t launch_merge_rows(const UpdateRows& u, const MergePlan& m, long long* row_off, int* row_len, int* row_cap,
+                             int32_t* pool, const int32_t* int_of, int32_t* scratch, hipStream_t s);
+hipError_t launch_open_affected(const int32_t* rows, long long t, const long long* row_off, const int* row_len,
+                                int* level_of, int32_t* list, RowDesc* desc, FrontierCount* fc, hipStream_t s);
+hipError_t launch_recheck_begin(RunScalars* sc, unsigned* xmax32, unsigned long long* xmax64,
+                                unsigned long long* min_bits, int* count, hipStream_t s);
+hipError_t launch_recheck_end(RunScalars* sc, const int* count, const Publish& pub, hipStream_t s);
 // foff: f entries of scratch, sums: scan_sums_capacity(f), total: 1.
 // arcs_hint: the host's estimate of the frontier's arcs (0: unknown), which
 // only sizes the grid.
 hipError_t launch_frontier_expand(const int32_t* frontier, long long f, const long long* row_off, const int* row_len,
-                                  const int32_t* pool, int* level_of, int level, int32_t* next, int* next_count,
-                                  unsigned long long* next_arcs, long long* foff, long long* sums, long long* total,
+                                  const int32_t* pool, int* level_of, int level, int32_t* next, FrontierCount* fc,
+                                  long long* foff, long long* sums, long long* total,
                                   unsigned long long arcs_hint, hipStream_t s);
-hipError_t launch_set_levels(const int32_t* rows, long long t, int* level_of, int level, hipStream_t s);
 hipError_t launch_clear_levels(const int32_t* rows, long long t, int* level_of, hipStream_t s);
 hipError_t launch_c_from_history(const int32_t* rows, long long count, double* const* X, int r, double* c,
                                  hipStream_t s);
@@ -455,8 +477,6 @@ hipError_t launch_c_from_history_f32(const int32_t* rows, long long count, float
 hipError_t launch_max_of_vector_f32(const float* x, long long n, unsigned* out, hipStream_t s);
 
 hipError_t launch_reset_flags(RunScalars* sc, hipStream_t s);
-hipError_t launch_gather_int(const int32_t* rows, long long t, const int* src, int* out, hipStream_t s);
-hipError_t launch_gather_ll(const int32_t* rows, long long t, const long long* src, long long* out, hipStream_t s);
 hipError_t launch_min_lower_active(const BoundArgs& b, const int32_t* act, const int* m_ptr,
                                    unsigned long long* min_bits, uint8_t* mark, long long n, hipStream_t s);
 hipError_t launch_reactivate_all(const BoundArgs& b, long long n, const unsigned long long* min_bits,
@@ -541,9 +561,9 @@ enum PairMode { PAIRS_UNDIRECTED = 0, PAIRS_DIRECTED = 1, PAIRS_REVERSED = 2 };
 // The arcs of a batch grouped by the row that stores them.
 struct RowGroups {
   std::vector<int32_t> rows;               // touched rows, ascending (caller ids)
-  std::vector<long long> ins_off, del_off; // per touched row: first arc in ins_dst / del_dst
-  std::vector<int> ins_cnt, del_cnt, delta;
-  std::vector<int32_t> ins_dst, del_dst;
+  std::vector<long long> ins_off, del_off; // [rows + 1] each row's first arc
+  std::vector<int32_t> ins_dst, del_dst;   // entries, ascending per row
+  std::vector<int32_t> ins_grp, del_grp;   // each arc's touched row
 };
 
 // A validated batch; prepared on the host without reading the graph, applied
@@ -552,7 +572,6 @@ struct PreparedBatch {
   long long n = 0;
   int mode = PAIRS_UNDIRECTED;
   long long n_ins = 0, n_del = 0;
-  std::vector<int32_t> pa;                 // existence-check arcs a -> b: a-ends, then b-ends
   RowGroups fwd;                           // by source row (the state's graph)
   RowGroups rev;                           // directed modes: by target row (the reverse graph)
 };

@@ -1131,19 +1131,7 @@ __global__ void init_run(RunScalars* sc, long long n, double* sigma, double* sig
   for (long long i = t; i < 2 * kDigits; i += stride) hist[i] = 0u;
 }
 
-__global__ void reset_flags(RunScalars* sc) {
-  sc->err = 0;
-  sc->done = 0;
-  sc->status = KATZ_OK;
-  sc->top_count = 0;
-  sc->kept_count = 0;
-  sc->progress = 0;
-  sc->cand_count[0] = 0;
-  sc->cand_count[1] = 0;
-  sc->dmax = 0;
-  sc->col_err = 0;
-  sc->rescale = 0;
-}
+__global__ void reset_flags(RunScalars* sc) { clear_flags(sc); }
 
 }  // namespace
 

@@ -410,3 +410,60 @@ def test_state_save_and_load_resume_bitwise(tmp_path, undirected):
         with pytest.raises(katz.KatzError) as e:
             katz.load_state(tmp_path / bad)
         assert e.value.code == katz.E_INVALID_ARG
+
+
+def _apply(n, rp, col, ins, dels, undirected=True):
+    src = np.repeat(np.arange(n, dtype=np.int64), np.diff(rp))
+    key = src * n + col
+    both = lambda p: np.concatenate([p[:, 0] * n + p[:, 1]] + ([p[:, 1] * n + p[:, 0]] if undirected else []))
+    key = np.concatenate([key[~np.isin(key, both(dels))], both(ins)])
+    return sg.from_edges(n, key // n, key % n, undirected=False)
+
+
+@pytest.mark.parametrize("hub_len", [4095, 4096, 4097, 8192, 12289])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_merge_chunk_edges(hub_len, flags):
+    """Updates of a hub whose row ends just before, at and past a 4096-entry merge
+    chunk: entries deleted and inserted at both ends of the row and on both sides
+    of every chunk boundary, a row emptied, an empty row filled; then undone."""
+    katz = K()
+    say("merge chunks", hub_len, flags)
+    n = 3 * hub_len + 50
+    nbr = 10 + 3 * np.arange(hub_len)                  # gaps of two ids between the hub's neighbours
+    extra = np.stack([nbr[:-1:7], nbr[1::7][:nbr[:-1:7].size]], 1)
+    extra = np.concatenate([extra, [[0, 2]]])
+    src = np.concatenate([np.full(hub_len, 1), extra[:, 0]])
+    rp, col = sg.from_edges(n, src, np.concatenate([nbr, extra[:, 1]]))
+    alpha = 1.0 / (1 + sg.max_degree(rp) + 3000)
+    st, _ = katz.create_state(*dev(rp, col), 20, alpha=alpha, eps=1e-9, degree_cap=sg.max_degree(rp) + 3000, flags=flags)
+    edge = sorted({p for b in range(0, hub_len + 1, 4096) for p in (b - 2, b - 1, b, b + 1) if 0 <= p < hub_len} |
+                  {0, 1, hub_len - 2, hub_len - 1})
+    dels = np.array([[1, nbr[p]] for p in edge] + [[0, 2]], dtype=np.int64)        # node 0's row becomes empty
+    ins = [[1, nbr[p] + 1] for p in edge] + [[1, nbr[p] - 1] for p in edge] + [[3, 4], [1, 5], [1, n - 1]]
+    ins += [[1, v] for v in nbr[hub_len // 2:hub_len // 2 + 600] + 2 if [1, v] not in ins]   # outgrows its capacity or not
+    ins = np.unique(np.array(ins, dtype=np.int64), axis=0)
+    for add, drop in ((ins, dels), (dels, ins), (ins, dels)):
+        res = st.update(add, drop)
+        rp, col = _apply(n, rp, col, add, drop)
+        check_against_static(katz, res, rp, col, alpha)
+    st.free()
+
+
+def test_state_with_more_hubs_than_a_binning_workgroup_holds():
+    """1100 rows of several segments side by side (a renumbered state puts them
+    first): their segment tables come from one 1024-row binning workgroup and the
+    next.  Updates re-bin them; results stay bitwise a static run's."""
+    katz = K()
+    say("many hubs")
+    hubs, leaves = 1100, 4200
+    n = hubs + leaves
+    a, b = np.meshgrid(np.arange(hubs), hubs + np.arange(leaves), indexing="ij")
+    rp, col = sg.from_edges(n, a.ravel(), b.ravel())
+    alpha = 1.0 / (1 + sg.max_degree(rp) + 10)
+    st, _ = katz.create_state(*dev(rp, col), 10, alpha=alpha, eps=1e-9, degree_cap=sg.max_degree(rp) + 10, max_iter=6)
+    ins = np.array([[0, 1], [2, 7], [1098, 1099]], dtype=np.int64)
+    dels = np.array([[5, hubs], [1099, n - 1]], dtype=np.int64)
+    res = st.update(ins, dels)
+    rp, col = _apply(n, rp, col, ins, dels)
+    check_against_static(katz, res, rp, col, alpha)
+    st.free()
