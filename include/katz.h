@@ -428,7 +428,10 @@ int katz_timing_read(katz_timing* out);
 
 /* ---- launch tuning of the walk kernels ------------------------------------
  * Process-wide launch shape of the walk step (the degree-binned SpMV of Eq.
- * (basic_recurrence), Section 3.2).  No setting but split_hot_bytes and
+ * (basic_recurrence), Section 3.2).  With hub_bytes, blocks_per_cu, walk_groups
+ * and split_hot_bytes all 0 the library chooses by the size of the walk vector: a
+ * shared LDS copy where it outgrows an L2, else one workgroup per work item.  No
+ * setting but split_hot_bytes and
  * bin_bounds changes any result bit: every row is still summed by the same
  * lane schedule, and the LDS copy holds exact walk entries.
  *   hub_bytes            single-graph static calls with the internal

@@ -272,6 +272,41 @@ BinBounds bounds_of(const katz_tuning& t) {
   return bb;
 }
 
+int cu_count(int dev);
+
+// The walk step's launch shape for a graph of n nodes (xs bytes per walk entry).
+struct LaunchShape {
+  long long grid = 0;   // persistent grid (0: one workgroup per work item)
+  int groups = 1;       // 256-thread groups per workgroup
+  int hub_n = 0;        // walk entries copied to LDS (renumbered graphs)
+};
+
+// With nothing tuned, a renumbered graph whose walk vector outgrows one XCD's L2
+// (4 MiB) takes the shape that the autotuner finds for such graphs: one workgroup of
+// four groups per CU that share a copy of the 156 KiB of entries most arcs point to.
+// Walk step without and with it, R-MAT (16 draws per node): 2^19 nodes FP32 (2 MiB)
+// 55 and 63 us, FP64 62 and 63; 10^6 FP32 (4 MiB) 102 and 105, FP64 115 and 107;
+// 2 10^6 FP32 241 and 211; 2^22 FP32 621 and 491, FP64 691 and 561.  Flat degrees
+// (Erdos-Renyi, 8 draws): 10^6 FP32 97 and 104, FP64 157 and 157; 2^22 931 and 929.
+constexpr long long kSharedCopyFrom = 4ll << 20;
+constexpr int kSharedCopyBytes = 159744;
+
+LaunchShape launch_shape(const katz_tuning& tu, long long n, int xs, bool renumbered, int dev) {
+  LaunchShape ls;
+  if (tu.hub_bytes == 0 && tu.blocks_per_cu == 0 && tu.walk_groups == 0 && tu.split_hot_bytes == 0) {
+    if (renumbered && n * xs > kSharedCopyFrom) {
+      ls.grid = cu_count(dev);
+      ls.groups = kWalkGroups;
+      ls.hub_n = (int)std::min<long long>(n, kSharedCopyBytes / xs);
+    }
+    return ls;
+  }
+  ls.grid = (long long)tu.blocks_per_cu * cu_count(dev);
+  ls.groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
+  if (renumbered && ls.grid > 0) ls.hub_n = (int)std::min<long long>(n, tu.hub_bytes / xs);
+  return ls;
+}
+
 int cu_count(int dev) {
   static std::mutex mu;
   static std::map<int, int> cache;
@@ -729,9 +764,7 @@ struct Run {
   int cur = 0;
   bool first_select = true;
   int grid = 1;
-  int hub_n = 0;               // walk entries copied to LDS (renumbered static runs)
-  long long walk_grid = 0;     // persistent walk grid (0: one workgroup per work item)
-  int walk_groups = 1;         // 256-thread groups per walk workgroup (1 or kWalkGroups)
+  LaunchShape shape;           // of the walk steps
   int split_n = 0;             // two-pass walk steps: hot entries are ids below split_n (0: one pass)
   // Renumbered static runs: walk step 2 also renames the caller's column ids
   // into col (walk_step<F32, true>).
@@ -791,7 +824,7 @@ IterArgs iter_args(const Run& run, const Bins& b, int r, bool rewalk, long long&
   ia.count_first = (int)b.count;
   ia.clog2_dmax = clog2((int)std::max<long long>(scale_dmax_of(run), 1));
   ia.rewalk = rewalk ? 1 : 0;
-  ia.hub_n = rewalk ? 0 : run.hub_n;
+  ia.hub_n = rewalk ? 0 : run.shape.hub_n;
   ia.alpha = run.S->alpha;
   ia.etap = run.fp32 ? run.S->etap[r] : 0.0;
   return ia;
@@ -886,11 +919,11 @@ int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
   const int tw = T.start(r == 1 ? T_FIRST : renum ? T_RENUM : T_STEP, s);
   if (r == 1) KATZ_HIP(launch_walk_first(ia, run.fp32, run.n, run.nnz, run.validate >= KATZ_VALIDATE_BASIC, s));
   long long grid = 1;
-  // The renumbering step runs 256-thread workgroups: as many of them as the
-  // tuned grid has groups.
+  // The renumbering step has no copy to fill: one workgroup per work item (R-MAT
+  // 22, FP64: 1575 us; on a persistent grid 1630).
   if (r >= 2)
-    KATZ_HIP(launch_walk_step(ia, run.fp32, tb, renum ? run.walk_grid * run.walk_groups : run.walk_grid, &grid, s,
-                              renum, renum ? 1 : run.walk_groups));
+    KATZ_HIP(launch_walk_step(ia, run.fp32, tb, renum ? 0 : run.shape.grid, &grid, s, renum,
+                              renum ? 1 : run.shape.groups));
   T.stop(tw, s);
   const long long nb = r == 1 ? std::max<long long>(1, (run.bins->count + kWG - 1) / kWG) : grid;
   run.walk_max = WalkMax{nullptr, 0};
@@ -1386,9 +1419,7 @@ int rank_in_arena(Arena& ar, const katz_csr* g, const katz_params* p, katz_resul
   run.coff = stg.relabel.coff;
   run.pmap = stg.relabel.pmap;
   run.ncol = stg.ncol;
-  run.walk_grid = (long long)tu.blocks_per_cu * cu_count(dev);
-  run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
-  run.hub_n = pl.reorder ? (int)std::min<long long>(g->n, tu.hub_bytes / (pl.fp32 ? 4 : 8)) : 0;
+  run.shape = launch_shape(tu, g->n, pl.fp32 ? 4 : 8, pl.reorder, dev);
   run.split_n = pl.split_n;
   run.bins = &b;
   run.w = &w;
@@ -1596,9 +1627,7 @@ int bounds_on(const katz_csr* g, const katz_params* p, int r_target, double* low
   run.coff = stg.relabel.coff;
   run.pmap = stg.relabel.pmap;
   run.ncol = stg.ncol;
-  run.walk_grid = (long long)tu.blocks_per_cu * cu_count(dev);
-  run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
-  run.hub_n = pl.reorder ? (int)std::min<long long>(g->n, tu.hub_bytes / (pl.fp32 ? 4 : 8)) : 0;
+  run.shape = launch_shape(tu, g->n, pl.fp32 ? 4 : 8, pl.reorder, dev);
   run.split_n = pl.split_n;
   run.bins = &b;
   run.w = &w;
@@ -1636,7 +1665,7 @@ int spmv(const Run& run, const double* v, double* y, hipStream_t s) {
   ia.x_out = y;
   ia.hub_n = 0;
   long long grid = 0;
-  KATZ_HIP(launch_walk_step(ia, 0, tb, run.walk_grid, &grid, s, false, run.walk_groups));
+  KATZ_HIP(launch_walk_step(ia, 0, tb, run.shape.grid, &grid, s, false, run.shape.groups));
   return KATZ_OK;
 }
 
@@ -1701,11 +1730,7 @@ int solve_on(const katz_csr* g, const katz_params* p, int method, double tol, do
   run.bins = &b;
   run.w = &w;
   run.S = &S;
-  {
-    const katz_tuning tu = current_tuning();
-    run.walk_grid = (long long)tu.blocks_per_cu * cu_count(dev);
-    run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
-  }
+  run.shape = launch_shape(current_tuning(), n, 8, false, dev);
   const int max_iter = p->max_iter ? p->max_iter : 1000;
   double* x0 = static_cast<double*>(w.x[0]);
   double* x1 = static_cast<double*>(w.x[1]);
@@ -2418,12 +2443,8 @@ Run state_run(katz_state* st) {
   run.ext_of = st->ext_of;
   run.int_of = st->int_of;
   if (st->ext_of) {
-    // Renumbered: whole-graph walks take the tuned launch shape with the LDS
-    // copy of the hottest entries, as static calls do.
-    const katz_tuning tu = current_tuning();
-    run.walk_grid = (long long)tu.blocks_per_cu * cu_count(st->device);
-    run.walk_groups = tu.walk_groups == kWalkGroups ? kWalkGroups : 1;
-    run.hub_n = run.walk_grid > 0 ? (int)std::min<long long>(st->n, tu.hub_bytes / (st->fp32 ? 4 : 8)) : 0;
+    // Renumbered: whole-graph walks take the launch shape of static calls.
+    run.shape = launch_shape(current_tuning(), st->n, st->fp32 ? 4 : 8, true, st->device);
   }
   return run;
 }
@@ -3270,9 +3291,9 @@ int apply_batch(katz_state* st, const PreparedBatch& pb, katz_result* out, hipSt
         // hottest entries of x_{i-1} in a renumbered state).
         KATZ_TRY(refresh_bins(st, s));
         IterArgs ia = iter_args(run, st->bins, i, true, tb);
-        ia.hub_n = run.hub_n;
+        ia.hub_n = run.shape.hub_n;
         if (i == 1) KATZ_HIP(launch_walk_first(ia, run.fp32, n, st->nnz, 0, s));
-        else KATZ_HIP(launch_walk_step(ia, run.fp32, tb, run.walk_grid, &g_used, s, false, run.walk_groups));
+        else KATZ_HIP(launch_walk_step(ia, run.fp32, tb, run.shape.grid, &g_used, s, false, run.shape.groups));
       } else {
         KATZ_TRY(bin_rows(st, st->lbins, st->sc2, st->clist, csize, s));
         const IterArgs ia = iter_args(run, st->lbins, i, true, tb);
