@@ -97,24 +97,27 @@ struct Arena {
   hipEvent_t last = nullptr;
   hipStream_t last_stream = nullptr;
   bool recorded = false;
-  // Batched calls: the stream their hipGraph replays on, and the instantiated
-  // graph of the last batch with the bytes of every argument it captured (a
-  // call whose arguments are byte-identical replays it without re-capturing).
-  hipStream_t graph_stream = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
-  std::vector<unsigned char> graph_key;
+  // Batched calls: pinned memory that their per-graph tables are uploaded from.
+  char* pin = nullptr;
+  size_t pin_cap = 0;
 
   ~Arena() {
     if (recorded) (void)hipEventSynchronize(last);
     if (last) (void)hipEventDestroy(last);
-    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-    if (graph_stream) (void)hipStreamDestroy(graph_stream);
+    if (pin) (void)hipHostFree(pin);
     if (base && !fixed) (void)hipFree(base);
   }
-  void drop_graph() {
-    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-    graph_exec = nullptr;
-    graph_key.clear();
+  int grow_pin(size_t bytes) {
+    if (bytes <= pin_cap) return KATZ_OK;
+    if (pin) (void)hipHostFree(pin);
+    pin = nullptr;
+    pin_cap = 0;
+    if (hipHostMalloc((void**)&pin, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return KATZ_E_OOM;
+    }
+    pin_cap = bytes;
+    return KATZ_OK;
   }
   // A call on stream s that takes over the workspace orders its work after
   // the previous call's.
@@ -149,7 +152,6 @@ struct Arena {
     if (bytes <= cap) return KATZ_OK;
     if (fixed) return KATZ_E_SCRATCH;
     if (recorded) KATZ_HIP(hipEventSynchronize(last));   // a stream-ordered call may still use it
-    drop_graph();                                          // its captured arguments point into the old buffer
     if (base) (void)hipFree(base);
     base = nullptr;
     cap = 0;
@@ -1804,8 +1806,6 @@ int solve_on(const katz_csr* g, const katz_params* p, int method, double tol, do
 // ---------------------------------------------------------------------------
 // Batched form: many graphs in one sequence of launches (katz_batch.hip).
 // ---------------------------------------------------------------------------
-constexpr int kItersPerGraph = 4;   // iterations captured in one hipGraph
-
 int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* out, hipStream_t s) {
   const Range range_call("katz_rank_static batch");
   const katz_tuning tu_b = current_tuning();   // one setting for the whole call
@@ -1866,7 +1866,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   double* galpha = nullptr;
   int* gclog2 = nullptr;
   int* gdmax = nullptr;
-  double *gsigma = nullptr, *gsigsum = nullptr, *etap = nullptr;
+  double *gsigma = nullptr, *gsigsum = nullptr, *eta = nullptr, *etap = nullptr, *grho = nullptr;
   unsigned long long* rest = nullptr;
   int* gexp = nullptr;
   unsigned* gxmax32 = nullptr;
@@ -1880,7 +1880,6 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   int* n_items = nullptr;
   int* xcd_of = nullptr;
   long long blk_cap = 0;
-  int* r_dev = nullptr;
   int* ndone = nullptr;
   int32_t** o_ids = nullptr;
   double** o_lo = nullptr;
@@ -1888,14 +1887,33 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   std::vector<void*> stage_rp(count, nullptr), stage_col(count, nullptr);
   int32_t* st_ids = nullptr;
   double *st_lo = nullptr, *st_up = nullptr;
+  size_t up1[2] = {}, up2[2] = {};
   auto lay = [&]() {
     ar.used = 0;
     bins_caps(b, total_n, total_nnz + count);
     w.sc = ar.take<RunScalars>(1);
     gsc = ar.take<RunScalars>(count);
+    // Uploaded before the binning ...
+    up1[0] = ar.used;
     gbase = ar.take<long long>(count + 1);
     gabase = ar.take<long long>(count + 1);
+    grp = ar.take<const void*>(count);
+    grp64 = ar.take<int>(count);
+    gnnz = ar.take<long long>(count);
+    gcol = ar.take<const int32_t*>(count);
+    up1[1] = ar.used;
+    // ... and once the longest rows are known.
+    up2[0] = ar.used;
     gcol_walk = ar.take<const int32_t*>(count);
+    galpha = ar.take<double>(count);
+    grho = ar.take<double>(count);
+    gclog2 = ar.take<int>(count);
+    gsel = ar.take<GraphSel>(count);
+    xcd_of = ar.take<int>(count);
+    o_ids = ar.take<int32_t*>(count);
+    o_lo = ar.take<double*>(count);
+    o_up = ar.take<double*>(count);
+    up2[1] = ar.used;
     if (reorder) {
       run_first = ar.take<long long>((size_t)count * NUM_BINS);
       run_last = ar.take<long long>((size_t)count * NUM_BINS);
@@ -1911,22 +1929,16 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
       rsums = ar.take<long long>(scan_sums_capacity(total_n));
       rtot = ar.take<long long>(2);
     }
-    grp = ar.take<const void*>(count);
-    grp64 = ar.take<int>(count);
-    gnnz = ar.take<long long>(count);
-    gcol = ar.take<const int32_t*>(count);
-    galpha = ar.take<double>(count);
-    gclog2 = ar.take<int>(count);
     gdmax = ar.take<int>(count);
     gsigma = ar.take<double>((size_t)count * stride);
     gsigsum = ar.take<double>((size_t)count * stride);
     gexp = ar.take<int>((size_t)count * stride);
     gxmax32 = ar.take<unsigned>((size_t)count * stride);
     gxmax64 = ar.take<unsigned long long>((size_t)count * stride);
+    eta = ar.take<double>((size_t)count * stride);
     etap = ar.take<double>((size_t)count * stride);
     rest = ar.take<unsigned long long>(count);
     gid_of = ar.take<int>(total_n);
-    gsel = ar.take<GraphSel>(count);
     // Workgroup slots of one walk step: at most one per 4 rows of up to 1024
     // arcs, one per longer row or segment, one per long row's combine wave group.
     blk_cap = total_n / 4 + total_nnz / 1025 + 2 * b.seg_cap + 64;
@@ -1934,13 +1946,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     blk_m = ar.take<double>(blk_cap);
     item_g = ar.take<int>(blk_cap);
     items = ar.take<int>(blk_cap * xcd_groups);
-    n_items = ar.take<int>(kXcds);
-    xcd_of = ar.take<int>(count);
-    r_dev = ar.take<int>(1);
+    n_items = ar.take<int>(2 * kXcds);
     ndone = ar.take<int>(1);
-    o_ids = ar.take<int32_t*>(count);
-    o_lo = ar.take<double*>(count);
-    o_up = ar.take<double*>(count);
     b.tab.blk = ar.take<long long>((size_t)kPrepTableRows * b.tab.nblocks);
     b.tab.totals = ar.take<long long>(kPrepTableRows);
     b.desc = ar.take<RowDesc>(total_n);
@@ -1976,15 +1983,22 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   ar.measuring = false;
   KATZ_TRY(ar.grow(ar.used));
   lay();
+  KATZ_TRY(ar.grow_pin(up2[1]));
+  // The pinned mirror of a table in the workspace.
+  auto host = [&ar](auto* dev) {
+    using P = std::remove_const_t<std::remove_pointer_t<decltype(dev)>>;
+    return reinterpret_cast<P*>(ar.pin + (reinterpret_cast<const char*>(dev) - ar.base));
+  };
 
   CallTimer T;
   T.call_begin(s);
   const int tp = T.start(T_PREP, s);
   // ---- per-graph tables ----
-  std::vector<long long> h_base(count + 1, 0), h_abase(count + 1, 0), h_nnz(count);
-  std::vector<const void*> h_rp(count);
-  std::vector<const int32_t*> h_col(count);
-  std::vector<int> h_rp64(count);
+  long long *h_base = host(gbase), *h_abase = host(gabase), *h_nnz = host(gnnz);
+  const void** h_rp = host(grp);
+  const int32_t** h_col = host(gcol);
+  int* h_rp64 = host(grp64);
+  h_base[0] = h_abase[0] = 0;
   for (int i = 0; i < count; ++i) {
     h_base[i + 1] = h_base[i] + g[i].n;
     h_abase[i + 1] = h_abase[i] + g[i].nnz;
@@ -1998,12 +2012,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     if (col_host[i])
       KATZ_HIP(hipMemcpyAsync(stage_col[i], g[i].col, (size_t)g[i].nnz * 4, hipMemcpyHostToDevice, s));
   }
-  KATZ_HIP(hipMemcpyAsync(gbase, h_base.data(), sizeof(long long) * (count + 1), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gnnz, h_nnz.data(), sizeof(long long) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gabase, h_abase.data(), sizeof(long long) * (count + 1), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(grp, h_rp.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(grp64, h_rp64.data(), sizeof(int) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gcol, h_col.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
+  KATZ_HIP(hipMemcpyAsync(ar.base + up1[0], ar.pin + up1[0], up1[1] - up1[0], hipMemcpyHostToDevice, s));
   KATZ_HIP(launch_reset_flags(w.sc, s));
   KATZ_HIP(hipMemsetAsync(gdmax, 0, sizeof(int) * count, s));
   int validate = 0;
@@ -2032,38 +2041,24 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     KATZ_HIP(launch_batch_rename(b.desc, b.bin_base, b.bin_count, b.segs, b.seg_total, b.huge, noff, gid_of, gbase,
                                  gcol, coff, pmap, ncol, s));
   }
-  std::vector<const int32_t*> h_cw(count);
+  const int32_t** h_cw = host(gcol_walk);
   for (int i = 0; i < count; ++i) h_cw[i] = reorder ? ncol : h_col[i];
-  KATZ_HIP(hipMemcpyAsync(gcol_walk, h_cw.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
 
   // ---- per-graph scalars, selection views, initial state ----
   std::vector<Scalars> S(count);
   for (int i = 0; i < count; ++i) KATZ_TRY(resolve_alpha(p[i].alpha, h_dmax[i], S[i]));
-  // FP32 eta tables per graph, from the graph's own longest row (the same
-  // tables a single-graph call builds, so results match it bitwise).
-  if (fp32)
-    for (int i = 0; i < count; ++i) fp32_tables(S[i], h_dmax[i], max_iter, b.bb);
-  std::vector<double> h_alpha(count), h_sigma((size_t)count * stride, 0.0), h_sigsum((size_t)count * stride, 0.0);
-  std::vector<int> h_clog2(count), h_exp((size_t)count * stride, 0);
-  std::vector<RunScalars> h_sc(count);
-  std::vector<GraphSel> h_sel(count);
-  std::vector<int32_t*> h_oids(count);
-  std::vector<double*> h_olo(count), h_oup(count);
+  double *h_alpha = host(galpha), *h_rho = host(grho);
+  int* h_clog2 = host(gclog2);
+  GraphSel* h_sel = host(gsel);
+  int32_t** h_oids = host(o_ids);
+  double **h_olo = host(o_lo), **h_oup = host(o_up);
   long long koff = 0;
   for (int i = 0; i < count; ++i) {
     h_alpha[i] = S[i].alpha;
     h_clog2[i] = clog2(std::max(h_dmax[i], 1));
-    h_sigma[(size_t)i * stride] = 1.0;
-    if (fp32) {
-      // x_0 = 1, so the first scale exponent is 1 + ceil(log2 d_max).
-      const int e1 = 1 + h_clog2[i];
-      h_exp[(size_t)i * stride + 1] = e1;
-      h_sigma[(size_t)i * stride + 1] = std::ldexp(S[i].alpha, e1);
-      h_sigsum[(size_t)i * stride + 1] = h_sigma[(size_t)i * stride + 1];
-    }
-    RunScalars z{};
-    z.m = (int)g[i].n;
-    h_sc[i] = z;
+    // FP32 rounding bound of the graph's own longest row, as a single-graph call's.
+    if (fp32) fp32_tables(S[i], h_dmax[i], 1, b.bb);
+    h_rho[i] = S[i].rho;
     GraphSel& gs = h_sel[i];
     gs = GraphSel{};
     BoundArgs& bd = gs.b;
@@ -2103,32 +2098,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     h_oup[i] = out_host ? st_up + koff : out[i].upper;
     koff += p[i].k;
   }
-  std::vector<double> h_etap((size_t)count * stride, 0.0);
-  if (fp32)
-    for (int i = 0; i < count; ++i)
-      for (int r = 0; r <= max_iter; ++r) h_etap[(size_t)i * stride + r] = S[i].etap[r];
-  KATZ_HIP(hipMemcpyAsync(galpha, h_alpha.data(), sizeof(double) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gclog2, h_clog2.data(), sizeof(int) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gsigma, h_sigma.data(), sizeof(double) * h_sigma.size(), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gsigsum, h_sigsum.data(), sizeof(double) * h_sigsum.size(), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gexp, h_exp.data(), sizeof(int) * h_exp.size(), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(etap, h_etap.data(), sizeof(double) * h_etap.size(), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gsc, h_sc.data(), sizeof(RunScalars) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(gsel, h_sel.data(), sizeof(GraphSel) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(o_ids, h_oids.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(o_lo, h_olo.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemcpyAsync(o_up, h_oup.data(), sizeof(void*) * count, hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemsetAsync(gxmax32, 0, sizeof(unsigned) * (size_t)count * stride, s));
-  KATZ_HIP(hipMemsetAsync(gxmax64, 0, sizeof(unsigned long long) * (size_t)count * stride, s));
-  KATZ_HIP(launch_fill_ones(w.x[0], total_n, fp32, s));
-  const int one = 1;
-  KATZ_HIP(hipMemcpyAsync(r_dev, &one, sizeof(int), hipMemcpyHostToDevice, s));
-  KATZ_HIP(hipMemsetAsync(ndone, 0, sizeof(int), s));
-  T.stop(tp, s);
-
-  // ---- the iteration, captured once and replayed ----
-  BatchWalk bw;
-  std::memset(&bw, 0, sizeof(bw));   // padding too: the bytes key the cached hipGraph
+  // ---- the iterations ----
+  BatchWalk bw{};
   bw.desc = b.desc;
   bw.segs = b.segs;
   bw.huge = b.huge;
@@ -2165,7 +2136,6 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   bw.e = w.e;
   bw.partial = w.partial;
   bw.etap = etap;
-  bw.r_dev = r_dev;
   bw.stride = stride;
   bw.blk_g = blk_g;
   bw.blk_m = blk_m;
@@ -2177,7 +2147,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   bw.xcd_groups = xcd_groups;
   bw.item_cap = blk_cap;
   bw.xcd_of = xcd_of;
-  std::vector<int> h_xcd(count, 0);
+  int* h_xcd = host(xcd_of);
+  std::fill(h_xcd, h_xcd + count, 0);
   if (xcd_groups > 1) {
     // Graphs to XCDs, largest first, each to the least loaded (by arcs).
     std::vector<int> order(count);
@@ -2192,7 +2163,6 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
       load[best] += g[i].nnz + g[i].n;
     }
   }
-  KATZ_HIP(hipMemcpyAsync(xcd_of, h_xcd.data(), sizeof(int) * count, hipMemcpyHostToDevice, s));
   bw.fp32 = fp32;
   const long long total_blocks = bw.first_block[NUM_BINS];
   long long walk_grid = (long long)tu_b.batch_blocks_per_cu * cu_count(dev);
@@ -2202,99 +2172,51 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     if (total_blocks + (nh + kWG / kWave - 1) / (kWG / kWave) > blk_cap) return KATZ_E_HIP;   // sizing bound broken
   }
 
-  if (!ar.graph_stream) KATZ_HIP(hipStreamCreateWithFlags(&ar.graph_stream, hipStreamNonBlocking));
-  hipStream_t cs = ar.graph_stream;
+  KATZ_HIP(hipMemcpyAsync(ar.base + up2[0], ar.pin + up2[0], up2[1] - up2[0], hipMemcpyHostToDevice, s));
+  const BatchNext next{gsigma, gsigsum, eta, etap, gexp, gxmax32, gxmax64, galpha, grho, gclog2, ndone, stride};
+  KATZ_HIP(launch_batch_begin(gsc, gbase, gdmax, count, n_items, next, fp32, s));
   KATZ_HIP(launch_batch_item_graphs(bw, total_blocks, item_g, s));
-  KATZ_HIP(hipMemsetAsync(n_items, 0, sizeof(int) * kXcds, s));
-  KATZ_HIP(hipStreamSynchronize(s));
-  // The captured launches and every value they take; all pointers lie in this
-  // call's workspace or its per-graph tables, so a batch of the same shape in
-  // the same workspace captures the same bytes.
-  std::vector<unsigned char> key;
-  auto put = [&key](const void* v, size_t bytes) {
-    const unsigned char* c = static_cast<const unsigned char*>(v);
-    key.insert(key.end(), c, c + bytes);
-  };
+  T.stop(tp, s);
+  const int ts = T.start(T_STEP, s);
   const long long n_huge = b.bin_count[BIN_HUGE];
-  const void* ptrs[] = {gsel, r_dev, gsc, gxmax32, gsigma, gsigsum, gexp, galpha, gclog2, ndone, n_items, items};
-  put(&bw, sizeof(bw));
-  put(ptrs, sizeof(ptrs));
-  put(&count, sizeof(count));
-  put(&stride, sizeof(stride));
-  put(&fp32, sizeof(fp32));
-  put(&total_blocks, sizeof(total_blocks));
-  put(&walk_grid, sizeof(walk_grid));
-  put(&n_huge, sizeof(n_huge));
-  if (!ar.graph_exec || key != ar.graph_key) {
-    ar.drop_graph();
-    hipGraph_t gr = nullptr;
-    KATZ_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    hipError_t ce = hipSuccess;
-    for (int it = 0; it < kItersPerGraph && ce == hipSuccess; ++it) {
-      ce = launch_batch_live_items(bw, total_blocks, items, n_items, cs);
-      if (ce == hipSuccess) ce = launch_walk_batch(bw, total_blocks, walk_grid, n_huge, cs);
-      if (ce == hipSuccess) ce = launch_select_wg(gsel, count, r_dev, fp32, cs);
-      if (ce == hipSuccess)
-        ce = launch_batch_advance(r_dev, count, gsc, gxmax32, gsigma, gsigsum, gexp, galpha, gclog2, stride, fp32,
-                                  ndone, n_items, cs);
-    }
-    const hipError_t ee = hipStreamEndCapture(cs, &gr);
-    if (ce != hipSuccess || ee != hipSuccess) {
-      if (gr) (void)hipGraphDestroy(gr);
-      (void)hipGetLastError();
-      return KATZ_E_HIP;
-    }
-    const hipError_t ie = hipGraphInstantiate(&ar.graph_exec, gr, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(gr);
-    if (ie != hipSuccess) {
-      ar.graph_exec = nullptr;
-      (void)hipGetLastError();
-      return KATZ_E_HIP;
-    }
-    ar.graph_key = std::move(key);
+  for (int r = 1; r <= max_iter; ++r) {
+    const Range range("katz iteration", r);
+    bw.r = r;
+    const unsigned seq = ++ar.hs.seq;
+    KATZ_HIP(launch_batch_live_items(bw, total_blocks, items, n_items, ndone, Publish{&ar.hs.flags[seq & 1], seq}, s));
+    KATZ_HIP(launch_walk_batch(bw, total_blocks, walk_grid, n_huge, s));
+    KATZ_HIP(launch_select_wg(gsel, count, r, fp32, next, s));
+    // The graphs that stopped before iteration r, which is on its way by now.
+    PassFlags f;
+    KATZ_TRY(wait_flags(ar.hs, seq, w.sc, &f, s));
+    if (f.m >= count) break;
   }
-  const int ts = T.start(T_STEP, cs);
-  const int max_replays = (max_iter + kItersPerGraph - 1) / kItersPerGraph + 1;
-  int replay = 0;
-  bool finished = false;
-  int* h_done = reinterpret_cast<int*>(ar.hs.bits);
-  while (!finished && replay < max_replays) {
-    KATZ_HIP(hipGraphLaunch(ar.graph_exec, cs));
-    KATZ_HIP(hipMemcpyAsync(&h_done[replay & 1], ndone, sizeof(int), hipMemcpyDeviceToHost, cs));
-    KATZ_HIP(hipEventRecord(ar.hs.ev[replay & 1], cs));
-    if (replay >= 1) {
-      KATZ_HIP(hipEventSynchronize(ar.hs.ev[(replay - 1) & 1]));
-      if (h_done[(replay - 1) & 1] >= count) finished = true;
-    }
-    ++replay;
-  }
-  T.stop(ts, cs);
-  KATZ_HIP(hipStreamSynchronize(cs));
+  T.stop(ts, s);
 
   // ---- outputs ----
   std::vector<RunScalars> fin(count);
-  KATZ_HIP(hipMemcpyAsync(fin.data(), gsc, sizeof(RunScalars) * count, hipMemcpyDeviceToHost, cs));
-  KATZ_HIP(hipStreamSynchronize(cs));
+  KATZ_HIP(hipMemcpyAsync(fin.data(), gsc, sizeof(RunScalars) * count, hipMemcpyDeviceToHost, s));
+  KATZ_HIP(hipStreamSynchronize(s));
   for (int i = 0; i < count; ++i)
     if (fin[i].err) return fin[i].err == 2 ? KATZ_E_HIP : KATZ_E_CSR;
-  const int tr = T.start(T_RESULT, cs);
-  KATZ_HIP(hipMemsetAsync(w.mark, 0, (size_t)total_n, cs));
-  KATZ_HIP(hipMemsetAsync(rest, 0, sizeof(unsigned long long) * count, cs));
-  KATZ_HIP(launch_batch_write(gsel, count, max_n, o_ids, o_lo, o_up, w.mark, rest, cs));
-  T.stop(tr, cs);
+  const int tr = T.start(T_RESULT, s);
+  KATZ_HIP(hipMemsetAsync(w.mark, 0, (size_t)total_n, s));
+  KATZ_HIP(hipMemsetAsync(rest, 0, sizeof(unsigned long long) * count, s));
+  KATZ_HIP(launch_batch_write(gsel, count, max_n, o_ids, o_lo, o_up, w.mark, rest, s));
+  T.stop(tr, s);
   std::vector<unsigned long long> h_rest(count);
-  KATZ_HIP(hipMemcpyAsync(h_rest.data(), rest, sizeof(unsigned long long) * count, hipMemcpyDeviceToHost, cs));
+  KATZ_HIP(hipMemcpyAsync(h_rest.data(), rest, sizeof(unsigned long long) * count, hipMemcpyDeviceToHost, s));
   if (out_host) {
     koff = 0;
     for (int i = 0; i < count; ++i) {
-      KATZ_HIP(hipMemcpyAsync(out[i].topk_ids, st_ids + koff, sizeof(int32_t) * p[i].k, hipMemcpyDefault, cs));
-      KATZ_HIP(hipMemcpyAsync(out[i].lower, st_lo + koff, sizeof(double) * p[i].k, hipMemcpyDefault, cs));
-      KATZ_HIP(hipMemcpyAsync(out[i].upper, st_up + koff, sizeof(double) * p[i].k, hipMemcpyDefault, cs));
+      KATZ_HIP(hipMemcpyAsync(out[i].topk_ids, st_ids + koff, sizeof(int32_t) * p[i].k, hipMemcpyDefault, s));
+      KATZ_HIP(hipMemcpyAsync(out[i].lower, st_lo + koff, sizeof(double) * p[i].k, hipMemcpyDefault, s));
+      KATZ_HIP(hipMemcpyAsync(out[i].upper, st_up + koff, sizeof(double) * p[i].k, hipMemcpyDefault, s));
       koff += p[i].k;
     }
   }
-  KATZ_HIP(hipStreamSynchronize(cs));
-  T.commit(cs);
+  KATZ_HIP(hipStreamSynchronize(s));
+  T.commit(s);
   int worst = KATZ_OK;
   for (int i = 0; i < count; ++i) {
     double rest_i;
@@ -2303,6 +2225,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     out[i].status = fin[i].done ? fin[i].status : KATZ_W_ITER_LIMIT;
     out[i].active_final = fin[i].m;
     out[i].alpha_used = S[i].alpha;
+    if (fp32) fp32_tables(S[i], h_dmax[i], std::max(1, fin[i].iterations), b.bb);
     out[i].eta = fp32 ? S[i].eta[std::max(1, fin[i].iterations)] : 0.0;
     out[i].rest_upper_max = (p[i].k == g[i].n) ? -std::numeric_limits<double>::infinity() : rest_i;
     worst = std::max(worst, out[i].status);

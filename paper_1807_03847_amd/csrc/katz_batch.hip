@@ -4,13 +4,17 @@
 // The graphs are not copied: their rows are binned together under global row
 // ids (graph g owns ids gbase[g] .. gbase[g+1] - 1), and every row carries the
 // graph id that locates its column array, its node base and its alpha.  One
-// iteration is three launches whose arguments never change, so a block of
-// iterations can be captured into a hipGraph and replayed:
-//   walk_batch     walk step of every row whose graph is still iterating,
-//   select_wg      one workgroup per graph (converged() of Algorithm 1),
-//   batch_advance  FP32 scales of the next iteration; r += 1.
-// The iteration number r lives in device memory.  The walk vector's r = 0
-// buffer holds ones, so the first iteration is an ordinary walk step.
+// iteration is
+//   batch_live_items  the work items of the graphs still iterating; tells the host
+//                     how many have stopped,
+//   walk_batch        their walk step (batch_huge_combine: rows of several
+//                     segments; batch_reduce_max: the per-graph maxima),
+//   select_wg         one workgroup per graph (converged() of Algorithm 1), which
+//                     also leaves the graph's FP32 scale of the next iteration,
+// launched one after another, the next iteration's before the host has seen this
+// one's end.  (Four iterations captured into a hipGraph and replayed ran up to seven
+// iterations past the last graph's end, 46 us each, and a new batch paid 1 ms for
+// the capture.)
 #include <algorithm>
 
 #include "katz_device.h"
@@ -280,7 +284,7 @@ __device__ __forceinline__ void batch_store_max(const BatchWalk& a, int r, int g
 // issues one atomic per graph it saw.
 template <bool F32>
 __global__ void __launch_bounds__(kWG) batch_reduce_max(BatchWalk a, long long nb) {
-  const int r = *a.r_dev;
+  const int r = a.r;
   if (r >= a.stride) return;
   extern __shared__ unsigned long long gmax_lds[];
   for (int i = threadIdx.x; i < a.count; i += kWG) gmax_lds[i] = 0ull;
@@ -328,8 +332,12 @@ __device__ __forceinline__ void batch_rows_group(const BatchWalk& a, int r, long
   if (valid && lane == 0) p = batch_prefetch<F32>(a, r, g, d.row);
   T sum = 0;
   if (valid) {
-    const T* x = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]) + a.gbase[g];
-    sum = batch_strided_sum<F32>(x, a.gcol[g] + d.off, d.len, lane, G);
+    if (r == 1) {
+      if (lane == 0) sum = (T)d.len;   // x_0 = 1
+    } else {
+      const T* x = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]) + a.gbase[g];
+      sum = batch_strided_sum<F32>(x, a.gcol[g] + d.off, d.len, lane, G);
+    }
   }
 #pragma unroll
   for (int o = G / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, G);
@@ -364,15 +372,17 @@ __device__ __forceinline__ typename Prec<F32>::T batch_block_sum(const typename 
 // Work items are taken from this iteration's list of live items (built by
 // batch_live_items); work item b writes workgroup slot b.  The grid may be
 // smaller than the list (persistent workgroups take items with a grid stride).
+// x_0 = 1, so a row's first sum is its length (no row or segment summed here is
+// longer than 2^24, where sums of ones in 32 bits are exact).
 template <bool F32>
 __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
   using T = typename Prec<F32>::T;
-  const int r = *a.r_dev;
+  const int r = a.r;
   if (r >= a.stride) return;
   // With XCD lists, the workgroups that the hardware places on XCD x (ids
   // x, x + 8, ...) take the items of list x only.
   const int x = blockIdx.x % a.xcd_groups;
-  const long long n_items = a.n_items[x];
+  const long long n_items = a.n_items[(r & 1) * kXcds + x];
   const int* list = a.items + (long long)x * a.item_cap;
   const long long step = gridDim.x / a.xcd_groups;
   const T* xin = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]);
@@ -389,7 +399,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
         // One segment of a long row (item graph gi): its partial sum only;
         // batch_huge_combine adds each row's partials in segment order.
         const SegDesc sd = a.segs[lb];
-        const T tot = batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + sd.off, sd.len);
+        const T tot = r == 1 ? (T)sd.len : batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + sd.off, sd.len);
         if (threadIdx.x == 0) reinterpret_cast<T*>(a.partial)[sd.part] = tot;
         break;
       }
@@ -397,7 +407,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
         const RowDesc d = a.desc[a.bin_base[BIN_B256] + lb];
         BatchIn p{0.0, 0.0, 0.0, 0.0f, 0};
         if (threadIdx.x == 0) p = batch_prefetch<F32>(a, r, gi, d.row);
-        const T tot = batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + d.off, d.len);
+        const T tot = r == 1 ? (T)d.len : batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + d.off, d.len);
         if (threadIdx.x == 0) {
           batch_epilogue<F32>(a, r, d.row, tot, vmax, p);
           g_mine = gi;
@@ -473,8 +483,14 @@ __global__ void __launch_bounds__(kWG) batch_item_graphs(BatchWalk a, long long 
 // item with rows of several graphs.  One atomic per workgroup appends the
 // workgroup's items (their order does not matter: each writes its own slot);
 // with XCD lists, one atomic per wave and list.
-__global__ void __launch_bounds__(kWG) batch_live_items(BatchWalk a, long long total, int* items, int* n_items) {
-  const int r = *a.r_dev;
+__global__ void __launch_bounds__(kWG) batch_live_items(BatchWalk a, long long total, int* items, int* counters,
+                                                        const int* ndone, Publish pub) {
+  const int r = a.r;
+  int* n_items = counters + (r & 1) * kXcds;
+  if (blockIdx.x == 0 && threadIdx.x < kXcds) {
+    counters[((r + 1) & 1) * kXcds + threadIdx.x] = 0;   // the last iteration's, for the next
+    if (threadIdx.x == 0) publish(pub, 0, -1, *ndone);
+  }
   if (r >= a.stride) return;
   const long long b = (long long)blockIdx.x * kWG + threadIdx.x;
   bool keep = false;
@@ -507,7 +523,7 @@ __global__ void __launch_bounds__(kWG) batch_live_items(BatchWalk a, long long t
 template <bool F32>
 __global__ void __launch_bounds__(kWG) batch_huge_combine(BatchWalk a, long long n_huge) {
   using T = typename Prec<F32>::T;
-  const int r = *a.r_dev;
+  const int r = a.r;
   if (r >= a.stride) return;
   double vmax = 0.0;
   int g_mine = -1;
@@ -532,52 +548,30 @@ __global__ void __launch_bounds__(kWG) batch_huge_combine(BatchWalk a, long long
   batch_store_max<F32>(a, r, g_mine, vmax, blockIdx.x);
 }
 
-// After the selection of iteration r: FP32 scales of iteration r + 1 for every
-// graph still iterating, then r += 1.  Counts the stopped graphs.
-__global__ void __launch_bounds__(kFinishThreads) batch_advance(int* r_dev, int count, RunScalars* gsc,
-                                                                const unsigned* gxmax32, double* gsigma,
-                                                                double* gsigsum, int* gexp, const double* galpha,
-                                                                const int* gclog2, int stride, int fp32,
-                                                                int* ndone, int* n_items) {
-  const int r = *r_dev;
-  __shared__ int s_done;
-  if (threadIdx.x == 0) s_done = 0;
-  __syncthreads();
-  int done = 0;
-  for (int g = threadIdx.x; g < count; g += kFinishThreads) {
-    const RunScalars& s = gsc[g];
-    if (s.done || s.err) {
-      ++done;
-      continue;
-    }
-    if (fp32 && r + 1 < stride) {
-      const long long at = (long long)g * stride;
-      const float M = __uint_as_float(gxmax32[at + r]);
-      int ex = 0;
-      if (M > 0.0f) {
-        (void)frexpf(M, &ex);
-        ex += gclog2[g];
-      }
-      const double sg = ldexp(galpha[g] * gsigma[at + r], ex);
-      gexp[at + r + 1] = ex;
-      gsigma[at + r + 1] = sg;
-      gsigsum[at + r + 1] = gsigsum[at + r] + sg;
-    }
-  }
-  atomicAdd(&s_done, done);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    *r_dev = r + 1;
-    *ndone = s_done;
-    for (int x = 0; x < kXcds; ++x) n_items[x] = 0;   // the next iteration's lists are rebuilt from zero
-  }
-}
-
-__global__ void __launch_bounds__(kWG) fill_ones(void* x, long long n, int fp32) {
+// Every graph's flags, work-item counters and first table entries: x_0 = 1 gives
+// the first FP32 scale the exponent 1 + ceil(log2 deg_max), and sums of ones are
+// exact below 2^24.
+__global__ void __launch_bounds__(kWG) batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count,
+                                                   int* n_items, BatchNext nx, int fp32) {
   const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i >= n) return;
-  if (fp32) reinterpret_cast<float*>(x)[i] = 1.0f;
-  else reinterpret_cast<double*>(x)[i] = 1.0;
+  if (i < 2 * kXcds) n_items[i] = 0;
+  if (i == 0) *nx.ndone = 0;
+  if (i >= count) return;
+  RunScalars z{};
+  z.m = (int)(gbase[i + 1] - gbase[i]);
+  gsc[i] = z;
+  const long long at = i * nx.stride;
+  nx.gsigma[at] = 1.0;
+  nx.gxmax32[at + 1] = 0u;
+  nx.gxmax64[at + 1] = 0ull;
+  if (!fp32) return;
+  const int e1 = 1 + nx.gclog2[i];
+  nx.gexp[at + 1] = e1;
+  nx.gsigma[at + 1] = ldexp(nx.galpha[i], e1);
+  nx.gsigsum[at + 1] = nx.gsigma[at + 1];
+  const double eta1 = gdmax[i] < (1 << 24) ? 0.0 : 0x1p-24;   // exact sums, or one rounding
+  nx.eta[at + 1] = eta1;
+  nx.etap[at + 1] = eta1 / (1.0 - eta1) * (1.0 + 0x1p-50);
 }
 
 // The bound factors of the graph's final iteration.
@@ -795,9 +789,10 @@ hipError_t launch_batch_dmax(const void* const* grp, const int* grp64, const lon
   return hipGetLastError();
 }
 
-hipError_t launch_fill_ones(void* x, long long n, int fp32, hipStream_t s) {
-  const unsigned nb = (unsigned)std::max<long long>(1, (n + kWG - 1) / kWG);
-  hipLaunchKernelGGL(fill_ones, dim3(nb), dim3(kWG), 0, s, x, n, fp32);
+hipError_t launch_batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count, int* n_items,
+                              const BatchNext& next, int fp32, hipStream_t s) {
+  const unsigned nb = (unsigned)((std::max(count, 2 * kXcds) + kWG - 1) / kWG);
+  hipLaunchKernelGGL(batch_begin, dim3(nb), dim3(kWG), 0, s, gsc, gbase, gdmax, count, n_items, next, fp32);
   return hipGetLastError();
 }
 
@@ -805,7 +800,7 @@ hipError_t launch_fill_ones(void* x, long long n, int fp32, hipStream_t s) {
 // max_grid > 0), batch_huge_combine for rows longer than one segment, and
 // batch_reduce_max for the per-graph maxima.
 // Workgroups of the batched walk kernel the device holds at once (the cap of a
-// persistent grid; queried before the iterations are captured).
+// persistent grid).
 long long batch_walk_resident(int fp32) {
   return resident_blocks(fp32 ? (const void*)walk_batch<true> : (const void*)walk_batch<false>, 0, kWG);
 }
@@ -833,19 +828,11 @@ hipError_t launch_walk_batch(const BatchWalk& a, long long total_blocks, long lo
     nb += cg;
   }
   if (!a.direct_max) {
-    const unsigned rg = (unsigned)std::min<long long>(64, (nb + 4095) / 4096);
+    const unsigned rg = (unsigned)std::min<long long>(256, (nb + 1023) / 1024);
     const size_t lds = sizeof(unsigned long long) * (size_t)a.count;
     if (a.fp32) hipLaunchKernelGGL(batch_reduce_max<true>, dim3(rg), dim3(kWG), lds, s, a, nb);
     else hipLaunchKernelGGL(batch_reduce_max<false>, dim3(rg), dim3(kWG), lds, s, a, nb);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_advance(int* r_dev, int count, RunScalars* gsc, const unsigned* gxmax32, double* gsigma,
-                                double* gsigsum, int* gexp, const double* galpha, const int* gclog2, int stride,
-                                int fp32, int* ndone, int* n_items, hipStream_t s) {
-  hipLaunchKernelGGL(batch_advance, dim3(1), dim3(kFinishThreads), 0, s, r_dev, count, gsc, gxmax32, gsigma, gsigsum,
-                     gexp, galpha, gclog2, stride, fp32, ndone, n_items);
   return hipGetLastError();
 }
 
@@ -857,9 +844,9 @@ hipError_t launch_batch_item_graphs(const BatchWalk& a, long long total_blocks, 
 }
 
 hipError_t launch_batch_live_items(const BatchWalk& a, long long total_blocks, int* items, int* n_items,
-                                   hipStream_t s) {
+                                   const int* ndone, const Publish& pub, hipStream_t s) {
   const unsigned nb = (unsigned)std::max<long long>(1, (total_blocks + kWG - 1) / kWG);
-  hipLaunchKernelGGL(batch_live_items, dim3(nb), dim3(kWG), 0, s, a, total_blocks, items, n_items);
+  hipLaunchKernelGGL(batch_live_items, dim3(nb), dim3(kWG), 0, s, a, total_blocks, items, n_items, ndone, pub);
   return hipGetLastError();
 }
 

@@ -262,9 +262,9 @@ struct SelArgs {
 // One graph's view for the one-workgroup selection (select_wg): every array
 // points at the graph's own region; node ids are global (base .. base + n).
 struct GraphSel {
-  BoundArgs b;                   // with a device iteration counter, r and x are refreshed
-  const void* xbuf[2];           // walk vector buffers by parity of r (device-counter mode)
-  const double* etap;            // FP32 form: eta'_r table (device-counter mode)
+  BoundArgs b;                   // in a batch, r and x are refreshed
+  const void* xbuf[2];           // walk vector buffers by parity of r (batches)
+  const double* etap;            // FP32 form: eta'_r table (batches)
   const int32_t* act[2];         // active-list buffers of this graph
   unsigned long long* keys;
   unsigned long long* cand_key;
@@ -282,7 +282,7 @@ struct GraphSel {
   int k;
   int max_iter;
   int identity_in;               // the active list is base .. base + n - 1
-  int cur;                       // host-driven mode: buffer holding M (act[cur])
+  int cur;                       // single graphs: buffer holding M (act[cur])
 };
 
 // The batched walk step (many graphs, global row ids).
@@ -307,10 +307,10 @@ struct BatchWalk {
   float* e;
   void* partial;
   const double* etap;           // eta'_r per graph: [count][stride]
-  const int* r_dev;
+  int r;                        // this iteration
   const int* item_g;            // per work item: the graph of all its rows, or -1 (rows of several graphs)
   const int* items;             // work items of this iteration (live graphs only), n_items[x] in list x
-  const int* n_items;           // [kXcds]
+  const int* n_items;           // [2][kXcds], by parity of r
   int* blk_g;                   // per workgroup: graph of all its rows, or -1
   double* blk_m;                // per workgroup: maximum new walk entry of that graph
   long long blk_base;           // first slot of this launch in blk_g / blk_m
@@ -322,6 +322,20 @@ struct BatchWalk {
   const int* xcd_of;            // per graph: the XCD whose workgroups take its items
   int stride;
   int fp32;
+};
+
+// What the selection of a batched graph leaves for its next iteration: the FP32
+// scale, its sum and exponent, the rounding bound, the cleared maximum; and the
+// count of stopped graphs.  All tables are [count][stride].
+struct BatchNext {
+  double *gsigma, *gsigsum, *eta, *etap;
+  int* gexp;
+  unsigned* gxmax32;
+  unsigned long long* gxmax64;
+  const double *galpha, *grho;
+  const int* gclog2;
+  int* ndone;
+  int stride;
 };
 
 // ---- launchers (katz_kernels.hip) ----------------------------------------
@@ -482,7 +496,8 @@ hipError_t launch_min_lower_active(const BoundArgs& b, const int32_t* act, const
 hipError_t launch_reactivate_all(const BoundArgs& b, long long n, const unsigned long long* min_bits,
                                  uint8_t* mark, int32_t* out, int* count, hipStream_t s);
 
-hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, int fp32, hipStream_t s);
+// One iteration's selection of every graph of a batch.
+hipError_t launch_select_wg(const GraphSel* gsel, int count, int r, int fp32, const BatchNext& next, hipStream_t s);
 // The workgroup maxima of the walk step before a single graph's selection, when
 // that launch reduces them itself (blkmax null: launch_reduce_blkmax did).
 struct WalkMax {
@@ -510,16 +525,17 @@ hipError_t launch_batch_rename(const RowDesc* desc, const long long* bin_base, c
                                const SegDesc* segs, long long seg_total, const HugeRow* huge, const long long* noff,
                                const int* gid_of, const long long* gbase, const int32_t* const* gcol,
                                const long long* coff, const IdLen* pmap, int32_t* ncol, hipStream_t s);
-hipError_t launch_fill_ones(void* x, long long n, int fp32, hipStream_t s);
+// Before iteration 1: every graph's flags and first table entries.
+hipError_t launch_batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count, int* n_items,
+                              const BatchNext& next, int fp32, hipStream_t s);
 hipError_t launch_walk_batch(const BatchWalk& a, long long total_blocks, long long max_grid, long long n_huge,
                              hipStream_t s);
 hipError_t launch_batch_item_graphs(const BatchWalk& a, long long total_blocks, int* item_g, hipStream_t s);
+// The work items of iteration a.r (a.n_items: two sets of kXcds counters, by parity
+// of r); publishes the graphs stopped before it.
 hipError_t launch_batch_live_items(const BatchWalk& a, long long total_blocks, int* items, int* n_items,
-                                   hipStream_t s);
+                                   const int* ndone, const Publish& pub, hipStream_t s);
 constexpr int kBatchMaxLdsGraphs = 8192;   // per-graph maxima reduced in LDS up to this many graphs
-hipError_t launch_batch_advance(int* r_dev, int count, RunScalars* gsc, const unsigned* gxmax32, double* gsigma,
-                                double* gsigsum, int* gexp, const double* galpha, const int* gclog2, int stride,
-                                int fp32, int* ndone, int* n_items, hipStream_t s);
 hipError_t launch_batch_write(const GraphSel* gsel, int count, long long max_n, int32_t* const* out_ids,
                               double* const* out_lo, double* const* out_up, uint8_t* mark,
                               unsigned long long* rest_bits, hipStream_t s);

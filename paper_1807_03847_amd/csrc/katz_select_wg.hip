@@ -11,8 +11,8 @@
 namespace katz {
 namespace {
 
-// The bound factors of iteration r, recomputed on the device when r comes from
-// a device counter (same expressions as the host-side bound arguments).
+// The bound factors of iteration r of a batched graph (same expressions as the
+// host-side bound arguments).
 __device__ void refresh_bounds(BoundArgs& b, const GraphSel& gs, int r) {
   b.r = r;
   b.x = (r & 1) ? gs.xbuf[1] : gs.xbuf[0];
@@ -430,11 +430,11 @@ __device__ __forceinline__ bool select_mid(const GraphSel& gs, const Publish& pu
 
 // Two kernels share the body, so that each reads its GraphSel from one address
 // space (global memory or the kernel arguments) and needs no private copy.
-// walk: the maxima of the walk step just run, when this launch reduces them
-// itself (one graph); null: they are in xmax32 / xmax64.
+// r: the iteration of a batch (0: one graph, whose arguments hold it).  walk: the
+// maxima of the walk step just run, when this launch reduces them itself (one
+// graph); null: they are in xmax32 / xmax64.
 template <bool F32>
-__device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_dev, const WalkMax* walk,
-                                             const Publish& pub) {
+__device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const WalkMax* walk, const Publish& pub) {
   RunScalars* sc = gs.sc;
   if (sc->done || sc->err) return;
   if (walk) {
@@ -449,11 +449,11 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
     if (walk->blkmax) reduce_walk_max<F32>(gs, *walk);
   }
   BoundArgs b = gs.b;
-  if (r_dev) refresh_bounds(b, gs, *r_dev);
-  const int cur = r_dev ? sc->cur : gs.cur;
+  if (r) refresh_bounds(b, gs, r);
+  const int cur = r ? sc->cur : gs.cur;
   const int32_t* act_in = cur ? gs.act[1] : gs.act[0];
   int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
-  const bool identity = r_dev ? (b.r == 1) : gs.identity_in;
+  const bool identity = r ? (b.r == 1) : gs.identity_in;
   const int m = identity ? gs.n : sc->m;
   const bool walk_zero = F32 ? (gs.xmax32[b.r] == 0u) : (gs.xmax64[b.r] == 0ull);
   __shared__ union {
@@ -752,22 +752,52 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, const int* r_de
   if (t == 0) finish_iteration<F32>(sc, pub, b, cur, k, s_kept, s_fail != 0, s_prog != 0, walk_zero, gs.max_iter);
 }
 
+// One workgroup per graph; then, while the graph goes on, what its next iteration
+// needs: the FP32 scale 2^e above deg_max * max(x~_r) and the rounding bound
+// eta_{r+1} (the host's recurrences), and a cleared maximum.
 template <bool F32>
-__global__ void __launch_bounds__(kFinishThreads) select_wg(const GraphSel* gsel, const int* r_dev) {
-  select_graph<F32>(gsel[blockIdx.x], r_dev, nullptr, Publish{nullptr, 0});
+__global__ void __launch_bounds__(kFinishThreads) select_wg(const GraphSel* gsel, int r, BatchNext nx) {
+  const int g = blockIdx.x;
+  RunScalars* sc = gsel[g].sc;
+  if (sc->done || sc->err) return;
+  select_graph<F32>(gsel[g], r, nullptr, Publish{nullptr, 0});
+  if (threadIdx.x != 0) return;
+  if (sc->done || sc->err) {   // written by this thread
+    atomicAdd(nx.ndone, 1);
+    return;
+  }
+  if (r + 1 >= nx.stride) return;
+  const long long at = (long long)g * nx.stride;
+  nx.gxmax32[at + r + 1] = 0u;
+  nx.gxmax64[at + r + 1] = 0ull;
+  if constexpr (F32) {
+    const float M = __uint_as_float(nx.gxmax32[at + r]);
+    int ex = 0;
+    if (M > 0.0f) {
+      (void)frexpf(M, &ex);
+      ex += nx.gclog2[g];
+    }
+    const double sg = ldexp(nx.galpha[g] * nx.gsigma[at + r], ex);
+    nx.gexp[at + r + 1] = ex;
+    nx.gsigma[at + r + 1] = sg;
+    nx.gsigsum[at + r + 1] = nx.gsigsum[at + r] + sg;
+    const double eta = ((1.0 + nx.eta[at + r]) * (1.0 + nx.grho[g]) - 1.0) * (1.0 + 0x1p-50);
+    nx.eta[at + r + 1] = eta;
+    nx.etap[at + r + 1] = eta / (1.0 - eta) * (1.0 + 0x1p-50);
+  }
 }
 
 template <bool F32>
 __global__ void __launch_bounds__(kFinishThreads) select_wg_one(GraphSel one, WalkMax walk, Publish pub) {
-  select_graph<F32>(one, nullptr, &walk, pub);
+  select_graph<F32>(one, 0, &walk, pub);
 }
 
 }  // namespace
 
-hipError_t launch_select_wg(const GraphSel* gsel, int count, const int* r_dev, int fp32, hipStream_t s) {
+hipError_t launch_select_wg(const GraphSel* gsel, int count, int r, int fp32, const BatchNext& next, hipStream_t s) {
   if (count > 0) {
-    if (fp32) hipLaunchKernelGGL(select_wg<true>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r_dev);
-    else hipLaunchKernelGGL(select_wg<false>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r_dev);
+    if (fp32) hipLaunchKernelGGL(select_wg<true>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r, next);
+    else hipLaunchKernelGGL(select_wg<false>, dim3(count), dim3(kFinishThreads), 0, s, gsel, r, next);
   }
   return hipGetLastError();
 }

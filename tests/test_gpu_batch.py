@@ -248,3 +248,28 @@ def test_batch_graph_replayed_across_calls():
         orc = oracle.rank_static(rp, col, pp["alpha"], pp["k"], pp["eps"])
         assert_topk_parity(rb.topk.cpu().numpy(), rb.lower.cpu().numpy(), rb.upper.cpu().numpy(), orc,
                            widened=True, check_status=False)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_iteration_limits(precision):
+    """Every graph stops at its own limit (1, 2, 3, ... iterations, or certified
+    before it): results, iterations and status are the single call's."""
+    katz = K()
+    graphs, params = batch_workload(8, 19, 10, 13)
+    rp, col = sg.star_graph(70000)          # a row of several segments
+    graphs.append((rp, col))
+    params.append(dict(k=5, alpha=0.5 / (1 + sg.max_degree(rp)), eps=1e-12))
+    limits = [1, 2, 3, 1, 4, 5, 1000, 2, 1]
+    say("batch iteration limits", precision)
+    for top in (9, 1):                      # all graphs; the first one with a limit of 1
+        g, p = graphs[:top], [dict(pp, max_iter=m) for pp, m in zip(params, limits)][:top]
+        if top == 1:
+            g, p = g * 2, p * 2
+        for (rp, col), pp, rb in zip(g, p, run_batch(g, p, precision)):
+            single = katz.rank_static(torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), pp["k"],
+                                      alpha=pp["alpha"], eps=pp["eps"], max_iter=pp["max_iter"], precision=precision)
+            assert torch.equal(single.topk, rb.topk)
+            assert (single.iterations, single.status) == (rb.iterations, rb.status)
+            assert rb.iterations <= pp["max_iter"]
+            if precision == "fp64":
+                assert torch.equal(single.lower, rb.lower) and torch.equal(single.upper, rb.upper)
