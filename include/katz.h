@@ -445,7 +445,8 @@ int katz_timing_read(katz_timing* out);
  *                        with a grid stride; 0 = one workgroup per work item.
  *                        0 .. 32.  A non-zero hub_bytes needs a non-zero
  *                        blocks_per_cu (the copy is filled once per workgroup).
- *   batch_blocks_per_cu  the same for the batched form (count > 1); 0 .. 32.
+ *   batch_blocks_per_cu  the same for the batched form (count > 1), at most as many
+ *                        as the device holds; 0 = as many as it holds.  0 .. 32.
  *   batch_tile           batched form: row groups per work item of the short-row
  *                        bins (each wave sums its rows group after group, each row
  *                        still by the same lanes); 0 or 1 = one group, up to 16.

@@ -1812,6 +1812,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   const int xcd_groups = tu_b.batch_xcd ? kXcds : 1;
   const int fp32 = p[0].precision == KATZ_FP32_MARGIN;
   long long total_n = 0, total_nnz = 0, max_n = 0, sum_k = 0;
+  long long n_hist = 0;   // graphs with a histogram of row lengths (BatchFloor)
   int max_iter = 1;
   for (int i = 0; i < count; ++i) {
     if ((p[i].precision == KATZ_FP32_MARGIN) != (fp32 != 0)) return KATZ_E_UNSUPPORTED;
@@ -1820,6 +1821,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     total_nnz += g[i].nnz;
     max_n = std::max<long long>(max_n, g[i].n);
     sum_k += p[i].k;
+    if (g[i].n > kFinishThreads) ++n_hist;
     max_iter = std::max(max_iter, p[i].max_iter ? p[i].max_iter : 1000);
   }
   // Renumbering pays where a walk vector outgrows one XCD's L2 (4 MiB).
@@ -1866,6 +1868,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   double* galpha = nullptr;
   int* gclog2 = nullptr;
   int* gdmax = nullptr;
+  int* ghist_of = nullptr;
+  double* gfloor = nullptr;
   double *gsigma = nullptr, *gsigsum = nullptr, *eta = nullptr, *etap = nullptr, *grho = nullptr;
   unsigned long long* rest = nullptr;
   int* gexp = nullptr;
@@ -1901,6 +1905,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
     grp64 = ar.take<int>(count);
     gnnz = ar.take<long long>(count);
     gcol = ar.take<const int32_t*>(count);
+    ghist_of = ar.take<int>(count);
     up1[1] = ar.used;
     // ... and once the longest rows are known.
     up2[0] = ar.used;
@@ -1929,7 +1934,8 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
       rsums = ar.take<long long>(scan_sums_capacity(total_n));
       rtot = ar.take<long long>(2);
     }
-    gdmax = ar.take<int>(count);
+    gdmax = ar.take<int>(count + (size_t)n_hist * kLenDigits);   // followed by the length histograms
+    gfloor = ar.take<double>(count);
     gsigma = ar.take<double>((size_t)count * stride);
     gsigsum = ar.take<double>((size_t)count * stride);
     gexp = ar.take<int>((size_t)count * stride);
@@ -1983,8 +1989,14 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   ar.measuring = false;
   KATZ_TRY(ar.grow(ar.used));
   lay();
-  KATZ_TRY(ar.grow_pin(up2[1]));
-  // The pinned mirror of a table in the workspace.
+  // Pinned: the mirrors of the uploaded tables, then what is read back.
+  const size_t pin_fin = (up2[1] + 255) / 256 * 256, pin_rest = pin_fin + sizeof(RunScalars) * count;
+  const size_t pin_dmax = pin_rest + sizeof(unsigned long long) * count;
+  KATZ_TRY(ar.grow_pin(pin_dmax + sizeof(int) * count));
+  const RunScalars* fin = reinterpret_cast<const RunScalars*>(ar.pin + pin_fin);
+  const unsigned long long* h_rest = reinterpret_cast<const unsigned long long*>(ar.pin + pin_rest);
+  const int* h_dmax = reinterpret_cast<const int*>(ar.pin + pin_dmax);
+  // The mirror of a table in the workspace.
   auto host = [&ar](auto* dev) {
     using P = std::remove_const_t<std::remove_pointer_t<decltype(dev)>>;
     return reinterpret_cast<P*>(ar.pin + (reinterpret_cast<const char*>(dev) - ar.base));
@@ -1997,13 +2009,15 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   long long *h_base = host(gbase), *h_abase = host(gabase), *h_nnz = host(gnnz);
   const void** h_rp = host(grp);
   const int32_t** h_col = host(gcol);
-  int* h_rp64 = host(grp64);
+  int *h_rp64 = host(grp64), *h_hist = host(ghist_of);
+  int hist_at = 0;
   h_base[0] = h_abase[0] = 0;
   for (int i = 0; i < count; ++i) {
     h_base[i + 1] = h_base[i] + g[i].n;
     h_abase[i + 1] = h_abase[i] + g[i].nnz;
     h_nnz[i] = g[i].nnz;
     h_rp64[i] = g[i].row_ptr_64;
+    h_hist[i] = g[i].n > kFinishThreads ? hist_at++ : -1;
     h_rp[i] = rp_host[i] ? stage_rp[i] : g[i].row_ptr;
     h_col[i] = col_host[i] ? (const int32_t*)stage_col[i] : g[i].col;
     if (rp_host[i])
@@ -2014,14 +2028,14 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   }
   KATZ_HIP(hipMemcpyAsync(ar.base + up1[0], ar.pin + up1[0], up1[1] - up1[0], hipMemcpyHostToDevice, s));
   KATZ_HIP(launch_reset_flags(w.sc, s));
-  KATZ_HIP(hipMemsetAsync(gdmax, 0, sizeof(int) * count, s));
+  const BatchFloor fl{ghist_of, reinterpret_cast<unsigned*>(gdmax + count), gfloor};
+  KATZ_HIP(hipMemsetAsync(gdmax, 0, sizeof(int) * (count + (size_t)n_hist * kLenDigits), s));
   int validate = 0;
   for (int i = 0; i < count; ++i) validate = std::max(validate, p[i].validate);
   KATZ_HIP(launch_batch_prep(gbase, grp, grp64, gnnz, gabase, gcol, count, total_n, total_nnz, gid_of, b.tab,
                              b.desc, b.segs, b.huge, w.sc, validate, b.bb, s));
-  KATZ_HIP(launch_batch_dmax(grp, grp64, gbase, count, total_n, gdmax, s));
-  std::vector<int> h_dmax(count);
-  KATZ_HIP(hipMemcpyAsync(h_dmax.data(), gdmax, sizeof(int) * count, hipMemcpyDeviceToHost, s));
+  KATZ_HIP(launch_batch_dmax(grp, grp64, gbase, count, total_n, gdmax, fl, s));
+  KATZ_HIP(hipMemcpyAsync(ar.pin + pin_dmax, gdmax, sizeof(int) * count, hipMemcpyDeviceToHost, s));
   KATZ_HIP(hipMemcpyAsync(ar.hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
   KATZ_HIP(hipStreamSynchronize(s));
   if (ar.hs.sc->err) return KATZ_E_CSR;
@@ -2165,8 +2179,12 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   }
   bw.fp32 = fp32;
   const long long total_blocks = bw.first_block[NUM_BINS];
-  long long walk_grid = (long long)tu_b.batch_blocks_per_cu * cu_count(dev);
-  if (walk_grid > 0) walk_grid = std::min(walk_grid, batch_walk_resident(fp32));
+  // Nothing set: as many workgroups as the device holds.  One per item (44 K of them,
+  // 48 graphs of 1.3 M nodes) takes as long while most graphs iterate, but 14 us where
+  // few or none do, against 5.
+  long long walk_grid = batch_walk_resident(fp32);
+  if (tu_b.batch_blocks_per_cu > 0)
+    walk_grid = std::min(walk_grid, (long long)tu_b.batch_blocks_per_cu * cu_count(dev));
   {
     const long long nh = b.bin_count[BIN_HUGE];
     if (total_blocks + (nh + kWG / kWave - 1) / (kWG / kWave) > blk_cap) return KATZ_E_HIP;   // sizing bound broken
@@ -2174,7 +2192,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
 
   KATZ_HIP(hipMemcpyAsync(ar.base + up2[0], ar.pin + up2[0], up2[1] - up2[0], hipMemcpyHostToDevice, s));
   const BatchNext next{gsigma, gsigsum, eta, etap, gexp, gxmax32, gxmax64, galpha, grho, gclog2, ndone, stride};
-  KATZ_HIP(launch_batch_begin(gsc, gbase, gdmax, count, n_items, next, fp32, s));
+  KATZ_HIP(launch_batch_begin(gsel, gdmax, count, n_items, next, fl, fp32, s));
   KATZ_HIP(launch_batch_item_graphs(bw, total_blocks, item_g, s));
   T.stop(tp, s);
   const int ts = T.start(T_STEP, s);
@@ -2182,6 +2200,11 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   for (int r = 1; r <= max_iter; ++r) {
     const Range range("katz iteration", r);
     bw.r = r;
+    if (r == 1) {
+      KATZ_HIP(launch_batch_first(bw, grp, grp64, reorder ? len32 : nullptr, gsel, gfloor, total_n, s));
+      KATZ_HIP(launch_select_wg(gsel, count, r, fp32, next, s));
+      continue;
+    }
     const unsigned seq = ++ar.hs.seq;
     KATZ_HIP(launch_batch_live_items(bw, total_blocks, items, n_items, ndone, Publish{&ar.hs.flags[seq & 1], seq}, s));
     KATZ_HIP(launch_walk_batch(bw, total_blocks, walk_grid, n_huge, s));
@@ -2194,8 +2217,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   T.stop(ts, s);
 
   // ---- outputs ----
-  std::vector<RunScalars> fin(count);
-  KATZ_HIP(hipMemcpyAsync(fin.data(), gsc, sizeof(RunScalars) * count, hipMemcpyDeviceToHost, s));
+  KATZ_HIP(hipMemcpyAsync(ar.pin + pin_fin, gsc, sizeof(RunScalars) * count, hipMemcpyDeviceToHost, s));
   KATZ_HIP(hipStreamSynchronize(s));
   for (int i = 0; i < count; ++i)
     if (fin[i].err) return fin[i].err == 2 ? KATZ_E_HIP : KATZ_E_CSR;
@@ -2204,8 +2226,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   KATZ_HIP(hipMemsetAsync(rest, 0, sizeof(unsigned long long) * count, s));
   KATZ_HIP(launch_batch_write(gsel, count, max_n, o_ids, o_lo, o_up, w.mark, rest, s));
   T.stop(tr, s);
-  std::vector<unsigned long long> h_rest(count);
-  KATZ_HIP(hipMemcpyAsync(h_rest.data(), rest, sizeof(unsigned long long) * count, hipMemcpyDeviceToHost, s));
+  KATZ_HIP(hipMemcpyAsync(ar.pin + pin_rest, rest, sizeof(unsigned long long) * count, hipMemcpyDeviceToHost, s));
   if (out_host) {
     koff = 0;
     for (int i = 0; i < count; ++i) {

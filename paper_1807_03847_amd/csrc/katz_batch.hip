@@ -4,7 +4,7 @@
 // The graphs are not copied: their rows are binned together under global row
 // ids (graph g owns ids gbase[g] .. gbase[g+1] - 1), and every row carries the
 // graph id that locates its column array, its node base and its alpha.  One
-// iteration is
+// iteration after the first (batch_first in place of the walk) is
 //   batch_live_items  the work items of the graphs still iterating; tells the host
 //                     how many have stopped,
 //   walk_batch        their walk step (batch_huge_combine: rows of several
@@ -117,26 +117,54 @@ __global__ void __launch_bounds__(kWG) batch_col_range(const int32_t* const* gco
   if (__ballot(bad) && lane_id() == 0) atomicOr(&sc->err, 1);
 }
 
-// Longest row of every graph: one atomic max per workgroup and graph met.
+// Digit of a row length: lengths up to 32 each have their own, longer ones share it
+// with lengths that agree in their leading 6 bits.  len_edge: a lower bound of the
+// lengths of a digit (up to the rounding of a length to 32 bits).
+__device__ __forceinline__ int len_digit(int len) {
+  return len > 0 ? (int)(__float_as_uint((float)len) >> 18) - (127 << 5) + 1 : 0;
+}
+__device__ __forceinline__ float len_edge(int d) {
+  return d > 0 ? __uint_as_float((unsigned)(d - 1 + (127 << 5)) << 18) : 0.0f;
+}
+
+// Longest row of every graph: one atomic max per workgroup and graph met; and the
+// histogram of its row lengths.
 __global__ void __launch_bounds__(kWG) batch_dmax(const void* const* grp, const int* grp64, const long long* gbase,
-                                                  int count, int* gdmax) {
+                                                  int count, int* gdmax, BatchFloor fl) {
   __shared__ int wm[kWG / kWave];
+  __shared__ unsigned h[kLenDigits];
   const long long r0 = (long long)blockIdx.x * kRowChunk;
   const long long r1 = min(r0 + kRowChunk, gbase[count]);
   for (int g = owner_of(gbase, count, r0); g < count && gbase[g] < r1; ++g) {
     const long long s = max(r0, gbase[g]) - gbase[g];
     const long long e = min(r1, gbase[g + 1]) - gbase[g];
+    const int hi = fl.hist_of[g];
+    if (hi >= 0) {
+      for (int d = threadIdx.x; d < kLenDigits; d += kWG) h[d] = 0u;
+      __syncthreads();
+    }
     int m = 0;
-    if (grp64[g]) {
-      const long long* rp = reinterpret_cast<const long long*>(grp[g]);
-      for (long long v = s + threadIdx.x; v < e; v += kWG) m = max(m, (int)min(rp[v + 1] - rp[v], (long long)INT_MAX));
-    } else {
-      const int* rp = reinterpret_cast<const int*>(grp[g]);
-      for (long long v = s + threadIdx.x; v < e; v += kWG) m = max(m, rp[v + 1] - rp[v]);
+    for (long long v0 = s; v0 < e; v0 += kWG) {
+      const long long v = v0 + threadIdx.x;
+      int len = 0;
+      if (v < e) {
+        if (grp64[g]) {
+          const long long* rp = reinterpret_cast<const long long*>(grp[g]);
+          len = (int)min(max(rp[v + 1] - rp[v], 0ll), (long long)INT_MAX);
+        } else {
+          const int* rp = reinterpret_cast<const int*>(grp[g]);
+          len = max(rp[v + 1] - rp[v], 0);
+        }
+      }
+      m = max(m, len);
+      if (hi >= 0) wave_hist_add(h, (unsigned)len_digit(len), v < e);
     }
     for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
     if (lane_id() == 0) wm[threadIdx.x / kWave] = m;
     __syncthreads();
+    if (hi >= 0)
+      for (int d = threadIdx.x; d < kLenDigits; d += kWG)
+        if (h[d]) atomicAdd(&fl.hist[(long long)hi * kLenDigits + d], h[d]);
     if (threadIdx.x == 0) {
       const int bm = max(max(wm[0], wm[1]), max(wm[2], wm[3]));
       if (bm > 0) atomicMax(&gdmax[g], bm);
@@ -332,12 +360,8 @@ __device__ __forceinline__ void batch_rows_group(const BatchWalk& a, int r, long
   if (valid && lane == 0) p = batch_prefetch<F32>(a, r, g, d.row);
   T sum = 0;
   if (valid) {
-    if (r == 1) {
-      if (lane == 0) sum = (T)d.len;   // x_0 = 1
-    } else {
-      const T* x = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]) + a.gbase[g];
-      sum = batch_strided_sum<F32>(x, a.gcol[g] + d.off, d.len, lane, G);
-    }
+    const T* x = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]) + a.gbase[g];
+    sum = batch_strided_sum<F32>(x, a.gcol[g] + d.off, d.len, lane, G);
   }
 #pragma unroll
   for (int o = G / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, G);
@@ -369,11 +393,64 @@ __device__ __forceinline__ typename Prec<F32>::T batch_block_sum(const typename 
   return tot;
 }
 
+// First walk step: x_0 = 1, so a row's sum is its length, and every graph's maximum
+// that of its longest row (batch_begin).  One thread per row, in the order of the
+// rows in memory: the binned order (walk_batch) puts 4 rows of 33..128 arcs in a
+// wave, which took 115 us on 1.3 M rows against 19 here.  It also starts every
+// graph's active list with the nodes that can stay in it: one whose lower bound and
+// up - eps are both below the graph's floor is neither among the top k nor kept.
+// The selection, one workgroup a graph, took 218 us on a list of all 125 K nodes of
+// the largest graph and takes 32 us on what is left.
+template <bool F32>
+__global__ void __launch_bounds__(kWG) batch_first(BatchWalk a, const void* const* grp, const int* grp64,
+                                                   const int* len32, const GraphSel* gsel, const double* floor,
+                                                   long long total) {
+  using T = typename Prec<F32>::T;
+  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
+  int g = 0;
+  bool keep = false;
+  if (i < total) {
+    g = a.gid_of[i];
+    int len;
+    if (len32) {
+      len = len32[i];
+    } else {
+      const long long v = i - a.gbase[g];
+      if (grp64[g]) {
+        const long long* rp = reinterpret_cast<const long long*>(grp[g]);
+        len = (int)(rp[v + 1] - rp[v]);
+      } else {
+        const int* rp = reinterpret_cast<const int*>(grp[g]);
+        len = rp[v + 1] - rp[v];
+      }
+    }
+    double vmax = 0.0;
+    batch_epilogue<F32>(a, 1, (int)i, (T)len, vmax, batch_prefetch<F32>(a, 1, g, (int)i));
+    const GraphSel& gs = gsel[g];
+    BoundArgs b = gs.b;
+    refresh_bounds(b, gs, 1);
+    double lo, up;
+    bound_eval_as<F32>(b, (int)i, lo, up);   // what this thread just stored
+    const double f = floor[g];
+    keep = lo >= f || !(up - b.eps < f);
+  }
+  unsigned long long pending = __ballot(keep);
+  while (pending) {                          // a round per graph of the wave's nodes
+    const int leader = __ffsll((long long)pending) - 1;
+    const int gl = __shfl(g, leader);
+    const unsigned long long same = __ballot(keep && g == gl) & pending;
+    int base = 0;
+    if (lane_id() == leader) base = atomicAdd(&gsel[gl].sc->m, __popcll(same));
+    base = __shfl(base, leader);
+    if ((same >> lane_id()) & 1ull)
+      const_cast<int32_t*>(gsel[gl].act[0])[base + __popcll(same & lanemask_lt())] = (int32_t)i;
+    pending &= ~same;
+  }
+}
+
 // Work items are taken from this iteration's list of live items (built by
 // batch_live_items); work item b writes workgroup slot b.  The grid may be
 // smaller than the list (persistent workgroups take items with a grid stride).
-// x_0 = 1, so a row's first sum is its length (no row or segment summed here is
-// longer than 2^24, where sums of ones in 32 bits are exact).
 template <bool F32>
 __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
   using T = typename Prec<F32>::T;
@@ -399,7 +476,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
         // One segment of a long row (item graph gi): its partial sum only;
         // batch_huge_combine adds each row's partials in segment order.
         const SegDesc sd = a.segs[lb];
-        const T tot = r == 1 ? (T)sd.len : batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + sd.off, sd.len);
+        const T tot = batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + sd.off, sd.len);
         if (threadIdx.x == 0) reinterpret_cast<T*>(a.partial)[sd.part] = tot;
         break;
       }
@@ -407,7 +484,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
         const RowDesc d = a.desc[a.bin_base[BIN_B256] + lb];
         BatchIn p{0.0, 0.0, 0.0, 0.0f, 0};
         if (threadIdx.x == 0) p = batch_prefetch<F32>(a, r, gi, d.row);
-        const T tot = r == 1 ? (T)d.len : batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + d.off, d.len);
+        const T tot = batch_block_sum<F32>(xin + a.gbase[gi], a.gcol[gi] + d.off, d.len);
         if (threadIdx.x == 0) {
           batch_epilogue<F32>(a, r, d.row, tot, vmax, p);
           g_mine = gi;
@@ -433,7 +510,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
         for (int k = 0; k < a.tile; ++k) batch_rows_group<F32, kBinLanes[BIN_G4]>(a, r, lb * a.tile + k, BIN_G4, gi, g_mine, vmax);
         break;
       case BIN_EMPTY: {
-        // Rows without arcs: x_r = 0 (and c_1 = 0, e = 0 at r = 1).
+        // Rows without arcs: x_r = 0.
         for (int k = 0; k < a.tile; ++k) {
           const long long i = (lb * a.tile + k) * kWG + threadIdx.x;
           if (i < a.bin_count[BIN_EMPTY]) {
@@ -441,10 +518,6 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
             const int g = gi >= 0 ? gi : a.gid_of[row];
             if (gi >= 0 || graph_live<F32>(a, g)) {
               reinterpret_cast<T*>(a.xbuf[r & 1])[row] = (T)0;
-              if (r == 1) {
-                a.c[row] = 0.0;
-                if constexpr (F32) a.e[row] = 0.0f;
-              }
             }
           }
         }
@@ -550,28 +623,52 @@ __global__ void __launch_bounds__(kWG) batch_huge_combine(BatchWalk a, long long
 
 // Every graph's flags, work-item counters and first table entries: x_0 = 1 gives
 // the first FP32 scale the exponent 1 + ceil(log2 deg_max), and sums of ones are
-// exact below 2^24.
-__global__ void __launch_bounds__(kWG) batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count,
-                                                   int* n_items, BatchNext nx, int fp32) {
-  const long long i = (long long)blockIdx.x * kWG + threadIdx.x;
-  if (i < 2 * kXcds) n_items[i] = 0;
-  if (i == 0) *nx.ndone = 0;
-  if (i >= count) return;
+// exact below 2^24.  One workgroup per graph: x_1 depends on the row length alone and
+// the lower bound grows with it, so the k-th lower bound is at least the one of the
+// lowest length in the k-th longest row's digit; 1 - 2^-20 is for the roundings.
+template <bool F32>
+__global__ void __launch_bounds__(kFinishThreads) batch_begin(const GraphSel* gsel, const int* gdmax, int* n_items,
+                                                              BatchNext nx, BatchFloor fl) {
+  const int g = blockIdx.x, t = threadIdx.x;
+  const GraphSel& gs = gsel[g];
+  if (g == 0 && t < 2 * kXcds) n_items[t] = 0;
+  if (g == 0 && t == 0) *nx.ndone = 0;
+  const int hi = fl.hist_of[g];
+  float edge = 0.0f;
+  if (hi >= 0) edge = len_edge(find_bucket(fl.hist + (long long)hi * kLenDigits, kLenDigits, gs.k, true).b);
+  if (t != 0) return;
   RunScalars z{};
-  z.m = (int)(gbase[i + 1] - gbase[i]);
-  gsc[i] = z;
-  const long long at = i * nx.stride;
+  *gs.sc = z;
+  const long long at = (long long)g * nx.stride;
   nx.gsigma[at] = 1.0;
-  nx.gxmax32[at + 1] = 0u;
-  nx.gxmax64[at + 1] = 0ull;
-  if (!fp32) return;
-  const int e1 = 1 + nx.gclog2[i];
-  nx.gexp[at + 1] = e1;
-  nx.gsigma[at + 1] = ldexp(nx.galpha[i], e1);
-  nx.gsigsum[at + 1] = nx.gsigma[at + 1];
-  const double eta1 = gdmax[i] < (1 << 24) ? 0.0 : 0x1p-24;   // exact sums, or one rounding
-  nx.eta[at + 1] = eta1;
-  nx.etap[at + 1] = eta1 / (1.0 - eta1) * (1.0 + 0x1p-50);
+  const int e1 = 1 + nx.gclog2[g];
+  if constexpr (F32) {
+    nx.gexp[at + 1] = e1;
+    nx.gxmax32[at + 1] = __float_as_uint(ldexpf((float)gdmax[g], -e1));
+    nx.gsigma[at + 1] = ldexp(nx.galpha[g], e1);
+    nx.gsigsum[at + 1] = nx.gsigma[at + 1];
+    const double eta1 = gdmax[g] < (1 << 24) ? 0.0 : 0x1p-24;   // exact sums, or one rounding
+    nx.eta[at + 1] = eta1;
+    nx.etap[at + 1] = eta1 / (1.0 - eta1) * (1.0 + 0x1p-50);
+  } else {
+    nx.gxmax64[at + 1] = (unsigned long long)__double_as_longlong(nx.galpha[g] * (double)gdmax[g]);
+  }
+  double floor = -1.0;
+  if (hi >= 0) {
+    BoundArgs b = gs.b;
+    refresh_bounds(b, gs, 1);
+    double lo, up;
+    if constexpr (F32) {
+      const float xs = ldexpf(edge, -e1);
+      const double s = nx.gsigma[at + 1] * (double)xs;
+      bounds_of<true>(b, s, xs, __double2float_ru(nx.etap[at + 1] * s * (1.0 + 0x1p-50)), lo, up);
+    } else {
+      const double s = nx.galpha[g] * (double)edge;
+      bounds_of<false>(b, s, s, 0.0f, lo, up);
+    }
+    floor = lo * (1.0 - 0x1p-20);
+  }
+  fl.floor[g] = floor;
 }
 
 // The bound factors of the graph's final iteration.
@@ -782,17 +879,17 @@ hipError_t launch_batch_prep(const long long* gbase, const void* const* grp, con
 }
 
 hipError_t launch_batch_dmax(const void* const* grp, const int* grp64, const long long* gbase, int count,
-                             long long total_n, int* gdmax, hipStream_t s) {
+                             long long total_n, int* gdmax, const BatchFloor& fl, hipStream_t s) {
   if (total_n <= 0) return hipSuccess;
   const unsigned nb = (unsigned)((total_n + kRowChunk - 1) / kRowChunk);
-  hipLaunchKernelGGL(batch_dmax, dim3(nb), dim3(kWG), 0, s, grp, grp64, gbase, count, gdmax);
+  hipLaunchKernelGGL(batch_dmax, dim3(nb), dim3(kWG), 0, s, grp, grp64, gbase, count, gdmax, fl);
   return hipGetLastError();
 }
 
-hipError_t launch_batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count, int* n_items,
-                              const BatchNext& next, int fp32, hipStream_t s) {
-  const unsigned nb = (unsigned)((std::max(count, 2 * kXcds) + kWG - 1) / kWG);
-  hipLaunchKernelGGL(batch_begin, dim3(nb), dim3(kWG), 0, s, gsc, gbase, gdmax, count, n_items, next, fp32);
+hipError_t launch_batch_begin(const GraphSel* gsel, const int* gdmax, int count, int* n_items, const BatchNext& next,
+                              const BatchFloor& fl, int fp32, hipStream_t s) {
+  if (fp32) hipLaunchKernelGGL(batch_begin<true>, dim3(count), dim3(kFinishThreads), 0, s, gsel, gdmax, n_items, next, fl);
+  else hipLaunchKernelGGL(batch_begin<false>, dim3(count), dim3(kFinishThreads), 0, s, gsel, gdmax, n_items, next, fl);
   return hipGetLastError();
 }
 
@@ -840,6 +937,17 @@ hipError_t launch_batch_item_graphs(const BatchWalk& a, long long total_blocks, 
   if (total_blocks <= 0) return hipSuccess;
   const unsigned nb = (unsigned)((total_blocks + kWG - 1) / kWG);
   hipLaunchKernelGGL(batch_item_graphs, dim3(nb), dim3(kWG), 0, s, a, total_blocks, item_g);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_first(const BatchWalk& a, const void* const* grp, const int* grp64, const int* len32,
+                              const GraphSel* gsel, const double* floor, long long total_n, hipStream_t s) {
+  if (total_n <= 0) return hipSuccess;
+  const unsigned nb = (unsigned)((total_n + kWG - 1) / kWG);
+  if (a.fp32) hipLaunchKernelGGL(batch_first<true>, dim3(nb), dim3(kWG), 0, s, a, grp, grp64, len32, gsel, floor,
+                                 total_n);
+  else hipLaunchKernelGGL(batch_first<false>, dim3(nb), dim3(kWG), 0, s, a, grp, grp64, len32, gsel, floor,
+                                 total_n);
   return hipGetLastError();
 }
 

@@ -73,25 +73,48 @@ __device__ __forceinline__ typename Prec<F32>::T ldx(const void* x, int32_t j) {
 // ---------------------------------------------------------------------------
 // The form is a template argument where several nodes are evaluated per thread:
 // a branch on b.fp32 around each would keep their loads from overlapping.
+// The bounds of a node from its c, walk entry xv and margin ev (FP32 form).
 template <bool F32>
-__device__ __forceinline__ void bound_eval_as(const BoundArgs& b, int v, double& lo, double& up) {
-  const double cv = b.c[v];
+__device__ __forceinline__ void bounds_of(const BoundArgs& b, double cv, typename Prec<F32>::T xv, float ev, double& lo,
+                                          double& up) {
   if constexpr (!F32) {
-    const double s = reinterpret_cast<const double*>(b.x)[v];
-    lo = b.undirected ? cv + b.alpha * s : cv;
-    up = cv + b.beta * s;
+    lo = b.undirected ? cv + b.alpha * xv : cv;
+    up = cv + b.beta * xv;
   } else {
-    const double s = b.sigma[b.r] * (double)reinterpret_cast<const float*>(b.x)[v];
-    const double down = (double)b.e[v] * b.f_e + b.tau_coef * b.sigma_sum[b.r];
+    const double s = b.sigma[b.r] * (double)xv;
+    const double down = (double)ev * b.f_e + b.tau_coef * b.sigma_sum[b.r];
     const double l = cv * b.f_lo_c + s * b.f_lo_s - down;
     lo = l > 0.0 ? l : 0.0;
     up = cv * b.f_hi_c + down + s * b.f_hi_s;
   }
 }
 
+template <bool F32>
+__device__ __forceinline__ void bound_eval_as(const BoundArgs& b, int v, double& lo, double& up) {
+  bounds_of<F32>(b, b.c[v], reinterpret_cast<const typename Prec<F32>::T*>(b.x)[v], F32 ? b.e[v] : 0.0f, lo, up);
+}
+
 __device__ __forceinline__ void bound_eval(const BoundArgs& b, int v, double& lo, double& up) {
   if (b.fp32) bound_eval_as<true>(b, v, lo, up);
   else bound_eval_as<false>(b, v, lo, up);
+}
+
+// The bound factors of iteration r of a batched graph (same expressions as the
+// host-side bound arguments).
+__device__ __forceinline__ void refresh_bounds(BoundArgs& b, const GraphSel& gs, int r) {
+  b.r = r;
+  b.x = (r & 1) ? gs.xbuf[1] : gs.xbuf[0];
+  if (b.fp32) {
+    const double u64 = 0x1p-53;
+    const double kap = (2.0 * r + 32.0) * u64;
+    const double ep = gs.etap[r];
+    b.kappa = kap;
+    b.f_lo_c = 1.0 - kap;
+    b.f_hi_c = 1.0 + kap;
+    b.f_e = 1.0 + kap;
+    b.f_lo_s = b.undirected ? b.alpha * (1.0 - ep) * (1.0 - kap) * (1.0 - 8.0 * u64) : 0.0;
+    b.f_hi_s = b.beta * (1.0 + ep) * (1.0 + kap) * (1.0 + 8.0 * u64);
+  }
 }
 
 // FP32 form: true while the part of the interval that further iterations

@@ -338,6 +338,15 @@ struct BatchNext {
   int stride;
 };
 
+// A floor under the k-th lower bound of iteration 1 of every graph larger than the
+// selection's one-node-per-thread form: from a histogram of its row lengths.
+constexpr int kLenDigits = 1024;
+struct BatchFloor {
+  const int* hist_of;           // per graph: its histogram, or -1
+  unsigned* hist;               // [.][kLenDigits]
+  double* floor;                // per graph (none: -1, below every bound)
+};
+
 // ---- launchers (katz_kernels.hip) ----------------------------------------
 // Binning scratch: the per-workgroup table (prep_table_rows x nblocks entries;
 // kBinParts where a graph is renumbered or a state binned, else 1) and its row
@@ -515,7 +524,7 @@ hipError_t launch_batch_prep(const long long* gbase, const void* const* grp, con
                              long long total_nnz, int* gid_of, const PrepTable& tab, RowDesc* desc, SegDesc* segs, HugeRow* huge, RunScalars* sc,
                              int validate, const BinBounds& bb, hipStream_t s);
 hipError_t launch_batch_dmax(const void* const* grp, const int* grp64, const long long* gbase, int count,
-                             long long total_n, int* gdmax, hipStream_t s);
+                             long long total_n, int* gdmax, const BatchFloor& fl, hipStream_t s);
 hipError_t launch_batch_relabel(const RowDesc* desc, long long total, const long long* gbase, int count,
                                 const RunScalars* sc, long long* run_first, long long* run_last,
                                 long long* run_start, int32_t* ext_of, int32_t* int_of, long long* coff, IdLen* pmap,
@@ -525,13 +534,17 @@ hipError_t launch_batch_rename(const RowDesc* desc, const long long* bin_base, c
                                const SegDesc* segs, long long seg_total, const HugeRow* huge, const long long* noff,
                                const int* gid_of, const long long* gbase, const int32_t* const* gcol,
                                const long long* coff, const IdLen* pmap, int32_t* ncol, hipStream_t s);
-// Before iteration 1: every graph's flags and first table entries.
-hipError_t launch_batch_begin(RunScalars* gsc, const long long* gbase, const int* gdmax, int count, int* n_items,
-                              const BatchNext& next, int fp32, hipStream_t s);
+// Before iteration 1: every graph's flags, first table entries and floor.
+hipError_t launch_batch_begin(const GraphSel* gsel, const int* gdmax, int count, int* n_items, const BatchNext& next,
+                              const BatchFloor& fl, int fp32, hipStream_t s);
 hipError_t launch_walk_batch(const BatchWalk& a, long long total_blocks, long long max_grid, long long n_huge,
                              hipStream_t s);
 hipError_t launch_batch_item_graphs(const BatchWalk& a, long long total_blocks, int* item_g, hipStream_t s);
-// The work items of iteration a.r (a.n_items: two sets of kXcds counters, by parity
+// Iteration 1's walk step of every row, and every graph's first active list.  len32:
+// the lengths by row (renumbered batches); null: the graphs' row pointers hold them.
+hipError_t launch_batch_first(const BatchWalk& a, const void* const* grp, const int* grp64, const int* len32,
+                              const GraphSel* gsel, const double* floor, long long total_n, hipStream_t s);
+// The work items of iteration a.r > 1 (a.n_items: two sets of kXcds counters, by parity
 // of r); publishes the graphs stopped before it.
 hipError_t launch_batch_live_items(const BatchWalk& a, long long total_blocks, int* items, int* n_items,
                                    const int* ndone, const Publish& pub, hipStream_t s);

@@ -11,26 +11,28 @@
 namespace katz {
 namespace {
 
-// The bound factors of iteration r of a batched graph (same expressions as the
-// host-side bound arguments).
-__device__ void refresh_bounds(BoundArgs& b, const GraphSel& gs, int r) {
-  b.r = r;
-  b.x = (r & 1) ? gs.xbuf[1] : gs.xbuf[0];
-  if (b.fp32) {
-    const double u64 = 0x1p-53;
-    const double kap = (2.0 * r + 32.0) * u64;
-    const double ep = gs.etap[r];
-    b.kappa = kap;
-    b.f_lo_c = 1.0 - kap;
-    b.f_hi_c = 1.0 + kap;
-    b.f_e = 1.0 + kap;
-    b.f_lo_s = b.undirected ? b.alpha * (1.0 - ep) * (1.0 - kap) * (1.0 - 8.0 * u64) : 0.0;
-    b.f_hi_s = b.beta * (1.0 + ep) * (1.0 + kap) * (1.0 + 8.0 * u64);
+constexpr int kSelIlp = 8;   // nodes per thread and pass of the key and deactivation passes
+
+// Positions of the nodes with pred in a list that *counter counts: one atomic per
+// wave for all U of a thread (each waits for its return).  Every lane of the wave
+// must call it.
+template <int U>
+__device__ __forceinline__ void wave_append_all(int* counter, const bool (&pred)[U], int (&pos)[U]) {
+  unsigned long long mask[U];
+  int sum = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    mask[u] = __ballot(pred[u]);
+    pos[u] = sum + __popcll(mask[u] & lanemask_lt());
+    sum += __popcll(mask[u]);
   }
+  if (!sum) return;
+  int base = 0;
+  if (lane_id() == 0) base = atomicAdd(counter, sum);
+  base = __shfl(base, 0);
+#pragma unroll
+  for (int u = 0; u < U; ++u) pos[u] += base;
 }
-
-
-constexpr int kSelIlp = 4;   // nodes per thread and pass of the key and deactivation passes
 
 struct SortArea {
   unsigned long long key[kMaxK];
@@ -453,7 +455,7 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
   const int cur = r ? sc->cur : gs.cur;
   const int32_t* act_in = cur ? gs.act[1] : gs.act[0];
   int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
-  const bool identity = r ? (b.r == 1) : gs.identity_in;
+  const bool identity = !r && gs.identity_in;
   const int m = identity ? gs.n : sc->m;
   const bool walk_zero = F32 ? (gs.xmax32[b.r] == 0u) : (gs.xmax64[b.r] == 0ull);
   __shared__ union {
@@ -504,7 +506,7 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
   __syncthreads();
   {
     unsigned long long kmin = ~0ull, kmax = 0ull;
-    // Four nodes per thread and pass, their loads issued together (a slot past
+    // kSelIlp nodes per thread and pass, their loads issued together (a slot past
     // the end evaluates node base, a valid index, and is dropped).
     for (int b0 = 0; b0 < m; b0 += kSelIlp * kFinishThreads) {   // same trip count for every thread
       unsigned long long kk[kSelIlp];
@@ -578,15 +580,17 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
         kk[u] = i < m ? keys[i] : 0ull;
         vv[u] = i < m ? (identity ? base_id + i : act_in[i]) : 0;
       }
+      bool pred[kSelIlp];
+      int pos[kSelIlp];
 #pragma unroll
-      for (int u = 0; u < kSelIlp; ++u) {
-        const bool pred = b0 + u * kFinishThreads + t < m && (kk[u] >> rem) == pre;
-        const int pos = wave_append(&s_cnt, pred);
-        if (pred) {
-          cand_key[pos] = kk[u];
-          cand_v[pos] = vv[u];
+      for (int u = 0; u < kSelIlp; ++u) pred[u] = b0 + u * kFinishThreads + t < m && (kk[u] >> rem) == pre;
+      wave_append_all(&s_cnt, pred, pos);
+#pragma unroll
+      for (int u = 0; u < kSelIlp; ++u)
+        if (pred[u]) {
+          cand_key[pos[u]] = kk[u];
+          cand_v[pos[u]] = vv[u];
         }
-      }
     }
   }
   __syncthreads();
@@ -662,7 +666,7 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
     cut = s_idpre;
   }
   // Deactivation: nodes past position k leave M when u - eps < l(M[k]).
-  // Four nodes per thread and pass as above (the order of M does not matter).
+  // kSelIlp nodes per thread and pass as above (the order of M does not matter).
   {
     bool prog = false;
     for (int base = 0; base < m; base += kSelIlp * kFinishThreads) {
@@ -681,12 +685,13 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
         if ((top[u] || keep[u]) && can_progress_as<F32>(b, v)) prog = true;
         vv[u] = v;
       }
+      int pt[kSelIlp], pk[kSelIlp];
+      wave_append_all(&s_top, top, pt);
+      wave_append_all(&s_kept, keep, pk);
 #pragma unroll
       for (int u = 0; u < kSelIlp; ++u) {
-        const int pt = wave_append(&s_top, top[u]);
-        if (top[u] && pt < k) act_out[pt] = vv[u];
-        const int pk = wave_append(&s_kept, keep[u]);
-        if (keep[u] && k + pk < n_g) act_out[k + pk] = vv[u];
+        if (top[u] && pt[u] < k) act_out[pt[u]] = vv[u];
+        if (keep[u] && k + pk[u] < n_g) act_out[k + pk[u]] = vv[u];
       }
     }
     if (prog) s_prog = 1;

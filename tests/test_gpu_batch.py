@@ -273,3 +273,29 @@ def test_batch_iteration_limits(precision):
             assert rb.iterations <= pp["max_iter"]
             if precision == "fp64":
                 assert torch.equal(single.lower, rb.lower) and torch.equal(single.upper, rb.upper)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_first_list_edges(precision):
+    """Sizes around the one-node-per-thread selection and every kind of k on
+    them (1, half, all but one, all), and rows of one length each: the first
+    active list holds the nodes that the single call ends with."""
+    katz = K()
+    graphs, params = [], []
+    for n in (1023, 1024, 1025, 2049, 9000):
+        rp, col = sg.barabasi_albert(n, 5, n)
+        for k in (1, n // 2, n - 1, n):
+            if k <= 4096:
+                graphs.append((rp, col))
+                params.append(dict(k=k, alpha=0.7 / (1 + sg.max_degree(rp)), eps=1e-7, max_iter=12))
+    rp, col = circulant(3000, [1, 2, 3])    # every length the same, all bounds tied
+    graphs.append((rp, col))
+    params.append(dict(k=70, alpha=0.1, eps=1e-7, max_iter=12))
+    say("batch first lists", precision, len(graphs))
+    for (rp, col), pp, rb in zip(graphs, params, run_batch(graphs, params, precision)):
+        single = katz.rank_static(torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), pp["k"],
+                                  alpha=pp["alpha"], eps=pp["eps"], max_iter=pp["max_iter"], precision=precision)
+        assert torch.equal(single.topk, rb.topk)
+        assert (single.iterations, single.status, single.active_final) == (rb.iterations, rb.status, rb.active_final)
+        if precision == "fp64":
+            assert torch.equal(single.lower, rb.lower) and torch.equal(single.upper, rb.upper)
