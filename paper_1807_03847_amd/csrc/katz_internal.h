@@ -572,11 +572,12 @@ hipError_t launch_csr_equal(const void* rp, int rp64, const int32_t* col, const 
                             const int32_t* rt_col, long long n, long long nnz, RunScalars* sc, hipStream_t s);
 hipError_t launch_fill_value(double* x, long long n, double v, hipStream_t s);
 hipError_t launch_foster_step(const double* y, const double* f, double* f_new, long long n, double* slots,
-                              double* out, hipStream_t s);
+                              double* out, unsigned long long* pub, hipStream_t s);
+hipError_t launch_cg_start(double* z, double* r, double* p, long long n, double* scal, hipStream_t s);
 hipError_t launch_cg_apply(const double* p, const double* y, double* q, long long n, double* slots, double* out,
                            double* scal, hipStream_t s);
 hipError_t launch_cg_update(double* z, double* r, const double* p, const double* q, long long n, double* slots,
-                            double* out, double* scal, hipStream_t s);
+                            double* out, double* scal, unsigned long long* pub, hipStream_t s);
 hipError_t launch_cg_direction(double* p, const double* r, const double* scal, long long n, hipStream_t s);
 hipError_t launch_write_scores(const double* x, double add, long long n, const int32_t* ext_of, double* out,
                                hipStream_t s);

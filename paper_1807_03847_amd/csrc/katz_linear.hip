@@ -94,8 +94,9 @@ __global__ void __launch_bounds__(kWG) cg_direction(double* p, const double* r, 
 // out[0] = the result; with the CG scalars also the step sizes:
 //   mode 1 (after cg_apply):  s[1] = s[0] / out  (a = r.r / p.q)
 //   mode 2 (after cg_update): s[2] = out / s[0]  (b = r'.r' / r.r), s[0] = out
+// pub: the word of pinned memory that the host polls for the result, or null.
 __global__ void __launch_bounds__(kWG) combine_slots(const double* slots, int nslots, int op, double* out,
-                                                     double* scal, int mode) {
+                                                     double* scal, int mode, unsigned long long* pub) {
   double v = 0.0;
   // Each thread combines a fixed stride of slots in order, then the block
   // combines the threads in a fixed tree: deterministic.
@@ -108,7 +109,19 @@ __global__ void __launch_bounds__(kWG) combine_slots(const double* slots, int ns
       scal[2] = v / scal[0];
       scal[0] = v;
     }
+    if (pub)
+      __hip_atomic_store(pub, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+}
+
+// CG from z = 0: r = p = 1, r.r = n.
+__global__ void __launch_bounds__(kWG) cg_start(double* z, double* r, double* p, long long n, double* scal) {
+  for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < n; i += (long long)gridDim.x * kWG) {
+    z[i] = 0.0;
+    r[i] = 1.0;
+    p[i] = 1.0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) scal[0] = (double)n;
 }
 
 // scores = x + add (Foster: f - 1), written through ext_of (internal -> caller id).
@@ -132,11 +145,11 @@ hipError_t launch_fill_value(double* x, long long n, double v, hipStream_t s) {
 }
 
 hipError_t launch_foster_step(const double* y, const double* f, double* f_new, long long n, double* slots,
-                              double* out, hipStream_t s) {
+                              double* out, unsigned long long* pub, hipStream_t s) {
   const unsigned g = grid_of(n);
   hipLaunchKernelGGL(foster_step, dim3(g), dim3(kWG), 0, s, y, f, f_new, n, slots);
   hipLaunchKernelGGL(combine_slots, dim3(1), dim3(kWG), 0, s, (const double*)slots, (int)g, 1, out,
-                     (double*)nullptr, 0);
+                     (double*)nullptr, 0, pub);
   return hipGetLastError();
 }
 
@@ -145,15 +158,21 @@ hipError_t launch_cg_apply(const double* p, const double* y, double* q, long lon
                            double* scal, hipStream_t s) {
   const unsigned g = grid_of(n);
   hipLaunchKernelGGL(cg_apply, dim3(g), dim3(kWG), 0, s, p, y, q, n, slots);
-  hipLaunchKernelGGL(combine_slots, dim3(1), dim3(kWG), 0, s, (const double*)slots, (int)g, 0, out, scal, 1);
+  hipLaunchKernelGGL(combine_slots, dim3(1), dim3(kWG), 0, s, (const double*)slots, (int)g, 0, out, scal, 1,
+                     (unsigned long long*)nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_cg_update(double* z, double* r, const double* p, const double* q, long long n, double* slots,
-                            double* out, double* scal, hipStream_t s) {
+                            double* out, double* scal, unsigned long long* pub, hipStream_t s) {
   const unsigned g = grid_of(n);
   hipLaunchKernelGGL(cg_update, dim3(g), dim3(kWG), 0, s, z, r, p, q, (const double*)(scal + 1), n, slots);
-  hipLaunchKernelGGL(combine_slots, dim3(1), dim3(kWG), 0, s, (const double*)slots, (int)g, 0, out, scal, 2);
+  hipLaunchKernelGGL(combine_slots, dim3(1), dim3(kWG), 0, s, (const double*)slots, (int)g, 0, out, scal, 2, pub);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_start(double* z, double* r, double* p, long long n, double* scal, hipStream_t s) {
+  hipLaunchKernelGGL(cg_start, dim3(grid_of(n)), dim3(kWG), 0, s, z, r, p, n, scal);
   return hipGetLastError();
 }
 
