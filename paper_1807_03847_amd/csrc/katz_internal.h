@@ -74,6 +74,9 @@ struct BinBounds {
   int g4 = 4, g8 = 8, g16 = 16, g32 = 32, w16 = kShortRowMax, w64 = kWaveRowMax;
 };
 
+// Slots of the renumbering step's map (katz_kernels.hip), 8 bytes each.
+constexpr int kHotSlotBits = 17;
+
 // Binning (katz_device.h): rows per workgroup, parts that a bin is cut into by
 // length (in a renumbered graph this orders the nodes of a bin by length, longest
 // first), and the lengths at which they are cut.
@@ -210,6 +213,9 @@ struct IterArgs {
   RunScalars* sc;
   int n;
   int r;
+  const int32_t* ext_of;         // internal -> caller id (renumbering step)
+  unsigned long long* hot_map;   // renumbering step: 2^kHotSlotBits words for its map, or null (no map)
+  int id_bits;                   // bits of a caller id, at least kHotSlotBits (with a map)
   int count_first;               // walk_first: number of descriptors to process
   int write_empty;
   int clog2_dmax;

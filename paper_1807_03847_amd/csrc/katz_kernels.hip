@@ -284,7 +284,52 @@ struct Stretch {
 // unfused step on the renamed columns, so the sum is bitwise the same.
 constexpr int kBatch = 8;
 
-template <bool F32, int G, bool Renumber>
+// kRenumberMapped: the renumbering step reads the most-referenced nodes' entries from
+// a map that stays in each XCD's L2.  In pmap, which is in caller order, they lie a
+// cache line each, and the step is bound by the lines that it misses: R-MAT 22 took
+// its 124 M arcs at 82 G/s, where gathers that hit L2 reach 265.  A slot holds the
+// node with the lowest internal id (the longest row) among those that hash to it:
+// {internal id, tag} and the row length.  The hash is a bijection of the ids' bits
+// (an odd factor modulo 2^bits): the slot is its leading kHotSlotBits, the tag the
+// rest, so equal tags are the same node.  Step, FP32, R-MAT 22 and 25, by slots:
+// none 1507 us and 17.6 ms, 2^16 1267 and 14.2, 2^17 (1 MiB) 1212 and 13.4, 2^18 1199
+// and 13.5, 2^19 1259 and 15.2, 2^20 1458 and 17.3.  With a level of 2^14 slots in
+// LDS before it 1174 and 13.5; non-temporal loads and stores undo the gain.
+constexpr int kPlainStep = 0, kRenumberStep = 1, kRenumberMapped = 2;
+constexpr int kHotTagBits = 31 - kHotSlotBits;
+constexpr int kHotNodes = (1 << (32 - kHotTagBits)) - 1;   // an empty slot reads as the id after the last
+
+struct HotPlace {
+  unsigned slot, tag;
+};
+
+__device__ __forceinline__ HotPlace hot_place(int id, int id_bits) {
+  const int shift = id_bits - kHotSlotBits;
+  const unsigned h = ((unsigned)id * 0x9e3779b1u) & ((1u << id_bits) - 1u);
+  return HotPlace{h >> shift, h & ((1u << shift) - 1u)};
+}
+
+__device__ __forceinline__ unsigned long long hot_entry(unsigned long long slot) {
+  return slot << 32 | slot >> (32 + kHotTagBits);
+}
+
+__device__ __forceinline__ bool hot_hit(unsigned long long slot, const HotPlace& at) {
+  return ((unsigned)(slot >> 32) & ((1u << kHotTagBits) - 1u)) == at.tag &&
+         (int)(slot >> (32 + kHotTagBits)) < kHotNodes;
+}
+
+__global__ void __launch_bounds__(kWG) hot_map_clear(unsigned long long* map) {
+  map[blockIdx.x * kWG + threadIdx.x] = ~0ull;
+}
+
+__global__ void __launch_bounds__(kWG) hot_map_fill(IterArgs a, unsigned long long* map) {
+  const int v = blockIdx.x * kWG + threadIdx.x;
+  if (v >= min(a.n, kHotNodes)) return;
+  const HotPlace at = hot_place(a.ext_of[v], a.id_bits);
+  atomicMin(&map[at.slot], (unsigned long long)((unsigned)v << kHotTagBits | at.tag) << 32 | (unsigned)a.desc[v].len);
+}
+
+template <bool F32, int G, int Renumber>
 __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                              const Stretch& st, int lane, const Epi<F32>& ep1) {
   using T = typename Prec<F32>::T;
@@ -312,12 +357,28 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
     }
     if constexpr (Renumber) {
       IdLen m[NB];
+      if constexpr (Renumber == kRenumberMapped) {
+        unsigned long long slot[NB];
 #pragma unroll
-      for (int u = 0; u < NB; ++u) m[u] = c[u] < 0 ? IdLen{0, 0} : a.pmap[c[u]];
+        for (int u = 0; u < NB; ++u) slot[u] = c[u] >= 0 ? a.hot_map[hot_place(c[u], a.id_bits).slot] : 0ull;
+        // {id, length} as one word, as pmap holds it.
+        unsigned long long w[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          w[u] = hot_entry(slot[u]);
+          if (c[u] >= 0 && !hot_hit(slot[u], hot_place(c[u], a.id_bits)))
+            w[u] = reinterpret_cast<const unsigned long long*>(a.pmap)[c[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) m[u] = IdLen{(int)(unsigned)w[u], (int)(w[u] >> 32)};
+      } else {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) m[u] = c[u] < 0 ? IdLen{0, 0} : a.pmap[c[u]];
+      }
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         const int j = j0 + u * G;
-        if (j < len) st.dst[j] = m[u].id;
+        if (j < len) st.dst[j] = c[u] < 0 ? 0 : m[u].id;
         sum += c[u] < 0 ? (T)0 : x_entry<F32>(a, ep1, (T)m[u].len);
       }
     } else {
@@ -338,7 +399,7 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
 }
 
 // The stretch of a whole row (desc.off indexes the walk's column array).
-template <bool Renumber>
+template <int Renumber>
 __device__ __forceinline__ Stretch row_stretch(const IterArgs& a, const RowDesc& d, bool valid) {
   if constexpr (Renumber) return Stretch{a.col_src + (valid ? a.coff[d.row] : 0), a.ncol + d.off, d.len};
   else return Stretch{a.col + d.off, nullptr, d.len};
@@ -346,7 +407,7 @@ __device__ __forceinline__ Stretch row_stretch(const IterArgs& a, const RowDesc&
 
 // tid: the thread's index in its 256-thread group (the workgroup, or one of
 // the groups of walk_step_grouped).
-template <bool F32, int G, bool Renumber>
+template <bool F32, int G, int Renumber>
 __device__ __forceinline__ void rows_group(const IterArgs& a, const typename Prec<F32>::T* hub, const Epi<F32>& ep,
                                            const Epi<F32>& ep1, long long lb, int bin, double& vmax, bool stop,
                                            int tid) {
@@ -370,7 +431,7 @@ __device__ __forceinline__ void rows_group(const IterArgs& a, const typename Pre
 // butterflies, then the four wave sums as (w0 + w1) + (w2 + w3) through part
 // (the group's four LDS slots).  Contains workgroup barriers: every thread of
 // the workgroup must call it the same number of times.
-template <bool F32, bool Renumber>
+template <bool F32, int Renumber>
 __device__ __forceinline__ typename Prec<F32>::T group_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                            const Stretch& st, const Epi<F32>& ep1, int tid,
                                                            typename Prec<F32>::T* part) {
@@ -384,7 +445,7 @@ __device__ __forceinline__ typename Prec<F32>::T group_sum(const IterArgs& a, co
   return tot;
 }
 
-template <bool F32, bool Renumber>
+template <bool F32, int Renumber>
 __device__ __forceinline__ typename Prec<F32>::T block_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                            const Stretch& st, const Epi<F32>& ep1) {
   __shared__ typename Prec<F32>::T part[kWG / kWave];
@@ -441,7 +502,7 @@ __global__ void __launch_bounds__(kWG) check_col_range(const int32_t* col, long 
 // (a persistent grid, which is what makes the LDS copy of the first a.hub_n
 // walk entries worth its fill).  Renumber: step 2 of a renumbered static run,
 // which also writes the renamed column ids (see strided_sum).
-template <bool F32, bool Renumber>
+template <bool F32, int Renumber>
 __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
   using T = typename Prec<F32>::T;
   // The stop flag (a launch enqueued ahead of the host's flag read skips its
@@ -1292,6 +1353,11 @@ hipError_t launch_walk_kernel(const IterArgs& a, int fp32, long long total_block
                               long long* used_out, hipStream_t s, bool renumber, int groups) {
   long long g = total_blocks > 0 ? total_blocks : 1;
   const size_t lds = (size_t)a.hub_n * (fp32 ? sizeof(float) : sizeof(double));
+  if (renumber && a.hot_map) {
+    hipLaunchKernelGGL(hot_map_clear, dim3((1 << kHotSlotBits) / kWG), dim3(kWG), 0, s, a.hot_map);
+    hipLaunchKernelGGL(hot_map_fill, dim3((unsigned)((std::min(a.n, kHotNodes) + kWG - 1) / kWG)), dim3(kWG), 0, s, a,
+                       a.hot_map);
+  }
   if (!renumber && groups == kWalkGroups) {
     // Workgroups of kWalkGroups groups; slots = virtual workgroups.
     g = (g + kWalkGroups - 1) / kWalkGroups;
@@ -1307,12 +1373,15 @@ hipError_t launch_walk_kernel(const IterArgs& a, int fp32, long long total_block
                                : (fp32 ? (const void*)walk_step<true, false> : (const void*)walk_step<false, false>);
       g = std::min(g, std::min(max_grid, resident_blocks(k, renumber ? 0 : lds, kWG)));
     }
-    if (renumber) {
-      if (fp32) hipLaunchKernelGGL((walk_step<true, true>), dim3((unsigned)g), dim3(kWG), 0, s, a);
-      else hipLaunchKernelGGL((walk_step<false, true>), dim3((unsigned)g), dim3(kWG), 0, s, a);
+    if (renumber && a.hot_map) {
+      if (fp32) hipLaunchKernelGGL((walk_step<true, kRenumberMapped>), dim3((unsigned)g), dim3(kWG), 0, s, a);
+      else hipLaunchKernelGGL((walk_step<false, kRenumberMapped>), dim3((unsigned)g), dim3(kWG), 0, s, a);
+    } else if (renumber) {
+      if (fp32) hipLaunchKernelGGL((walk_step<true, kRenumberStep>), dim3((unsigned)g), dim3(kWG), 0, s, a);
+      else hipLaunchKernelGGL((walk_step<false, kRenumberStep>), dim3((unsigned)g), dim3(kWG), 0, s, a);
     } else {
-      if (fp32) hipLaunchKernelGGL((walk_step<true, false>), dim3((unsigned)g), dim3(kWG), lds, s, a);
-      else hipLaunchKernelGGL((walk_step<false, false>), dim3((unsigned)g), dim3(kWG), lds, s, a);
+      if (fp32) hipLaunchKernelGGL((walk_step<true, kPlainStep>), dim3((unsigned)g), dim3(kWG), lds, s, a);
+      else hipLaunchKernelGGL((walk_step<false, kPlainStep>), dim3((unsigned)g), dim3(kWG), lds, s, a);
     }
     *used_out = g;
   }

@@ -470,3 +470,33 @@ def test_two_pass_walk_step(precision):
                 assert torch.equal(res.upper, ref.upper) and res.iterations == ref.iterations
     finally:
         katz.tuning_set(**saved)
+
+
+@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1, (1 << 22) + 13])
+def test_renumbering_map_is_invisible(n):
+    """Above 2^21 nodes the renumbering step reads the hot nodes' entries through
+    a hash map: all bits are those of the run in caller order (the first size is
+    the last one without the map; the others need 22 and 23 id bits), and ids out
+    of range still fail, the next one after the last node among them."""
+    katz = K()
+    rng = np.random.default_rng(n)
+    m = 2_500_000
+    src = rng.integers(0, n, m)
+    dst = ((n * rng.random(m) ** 6).astype(np.int64) * 1_000_003 + 17) % n   # hot ids all over the range
+    dst[:3] = (0, n - 1, n - 1)
+    rp, col = sg.from_edges(n, src, dst)
+    rp_t, col_t = dev(rp, col)
+    say("renumbering map", n, len(col))
+    for precision in ("fp64", "fp32"):
+        a = katz.rank_static(rp_t, col_t, 100, eps=1e-6, precision=precision, flags=katz.FLAG_REORDER)
+        b = katz.rank_static(rp_t, col_t, 100, eps=1e-6, precision=precision, flags=katz.FLAG_NO_REORDER)
+        assert a.iterations == b.iterations and a.iterations >= 2 and a.status == b.status
+        assert torch.equal(a.topk, b.topk)
+        assert torch.equal(a.lower, b.lower) and torch.equal(a.upper, b.upper)
+        assert a.rest_upper_max == b.rest_upper_max
+    for bad in (n, -1):
+        col_bad = col_t.clone()
+        col_bad[len(col) // 2] = bad
+        with pytest.raises(katz.KatzError) as e:
+            katz.rank_static(rp_t, col_bad, 100, eps=1e-6, flags=katz.FLAG_REORDER)
+        assert e.value.code == katz.E_CSR
