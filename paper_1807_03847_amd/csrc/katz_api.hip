@@ -779,6 +779,10 @@ struct Run {
   Publish pub = {};            // where the next selection publishes its flags
   long long m_known = -1;      // |M| before the first pass, if known
 
+  // The active list begins with the last pass's top-k (or, before the first pass, with
+  // the longest rows), from which sel_filter takes its floor.
+  bool top_first = false;
+
   // Whether one workgroup may run converged() (its LDS sort holds the top-k).
   bool one_workgroup_select() const { return (criterion == KATZ_TOPK || criterion == KATZ_RANKING) && k <= kMaxK; }
 };
@@ -906,9 +910,34 @@ int ensure_levels(katz_state* st, int r);
 
 int refresh_bins(katz_state* st, hipStream_t s);
 
-// small_m: the one-workgroup selection follows and reduces the step's maxima
-// itself when there are few (run.walk_max); else a launch of its own does.
-int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
+// Which launches select: several with histograms, several that filter by a floor, or
+// one workgroup.  The latter two reduce the walk step's maxima themselves.
+enum Select { SEL_WIDE, SEL_FILTER, SEL_ONE };
+
+// The choice by the active nodes known to be at most m.  One workgroup: sets that its
+// registers hold (17 us for 16384 nodes of the FP64 form, 8192 of the FP32 form), and
+// up to kSmallActive where there is no floor (46 us and more).  Filtered sets take
+// 27 us and more.
+Select select_form(const Run& run, long long m) {
+  if (!run.one_workgroup_select()) return SEL_WIDE;
+  if (m <= (run.fp32 ? kMidNodes32 : kMidNodes64)) return SEL_ONE;
+  if (run.top_first && run.k <= kFinishThreads) return SEL_FILTER;
+  return m <= kSmallActive ? SEL_ONE : SEL_WIDE;
+}
+
+// A renumbered run's first active list begins with the longest rows.  Rows of one bin
+// are not sorted, so the nodes that are not behind the last of the first k lie in the
+// bins up to the k-th's: few enough for one workgroup to sort out (kSmallCand).
+bool longest_rows_first(const Bins& b, int k) {
+  for (int i = 0; i < NUM_BINS; ++i)
+    if (k <= b.bin_base[i] + b.bin_count[i]) return b.bin_base[i] + b.bin_count[i] <= kSmallCand;
+  return false;
+}
+
+// sel: the selection that follows.  It reduces the step's maxima itself when it is
+// the filtered one, or one workgroup and they are few (run.walk_max); else a launch
+// of its own does.
+int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T, Select sel) {
   // A dynamic state re-bins its rows lazily, before the first whole-graph walk
   // after the updates that changed row lengths.
   if (run.st) KATZ_TRY(refresh_bins(run.st, s));
@@ -943,20 +972,21 @@ int enqueue_walk(Run& run, int r, hipStream_t s, CallTimer& T, bool small_m) {
   T.stop(tw, s);
   const long long nb = r == 1 ? std::max<long long>(1, (run.bins->count + kWG - 1) / kWG) : grid;
   run.walk_max = WalkMax{nullptr, 0};
-  if (small_m && nb <= kFusedMaxSlots) run.walk_max = WalkMax{run.w->blkmax, (int)nb};
+  if (sel == SEL_FILTER || (sel == SEL_ONE && nb <= kFusedMaxSlots)) run.walk_max = WalkMax{run.w->blkmax, (int)nb};
   else KATZ_HIP(launch_reduce_blkmax(run.w->blkmax, nb, run.fp32, run.w->xmax32, run.w->xmax64, r, run.w->sc, s));
   return KATZ_OK;
 }
 
-// small_m: the active set is known to hold at most kSmallActive nodes, so one
-// workgroup runs the whole of converged().
-int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, bool small_m) {
+// m: |M| is known to be at most this.
+int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, Select sel, long long m) {
   const int ts = T.start(T_SELECT, s);
   if (run.criterion == KATZ_SCORE) {
     KATZ_HIP(launch_score_check(sel_args(run, r), s));
   } else if (run.criterion == KATZ_PAIR) {
     KATZ_HIP(launch_pair_check(sel_args(run, r), run.pair_u, run.pair_v, s));
-  } else if (small_m) {
+  } else if (sel == SEL_FILTER) {
+    KATZ_HIP(launch_filtered_select(sel_args(run, r), run.walk_max, m, run.grid, s));
+  } else if (sel == SEL_ONE) {
     GraphSel gs{};
     gs.b = bound_args(run, r);
     gs.act[0] = run.w->act[0];
@@ -998,6 +1028,7 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, b
   T.stop(ts, s);
   run.cur ^= 1;
   run.first_select = false;
+  run.top_first = true;
   return KATZ_OK;
 }
 
@@ -1074,7 +1105,7 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
     run.pub = Publish{&hs.flags[seq & 1], seq};
     at[0] = PassAt{r - 1, run.cur ^ 1};
     run.walk_max = WalkMax{nullptr, 0};
-    KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, m_known <= kSmallActive));
+    KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, select_form(run, m_known), m_known));
     KATZ_TRY(wait_flags(hs, seq, run.w->sc, &last, s));
     stopped = last.stopped();
     m_known = last.m;
@@ -1082,16 +1113,16 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
   }
   while (!stopped) {
     const Range range("katz iteration", r);
-    const bool small_m = m_known <= kSmallActive && run.one_workgroup_select();
+    const Select sel = select_form(run, m_known);
     run.pub = polled ? Publish{&hs.flags[(hs.seq + 1) & 1], hs.seq + 1} : Publish{nullptr, 0};
     const bool select_only = pass == 0 && check_first;
     at[pass & 1] = PassAt{select_only ? r - 1 : r, run.cur ^ 1};
     if (select_only) {
-      KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, false));
+      KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, SEL_WIDE, m_known));
     } else if (r <= run.max_iter) {
       if (run.st) KATZ_TRY(ensure_levels(run.st, r));
-      KATZ_TRY(enqueue_walk(run, r, s, T, small_m));
-      KATZ_TRY(enqueue_select(run, hs, r, s, T, small_m));
+      KATZ_TRY(enqueue_walk(run, r, s, T, sel));
+      KATZ_TRY(enqueue_select(run, hs, r, s, T, sel, m_known));
       ++r;
     } else {
       break;
@@ -1447,6 +1478,7 @@ int rank_in_arena(Arena& ar, const katz_csr* g, const katz_params* p, katz_resul
   run.k = klen;
   run.max_iter = pl.max_iter;
   run.grid = (int)std::min<long long>((g->n + kWG - 1) / kWG, 2048);
+  if (pl.reorder) run.top_first = longest_rows_first(b, klen);
   KATZ_TRY(iterate(run, ar.hs, 1, false, s, T));
   KATZ_TRY(check_columns_if_unread(pl, stg, w, ar.hs, s));
   return write_result(run, ar.hs, out, stg.out_ids, stg.out_lo, stg.out_up, s, T);
@@ -1650,7 +1682,7 @@ int bounds_on(const katz_csr* g, const katz_params* p, int r_target, double* low
   run.S = &S;
   CallTimer T;
   T.call_begin(s);
-  for (int r = 1; r <= r_target; ++r) KATZ_TRY(enqueue_walk(run, r, s, T, false));
+  for (int r = 1; r <= r_target; ++r) KATZ_TRY(enqueue_walk(run, r, s, T, SEL_WIDE));
   if (!async) {
     KATZ_HIP(hipMemcpyAsync(ar.hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
     KATZ_HIP(hipStreamSynchronize(s));

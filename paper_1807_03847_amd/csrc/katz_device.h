@@ -300,6 +300,58 @@ __device__ inline int block_reserve(int* counter, unsigned mask) {
   return base + ex;
 }
 
+namespace {
+
+// One record per thread: the exchange of the sort's long strides, and (select_small)
+// each node's id and upper bound by the slot its record carries.
+struct SmallArea {
+  unsigned long long key[kFinishThreads];
+  int ext[kFinishThreads];
+  int slot[kFinishThreads];
+  int v[kFinishThreads];   // node id, bit 31: can_progress
+  double up[kFinishThreads];
+};
+
+// Sorts m <= kFinishThreads records, one per thread (threads at and past m hold
+// padding: ~0, INT_MAX), ascending by (key, ext).  Strides below a wave are lane
+// exchanges, longer ones go through the LDS: m = 1024 takes 10 of them.  Every
+// thread of the workgroup must call it.
+__device__ __forceinline__ void sort_records(int m, unsigned long long& key, int& ext, int& slot, SmallArea& sm) {
+  const int t = threadIdx.x;
+  int P = kWave;
+  while (P < m) P <<= 1;
+  for (int size = 2; size <= P; size <<= 1) {
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      unsigned long long ok;
+      int oe, os;
+      if (stride >= kWave) {
+        sm.key[t] = key;
+        sm.ext[t] = ext;
+        sm.slot[t] = slot;
+        __syncthreads();
+        ok = sm.key[t ^ stride];
+        oe = sm.ext[t ^ stride];
+        os = sm.slot[t ^ stride];
+        __syncthreads();
+      } else {
+        ok = __shfl_xor(key, stride);
+        oe = __shfl_xor(ext, stride);
+        os = __shfl_xor(slot, stride);
+      }
+      const bool take_min = ((t & stride) == 0) == ((t & size) == 0);
+      const bool other_first = ok < key || (ok == key && oe < ext);
+      const bool same = ok == key && oe == ext;   // padding records
+      if (!same && other_first == take_min) {
+        key = ok;
+        ext = oe;
+        slot = os;
+      }
+    }
+  }
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------------------
 // Binning, shared by every row source (header-only templates; each kernel source
 // instantiates its own copies): prep_count, prep_scan, prep_place.

@@ -520,8 +520,13 @@ struct WalkMax {
   int count;
 };
 hipError_t launch_select_wg_one(const GraphSel& one, const WalkMax& walk, const Publish& pub, hipStream_t s);
+// launch_select_iteration's result for an active list that begins with k likely top
+// nodes (sel_filter), with the maxima of the walk step just run.  m: no fewer than
+// the list's nodes.
+hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, int max_grid, hipStream_t s);
 // Workgroup maxima at or below which the one-workgroup selection reduces them.
 constexpr long long kFusedMaxSlots = 8192;
+constexpr int kMidNodes32 = 8 * kFinishThreads, kMidNodes64 = 16 * kFinishThreads;   // kMidActive of select_mid
 constexpr int kSmallActive = 1 << 16;   // |M| at or below which one workgroup selects
 
 // ---- batched form (katz_batch.hip) --------------------------------------------

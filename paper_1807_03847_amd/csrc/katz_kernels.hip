@@ -6,9 +6,10 @@
 //                                 row, fused with the update of c_r (and of the
 //                                 FP32 margin accumulator); in a renumbered run,
 //                                 step 2 also renames the column ids,
-//   sel_hist / sel_scan / sel_compact (levels 0, 1), sel_finish
-//                                 radix select of the k-th largest lower bound
-//                                 over the active set M,
+//   sel_filter, or sel_hist / sel_scan / sel_compact (levels 0, 1); sel_finish
+//                                 the k-th largest lower bound over the active
+//                                 set M: candidates at or above a floor, or by
+//                                 a radix select,
 //   sel_apply                     deactivation u - eps < l(M[k]) and compaction
 //                                 of M (converged() of Algorithm 1),
 //   sel_check                     LDS sort of the top-k and the adjacent-pair
@@ -838,27 +839,167 @@ __global__ void __launch_bounds__(kWG) sel_compact(SelArgs a, int level) {
   }
 }
 
+// Bounds of the kIPT nodes of a thread in group g0 of the active list (places past
+// m evaluate node 0, a valid index, and are dropped).
+template <bool F32>
+__device__ __forceinline__ void eval_group(const SelArgs& a, long long g0, int m, int (&v)[kIPT], double (&lo)[kIPT],
+                                           double (&up)[kIPT]) {
+#pragma unroll
+  for (int j = 0; j < kIPT; ++j) {
+    const long long i = g0 + (long long)j * kWG + threadIdx.x;
+    v[j] = i < m ? (a.identity_in ? (int)i : a.act_in[i]) : 0;
+  }
+  // All loads first: a branch among them (directed or not) would hold the others back.
+  using T = typename Prec<F32>::T;
+  double cv[kIPT];
+  T xv[kIPT];
+  float ev[kIPT];
+#pragma unroll
+  for (int j = 0; j < kIPT; ++j) {
+    cv[j] = a.b.c[v[j]];
+    xv[j] = reinterpret_cast<const T*>(a.b.x)[v[j]];
+    ev[j] = F32 ? a.b.e[v[j]] : 0.0f;
+  }
+#pragma unroll
+  for (int j = 0; j < kIPT; ++j) bounds_of<F32>(a.b, cv[j], xv[j], ev[j], lo[j], up[j]);
+}
+
+// The candidates of the k-th lower bound, when the active list begins with k nodes
+// that are likely to be the top-k: the last pass's, or in the first pass the longest
+// rows.  The last of those k in ranking order (lower bound descending, caller id
+// ascending) is at or below the k-th node of M, so the candidates are the nodes that
+// are not behind it: k of them when the order has not changed, also where all nodes
+// tie.  One launch in place of the walk maxima, two levels of histograms, scans and
+// compactions (seven, 4.5 us each where they do little): R-MAT with 150 K nodes 57 -> 27 us,
+// R-MAT 22 95 -> 62 a pass.  Bound by the reads of c, x and e on large sets.
+template <bool F32>
+__global__ void __launch_bounds__(kWG) sel_filter(SelArgs a, WalkMax walk) {
+  RunScalars* sc = a.sc;
+  if (stopped(sc)) return;
+  if (sc->col_err) {   // walk step 2 of a renumbered run found a bad column id
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->err = 1;
+    return;
+  }
+  __shared__ double s_max[kWG / kWave];
+  __shared__ unsigned long long s_key[kWG / kWave];
+  __shared__ int s_ext[kWG / kWave];
+  const int t = threadIdx.x, w = t / kWave;
+  // The step's largest walk entry.
+  double wm = 0.0;
+  for (long long i = (long long)blockIdx.x * kWG + t; i < walk.count; i += (long long)gridDim.x * kWG)
+    wm = fmax(wm, F32 ? (double)reinterpret_cast<const float*>(walk.blkmax)[i]
+                            : reinterpret_cast<const double*>(walk.blkmax)[i]);
+  // The floor: every workgroup evaluates the k nodes itself.
+  unsigned long long fk = ~0ull;
+  int fe = 0;
+  for (int i = t; i < a.k; i += kWG) {
+    const int v = a.identity_in ? i : a.act_in[i];
+    double lo, up;
+    bound_eval_as<F32>(a.b, v, lo, up);
+    const unsigned long long key = key_of(lo);
+    const int e = ext_id(a, v);
+    if (key < fk || (key == fk && e > fe)) {
+      fk = key;
+      fe = e;
+    }
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    wm = fmax(wm, __shfl_xor(wm, o));
+    const unsigned long long ok = __shfl_xor(fk, o);
+    const int oe = __shfl_xor(fe, o);
+    if (ok < fk || (ok == fk && oe > fe)) {
+      fk = ok;
+      fe = oe;
+    }
+  }
+  if (lane_id() == 0) {
+    s_max[w] = wm;
+    s_key[w] = fk;
+    s_ext[w] = fe;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kWG / kWave; ++q) {
+    wm = fmax(wm, s_max[q]);
+    if (s_key[q] < fk || (s_key[q] == fk && s_ext[q] > fe)) {
+      fk = s_key[q];
+      fe = s_ext[q];
+    }
+  }
+  // Non-negative values: the IEEE bit patterns order like the values.
+  if (t == 0 && wm > 0.0) {
+    if constexpr (F32) atomicMax(const_cast<unsigned*>(&a.xmax32[a.b.r]), __float_as_uint((float)wm));
+    else atomicMax(const_cast<unsigned long long*>(&a.xmax64[a.b.r]), (unsigned long long)__double_as_longlong(wm));
+  }
+  const int m = sc->m;
+  for (long long g0 = (long long)blockIdx.x * kGroup; g0 < m; g0 += (long long)gridDim.x * kGroup) {
+    int v[kIPT];
+    double lo[kIPT], up[kIPT];
+    eval_group<F32>(a, g0, m, v, lo, up);
+    unsigned mask = 0;
+#pragma unroll
+    for (int j = 0; j < kIPT; ++j) {
+      const unsigned long long key = key_of(lo[j]);
+      const bool in = g0 + (long long)j * kWG + t < m;
+      if (in && (key > fk || (key == fk && ext_id(a, v[j]) <= fe))) mask |= 1u << j;
+    }
+    int pos = block_reserve(&sc->cand_count[0], mask);
+#pragma unroll
+    for (int j = 0; j < kIPT; ++j) {
+      if (mask >> j & 1u) {
+        a.cand_key[0][pos] = key_of(lo[j]);
+        a.cand_v[0][pos] = v[j];
+        ++pos;
+      }
+    }
+  }
+}
+
 constexpr int kFinishIlp = 4;   // candidates per thread and pass of sel_finish
 
+// The need-th of cnt <= kFinishThreads records, one per thread.
+__device__ __forceinline__ void finish_sorted(const SelArgs& a, int cnt, unsigned long long key, int ext, int slot,
+                                              int need, SmallArea& rec) {
+  sort_records(cnt, key, ext, slot, rec);
+  if ((int)threadIdx.x == need - 1) {
+    a.sc->theta_key = ~key;
+    a.sc->theta = __longlong_as_double((long long)~key);
+    a.sc->cut_ext = ext;
+  }
+}
+
 // Resolves the remaining digits of the k-th key and the id cut inside its ties.
-__global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a) {
+// filtered: the candidates are sel_filter's, with all digits to resolve.  At most one
+// candidate per thread: they are sorted instead (14 us of digits, 5 of sort).
+__global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a, bool filtered) {
   if (stopped(a.sc)) return;
-  __shared__ unsigned h[kDigits];
+  __shared__ union {
+    unsigned h[kDigits];
+    SmallArea rec;
+  } sm;
+  unsigned* const h = sm.h;
   __shared__ unsigned long long s_prefix, s_kmin, s_kmax;
-  __shared__ int s_need, s_count;
-  const bool from1 = a.sc->cand_count[0] > kSmallCand;
+  __shared__ int s_need, s_count, s_place;
+  const bool from1 = !filtered && a.sc->cand_count[0] > kSmallCand;
   const unsigned long long* ck = a.cand_key[from1 ? 1 : 0];
   const int32_t* cv = a.cand_v[from1 ? 1 : 0];
   const int cnt = a.sc->cand_count[from1 ? 1 : 0];
+  if (cnt <= kFinishThreads) {
+    const int t = threadIdx.x;
+    unsigned long long key = t < cnt ? ~ck[t] : ~0ull;
+    const int ext = t < cnt ? ext_id(a, cv[t]) : INT_MAX, slot = 0;
+    finish_sorted(a, cnt, key, ext, slot, filtered ? a.k : a.sc->need, sm.rec);
+    return;
+  }
   if (threadIdx.x == 0) {
-    s_prefix = a.sc->prefix;
-    s_need = a.sc->need;
+    s_prefix = filtered ? 0ull : a.sc->prefix;
+    s_need = filtered ? a.k : a.sc->need;
     s_count = cnt;
     s_kmin = ~0ull;
     s_kmax = 0ull;
   }
   __syncthreads();
-  const int first = from1 ? 2 : 1;
+  const int first = filtered ? 0 : from1 ? 2 : 1;
   const bool track = cnt > kSmallCand;   // only a large candidate set repays the min/max
   for (int level = first; level < kSelectLevels; ++level) {
     const int shift = level < 5 ? 51 - kDigitBits * level : 0;
@@ -916,8 +1057,28 @@ __global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a) {
       s_prefix = (pre << width) | (unsigned)bk.b;
       s_need = bk.need;
       s_count = bk.count;
+      s_place = 0;
     }
     __syncthreads();
+    // One record per thread: the bucket's are sorted instead of taking further digits.
+    if (s_count <= kFinishThreads && shift > 0) {
+      for (int i0 = 0; i0 < cnt; i0 += kFinishThreads) {
+        const int i = i0 + (int)threadIdx.x;
+        const bool in = i < cnt && (ck[i] >> shift) == s_prefix;
+        const int pos = wave_append(&s_place, in);
+        if (in) {
+          sm.rec.key[pos] = ~ck[i];
+          sm.rec.ext[pos] = ext_id(a, cv[i]);
+        }
+      }
+      __syncthreads();
+      const int t = threadIdx.x, held = s_count;
+      unsigned long long key = t < held ? sm.rec.key[t] : ~0ull;
+      int ext = t < held ? sm.rec.ext[t] : INT_MAX, slot = 0;
+      __syncthreads();
+      finish_sorted(a, held, key, ext, slot, s_need, sm.rec);
+      return;
+    }
   }
   const unsigned long long theta_key = s_prefix;
   const int need = s_need;        // how many of the tied keys belong to the top-k
@@ -975,7 +1136,10 @@ __global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a) {
 }
 
 // converged(), first half: nodes past position k leave M when u - eps < l(M[k]).
-__global__ void __launch_bounds__(kWG) sel_apply(SelArgs a) {
+// block_prog: a zeroed word per workgroup for sel_check (an atomic on one word takes
+// 2048 workgroups 20 us, as long as their reads), or null.
+template <bool F32>
+__global__ void __launch_bounds__(kWG) sel_apply(SelArgs a, unsigned* block_prog) {
   if (stopped(a.sc)) return;
   __shared__ int s_prog;
   if (threadIdx.x == 0) s_prog = 0;
@@ -987,25 +1151,18 @@ __global__ void __launch_bounds__(kWG) sel_apply(SelArgs a) {
   bool prog = false;
   for (long long g0 = (long long)blockIdx.x * kGroup; g0 < m; g0 += (long long)gridDim.x * kGroup) {
     int v[kIPT];
+    double lo[kIPT], up[kIPT];
+    eval_group<F32>(a, g0, m, v, lo, up);
     unsigned mt = 0, mk = 0;
 #pragma unroll
     for (int j = 0; j < kIPT; ++j) {
-      const long long i = g0 + (long long)j * kWG + threadIdx.x;
-      v[j] = 0;
-      if (i < m) {
-        v[j] = a.identity_in ? (int)i : a.act_in[i];
-        const unsigned long long key = a.keys[i];
-        const bool top = key > tk || (key == tk && ext_id(a, v[j]) <= cut);
-        bool keep = false;
-        if (!top) {
-          double lo, up;
-          bound_eval(a.b, v[j], lo, up);
-          keep = !(up - eps < theta);
-        }
-        if (top) mt |= 1u << j;
-        if (keep) mk |= 1u << j;
-        if ((top || keep) && !prog && can_progress(a.b, v[j])) prog = true;
-      }
+      const bool in = g0 + (long long)j * kWG + threadIdx.x < m;
+      const unsigned long long key = key_of(lo[j]);
+      const bool top = in && (key > tk || (key == tk && ext_id(a, v[j]) <= cut));
+      const bool keep = in && !top && !(up[j] - eps < theta);
+      if (top) mt |= 1u << j;
+      if (keep) mk |= 1u << j;
+      if (F32 && (top || keep) && !prog && can_progress_as<F32>(a.b, v[j])) prog = true;
     }
     int pt = block_reserve(&a.sc->top_count, mt);
     int pk = block_reserve(&a.sc->kept_count, mk);
@@ -1021,15 +1178,32 @@ __global__ void __launch_bounds__(kWG) sel_apply(SelArgs a) {
       }
     }
   }
-  if (prog) s_prog = 1;
-  __syncthreads();
-  if (threadIdx.x == 0 && s_prog) atomicOr(&a.sc->progress, 1);
+  if constexpr (F32) {   // the FP64 form can always go on
+    if (prog) s_prog = 1;
+    __syncthreads();
+    if (threadIdx.x == 0 && s_prog) {
+      if (block_prog) block_prog[blockIdx.x] = 1u;
+      else atomicOr(&a.sc->progress, 1);
+    }
+  }
 }
 
 // converged(), second half: sort the top-k by (l desc, id asc) in LDS and test
 // every adjacent pair for eps-separation; decide whether the run stops.
-__global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
+// block_prog: sel_apply's words, cleared here.
+__global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned* block_prog, int grid) {
   if (stopped(a.sc)) return;
+  __shared__ int s_prog;
+  if (threadIdx.x == 0) s_prog = 0;
+  __syncthreads();
+  if (a.b.fp32) {
+    for (int i = threadIdx.x; i < grid; i += kFinishThreads) {
+      if (block_prog[i]) s_prog = 1;
+      block_prog[i] = 0u;
+    }
+    __syncthreads();
+  }
+  const bool progress = s_prog != 0;
   if (a.sc->top_count != a.k) {
     // The selection must produce exactly k top nodes; anything else is an
     // internal inconsistency and stops the run before ids are dereferenced.
@@ -1047,7 +1221,7 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
   // the top-k survived) and as the output when the run stops here for another
   // reason; otherwise the iteration goes on and the sort is skipped.
   const bool walk_zero = a.b.fp32 ? (a.xmax32[a.b.r] == 0u) : (a.xmax64[a.b.r] == 0ull);
-  const bool need_sort = a.sc->kept_count == 0 || walk_zero || (a.b.fp32 && !a.sc->progress) ||
+  const bool need_sort = a.sc->kept_count == 0 || walk_zero || (a.b.fp32 && !progress) ||
                          a.b.r >= a.max_iter;
   int P = 1;
   while (P < k) P <<= 1;
@@ -1104,7 +1278,7 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
     int status = -1;
     if (certified) status = KATZ_OK;
     else if (walk_zero) status = KATZ_W_EXACT_TIES;
-    else if (a.b.fp32 && !sc->progress) status = KATZ_W_PRECISION_LIMIT;
+    else if (a.b.fp32 && !progress) status = KATZ_W_PRECISION_LIMIT;
     else if (a.b.r >= a.max_iter) status = KATZ_W_ITER_LIMIT;
     sc->iterations = a.b.r;
     sc->cur = a.act_out_idx;
@@ -1113,7 +1287,6 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a) {
     sc->kept_count = 0;
     sc->cand_count[0] = 0;
     sc->cand_count[1] = 0;
-    sc->progress = 0;
     if (status >= 0) {
       sc->status = status;
       sc->done = 1;
@@ -1430,6 +1603,17 @@ hipError_t launch_walk_step(const IterArgs& a, int fp32, long long total_blocks,
   return hipGetLastError();
 }
 
+namespace {
+void launch_finish_apply(const SelArgs& a, int grid, bool filtered, bool check, hipStream_t s) {
+  hipLaunchKernelGGL(sel_finish, dim3(1), dim3(kFinishThreads), 0, s, a, filtered);
+  // The second level of histograms is free by then (grid <= 2048).
+  unsigned* const block_prog = a.hist + kDigits;
+  if (a.b.fp32) hipLaunchKernelGGL(sel_apply<true>, dim3(grid), dim3(kWG), 0, s, a, check ? block_prog : nullptr);
+  else hipLaunchKernelGGL(sel_apply<false>, dim3(grid), dim3(kWG), 0, s, a, nullptr);
+  if (check) hipLaunchKernelGGL(sel_check, dim3(1), dim3(kFinishThreads), 0, s, a, block_prog, grid);
+}
+}  // namespace
+
 hipError_t launch_select_iteration(const SelArgs& a, int grid, hipStream_t s, bool check) {
   hipLaunchKernelGGL(sel_hist0, dim3(grid), dim3(kWG), 0, s, a);
   hipLaunchKernelGGL(sel_scan, dim3(1), dim3(kFinishThreads), 0, s, a, 0);
@@ -1437,9 +1621,17 @@ hipError_t launch_select_iteration(const SelArgs& a, int grid, hipStream_t s, bo
   hipLaunchKernelGGL(sel_hist1, dim3(grid), dim3(kWG), 0, s, a);
   hipLaunchKernelGGL(sel_scan, dim3(1), dim3(kFinishThreads), 0, s, a, 1);
   hipLaunchKernelGGL(sel_compact, dim3(grid), dim3(kWG), 0, s, a, 1);
-  hipLaunchKernelGGL(sel_finish, dim3(1), dim3(kFinishThreads), 0, s, a);
-  hipLaunchKernelGGL(sel_apply, dim3(grid), dim3(kWG), 0, s, a);
-  if (check) hipLaunchKernelGGL(sel_check, dim3(1), dim3(kFinishThreads), 0, s, a);
+  launch_finish_apply(a, grid, false, check, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, int max_grid, hipStream_t s) {
+  // Every workgroup of the filter evaluates the k nodes of the floor: no more
+  // workgroups than groups of nodes (20 K nodes, k = 1000, 2048 workgroups: 16 us).
+  const int grid = (int)std::min<long long>(max_grid, std::max((m + kGroup - 1) / kGroup, (walk.count + 4095ll) / 4096));
+  if (a.b.fp32) hipLaunchKernelGGL(sel_filter<true>, dim3(grid), dim3(kWG), 0, s, a, walk);
+  else hipLaunchKernelGGL(sel_filter<false>, dim3(grid), dim3(kWG), 0, s, a, walk);
+  launch_finish_apply(a, grid, true, true, s);
   return hipGetLastError();
 }
 

@@ -500,3 +500,38 @@ def test_renumbering_map_is_invisible(n):
         with pytest.raises(katz.KatzError) as e:
             katz.rank_static(rp_t, col_bad, 100, eps=1e-6, flags=katz.FLAG_REORDER)
         assert e.value.code == katz.E_CSR
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape", ["rmat", "ties", "hubs"])
+def test_filtered_selection(shape, precision):
+    """Active sets past one workgroup's registers are filtered by the last top-k
+    (renumbered graphs: from the longest rows on).  ties: every bound of a
+    regular graph is the same, so ids decide; hubs: the longest rows lead in the
+    first pass and a clique of shorter ones in the next, so the floor lets the
+    whole clique through.  k around the sort's width, against the oracle, and
+    bitwise the run in caller order, which starts without a floor."""
+    katz = K()
+    rng = np.random.default_rng(5)
+    if shape == "rmat":
+        rp, col = sg.rmat(15, 8)
+    elif shape == "ties":
+        n = 40000
+        i = np.arange(n)
+        rp, col = sg.from_edges(n, np.concatenate([i, i, i]), np.concatenate([(i + d) % n for d in (1, 7, 100)]))
+    else:
+        n, m = 40000, 1500                      # m nodes with random arcs among them, 60 stars on the leaves
+        src = np.concatenate([rng.integers(0, m, 100 * m), np.repeat(m + np.arange(60), 400)])
+        dst = np.concatenate([rng.integers(0, m, 100 * m), 2000 + np.arange(60 * 400)])
+        rp, col = sg.from_edges(n, src, dst)
+    for k in (1, 50, 1000, 1023, 1024, 1025):
+        say("filtered selection", shape, precision, k)
+        for max_iter in (2, 3, 8):
+            orc, a = run_both(rp, col, k, 1e-9, precision=precision, max_iter=max_iter)
+            b = katz.rank_static(*dev(rp, col), k, eps=1e-9, precision=precision, max_iter=max_iter,
+                                 flags=katz.FLAG_NO_REORDER)
+            assert torch.equal(a.topk, b.topk) and torch.equal(a.lower, b.lower) and torch.equal(a.upper, b.upper)
+            assert (a.iterations, a.status, a.active_final) == (b.iterations, b.status, b.active_final)
+            if precision == "fp64":
+                assert a.iterations == orc.iterations
+                check(orc, a)
