@@ -216,6 +216,7 @@ struct IterArgs {
   const int32_t* ext_of;         // internal -> caller id (renumbering step)
   unsigned long long* hot_map;   // renumbering step: 2^kHotSlotBits words for its map, or null (no map)
   int id_bits;                   // bits of a caller id, at least kHotSlotBits (with a map)
+  int stream;                    // read the column array non-temporally
   int count_first;               // walk_first: number of descriptors to process
   int write_empty;
   int clog2_dmax;

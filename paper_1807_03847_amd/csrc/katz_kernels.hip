@@ -283,6 +283,9 @@ struct Stretch {
 // out, and the neighbour's x_1 is formed from its length exactly as the first
 // walk step stored it.  The values added, and their order, are those of the
 // unfused step on the renamed columns, so the sum is bitwise the same.
+// kStreamStep: a column array that outgrows the memory-side cache is read
+// non-temporally where the lanes of a row read whole lines (64 lanes and more; with
+// fewer, a line's later reads would miss it), which leaves the caches to the entries.
 constexpr int kBatch = 8;
 
 // kRenumberMapped: the renumbering step reads the most-referenced nodes' entries from
@@ -296,7 +299,7 @@ constexpr int kBatch = 8;
 // none 1507 us and 17.6 ms, 2^16 1267 and 14.2, 2^17 (1 MiB) 1212 and 13.4, 2^18 1199
 // and 13.5, 2^19 1259 and 15.2, 2^20 1458 and 17.3.  With a level of 2^14 slots in
 // LDS before it 1174 and 13.5; non-temporal loads and stores undo the gain.
-constexpr int kPlainStep = 0, kRenumberStep = 1, kRenumberMapped = 2;
+constexpr int kPlainStep = 0, kRenumberStep = 1, kRenumberMapped = 2, kStreamStep = 3;
 constexpr int kHotTagBits = 31 - kHotSlotBits;
 constexpr int kHotNodes = (1 << (32 - kHotTagBits)) - 1;   // an empty slot reads as the id after the last
 
@@ -330,7 +333,9 @@ __global__ void __launch_bounds__(kWG) hot_map_fill(IterArgs a, unsigned long lo
   atomicMin(&map[at.slot], (unsigned long long)((unsigned)v << kHotTagBits | at.tag) << 32 | (unsigned)a.desc[v].len);
 }
 
-template <bool F32, int G, int Renumber>
+template <int Mode> constexpr bool kRenumbers = Mode == kRenumberStep || Mode == kRenumberMapped;
+
+template <bool F32, int G, int Mode>
 __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                              const Stretch& st, int lane, const Epi<F32>& ep1) {
   using T = typename Prec<F32>::T;
@@ -339,7 +344,7 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
   const int len = st.len;
   // Loads in flight per lane; the elements a lane adds, and their order, do
   // not depend on it (the FP64 renumbering step uses four to avoid spills).
-  constexpr int NB = (Renumber && !F32) ? 4 : kBatch;
+  constexpr int NB = (kRenumbers<Mode> && !F32) ? 4 : kBatch;
   T sum = 0;
   bool bad = false;
   for (int j0 = lane; j0 < len; j0 += NB * G) {
@@ -347,8 +352,9 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int j = j0 + u * G;
-      int32_t cc = j < len ? st.src[j] : -1;
-      if constexpr (Renumber) {
+      int32_t cc = -1;
+      if (j < len) cc = Mode == kStreamStep && G >= kWave ? __builtin_nontemporal_load(&st.src[j]) : st.src[j];
+      if constexpr (kRenumbers<Mode>) {
         if (j < len && (unsigned)cc >= (unsigned)a.n) {
           bad = true;
           cc = -1;
@@ -356,9 +362,9 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
       }
       c[u] = cc;
     }
-    if constexpr (Renumber) {
+    if constexpr (kRenumbers<Mode>) {
       IdLen m[NB];
-      if constexpr (Renumber == kRenumberMapped) {
+      if constexpr (Mode == kRenumberMapped) {
         unsigned long long slot[NB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) slot[u] = c[u] >= 0 ? a.hot_map[hot_place(c[u], a.id_bits).slot] : 0ull;
@@ -395,20 +401,20 @@ __device__ __forceinline__ typename Prec<F32>::T strided_sum(const IterArgs& a, 
       for (int u = 0; u < NB; ++u) sum += v[u];
     }
   }
-  if (Renumber && bad) atomicOr(&a.sc->col_err, 1);
+  if (kRenumbers<Mode> && bad) atomicOr(&a.sc->col_err, 1);
   return sum;
 }
 
 // The stretch of a whole row (desc.off indexes the walk's column array).
-template <int Renumber>
+template <int Mode>
 __device__ __forceinline__ Stretch row_stretch(const IterArgs& a, const RowDesc& d, bool valid) {
-  if constexpr (Renumber) return Stretch{a.col_src + (valid ? a.coff[d.row] : 0), a.ncol + d.off, d.len};
+  if constexpr (kRenumbers<Mode>) return Stretch{a.col_src + (valid ? a.coff[d.row] : 0), a.ncol + d.off, d.len};
   else return Stretch{a.col + d.off, nullptr, d.len};
 }
 
 // tid: the thread's index in its 256-thread group (the workgroup, or one of
 // the groups of walk_step_grouped).
-template <bool F32, int G, int Renumber>
+template <bool F32, int G, int Mode>
 __device__ __forceinline__ void rows_group(const IterArgs& a, const typename Prec<F32>::T* hub, const Epi<F32>& ep,
                                            const Epi<F32>& ep1, long long lb, int bin, double& vmax, bool stop,
                                            int tid) {
@@ -422,7 +428,7 @@ __device__ __forceinline__ void rows_group(const IterArgs& a, const typename Pre
   Prev pv{0.0, 0.0f};
   if (valid && lane == 0) pv = load_prev<F32>(a, d.row);
   if (stop) return;
-  T sum = strided_sum<F32, G, Renumber>(a, hub, row_stretch<Renumber>(a, d, valid), lane, ep1);
+  T sum = strided_sum<F32, G, Mode>(a, hub, row_stretch<Mode>(a, d, valid), lane, ep1);
 #pragma unroll
   for (int o = G / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, G);
   if (valid && lane == 0) finish_row<F32>(a, ep, d.row, sum, vmax, pv);
@@ -432,12 +438,12 @@ __device__ __forceinline__ void rows_group(const IterArgs& a, const typename Pre
 // butterflies, then the four wave sums as (w0 + w1) + (w2 + w3) through part
 // (the group's four LDS slots).  Contains workgroup barriers: every thread of
 // the workgroup must call it the same number of times.
-template <bool F32, int Renumber>
+template <bool F32, int Mode>
 __device__ __forceinline__ typename Prec<F32>::T group_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                            const Stretch& st, const Epi<F32>& ep1, int tid,
                                                            typename Prec<F32>::T* part) {
   using T = typename Prec<F32>::T;
-  T sum = strided_sum<F32, kWG, Renumber>(a, hub, st, tid, ep1);
+  T sum = strided_sum<F32, kWG, Mode>(a, hub, st, tid, ep1);
   for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
   if (lane_id() == 0) part[tid / kWave] = sum;
   __syncthreads();
@@ -446,11 +452,11 @@ __device__ __forceinline__ typename Prec<F32>::T group_sum(const IterArgs& a, co
   return tot;
 }
 
-template <bool F32, int Renumber>
+template <bool F32, int Mode>
 __device__ __forceinline__ typename Prec<F32>::T block_sum(const IterArgs& a, const typename Prec<F32>::T* hub,
                                                            const Stretch& st, const Epi<F32>& ep1) {
   __shared__ typename Prec<F32>::T part[kWG / kWave];
-  return group_sum<F32, Renumber>(a, hub, st, ep1, threadIdx.x, part);
+  return group_sum<F32, Mode>(a, hub, st, ep1, threadIdx.x, part);
 }
 
 // Per-workgroup maximum of the new walk entries, stored without atomics (a
@@ -503,7 +509,7 @@ __global__ void __launch_bounds__(kWG) check_col_range(const int32_t* col, long 
 // (a persistent grid, which is what makes the LDS copy of the first a.hub_n
 // walk entries worth its fill).  Renumber: step 2 of a renumbered static run,
 // which also writes the renamed column ids (see strided_sum).
-template <bool F32, int Renumber>
+template <bool F32, int Mode>
 __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
   using T = typename Prec<F32>::T;
   // The stop flag (a launch enqueued ahead of the host's flag read skips its
@@ -514,10 +520,10 @@ __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
   // A persistent grid visits many work items per workgroup: stop at once.
   if (stop && (long long)gridDim.x < total) return;
   const Epi<F32> ep = compute_epi<F32>(a);
-  const Epi<F32> ep1 = Renumber ? compute_epi_at<F32>(a, 1) : ep;
+  const Epi<F32> ep1 = kRenumbers<Mode> ? compute_epi_at<F32>(a, 1) : ep;
   extern __shared__ __align__(16) unsigned char walk_lds[];
   T* hub = reinterpret_cast<T*>(walk_lds);
-  if (!Renumber && a.hub_n > 0) {
+  if (!kRenumbers<Mode> && a.hub_n > 0) {
     const T* x = reinterpret_cast<const T*>(a.x_in);
     if (!stop)
       for (int i = threadIdx.x; i < a.hub_n; i += kWG) hub[i] = x[i];
@@ -540,13 +546,13 @@ __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
         // adds the partials of each row in segment order after this launch.
         const SegDesc sd = a.segs[lb];
         Stretch st{a.col + sd.off, nullptr, sd.len};
-        if constexpr (Renumber) {
+        if constexpr (kRenumbers<Mode>) {
           const HugeRow h = a.huge[sd.hrow];
           st.src = a.col_src + a.coff[h.row] + (long long)(sd.part - h.part0) * kSeg;
           st.dst = a.ncol + sd.off;
         }
         if (stop) break;
-        const T tot = block_sum<F32, Renumber>(a, hub, st, ep1);
+        const T tot = block_sum<F32, Mode>(a, hub, st, ep1);
         if (threadIdx.x == 0) {
           T* part = reinterpret_cast<T*>(a.partial);
           part[sd.part] = a.pass == 2 ? part[sd.part] + tot : tot;
@@ -557,18 +563,18 @@ __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
         const RowDesc d = a.desc[a.bin_base[BIN_B256] + lb];
         Prev pv{0.0, 0.0f, 0.0};
         if (threadIdx.x == 0) pv = load_prev<F32>(a, d.row);
-        const Stretch st = row_stretch<Renumber>(a, d, true);
+        const Stretch st = row_stretch<Mode>(a, d, true);
         if (stop) break;
-        const T tot = block_sum<F32, Renumber>(a, hub, st, ep1);
+        const T tot = block_sum<F32, Mode>(a, hub, st, ep1);
         if (threadIdx.x == 0) finish_row<F32>(a, ep, d.row, tot, vmax, pv);
         break;
       }
-      case BIN_W64: rows_group<F32, kBinLanes[BIN_W64], Renumber>(a, hub, ep, ep1, lb, BIN_W64, vmax, stop, threadIdx.x); break;
-      case BIN_W16: rows_group<F32, kBinLanes[BIN_W16], Renumber>(a, hub, ep, ep1, lb, BIN_W16, vmax, stop, threadIdx.x); break;
-      case BIN_G32: rows_group<F32, kBinLanes[BIN_G32], Renumber>(a, hub, ep, ep1, lb, BIN_G32, vmax, stop, threadIdx.x); break;
-      case BIN_G16: rows_group<F32, kBinLanes[BIN_G16], Renumber>(a, hub, ep, ep1, lb, BIN_G16, vmax, stop, threadIdx.x); break;
-      case BIN_G8: rows_group<F32, kBinLanes[BIN_G8], Renumber>(a, hub, ep, ep1, lb, BIN_G8, vmax, stop, threadIdx.x); break;
-      case BIN_G4: rows_group<F32, kBinLanes[BIN_G4], Renumber>(a, hub, ep, ep1, lb, BIN_G4, vmax, stop, threadIdx.x); break;
+      case BIN_W64: rows_group<F32, kBinLanes[BIN_W64], Mode>(a, hub, ep, ep1, lb, BIN_W64, vmax, stop, threadIdx.x); break;
+      case BIN_W16: rows_group<F32, kBinLanes[BIN_W16], Mode>(a, hub, ep, ep1, lb, BIN_W16, vmax, stop, threadIdx.x); break;
+      case BIN_G32: rows_group<F32, kBinLanes[BIN_G32], Mode>(a, hub, ep, ep1, lb, BIN_G32, vmax, stop, threadIdx.x); break;
+      case BIN_G16: rows_group<F32, kBinLanes[BIN_G16], Mode>(a, hub, ep, ep1, lb, BIN_G16, vmax, stop, threadIdx.x); break;
+      case BIN_G8: rows_group<F32, kBinLanes[BIN_G8], Mode>(a, hub, ep, ep1, lb, BIN_G8, vmax, stop, threadIdx.x); break;
+      case BIN_G4: rows_group<F32, kBinLanes[BIN_G4], Mode>(a, hub, ep, ep1, lb, BIN_G4, vmax, stop, threadIdx.x); break;
       case BIN_EMPTY: {
         // Only at r = 2: the buffer of x_2 was never written for empty rows.
         const long long i = lb * kWG + threadIdx.x;
@@ -593,7 +599,7 @@ __global__ void __launch_bounds__(kWG) walk_step(IterArgs a) {
 // 1025..4096 arcs) come first and go in rounds that every group takes part in,
 // an empty share when it has no item, since those sums meet at workgroup-wide
 // barriers; the row-group items after them have no barriers.
-template <bool F32>
+template <bool F32, int Mode>
 __global__ void __launch_bounds__(kWG * kWalkGroups) walk_step_grouped(IterArgs a) {
   using T = typename Prec<F32>::T;
   constexpr int S = kWalkGroups;
@@ -639,7 +645,7 @@ __global__ void __launch_bounds__(kWG * kWalkGroups) walk_step_grouped(IterArgs 
       st = Stretch{a.col + d.off, nullptr, d.len};
       if (tid == 0) pv = load_prev<F32>(a, d.row);
     }
-    const T tot = group_sum<F32, false>(a, hub, st, ep, tid, part[grp]);
+    const T tot = group_sum<F32, Mode>(a, hub, st, ep, tid, part[grp]);
     if (tid == 0) {
       if (b < n_seg) {
         T* pt = reinterpret_cast<T*>(a.partial);
@@ -654,12 +660,12 @@ __global__ void __launch_bounds__(kWG * kWalkGroups) walk_step_grouped(IterArgs 
     while (bin < NUM_BINS && b >= a.first_block[bin + 1]) ++bin;
     const long long lb = b - a.first_block[bin];
     switch (bin) {
-      case BIN_W64: rows_group<F32, kBinLanes[BIN_W64], false>(a, hub, ep, ep, lb, BIN_W64, vmax, false, tid); break;
-      case BIN_W16: rows_group<F32, kBinLanes[BIN_W16], false>(a, hub, ep, ep, lb, BIN_W16, vmax, false, tid); break;
-      case BIN_G32: rows_group<F32, kBinLanes[BIN_G32], false>(a, hub, ep, ep, lb, BIN_G32, vmax, false, tid); break;
-      case BIN_G16: rows_group<F32, kBinLanes[BIN_G16], false>(a, hub, ep, ep, lb, BIN_G16, vmax, false, tid); break;
-      case BIN_G8: rows_group<F32, kBinLanes[BIN_G8], false>(a, hub, ep, ep, lb, BIN_G8, vmax, false, tid); break;
-      case BIN_G4: rows_group<F32, kBinLanes[BIN_G4], false>(a, hub, ep, ep, lb, BIN_G4, vmax, false, tid); break;
+      case BIN_W64: rows_group<F32, kBinLanes[BIN_W64], Mode>(a, hub, ep, ep, lb, BIN_W64, vmax, false, tid); break;
+      case BIN_W16: rows_group<F32, kBinLanes[BIN_W16], Mode>(a, hub, ep, ep, lb, BIN_W16, vmax, false, tid); break;
+      case BIN_G32: rows_group<F32, kBinLanes[BIN_G32], Mode>(a, hub, ep, ep, lb, BIN_G32, vmax, false, tid); break;
+      case BIN_G16: rows_group<F32, kBinLanes[BIN_G16], Mode>(a, hub, ep, ep, lb, BIN_G16, vmax, false, tid); break;
+      case BIN_G8: rows_group<F32, kBinLanes[BIN_G8], Mode>(a, hub, ep, ep, lb, BIN_G8, vmax, false, tid); break;
+      case BIN_G4: rows_group<F32, kBinLanes[BIN_G4], Mode>(a, hub, ep, ep, lb, BIN_G4, vmax, false, tid); break;
       case BIN_EMPTY: {
         const long long i = lb * kWG + tid;
         if (a.pass != 1 && i < a.bin_count[BIN_EMPTY]) {
@@ -1534,28 +1540,22 @@ hipError_t launch_walk_kernel(const IterArgs& a, int fp32, long long total_block
   if (!renumber && groups == kWalkGroups) {
     // Workgroups of kWalkGroups groups; slots = virtual workgroups.
     g = (g + kWalkGroups - 1) / kWalkGroups;
-    const void* k = fp32 ? (const void*)walk_step_grouped<true> : (const void*)walk_step_grouped<false>;
+    using Kernel = void (*)(IterArgs);
+    const Kernel k = a.stream ? (fp32 ? walk_step_grouped<true, kStreamStep> : walk_step_grouped<false, kStreamStep>)
+                              : (fp32 ? walk_step_grouped<true, kPlainStep> : walk_step_grouped<false, kPlainStep>);
     if (max_grid > 0) g = std::min(g, max_grid);
-    g = std::max<long long>(1, std::min(g, resident_blocks(k, lds, kWG * kWalkGroups)));
-    if (fp32) hipLaunchKernelGGL(walk_step_grouped<true>, dim3((unsigned)g), dim3(kWG * kWalkGroups), lds, s, a);
-    else hipLaunchKernelGGL(walk_step_grouped<false>, dim3((unsigned)g), dim3(kWG * kWalkGroups), lds, s, a);
+    g = std::max<long long>(1, std::min(g, resident_blocks((const void*)k, lds, kWG * kWalkGroups)));
+    hipLaunchKernelGGL(k, dim3((unsigned)g), dim3(kWG * kWalkGroups), lds, s, a);
     *used_out = g * kWalkGroups;
   } else {
-    if (max_grid > 0) {
-      const void* k = renumber ? (fp32 ? (const void*)walk_step<true, true> : (const void*)walk_step<false, true>)
-                               : (fp32 ? (const void*)walk_step<true, false> : (const void*)walk_step<false, false>);
-      g = std::min(g, std::min(max_grid, resident_blocks(k, renumber ? 0 : lds, kWG)));
-    }
-    if (renumber && a.hot_map) {
-      if (fp32) hipLaunchKernelGGL((walk_step<true, kRenumberMapped>), dim3((unsigned)g), dim3(kWG), 0, s, a);
-      else hipLaunchKernelGGL((walk_step<false, kRenumberMapped>), dim3((unsigned)g), dim3(kWG), 0, s, a);
-    } else if (renumber) {
-      if (fp32) hipLaunchKernelGGL((walk_step<true, kRenumberStep>), dim3((unsigned)g), dim3(kWG), 0, s, a);
-      else hipLaunchKernelGGL((walk_step<false, kRenumberStep>), dim3((unsigned)g), dim3(kWG), 0, s, a);
-    } else {
-      if (fp32) hipLaunchKernelGGL((walk_step<true, kPlainStep>), dim3((unsigned)g), dim3(kWG), lds, s, a);
-      else hipLaunchKernelGGL((walk_step<false, kPlainStep>), dim3((unsigned)g), dim3(kWG), lds, s, a);
-    }
+    using Kernel = void (*)(IterArgs);
+    const Kernel k = renumber ? (a.hot_map ? (fp32 ? walk_step<true, kRenumberMapped> : walk_step<false, kRenumberMapped>)
+                                           : (fp32 ? walk_step<true, kRenumberStep> : walk_step<false, kRenumberStep>))
+                     : a.stream ? (fp32 ? walk_step<true, kStreamStep> : walk_step<false, kStreamStep>)
+                                : (fp32 ? walk_step<true, kPlainStep> : walk_step<false, kPlainStep>);
+    const size_t dyn = renumber ? 0 : lds;
+    if (max_grid > 0) g = std::min(g, std::min(max_grid, resident_blocks((const void*)k, dyn, kWG)));
+    hipLaunchKernelGGL(k, dim3((unsigned)g), dim3(kWG), dyn, s, a);
     *used_out = g;
   }
   return hipGetLastError();
