@@ -137,12 +137,14 @@ __device__ __forceinline__ void reduce_walk_max(const GraphSel& gs, const WalkMa
 }
 
 // converged() for up to 16384 nodes (FP32 form: 8192) with the top-k in one record per
-// thread: every thread keeps the keys of its nodes in registers, so the digits of the radix select read no memory, and once the
-// k-th key's bucket holds at most one record per thread its records are sorted
-// instead of taking further digits.  False, with nothing written, when a bucket
-// of more records than that carries one key (many ties): the general path
-// resolves those.  The general path reads and writes every key several times
-// from one workgroup: 16384 nodes take it 46 us, this 17 us.
+// thread: every thread keeps the keys of its nodes in registers.  The nodes not behind
+// the last of the list's first k are the candidates for the top-k; at most one per
+// thread, they are sorted.  More go through radix digits, which read no memory, until
+// the k-th key's bucket is that small.  False, with nothing written, when a bucket of
+// more records than that carries one key (many ties): the general path resolves those.
+// The general path reads and writes every key several times from one workgroup: 16384
+// nodes take it 46 us.  On 2000 nodes the digits took 25 us, four places a thread and
+// the floor 14.
 template <bool F32> constexpr int kMidPer = F32 ? 8 : 16;   // nodes per thread (FP32: more would spill)
 template <bool F32> constexpr int kMidActive = kMidPer<F32> * kFinishThreads;
 constexpr int kMidIlp = 8;   // nodes whose loads overlap
@@ -153,29 +155,29 @@ struct MidArea {
   unsigned h[kDigits];
 };
 
-template <bool F32>
+template <bool F32, int kPer>
 __device__ __forceinline__ bool select_mid(const GraphSel& gs, const Publish& pub, const BoundArgs& b, int cur,
                                            bool identity, int m, bool walk_zero, MidArea& sm) {
-  __shared__ unsigned long long s_kmin, s_kmax, s_theta;
+  __shared__ unsigned long long s_kmin, s_kmax, s_theta, s_fkey[kFinishWaves];
+  __shared__ int s_fext[kFinishWaves];
   __shared__ unsigned s_place;
-  __shared__ int s_cnt, s_fail, s_prog, s_cut;
+  __shared__ int s_cnt, s_cand, s_fail, s_prog, s_cut;
   const int32_t* act_in = cur ? gs.act[1] : gs.act[0];
   int32_t* act_out = const_cast<int32_t*>(cur ? gs.act[0] : gs.act[1]);
   const int32_t* const ext_of = gs.ext_of;
-  constexpr int kPer = kMidPer<F32>;
   const int k = gs.k;
   const int t = threadIdx.x;
   if (t == 0) {
     s_kmin = ~0ull;
     s_kmax = 0ull;
     s_cnt = 0;
+    s_cand = 0;
     s_place = 0;
     s_fail = 0;
     s_prog = 0;
   }
   __syncthreads();
   unsigned long long key[kPer];
-  unsigned long long kmin = ~0ull, kmax = 0ull;
   {
     int node[kPer];   // slots past m hold a valid node that is dropped
     if (identity) {
@@ -185,55 +187,109 @@ __device__ __forceinline__ bool select_mid(const GraphSel& gs, const Publish& pu
 #pragma unroll
       for (int u = 0; u < kPer; ++u) node[u] = act_in[u * kFinishThreads + t < m ? u * kFinishThreads + t : 0];
     }
+    const int ext0 = t < k && ext_of ? ext_of[node[0]] : node[0];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int i = u * kFinishThreads + t;
       double lo, up;
       bound_eval_as<F32>(b, node[u], lo, up);
       key[u] = key_of(lo);
-      if (i < m) {
+      if (u % kMidIlp == kMidIlp - 1) __builtin_amdgcn_sched_barrier(0);   // loads in flight, within the registers
+    }
+    // The last of the list's first k in ranking order (sel_filter's floor: they are
+    // the last top-k, or in the first pass of a renumbered run the longest rows).
+    unsigned long long fk = t < k ? key[0] : ~0ull;
+    int fe = t < k ? ext0 : 0;
+    for (int o = 32; o >= 1; o >>= 1) {
+      const unsigned long long ok = __shfl_xor(fk, o);
+      const int oe = __shfl_xor(fe, o);
+      if (ok < fk || (ok == fk && oe > fe)) {
+        fk = ok;
+        fe = oe;
+      }
+    }
+    if (lane_id() == 0) {
+      s_fkey[t / kWave] = fk;
+      s_fext[t / kWave] = fe;
+    }
+  }
+  __syncthreads();
+  // One bit per node that is not behind the floor.
+  unsigned mc = 0;
+  {
+    unsigned long long fk = s_fkey[lane_id() % kFinishWaves];
+    int fe = s_fext[lane_id() % kFinishWaves];
+    for (int o = kFinishWaves / 2; o >= 1; o >>= 1) {
+      const unsigned long long ok = __shfl_xor(fk, o);
+      const int oe = __shfl_xor(fe, o);
+      if (ok < fk || (ok == fk && oe > fe)) {
+        fk = ok;
+        fe = oe;
+      }
+    }
+    int held = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = u * kFinishThreads + t;
+      bool in = i < m && key[u] > fk;
+      if (i < m && key[u] == fk) {
+        const int v = identity ? gs.base + i : act_in[i];
+        in = (ext_of ? ext_of[v] : v) <= fe;
+      }
+      mc |= (unsigned)in << u;
+      held += __popcll(__ballot(in));
+    }
+    if (lane_id() == 0 && held) atomicAdd(&s_cand, held);
+  }
+  __syncthreads();
+  const bool floored = s_cand <= kFinishThreads;
+  unsigned long long pre = 0;
+  int rem = 0, need = k, cnt = s_cand;
+  if (!floored) {
+    // Too many: radix digits until the k-th key's bucket is small enough.
+    unsigned long long kmin = ~0ull, kmax = 0ull;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (u * kFinishThreads + t < m) {
         kmin = key[u] < kmin ? key[u] : kmin;
         kmax = key[u] > kmax ? key[u] : kmax;
       }
-      if (u % kMidIlp == kMidIlp - 1) __builtin_amdgcn_sched_barrier(0);   // loads in flight, within the registers
+    for (int o = 32; o >= 1; o >>= 1) {
+      const unsigned long long a = __shfl_xor(kmin, o), c = __shfl_xor(kmax, o);
+      kmin = a < kmin ? a : kmin;
+      kmax = c > kmax ? c : kmax;
+    }
+    if (lane_id() == 0) {
+      atomicMin(&s_kmin, kmin);
+      atomicMax(&s_kmax, kmax);
+    }
+    __syncthreads();
+    const unsigned long long kdiff = s_kmin ^ s_kmax;
+    rem = kdiff ? 64 - __clzll((long long)kdiff) : 0;   // low bits still to resolve
+    pre = s_kmin >> rem;                                // resolved high bits (keys are below 2^63: rem < 64)
+    cnt = m;
+    while (cnt > kFinishThreads) {
+      if (rem == 0) return false;
+      const int w = min(kDigitBits, rem);
+      const int shift = rem - w;
+      for (int d = t; d < kDigits; d += kFinishThreads) sm.h[d] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        wave_hist_add(sm.h, (unsigned)((key[u] >> shift) & ((1u << w) - 1u)),
+                      u * kFinishThreads + t < m && (key[u] >> rem) == pre);
+      __syncthreads();
+      const Bucket bk = find_bucket(sm.h, 1 << w, need, true);
+      pre = (pre << w) | (unsigned)bk.b;
+      need = bk.need;
+      cnt = bk.count;
+      rem = shift;
     }
   }
-  for (int o = 32; o >= 1; o >>= 1) {
-    const unsigned long long a = __shfl_xor(kmin, o), c = __shfl_xor(kmax, o);
-    kmin = a < kmin ? a : kmin;
-    kmax = c > kmax ? c : kmax;
-  }
-  if (lane_id() == 0) {
-    atomicMin(&s_kmin, kmin);
-    atomicMax(&s_kmax, kmax);
-  }
-  __syncthreads();
-  const unsigned long long kdiff = s_kmin ^ s_kmax;
-  int rem = kdiff ? 64 - __clzll((long long)kdiff) : 0;   // low bits still to resolve
-  unsigned long long pre = s_kmin >> rem;                 // resolved high bits (keys are below 2^63: rem < 64)
-  int need = k, cnt = m;
-  while (cnt > kFinishThreads) {
-    if (rem == 0) return false;
-    const int w = min(kDigitBits, rem);
-    const int shift = rem - w;
-    for (int d = t; d < kDigits; d += kFinishThreads) sm.h[d] = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      wave_hist_add(sm.h, (unsigned)((key[u] >> shift) & ((1u << w) - 1u)),
-                    u * kFinishThreads + t < m && (key[u] >> rem) == pre);
-    __syncthreads();
-    const Bucket bk = find_bucket(sm.h, 1 << w, need, true);
-    pre = (pre << w) | (unsigned)bk.b;
-    need = bk.need;
-    cnt = bk.count;
-    rem = shift;
-  }
-  // The bucket's records, sorted: the need-th is the last of the top-k.
+  // The candidates' or the bucket's records, sorted: the need-th is the last of the top-k.
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     const int i = u * kFinishThreads + t;
-    const bool in = i < m && (key[u] >> rem) == pre;
+    const bool in = floored ? (mc >> u & 1u) != 0 : i < m && (key[u] >> rem) == pre;
     if (__ballot(in)) {
       const int pos = wave_append(&s_cnt, in);
       if (in) {
@@ -420,8 +476,13 @@ __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const Wa
     select_small<F32>(gs, pub, b, cur, identity, m, walk_zero, sm.small);
     return;
   }
-  if (walk && m <= kMidActive<F32> && gs.k <= kFinishThreads && select_mid<F32>(gs, pub, b, cur, identity, m, walk_zero, sm.mid))
-    return;
+  if (walk && gs.k <= kFinishThreads) {
+    if (m <= 4 * kFinishThreads) {
+      if (select_mid<F32, 4>(gs, pub, b, cur, identity, m, walk_zero, sm.mid)) return;
+    } else if (m <= kMidActive<F32>) {
+      if (select_mid<F32, kMidPer<F32>>(gs, pub, b, cur, identity, m, walk_zero, sm.mid)) return;
+    }
+  }
   const int k = gs.k;
   // The graph's arrays and sizes as locals: read from gs once, not again after
   // every store (gs may sit in global memory, which the stores could alias).
