@@ -6,6 +6,8 @@
 // iteration behind.  Static calls take their workspace from a per-device pool
 // of grow-only arenas; a dynamic state (Algorithm 2) owns its memory: the graph
 // as a CSR with per-row slack, the walk history x_1..x_r, c_r and M.
+#include <sched.h>
+
 #include <algorithm>
 #include <map>
 #include <chrono>
@@ -1051,6 +1053,13 @@ struct PassFlags {
   bool stopped() const { return err || status >= 0; }
 };
 
+// Between two looks at a polled word: now and then the CPU goes to whatever else
+// wants it, so that threads that wait do not hold up threads that work.
+void poll_pause(long long spins) {
+  if ((spins & 0x3f) == 0) sched_yield();
+  else __builtin_ia32_pause();
+}
+
 // Waits until pass `seq` has published its flags, polling their word; when the
 // stream has drained without them (an error made the pass return early), reads
 // the device flags.
@@ -1077,7 +1086,7 @@ int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out
       *out = PassFlags{(int)(w >> 31 & 3), (int)(w >> 33 & 15) - 1, (int)(w & INT32_MAX)};
       return KATZ_OK;
     }
-    __builtin_ia32_pause();
+    poll_pause(spins);
   }
 }
 
@@ -1765,7 +1774,7 @@ int wait_result(const unsigned long long* word, const double* dev, double* host,
       std::memcpy(host, &w, sizeof(double));
       return KATZ_OK;
     }
-    __builtin_ia32_pause();
+    poll_pause(spins);
   }
 }
 
