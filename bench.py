@@ -48,6 +48,15 @@ def algorithmic_bytes_per_walk_step(n, nnz, precision, rp64):
     return 4 * nnz + per_node * n
 
 
+def grouped_walk(tuning, n):
+    """Whether an FP32 walk step of a renumbered graph runs the grouped kernel: it is
+    set, or nothing is and the walk vector is above 4 MiB."""
+    if tuning.get("walk_groups") == 4:
+        return True
+    unset = not any(tuning.get(f) for f in ("hub_bytes", "blocks_per_cu", "walk_groups", "split_hot_bytes"))
+    return unset and 4 * n > 4 << 20
+
+
 def counters_path(scale):
     return os.path.join(ROOT, "profiles", f"walk_step_rmat{scale}_counters.json")
 
@@ -192,7 +201,7 @@ def run_static(args, katz, sg, torch, np, wl):
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "walk_step_grouped<fp32>" if tunings["fp32"].get("walk_groups") == 4 else "walk_step<fp32>",
+            "kernel": "walk_step_grouped<fp32>" if grouped_walk(tunings["fp32"], n) else "walk_step<fp32>",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
