@@ -272,7 +272,8 @@ int katz_bounds(const katz_csr* g, const katz_params* p, int32_t r,
  * device array of 64 MiB that every device using the library holds until the
  * process ends, and its flag read-backs go to static host memory (so the host
  * waits for them: after each iteration, or on graphs up to 2^24 nodes and arcs
- * after every fourth, instead of reading the stop flag one iteration behind).  The first call on a device looks up that device's copy of the
+ * after every eighth, instead of reading the stop flag one iteration behind).
+ * The first call on a device looks up that device's copy of the
  * array (hipGetSymbolAddress).  The phase timers (katz_timing_*) are not
  * recorded.
  *

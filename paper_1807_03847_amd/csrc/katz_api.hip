@@ -1096,9 +1096,11 @@ int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out
 // graphs the copy is below 2% of a pass, and the host sleeps through it.
 constexpr long long kPolledSize = 1ll << 24;
 // Without pinned memory (the allocation-free call) each read-back stalls the
-// stream for about 30 us, while a pass enqueued past the stop returns at once
-// (two launches, 8 us): small graphs read the flags every fourth pass.
-constexpr int kCopiedPasses = 4;
+// stream for 30 to 45 us, while a pass enqueued past the stop returns at once (two
+// launches, 8 us): small graphs read the flags every eighth pass.  A call on 2000
+// nodes (18 passes) 516 us at every fourth, 494 sixth, 452 eighth, 505 twelfth; on
+// 300 to 60000 nodes the eighth takes 2 to 13% off the fourth.
+constexpr int kCopiedPasses = 8;
 
 // Iterates until the device stop flag: walk step r_next, selection,
 // converged(); then r_next + 1, ...  With check_first, the first pass is only a
