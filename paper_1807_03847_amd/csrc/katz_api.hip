@@ -929,13 +929,14 @@ int refresh_bins(katz_state* st, hipStream_t s);
 // one workgroup.  The latter two reduce the walk step's maxima themselves.
 enum Select { SEL_WIDE, SEL_FILTER, SEL_ONE };
 
-// The choice by the active nodes known to be at most m.  One workgroup: sets that its
-// registers hold (17 us for 16384 nodes of the FP64 form, 8192 of the FP32 form), and
-// up to kSmallActive where there is no floor (46 us and more).  Filtered sets take
-// 27 us and more.
+// The choice by the active nodes known to be at most m.  One workgroup: up to
+// kFilterFrom nodes (select_mid, 14 to 20 us), and up to kSmallActive where there is no
+// floor (46 us and more).  Filtered passes, four launches, take 24 us and more: calls
+// on 6000 to 10000 nodes take the same either way, on 16384 (FP64, select_mid 29 us)
+// 640 us by one workgroup and 612 filtered; from 4096 nodes on, FP32 calls lose 4%.
 Select select_form(const Run& run, long long m) {
   if (!run.one_workgroup_select()) return SEL_WIDE;
-  if (m <= (run.fp32 ? kMidNodes32 : kMidNodes64)) return SEL_ONE;
+  if (m <= kFilterFrom) return SEL_ONE;
   if (run.top_first && run.k <= kFinishThreads) return SEL_FILTER;
   return m <= kSmallActive ? SEL_ONE : SEL_WIDE;
 }

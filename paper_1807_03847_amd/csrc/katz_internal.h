@@ -527,7 +527,7 @@ hipError_t launch_select_wg_one(const GraphSel& one, const WalkMax& walk, const 
 hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, int max_grid, hipStream_t s);
 // Workgroup maxima at or below which the one-workgroup selection reduces them.
 constexpr long long kFusedMaxSlots = 8192;
-constexpr int kMidNodes32 = 8 * kFinishThreads, kMidNodes64 = 16 * kFinishThreads;   // kMidActive of select_mid
+constexpr int kFilterFrom = 8 * kFinishThreads;   // above: filtered selections (katz_api.hip, select_form)
 constexpr int kSmallActive = 1 << 16;   // |M| at or below which one workgroup selects
 
 // ---- batched form (katz_batch.hip) --------------------------------------------
