@@ -532,6 +532,8 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
 // Graph of each work item: the graph of all its rows, or -1 when its rows
 // belong to several graphs (rows of a bin are in global-id order, so the
 // first and last row decide).  Segments and single-row items have one graph.
+// Also empties every item's slot: batch_reduce_max reads all of them, and the items
+// of a graph that stops in iteration 1, which has no walk, never write theirs.
 __global__ void __launch_bounds__(kWG) batch_item_graphs(BatchWalk a, long long total, int* item_g) {
   const long long b = (long long)blockIdx.x * kWG + threadIdx.x;
   if (b >= total) return;
@@ -550,6 +552,7 @@ __global__ void __launch_bounds__(kWG) batch_item_graphs(BatchWalk a, long long 
     g = g0 == g1 ? g0 : -1;
   }
   item_g[b] = g;
+  a.blk_g[b] = -1;
 }
 
 // This iteration's work items: those whose graph is still iterating, and every

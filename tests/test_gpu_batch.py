@@ -299,3 +299,28 @@ def test_batch_first_list_edges(precision):
         assert (single.iterations, single.status, single.active_final) == (rb.iterations, rb.status, rb.active_final)
         if precision == "fp64":
             assert torch.equal(single.lower, rb.lower) and torch.equal(single.upper, rb.upper)
+
+
+def assert_bitwise_single(graphs, params, res, precision):
+    katz = K()
+    for (rp, col), pp, rb in zip(graphs, params, res):
+        single = katz.rank_static(torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), pp["k"],
+                                  precision=precision, **{f: v for f, v in pp.items() if f != "k"})
+        assert torch.equal(single.topk, rb.topk)
+        assert torch.equal(single.lower, rb.lower) and torch.equal(single.upper, rb.upper)
+        assert (single.iterations, single.status, single.eta) == (rb.iterations, rb.status, rb.eta)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_graphs_that_stop_in_the_first_iteration(precision):
+    """Graphs that stop in iteration 1, which has no walk launch, leave no work item
+    that ever ran; the others go on in a workspace that a batch of another layout
+    has filled before: the largest walk entries of those, and so their FP32 scales
+    and bounds, are the single call's."""
+    fill_g, fill_p = batch_workload(20, 23, 10, 12)
+    graphs, params = batch_workload(10, 29, 9, 11)
+    for i in range(0, 10, 2):
+        params[i]["max_iter"] = 1
+    say("batch stopping at once", precision)
+    run_batch(fill_g, fill_p, precision)
+    assert_bitwise_single(graphs, params, run_batch(graphs, params, precision), precision)
