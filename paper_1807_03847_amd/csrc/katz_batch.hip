@@ -260,10 +260,19 @@ __device__ __forceinline__ void graph_max_atomic(const BatchWalk& a, int r, int 
 // the slots into the per-graph maxima (no same-address atomics in the walk);
 // rows of several graphs in one workgroup (only where a bin crosses a graph
 // boundary) update the per-graph maxima with atomics.  All threads call it.
+//
+// round: how many items the workgroup has taken before this one.  The waves' entries
+// lie in one of two sets by its parity: thread 0 reads a round's set after that
+// round's barrier, and the set is written again two rounds later, past the barrier
+// between, which thread 0 reaches only once it has read.  With one set, a wave done
+// with its next item (short rows have no barrier of their own) would overwrite it.
 template <bool F32>
-__device__ __forceinline__ void batch_store_max(const BatchWalk& a, int r, int g, double vmax, long long slot) {
-  __shared__ int s_g[kWG / kWave];
-  __shared__ double s_m[kWG / kWave];
+__device__ __forceinline__ void batch_store_max(const BatchWalk& a, int r, int g, double vmax, long long slot,
+                                                int round = 0) {
+  __shared__ int s_graph[2][kWG / kWave];
+  __shared__ double s_max[2][kWG / kWave];
+  int* const s_g = s_graph[round & 1];
+  double* const s_m = s_max[round & 1];
   const unsigned long long present = __ballot(g >= 0);
   const int src = present ? __ffsll((long long)present) - 1 : 0;
   const int g0 = __shfl(g, src);
@@ -463,7 +472,8 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
   const int* list = a.items + (long long)x * a.item_cap;
   const long long step = gridDim.x / a.xcd_groups;
   const T* xin = reinterpret_cast<const T*>(a.xbuf[(r + 1) & 1]);
-  for (long long t = blockIdx.x / a.xcd_groups; t < n_items; t += step) {
+  int round = 0;
+  for (long long t = blockIdx.x / a.xcd_groups; t < n_items; t += step, ++round) {
     const long long b = list[t];
     const int gi = a.item_g[b];
     double vmax = 0.0;
@@ -525,7 +535,7 @@ __global__ void __launch_bounds__(kWG) walk_batch(BatchWalk a) {
       }
       default: break;
     }
-    batch_store_max<F32>(a, r, g_mine, vmax, b);
+    batch_store_max<F32>(a, r, g_mine, vmax, b, round);
   }
 }
 

@@ -324,3 +324,23 @@ def test_batch_graphs_that_stop_in_the_first_iteration(precision):
     say("batch stopping at once", precision)
     run_batch(fill_g, fill_p, precision)
     assert_bitwise_single(graphs, params, run_batch(graphs, params, precision), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_more_items_than_workgroups(precision):
+    """A batch of several times as many work items (16 rows of 33 to 128 arcs each)
+    as the device holds workgroups, so that every workgroup takes several in a row:
+    items of one workgroup belong to different graphs, and graphs meet inside items.
+    Every graph's largest walk entry, and so its FP32 scales, iterations and bounds,
+    are the single call's."""
+    graphs, params = [], []
+    for i in range(160):
+        n = 900 + 37 * (i % 23)
+        rp, col = sg.barabasi_albert(n, 20 + i % 9, 700 + i)
+        graphs.append((rp, col))
+        params.append(dict(k=10 + i % 40, alpha=(0.3 + 0.004 * i) / (1 + sg.max_degree(rp)), eps=1e-7))
+    rows = sum(int(((np.diff(rp) > 32) & (np.diff(rp) <= 128)).sum()) for rp, _ in graphs)
+    slots = 8 * torch.cuda.get_device_properties(0).multi_processor_count   # 2048 threads a compute unit
+    say("batch of many items", precision, rows // 16, "items of 16 rows,", slots, "workgroups")
+    assert rows // 16 > 2 * slots
+    assert_bitwise_single(graphs, params, run_batch(graphs, params, precision), precision)
