@@ -2395,31 +2395,35 @@ int ensure_levels(katz_state* st, int r) {
   return KATZ_OK;
 }
 
-// Bins sized for the pool capacity (an upper bound of the arc count).
-int alloc_bins(katz_state* st, Bins& b) {
-  if (b.desc) {
-    dfree(st, b.desc);
-    dfree(st, b.segs);
-    dfree(st, b.huge);
-    dfree(st, b.tab.blk);
-    dfree(st, b.tab.totals);
-  }
-  bins_caps(b, st->n, st->pool_cap);
-  b.desc = dalloc<RowDesc>(st, st->n);
+// New arrays for the segments of rows longer than one, arcs an upper bound of the
+// graph's.  Those that b holds are the caller's; on failure so is what b holds then.
+int alloc_segments(katz_state* st, Bins& b, long long arcs) {
+  bins_caps(b, st->n, arcs);
   b.segs = dalloc<SegDesc>(st, b.seg_cap);
   b.huge = dalloc<HugeRow>(st, b.huge_cap);
+  return b.segs && b.huge ? KATZ_OK : KATZ_E_OOM;
+}
+
+void free_segments(katz_state* st, const Bins& b) {
+  dfree(st, b.segs);
+  dfree(st, b.huge);
+}
+
+// Bins sized for the pool capacity (an upper bound of the arc count).
+int alloc_bins(katz_state* st, Bins& b) {
+  KATZ_TRY(alloc_segments(st, b, st->pool_cap));
+  b.desc = dalloc<RowDesc>(st, st->n);
   b.tab.blk = dalloc<long long>(st, (size_t)kPrepTableRows * b.tab.nblocks);
   b.tab.totals = dalloc<long long>(st, kPrepTableRows);
-  if (!b.desc || !b.segs || !b.huge || !b.tab.blk || !b.tab.totals) return KATZ_E_OOM;
+  if (!b.desc || !b.tab.blk || !b.tab.totals) return KATZ_E_OOM;
   return KATZ_OK;
 }
 
-int alloc_partial(katz_state* st) {
-  if (st->w.partial) dfree(st, st->w.partial);
-  if (st->w.blkmax) dfree(st, st->w.blkmax);
-  st->w.partial = dalloc<double>(st, st->bins.seg_cap);
-  st->w.blkmax = dalloc<double>(st, st->n + 2 * st->bins.seg_cap + 16);
-  return st->w.partial && st->w.blkmax ? KATZ_OK : KATZ_E_OOM;
+// The walk's partial sums and workgroup maxima, for bins of seg_cap segments.
+int alloc_partial(katz_state* st, long long seg_cap, void*& partial, void*& blkmax) {
+  partial = dalloc<double>(st, seg_cap);
+  blkmax = dalloc<double>(st, st->n + 2 * seg_cap + 16);
+  return partial && blkmax ? KATZ_OK : KATZ_E_OOM;
 }
 
 // Bins the rows `ids[0..count)` (or every row when ids is null) of the slack CSR.
@@ -2623,7 +2627,7 @@ int rename_slack(katz_state* st, SlackRef c, hipStream_t s) {
 int alloc_run_buffers(katz_state* st, hipStream_t s) {
   Work& w = st->w;
   const long long n = st->n;
-  KATZ_TRY(alloc_partial(st));
+  KATZ_TRY(alloc_partial(st, st->bins.seg_cap, w.partial, w.blkmax));
   w.c = dalloc<double>(st, n);
   w.act[0] = dalloc<int32_t>(st, n);
   w.act[1] = dalloc<int32_t>(st, n);
@@ -2896,21 +2900,50 @@ int grow_buf(katz_state* st, T*& p, size_t& cap, size_t count) {
 }
 
 
-// Moves the pool to a larger allocation.
+// Moves the pool to a larger allocation; with the forward graph's also what is sized by
+// it.  Everything is allocated before anything is replaced: a failure leaves the state
+// as it was.
 int grow_pool(katz_state* st, SlackRef c, long long need, hipStream_t s) {
   if (c.pool_used + need <= c.pool_cap) return KATZ_OK;
   const long long cap = std::max(c.pool_cap * 2, c.pool_used + need + 4096);
   int32_t* np = dalloc<int32_t>(st, cap);
-  if (!np) return KATZ_E_OOM;
-  KATZ_HIP(hipMemcpyAsync(np, c.pool, sizeof(int32_t) * c.pool_used, hipMemcpyDeviceToDevice, s));
-  KATZ_HIP(hipStreamSynchronize(s));
+  Bins bins = st->bins, lbins = st->lbins;
+  bins.segs = lbins.segs = nullptr;
+  bins.huge = lbins.huge = nullptr;
+  void *partial = nullptr, *blkmax = nullptr;
+  int rc = np ? KATZ_OK : KATZ_E_OOM;
+  if (c.forward) {
+    if (rc == KATZ_OK) rc = alloc_segments(st, bins, cap);
+    if (rc == KATZ_OK) rc = alloc_segments(st, lbins, cap);
+    if (rc == KATZ_OK) rc = alloc_partial(st, bins.seg_cap, partial, blkmax);
+  }
+  if (rc == KATZ_OK && (hipMemcpyAsync(np, c.pool, sizeof(int32_t) * c.pool_used, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+                        hipStreamSynchronize(s) != hipSuccess)) {
+    (void)hipGetLastError();
+    rc = KATZ_E_HIP;
+  }
+  if (rc != KATZ_OK) {
+    free_segments(st, bins);
+    free_segments(st, lbins);
+    dfree(st, partial);
+    dfree(st, blkmax);
+    dfree(st, np);
+    return rc;
+  }
   dfree(st, c.pool);
   c.pool = np;
   c.pool_cap = cap;
   if (c.forward) {
-    KATZ_TRY(alloc_bins(st, st->bins));
-    KATZ_TRY(alloc_bins(st, st->lbins));
-    KATZ_TRY(alloc_partial(st));
+    free_segments(st, st->bins);
+    free_segments(st, st->lbins);
+    dfree(st, st->w.partial);
+    dfree(st, st->w.blkmax);
+    st->bins = bins;
+    st->lbins = lbins;
+    st->w.partial = partial;
+    st->w.blkmax = blkmax;
+    st->bins_stale = true;      // the long rows' new arrays are empty
+    st->bins_pending = false;
   }
   return KATZ_OK;
 }
