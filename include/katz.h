@@ -455,7 +455,8 @@ int katz_timing_read(katz_timing* out);
  *                        groups that share one LDS copy of hub_bytes, each group
  *                        working as one workgroup does (blocks_per_cu then counts
  *                        these 1024-thread workgroups); 0 or 1 = 256-thread
- *                        workgroups.
+ *                        workgroups (1 with hub_bytes and blocks_per_cu 0: one
+ *                        workgroup per work item whatever the graph's size).
  *   batch_xcd            batched form: 1 = give every graph to one of the eight
  *                        XCDs (balanced by arcs) and let the workgroups that the
  *                        hardware places on an XCD take only its graphs' work
@@ -503,9 +504,9 @@ int katz_tuning_get(katz_tuning* t);
 int katz_tuning_set(const katz_tuning* t);
 /* Autotuner: times katz_rank_static(count, g, p) on `stream` under each
  * candidate launch shape (two calls each, the second timed), installs the
- * fastest and copies it to *best (may be NULL).  count = 1 tunes hub_bytes and
- * blocks_per_cu, count > 1 tunes batch_blocks_per_cu and batch_tile; the other
- * fields keep their values.  Inputs as for katz_rank_static; returns the first error of a
+ * fastest and copies it to *best (may be NULL).  count = 1 tunes hub_bytes,
+ * blocks_per_cu, walk_groups and bin_bounds, count > 1 the batch_ fields and
+ * bin_bounds; the other fields keep their values.  Inputs as for katz_rank_static; returns the first error of a
  * ranking call (the setting is then left unchanged), or KATZ_OK. */
 int katz_autotune(int32_t count, const katz_csr* g, const katz_params* p, katz_tuning* best, void* stream);
 /* Autotuner cache: with a path set, katz_autotune first looks its workload up
@@ -515,7 +516,9 @@ int katz_autotune(int32_t count, const katz_csr* g, const katz_params* p, katz_t
  * arcs, and the precision, criterion, flags and direction of the first graph.
  * One line per entry: the key, a tab, the 13 katz_tuning fields before
  * `reserved` as decimal integers; the last valid line of a key wins, and lines
- * that do not parse or hold an invalid setting are ignored.  The file is read
+ * that do not parse or hold an invalid setting are ignored.  An entry of a single
+ * graph that leaves the launch shape unset stands for one workgroup per work item
+ * (walk_groups = 1), which is what unset fields once meant.  The file is read
  * and appended by plain stdio calls (no locking between processes).  path =
  * NULL or "" turns the cache off (the default).  Returns KATZ_OK. */
 int katz_autotune_cache(const char* path);

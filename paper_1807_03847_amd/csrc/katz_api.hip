@@ -295,9 +295,13 @@ struct LaunchShape {
 constexpr long long kSharedCopyFrom = 4ll << 20;
 constexpr int kSharedCopyBytes = 159744;
 
+bool shape_unset(const katz_tuning& tu) {
+  return tu.hub_bytes == 0 && tu.blocks_per_cu == 0 && tu.walk_groups == 0 && tu.split_hot_bytes == 0;
+}
+
 LaunchShape launch_shape(const katz_tuning& tu, long long n, int xs, bool renumbered, int dev) {
   LaunchShape ls;
-  if (tu.hub_bytes == 0 && tu.blocks_per_cu == 0 && tu.walk_groups == 0 && tu.split_hot_bytes == 0) {
+  if (shape_unset(tu)) {
     if (renumbered && n * xs > kSharedCopyFrom) {
       ls.grid = cu_count(dev);
       ls.groups = kWalkGroups;
@@ -3945,6 +3949,8 @@ KATZ_EXPORT int katz_autotune(int32_t count, const katz_csr* g, const katz_param
     cache_key = katz::tune_key(count, g, p);
     katz_tuning hit{};
     if (!cache_key.empty() && katz::cache_lookup(cache_path, cache_key, hit)) {
+      // Entries from when nothing set meant one workgroup per work item.
+      if (count == 1 && katz::shape_unset(hit)) hit.walk_groups = 1;
       std::lock_guard<std::mutex> lk(katz::g_tuning.mu);
       katz::g_tuning.t = hit;
       if (best) *best = hit;
@@ -3953,8 +3959,10 @@ KATZ_EXPORT int katz_autotune(int32_t count, const katz_csr* g, const katz_param
   }
   // {hub_bytes, blocks_per_cu, walk_groups}: hub copies sized so that 3..8
   // workgroups fill the 160 KiB of LDS of a CU (with the kernel's own few bytes
-  // of static LDS), and one 1024-thread workgroup with a copy of 64..156 KiB.
-  static const int kSingle[][3] = {{0, 0, 0},      {0, 4, 0},      {0, 8, 0},       {0, 16, 0},      {16384, 4, 0},
+  // of static LDS), and one 1024-thread workgroup with a copy of 64..156 KiB.  {0, 0,
+  // 1} is one workgroup per work item on a graph of any size, which {0, 0, 0} is on
+  // small ones only (launch_shape); its other shape comes last.
+  static const int kSingle[][3] = {{0, 0, 1},      {0, 4, 0},      {0, 8, 0},       {0, 16, 0},      {16384, 4, 0},
                                    {20416, 8, 0},  {24512, 6, 0},  {32704, 5, 0},   {32768, 4, 0},   {40896, 4, 0},
                                    {54208, 3, 0},  {65536, 2, 0},  {65536, 1, 4},   {98304, 1, 4},   {131072, 1, 4},
                                    {159744, 1, 4}};

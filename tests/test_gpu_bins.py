@@ -255,3 +255,33 @@ def test_binning_block_edges(katz, n, table, rp64):
             olo, oup = oracle.bounds(rp, col, alpha, 4)
             np.testing.assert_allclose(lo.cpu().numpy(), olo, rtol=1e-12, atol=0)
             np.testing.assert_allclose(up.cpu().numpy(), oup, rtol=1e-12, atol=0)
+
+
+def test_autotune_keeps_the_shape_of_one_workgroup_per_item(katz, tmp_path):
+    """One workgroup per work item, which unset launch fields mean on small graphs
+    only: the autotuner names it (walk_groups = 1), a stored entry that leaves the
+    fields unset installs it, and on a graph whose walk vector outgrows an L2 it gives
+    the bits of the library's own choice."""
+    path = tmp_path / "tune.txt"
+    katz.autotune_cache(path)
+    try:
+        rp, col = sg.rmat(11, seed=6)
+        say("autotune shapes")
+        best = katz.autotune(*dev(rp, col), 20, eps=1e-6, precision="fp32")
+        assert any(best[f] for f in ("hub_bytes", "blocks_per_cu", "walk_groups", "split_hot_bytes"))
+        key = path.read_text().split("\t")[0]
+        path.write_text(key + "\t0 0 4 2 0 0 0 0 0 0 0 0 0\n")
+        hit = katz.autotune(*dev(rp, col), 20, eps=1e-6, precision="fp32")
+        assert hit == katz.tuning_get()
+        assert (hit["hub_bytes"], hit["blocks_per_cu"], hit["walk_groups"]) == (0, 0, 1)
+        assert (hit["batch_blocks_per_cu"], hit["batch_tile"]) == (4, 2)
+    finally:
+        katz.autotune_cache(None)
+    rp_t, col_t = sg.rmat_device(20, 8, seed=3)
+    say("shapes above an L2")
+    katz.tuning_set()
+    a = katz.rank_static(rp_t, col_t, 100, eps=1e-6)
+    katz.tuning_set(walk_groups=1)
+    b = katz.rank_static(rp_t, col_t, 100, eps=1e-6)
+    assert torch.equal(a.topk, b.topk) and torch.equal(a.lower, b.lower) and torch.equal(a.upper, b.upper)
+    assert (a.iterations, a.status, a.rest_upper_max) == (b.iterations, b.status, b.rest_upper_max)
