@@ -788,6 +788,10 @@ struct Run {
   // The active list begins with the last pass's top-k (or, before the first pass, with
   // the longest rows), from which sel_filter takes its floor.
   bool top_first = false;
+  // Whether the last filtered selection whose flags the host has seen listed more than
+  // kSmallCand candidates.
+  enum Listed { LISTED_UNKNOWN, LISTED_FEW, LISTED_MANY } listed = LISTED_UNKNOWN;
+  long long refine_from = 0;   // with that unknown, sets above this size are refined (iterate)
 
   // Whether one workgroup may run converged() (its LDS sort holds the top-k).
   bool one_workgroup_select() const { return (criterion == KATZ_TOPK || criterion == KATZ_RANKING) && k <= kMaxK; }
@@ -945,6 +949,11 @@ Select select_form(const Run& run, long long m) {
   return m <= kSmallActive ? SEL_ONE : SEL_WIDE;
 }
 
+// Until a filtered pass's candidates have been counted, sets above this size go through
+// sel_refine, which costs 4 us where it has nothing to do: R-MAT of 150 K nodes would
+// lose 9 us of 330 to it, and up to here one workgroup needs 0.5 ms for a whole set.
+constexpr long long kRefineFrom = 1ll << 18;
+
 // A renumbered run's first active list begins with the longest rows.  Rows of one bin
 // are not sorted, so the nodes that are not behind the last of the first k lie in the
 // bins up to the k-th's: few enough for one workgroup to sort out (kSmallCand).
@@ -1005,7 +1014,10 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, S
   } else if (run.criterion == KATZ_PAIR) {
     KATZ_HIP(launch_pair_check(sel_args(run, r), run.pair_u, run.pair_v, s));
   } else if (sel == SEL_FILTER) {
-    KATZ_HIP(launch_filtered_select(sel_args(run, r), run.walk_max, m, run.grid, s));
+    // The first pass's floor, the longest rows, is known to leave few.
+    const bool refine = run.listed == Run::LISTED_MANY ||
+                        (run.listed == Run::LISTED_UNKNOWN && !run.first_select && m > run.refine_from);
+    KATZ_HIP(launch_filtered_select(sel_args(run, r), run.walk_max, m, refine, run.grid, s));
   } else if (sel == SEL_ONE) {
     GraphSel gs{};
     gs.b = bound_args(run, r);
@@ -1055,6 +1067,7 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, S
 // What the host learns of a finished pass.
 struct PassFlags {
   int err = 0, status = -1, m = 0;   // status: -1 while the run goes on
+  bool many = false;                 // RunScalars::many
   bool stopped() const { return err || status >= 0; }
 };
 
@@ -1083,12 +1096,12 @@ int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out
       if (w >> 40 != (seq & 0xffffffu)) {
         KATZ_HIP(hipMemcpyAsync(hs.sc, dev, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
         KATZ_HIP(hipStreamSynchronize(s));
-        *out = PassFlags{hs.sc->err, hs.sc->done ? hs.sc->status : -1, hs.sc->m};
+        *out = PassFlags{hs.sc->err, hs.sc->done ? hs.sc->status : -1, hs.sc->m, hs.sc->many != 0};
         return KATZ_OK;
       }
     }
     if (w >> 40 == (seq & 0xffffffu)) {
-      *out = PassFlags{(int)(w >> 31 & 3), (int)(w >> 33 & 15) - 1, (int)(w & INT32_MAX)};
+      *out = PassFlags{(int)(w >> 31 & 3), (int)(w >> 33 & 15) - 1, (int)(w & INT32_MAX), (w >> 37 & 1) != 0};
       return KATZ_OK;
     }
     poll_pause(spins);
@@ -1123,7 +1136,13 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
   PassFlags last;             // of the last pass waited for
   struct PassAt {
     int r, cur;               // the pass's iteration, the active list it wrote
+    Select sel;
   } at[2] = {};
+  // What a finished pass tells of the candidates.
+  auto learn = [&run](const PassAt& a, bool many) {
+    if (a.sel == SEL_FILTER) run.listed = many ? Run::LISTED_MANY : Run::LISTED_FEW;
+  };
+  run.refine_from = copy_every > 1 ? kSmallActive : kRefineFrom;
   // Upper bound of |M| from the latest flags read back; M never grows inside
   // this loop, so a bound read one pass behind stays valid.
   long long m_known = run.m_known >= 0 ? run.m_known : run.n;
@@ -1132,7 +1151,7 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
     // enqueued before that is known.
     const unsigned seq = ++hs.seq;
     run.pub = Publish{&hs.flags[seq & 1], seq};
-    at[0] = PassAt{r - 1, run.cur ^ 1};
+    at[0] = PassAt{r - 1, run.cur ^ 1, SEL_WIDE};
     run.walk_max = WalkMax{nullptr, 0};
     KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, select_form(run, m_known), m_known));
     KATZ_TRY(wait_flags(hs, seq, run.w->sc, &last, s));
@@ -1145,7 +1164,7 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
     const Select sel = select_form(run, m_known);
     run.pub = polled ? Publish{&hs.flags[(hs.seq + 1) & 1], hs.seq + 1} : Publish{nullptr, 0};
     const bool select_only = pass == 0 && check_first;
-    at[pass & 1] = PassAt{select_only ? r - 1 : r, run.cur ^ 1};
+    at[pass & 1] = PassAt{select_only ? r - 1 : r, run.cur ^ 1, sel};
     if (select_only) {
       KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, SEL_WIDE, m_known));
     } else if (r <= run.max_iter) {
@@ -1162,6 +1181,7 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
         KATZ_TRY(wait_flags(hs, hs.seq - 1, run.w->sc, &last, s));
         stopped = last.stopped();
         m_known = last.m;
+        learn(at[(pass - 1) & 1], last.many);
       }
     } else if ((pass + 1) % copy_every == 0) {
       KATZ_HIP(hipMemcpyAsync(&hs.ring[pass & 1], run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
@@ -1173,6 +1193,7 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
         const RunScalars& prev = hs.ring[seen & 1];
         if (prev.err || prev.done) stopped = true;
         m_known = prev.m;
+        learn(at[seen & 1], prev.many != 0);
       }
     }
     ++pass;

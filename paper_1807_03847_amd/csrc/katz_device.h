@@ -157,9 +157,9 @@ __device__ __forceinline__ void clear_flags(RunScalars* sc) {
 // A finished pass's flags to pinned host memory: one 64-bit word, so that the
 // host, which polls it, needs no ordering with other stores.  status: -1 while
 // the run goes on.  One thread.
-__device__ __forceinline__ void publish(const Publish& p, int err, int status, int m) {
+__device__ __forceinline__ void publish(const Publish& p, int err, int status, int m, bool many = false) {
   if (!p.to) return;
-  __hip_atomic_store(p.to, pass_word(p.seq, err, status, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(p.to, pass_word(p.seq, err, status, m, many), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Exclusive scan of a long long array of length len with one 1024-thread block.

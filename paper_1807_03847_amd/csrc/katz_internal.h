@@ -137,7 +137,7 @@ struct RunScalars {
   int progress;       // FP32 form: some active interval can still shrink
   int cand_count[2];  // candidates compacted at select levels 0 and 1
   int need;           // rank still to find inside the current bucket
-  int level;          // select digits resolved so far
+  int many;           // the last filtered selection listed more than kSmallCand candidates
   int cut_ext;        // ties with key == theta_key are top iff ext id <= cut_ext
   int fail;           // adjacent-pair test failed
   int dmax;           // prep: maximum row length
@@ -167,10 +167,11 @@ struct Publish {
 };
 
 // The published word: |M| in bits 0..30, then err (2 bits), status + 1 (4 bits;
-// 0 while the run goes on) and the low 24 bits of the pass's number.
-__host__ __device__ inline unsigned long long pass_word(unsigned seq, int err, int status, int m) {
+// 0 while the run goes on), RunScalars::many (1 bit) and, from bit 40, the low 24 bits
+// of the pass's number.
+__host__ __device__ inline unsigned long long pass_word(unsigned seq, int err, int status, int m, bool many) {
   return (unsigned long long)(unsigned)m | (unsigned long long)err << 31 | (unsigned long long)(status + 1) << 33 |
-         (unsigned long long)(seq & 0xffffffu) << 40;
+         (unsigned long long)many << 37 | (unsigned long long)(seq & 0xffffffu) << 40;
 }
 
 // Bound evaluation parameters of one iteration.
@@ -523,8 +524,9 @@ struct WalkMax {
 hipError_t launch_select_wg_one(const GraphSel& one, const WalkMax& walk, const Publish& pub, hipStream_t s);
 // launch_select_iteration's result for an active list that begins with k likely top
 // nodes (sel_filter), with the maxima of the walk step just run.  m: no fewer than
-// the list's nodes.
-hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, int max_grid, hipStream_t s);
+// the list's nodes.  refine: the candidates may be many (sel_refine).
+hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, bool refine, int max_grid,
+                                  hipStream_t s);
 // Workgroup maxima at or below which the one-workgroup selection reduces them.
 constexpr long long kFusedMaxSlots = 8192;
 constexpr int kFilterFrom = 8 * kFinishThreads;   // above: filtered selections (katz_api.hip, select_form)

@@ -799,7 +799,6 @@ __global__ void __launch_bounds__(kFinishThreads) sel_scan(SelArgs a, int level)
   if (threadIdx.x == 0) {
     a.sc->need = bk.need;
     a.sc->prefix = (level == 0) ? (unsigned long long)bk.b : ((a.sc->prefix << kDigitBits) | (unsigned)bk.b);
-    a.sc->level = level + 1;
   }
 }
 
@@ -961,6 +960,84 @@ __global__ void __launch_bounds__(kWG) sel_filter(SelArgs a, WalkMax walk) {
   }
 }
 
+// Fewer candidates where sel_filter lists too many for sel_finish, one workgroup: a
+// floor that was good for the last pass is poor on graphs of like degrees (2^20 nodes
+// of a grid without 10% of its edges: 680 K candidates for k = 100 in pass 2).  A new
+// floor comes from 1024 candidates spread over the list: lambda = 1024 k / count of them
+// are expected among the top k, and the floor is the one lambda + 4 sqrt(lambda) + 4 deep
+// (ids order ties), so that the list it leaves, of about count / 1024 times that depth,
+// is shorter than k once in 10^5 passes or less; sel_finish then takes the first list.
+// Every workgroup sorts the sample itself; the rest is one read of the list.  2^20 nodes
+// of that grid: 25 us here and 16 to 30 in sel_finish, where the whole list took 0.5 to
+// 1.2 ms in each of the first passes; 4.5 us where there is nothing to do.  Calls on it
+// (k = 100, FP64) 9.95 -> 6.14 ms, on 2^22 nodes 43.3 -> 26.3, on a mesh of 100^3 nodes
+// 62.4 -> 20.6.
+__global__ void __launch_bounds__(kFinishThreads) sel_refine(SelArgs a) {
+  if (stopped(a.sc)) return;
+  const int cnt = a.sc->cand_count[0];
+  if (cnt <= kSmallCand) return;
+  __shared__ SmallArea rec;
+  __shared__ unsigned long long s_key;
+  __shared__ int s_ext, s_place[kFinishThreads / kWave], s_base;
+  const int t = threadIdx.x, w = t / kWave;
+  {
+    const long long i = (long long)t * cnt / kFinishThreads;
+    unsigned long long key = ~a.cand_key[0][i];
+    int ext = ext_id(a, a.cand_v[0][i]), slot = 0;
+    sort_records(kFinishThreads, key, ext, slot, rec);
+    const double lambda = (double)a.k * kFinishThreads / cnt;
+    if (t == (int)(lambda + 4.0 * sqrt(lambda)) + 3) {
+      s_key = ~key;
+      s_ext = ext;
+    }
+  }
+  __syncthreads();
+  const unsigned long long fk = s_key;
+  const int fe = s_ext;
+  constexpr int kRound = kFinishThreads * kIPT;
+  for (long long g0 = (long long)blockIdx.x * kRound; g0 < cnt; g0 += (long long)gridDim.x * kRound) {
+    unsigned long long key[kIPT];
+    unsigned mask = 0;
+#pragma unroll
+    for (int j = 0; j < kIPT; ++j) {
+      const long long i = g0 + (long long)j * kFinishThreads + t;
+      key[j] = i < cnt ? a.cand_key[0][i] : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < kIPT; ++j) {
+      const long long i = g0 + (long long)j * kFinishThreads + t;
+      if (i < cnt && (key[j] > fk || (key[j] == fk && ext_id(a, a.cand_v[0][i]) <= fe))) mask |= 1u << j;
+    }
+    int inc = __popc(mask);
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane_id() >= o) inc += y;
+    }
+    if (lane_id() == kWave - 1) s_place[w] = inc;
+    __syncthreads();
+    if (t == 0) {
+      int sum = 0;
+      for (int q = 0; q < kFinishThreads / kWave; ++q) {
+        const int c = s_place[q];
+        s_place[q] = sum;
+        sum += c;
+      }
+      s_base = sum > 0 ? atomicAdd(&a.sc->cand_count[1], sum) : 0;
+    }
+    __syncthreads();
+    int pos = s_base + s_place[w] + inc - __popc(mask);
+#pragma unroll
+    for (int j = 0; j < kIPT; ++j) {
+      if (mask >> j & 1u) {
+        a.cand_key[1][pos] = key[j];
+        a.cand_v[1][pos] = a.cand_v[0][g0 + (long long)j * kFinishThreads + t];
+        ++pos;
+      }
+    }
+    __syncthreads();
+  }
+}
+
 constexpr int kFinishIlp = 4;   // candidates per thread and pass of sel_finish
 
 // The need-th of cnt <= kFinishThreads records, one per thread.
@@ -975,7 +1052,8 @@ __device__ __forceinline__ void finish_sorted(const SelArgs& a, int cnt, unsigne
 }
 
 // Resolves the remaining digits of the k-th key and the id cut inside its ties.
-// filtered: the candidates are sel_filter's, with all digits to resolve.  At most one
+// filtered: the candidates are sel_filter's, or those that sel_refine left of them, with
+// all digits to resolve.  At most one
 // candidate per thread: they are sorted instead (14 us of digits, 5 of sort).
 __global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a, bool filtered) {
   if (stopped(a.sc)) return;
@@ -986,7 +1064,7 @@ __global__ void __launch_bounds__(kFinishThreads) sel_finish(SelArgs a, bool fil
   unsigned* const h = sm.h;
   __shared__ unsigned long long s_prefix, s_kmin, s_kmax;
   __shared__ int s_need, s_count, s_place;
-  const bool from1 = !filtered && a.sc->cand_count[0] > kSmallCand;
+  const bool from1 = filtered ? a.sc->cand_count[1] >= a.k : a.sc->cand_count[0] > kSmallCand;
   const unsigned long long* ck = a.cand_key[from1 ? 1 : 0];
   const int32_t* cv = a.cand_v[from1 ? 1 : 0];
   const int cnt = a.sc->cand_count[from1 ? 1 : 0];
@@ -1289,6 +1367,8 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned*
     sc->iterations = a.b.r;
     sc->cur = a.act_out_idx;
     sc->m = k + kept;
+    const bool many = sc->cand_count[0] > kSmallCand;
+    sc->many = many ? 1 : 0;
     sc->top_count = 0;
     sc->kept_count = 0;
     sc->cand_count[0] = 0;
@@ -1297,7 +1377,7 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned*
       sc->status = status;
       sc->done = 1;
     }
-    publish(a.pub, 0, status, k + kept);
+    publish(a.pub, 0, status, k + kept, many);
   }
 }
 
@@ -1625,12 +1705,18 @@ hipError_t launch_select_iteration(const SelArgs& a, int grid, hipStream_t s, bo
   return hipGetLastError();
 }
 
-hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, int max_grid, hipStream_t s) {
+hipError_t launch_filtered_select(const SelArgs& a, const WalkMax& walk, long long m, bool refine, int max_grid,
+                                  hipStream_t s) {
   // Every workgroup of the filter evaluates the k nodes of the floor: no more
   // workgroups than groups of nodes (20 K nodes, k = 1000, 2048 workgroups: 16 us).
   const int grid = (int)std::min<long long>(max_grid, std::max((m + kGroup - 1) / kGroup, (walk.count + 4095ll) / 4096));
   if (a.b.fp32) hipLaunchKernelGGL(sel_filter<true>, dim3(grid), dim3(kWG), 0, s, a, walk);
   else hipLaunchKernelGGL(sel_filter<false>, dim3(grid), dim3(kWG), 0, s, a, walk);
+  if (refine) {
+    const long long per = kFinishThreads * kIPT;
+    hipLaunchKernelGGL(sel_refine, dim3((unsigned)std::min<long long>(512, (m + per - 1) / per)), dim3(kFinishThreads), 0,
+                       s, a);
+  }
   launch_finish_apply(a, grid, true, true, s);
   return hipGetLastError();
 }

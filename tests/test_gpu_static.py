@@ -535,3 +535,62 @@ def test_filtered_selection(shape, precision):
             if precision == "fp64":
                 assert a.iterations == orc.iterations
                 check(orc, a)
+
+
+def permuted_grid(rows, cols, drop, seed):
+    """A grid of degree at most 4 without a share of its edges, its nodes renamed at random."""
+    rng = np.random.default_rng(seed)
+    i = np.arange(rows * cols).reshape(rows, cols)
+    a = np.concatenate([i[:, :-1].ravel(), i[:-1].ravel()])
+    b = np.concatenate([i[:, 1:].ravel(), i[1:].ravel()])
+    keep = rng.random(len(a)) >= drop
+    perm = rng.permutation(rows * cols)
+    return sg.from_edges(rows * cols, perm[a[keep]], perm[b[keep]])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("rows,cols,drop", [(640, 640, 0.1), (640, 640, 0.0), (515, 1030, 0.3), (200, 203, 0.1)])
+def test_selection_with_poor_floors(rows, cols, drop, precision):
+    """Graphs of like degrees, where the last top-k lies below most of the active set:
+    more candidates than one workgroup sorts out (16384), many of them tied, on sets
+    above 2^18 nodes (refined from the second pass on) and below (once the host has
+    seen the count).  With eps = 0 the top-k after r iterations is the head of all
+    nodes by lower bound, then id."""
+    katz = K()
+    rp, col = permuted_grid(rows, cols, drop, 3)
+    rp_t, col_t = dev(rp, col)
+    for r in (2, 3, 4, 6, 9):
+        lo, up = katz.bounds(rp_t, col_t, r, precision=precision)
+        order = torch.argsort(lo, descending=True, stable=True).int()
+        for k in (1, 100, 777, 1024):
+            say("poor floors", rows, cols, drop, precision, r, k)
+            for flags in (0, katz.FLAG_NO_REORDER):
+                a = katz.rank_static(rp_t, col_t, k, eps=0.0, precision=precision, max_iter=r, flags=flags)
+                if a.iterations < r:
+                    continue
+                ids = order[:k]
+                assert torch.equal(a.topk, ids)
+                assert torch.equal(a.lower, lo[ids.long()]) and torch.equal(a.upper, up[ids.long()])
+
+
+def test_selection_time_with_poor_floors():
+    """Device time of the selections of passes 2 to 8, whose floors let most of two
+    million nodes of a grid through, against the walk steps of those passes: one
+    workgroup working through such candidates takes ten times as long as the walk,
+    candidates thinned out by the whole device about as long."""
+    katz = K()
+    rp_t, col_t = dev(*permuted_grid(1024, 2048, 0.1, 3))
+    ms = {}
+    try:
+        for passes in (1, 8):
+            katz.rank_static(rp_t, col_t, 100, eps=1e-6, max_iter=passes)
+            katz.timing_enable(True)
+            for _ in range(3):
+                katz.rank_static(rp_t, col_t, 100, eps=1e-6, max_iter=passes)
+            ms[passes] = katz.timing_read()
+    finally:
+        katz.timing_enable(False)
+    select = ms[8]["select_ms"] - ms[1]["select_ms"]
+    walk = ms[8]["walk_step_ms"] + ms[8]["renumber_step_ms"]
+    say("selection and walk of seven passes, ms a call", round(select / 3, 3), round(walk / 3, 3))
+    assert select < 3 * walk
