@@ -467,3 +467,39 @@ def test_state_with_more_hubs_than_a_binning_workgroup_holds():
     rp, col = _apply(n, rp, col, ins, dels)
     check_against_static(katz, res, rp, col, alpha)
     st.free()
+
+
+BINS_CHILD = r"""
+side = 260
+n = side * side
+i = np.arange(n).reshape(side, side)
+a = np.concatenate([i[:, :-1].ravel(), i[:-1].ravel()])
+b = np.concatenate([i[:, 1:].ravel(), i[1:].ravel()])
+rng = np.random.default_rng(2)
+keep = rng.random(len(a)) >= 0.2
+rp, col = sg.from_edges(n, a[keep], b[keep])
+dev = lambda a, t: torch.from_numpy(np.ascontiguousarray(np.asarray(a, dtype=t))).cuda()
+state, res = katz.create_state(dev(rp, np.int64), dev(col, np.int32), 20, alpha=0.1, eps=1e-6, degree_cap=6)
+whole = lambda log: sum("prep_place" in name and "SlackRows" in name for name, _ in log)
+gone = np.stack([a[~keep], b[~keep]], 1)[:64].astype(np.int32)
+for step, batch in enumerate(gone.reshape(8, 8, 2)):
+    print("[gpu-case] update", step, flush=True)
+    before = res.iterations
+    res, log = launches(lambda: state.update(batch))
+    assert res.status == katz.OK
+    print("iterations", before, res.iterations, "binned", whole(log), "launches", len(log), flush=True)
+    # The creation walked the whole graph, so the first update may bin it ahead of a walk.
+    if step > 0 and last == before == res.iterations:
+        assert whole(log) == 0
+        print("small", flush=True)
+    last = before
+"""
+
+
+def test_small_updates_leave_the_whole_graph_unbinned(tmp_path):
+    """Updates whose affected set stays small, as on a grid, do not bin the whole graph:
+    they walk it only where the ranking takes further iterations."""
+    from tests.launch_log import run_child
+    say("bins of small updates")
+    out = run_child(tmp_path, BINS_CHILD)
+    assert out.count("small") >= 3
