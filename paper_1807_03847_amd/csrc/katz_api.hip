@@ -99,13 +99,16 @@ struct Arena {
   hipEvent_t last = nullptr;
   hipStream_t last_stream = nullptr;
   bool recorded = false;
-  // Batched calls: pinned memory that their per-graph tables are uploaded from.
+  // Batched calls: pinned memory that their per-graph tables are uploaded from, and the
+  // stream that they iterate on.
   char* pin = nullptr;
   size_t pin_cap = 0;
+  hipStream_t batch_stream = nullptr;
 
   ~Arena() {
     if (recorded) (void)hipEventSynchronize(last);
     if (last) (void)hipEventDestroy(last);
+    if (batch_stream) (void)hipStreamDestroy(batch_stream);
     if (pin) (void)hipHostFree(pin);
     if (base && !fixed) (void)hipFree(base);
   }
@@ -1936,6 +1939,12 @@ int solve_on(const katz_csr* g, const katz_params* p, int method, double tol, do
 // ---------------------------------------------------------------------------
 // Batched form: many graphs in one sequence of launches (katz_batch.hip).
 // ---------------------------------------------------------------------------
+// A stream that is idle when the scope is left.
+struct FinishedStream {
+  hipStream_t s;
+  ~FinishedStream() { (void)hipStreamSynchronize(s); }
+};
+
 int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* out, hipStream_t s) {
   const Range range_call("katz_rank_static batch");
   const katz_tuning tu_b = current_tuning();   // one setting for the whole call
@@ -2167,8 +2176,16 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   KATZ_HIP(launch_batch_dmax(grp, grp64, gbase, count, total_n, gdmax, fl, s));
   KATZ_HIP(hipMemcpyAsync(ar.pin + pin_dmax, gdmax, sizeof(int) * count, hipMemcpyDeviceToHost, s));
   KATZ_HIP(hipMemcpyAsync(ar.hs.sc, w.sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+  T.stop(tp, s);
   KATZ_HIP(hipStreamSynchronize(s));
   if (ar.hs.sc->err) return KATZ_E_CSR;
+  // The caller's stream has finished all that the call depends on.  The rest runs on a
+  // stream of the workspace, so that calls of several threads on one stream, the default
+  // one above all, overlap.
+  if (!ar.batch_stream) KATZ_HIP(hipStreamCreateWithFlags(&ar.batch_stream, hipStreamNonBlocking));
+  const FinishedStream own{ar.batch_stream};
+  s = own.s;
+  const int tp2 = T.start(T_PREP, s);
   b.read_back(*ar.hs.sc, total_n);
   if (reorder && total_n > 0) {
     // Rename every graph's nodes by its binned order, bin the renamed rows
@@ -2324,7 +2341,7 @@ int rank_batch(int count, const katz_csr* g, const katz_params* p, katz_result* 
   const BatchNext next{gsigma, gsigsum, eta, etap, gexp, gxmax32, gxmax64, galpha, grho, gclog2, ndone, stride};
   KATZ_HIP(launch_batch_begin(gsel, gdmax, count, n_items, next, fl, fp32, s));
   KATZ_HIP(launch_batch_item_graphs(bw, total_blocks, item_g, s));
-  T.stop(tp, s);
+  T.stop(tp2, s);
   const int ts = T.start(T_STEP, s);
   const long long n_huge = b.bin_count[BIN_HUGE];
   for (int r = 1; r <= max_iter; ++r) {

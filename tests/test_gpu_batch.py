@@ -344,3 +344,36 @@ def test_batch_more_items_than_workgroups(precision):
     say("batch of many items", precision, rows // 16, "items of 16 rows,", slots, "workgroups")
     assert rows // 16 > 2 * slots
     assert_bitwise_single(graphs, params, run_batch(graphs, params, precision), precision)
+
+
+STREAMS_CHILD = r"""
+graphs, params = [], []
+for i in range(6):
+    rp, col = sg.barabasi_albert(1500 + 500 * i, 8, 60 + i)
+    graphs.append((torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), True))
+    params.append(dict(k=20, eps=1e-7, precision=sys.argv[2]))
+torch.cuda.synchronize()
+other = torch.cuda.Stream()
+for stream in (torch.cuda.default_stream(), other):
+    with torch.cuda.stream(stream):
+        res, log = launches(lambda: katz.rank_static_batch(graphs, params))
+    walks = [s for name, s in log if "walk_batch" in name]
+    preps = [s for name, s in log if "prep_place" in name]
+    print("[gpu-case] streams", stream.cuda_stream, len(walks), len(preps), flush=True)
+    assert walks and preps
+    assert all(s == stream.cuda_stream for s in preps)        # after the caller's earlier work
+    assert all(s not in (0, stream.cuda_stream) for s in walks)
+    for (rp, col, _), pp, r in zip(graphs, params, res):
+        one = katz.rank_static(rp, col, pp["k"], eps=pp["eps"], precision=pp["precision"])
+        assert torch.equal(one.topk, r.topk) and torch.equal(one.lower, r.lower)
+print("ok")
+"""
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batches_iterate_on_a_stream_of_their_own(tmp_path, precision):
+    """A batched call reads its graphs on the caller's stream and iterates on its
+    workspace's, so that calls of several threads on the default stream overlap."""
+    from tests.launch_log import run_child
+    say("batch streams", precision)
+    assert run_child(tmp_path, STREAMS_CHILD, precision).rstrip().endswith("ok")
