@@ -959,8 +959,9 @@ Select select_form(const Run& run, long long m) {
 constexpr long long kRefineFrom = 1ll << 18;
 
 // A renumbered run's first active list begins with the longest rows.  Rows of one bin
-// are not sorted, so the nodes that are not behind the last of the first k lie in the
-// bins up to the k-th's: few enough for one workgroup to sort out (kSmallCand).
+// are not sorted (but cut into parts), so the nodes that are not behind the last of the
+// first k lie in the bins up to the k-th's: few enough for one workgroup to sort out
+// (kSmallCand).
 bool longest_rows_first(const Bins& b, int k) {
   for (int i = 0; i < NUM_BINS; ++i)
     if (k <= b.bin_base[i] + b.bin_count[i]) return b.bin_base[i] + b.bin_count[i] <= kSmallCand;
@@ -1114,14 +1115,19 @@ int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out
 
 // Graphs up to this many nodes and arcs take their flags by polling.  A pass
 // (walk step, selection) on them is 15 to 100 us, of which a copy of the flags
-// and its event took 15 to 20 us and the host's wake-up as much again; on larger
-// graphs the copy is below 2% of a pass, and the host sleeps through it.
+// and its event took 15 to 20 us and the host's return as much again; on larger
+// graphs the copy is below 2% of a pass.  The re-check of an update, the iterations of
+// a batch and the solvers' steps poll at every size.  A CPU is as busy either way: HIP's
+// own waits spin here too (CPU time over wall time of a call 1.00 with and without the
+// polling, R-MAT 22), and wait_flags yields now and then.
 constexpr long long kPolledSize = 1ll << 24;
 // Without pinned memory (the allocation-free call) each read-back stalls the
 // stream for 30 to 45 us, while a pass enqueued past the stop returns at once (two
 // launches, 8 us): small graphs read the flags every eighth pass.  A call on 2000
-// nodes (18 passes) 516 us at every fourth, 494 sixth, 452 eighth, 505 twelfth; on
-// 300 to 60000 nodes the eighth takes 2 to 13% off the fourth.
+// nodes (18 passes) 516 us at every fourth, 494 sixth, 452 eighth, 505 twelfth.  Up to
+// the scratch's limit, at every pass, fourth and eighth: Erdos-Renyi 120000 nodes (FP32,
+// 18 passes) 1115, 934 and 916, 280000 (16) 988, 840 and 783; R-MAT 2^15 (9 passes, which
+// run on to 16) 530, 511 and 625, 2^18 (8) 599, 513 and 559.
 constexpr int kCopiedPasses = 8;
 
 // Iterates until the device stop flag: walk step r_next, selection,

@@ -2,8 +2,11 @@
 //
 // Layout of a ranking run on the device
 //   * Rows are binned by length (degree-binned scheduling).  Each bin holds
-//     RowDesc records {offset, row, length} in ascending row order.  A bin has a
-//     fixed number of lanes per row, so the summation order of every row, and
+//     RowDesc records {offset, row, length}, in ascending row order where it is
+//     not cut: batches, whose renumbering and item graphs need that order, runs in
+//     caller order, the levels of an update.  Renumbered graphs and states cut it
+//     into kBinParts parts by length, longest first, rows ascending in each.  A bin
+//     has a fixed number of lanes per row, so the summation order of every row, and
 //     therefore its floating-point result, depends only on the row's length.
 //   * Rows longer than kBlockRowMax are cut into segments of kSeg arcs; one
 //     workgroup sums a segment, and a second launch (one wave per row) adds a
@@ -29,8 +32,8 @@
 namespace katz {
 
 constexpr int kWG = 256;                 // threads per workgroup (4 waves of 64)
-constexpr int kXcds = 8;
-constexpr int kWalkGroups = 4;           // 256-thread groups per workgroup of walk_step_grouped                 // XCDs of an MI355X; workgroups go to them round-robin by id
+constexpr int kXcds = 8;                 // XCDs of an MI355X; workgroups go to them round-robin by id
+constexpr int kWalkGroups = 4;           // 256-thread groups per workgroup of walk_step_grouped
 constexpr int kWave = 64;
 constexpr int kPerLane = 16;             // max row elements summed serially per lane
 constexpr int kSeg = kWG * kPerLane;     // arcs per huge-row segment (4096)

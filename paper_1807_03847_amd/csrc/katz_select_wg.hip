@@ -137,7 +137,9 @@ __device__ __forceinline__ void reduce_walk_max(const GraphSel& gs, const WalkMa
 }
 
 // converged() for up to 16384 nodes (FP32 form: 8192) with the top-k in one record per
-// thread: every thread keeps the keys of its nodes in registers.  The nodes not behind
+// thread: every thread keeps the keys of its nodes in registers.  Above 8192 nodes only
+// lists without a floor come here (the first pass of a run in caller order, the re-check
+// of an update); those with one are filtered (select_form).  The nodes not behind
 // the last of the list's first k are the candidates for the top-k; at most one per
 // thread, they are sorted.  More go through radix digits, which read no memory, until
 // the k-th key's bucket is that small.  False, with nothing written, when a bucket of

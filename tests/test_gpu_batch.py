@@ -222,6 +222,8 @@ def test_batch_column_errors():
     assert len(res) == len(graphs)
 
 
+# Batches are no longer captured into a hipGraph; what the next test checks is the
+# workspace, and the pinned memory that its tables go up from, reused across calls.
 def test_batch_graph_replayed_across_calls():
     """A batch of the same shape in the same workspace replays the hipGraph the
     previous call instantiated: three calls on one batch, a different batch in

@@ -75,8 +75,9 @@ def test_er_fp32_margin(seed):
 
 
 # --------------------------------------------------------------------------------
-# The one-workgroup selection: one record per thread up to 1024 active nodes, keys
-# in registers up to 16384, radix digits over memory beyond (and for many ties).
+# The selection: one record per thread up to 1024 active nodes, keys in registers up to
+# 8192 (FP64 form without a floor, as in caller order: 16384), beyond that filtered where
+# the list has a floor, else radix digits over memory (and for many ties).
 # --------------------------------------------------------------------------------
 @pytest.mark.parametrize("n,k", [(2, 1), (63, 63), (64, 9), (65, 64), (1023, 1023), (1024, 500), (1025, 1), (1025, 1025),
                                  (2049, 1024), (5000, 1025), (16384, 1024), (16385, 1000), (16385, 1)])
