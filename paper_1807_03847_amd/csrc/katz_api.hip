@@ -958,6 +958,14 @@ Select select_form(const Run& run, long long m) {
 // lose 9 us of 330 to it, and up to here one workgroup needs 0.5 ms for a whole set.
 constexpr long long kRefineFrom = 1ll << 18;
 
+// Lists longer than this are sorted once the host has seen that they have to be, a stop
+// of 20 us an iteration; the others' sort is launched each time, and its few kernels
+// return at once where it is not needed.  Calls with the stop and with the launches, FP64,
+// 25 iterations at most: Erdos-Renyi 10^6, k = 5000 5711 and 5477 us, 12000 5883 and 5677,
+// 100000 6151 and 6092, k = n 5823 and 5916; R-MAT 20, 5000 1637 and 1624, 400000 2012 and
+// 2061; Erdos-Renyi 50000, 30000 2253 and 2317.
+constexpr int kGatedSort = 1 << 14;
+
 // A renumbered run's first active list begins with the longest rows.  Rows of one bin
 // are not sorted (but cut into parts), so the nodes that are not behind the last of the
 // first k lie in the bins up to the k-th's: few enough for one workgroup to sort out
@@ -1052,13 +1060,14 @@ int enqueue_select(Run& run, HostSync& hs, int r, hipStream_t s, CallTimer& T, S
     // Every node ranked (k = n): nothing to select, the list is every node.
     if (!large || run.k < run.n) KATZ_HIP(launch_select_iteration(sa, run.grid, s, !large));
     if (large) {
-      // The flag comes back before the sort's launches (10 and more, 5 to 13 us
-      // each at 5e5 records) are known to be needed: one read-back of about
-      // 20 us per iteration, where the last iteration or two need the sort.
       KATZ_HIP(launch_large_test(sa, run.w->sort, s));
-      KATZ_HIP(hipMemcpyAsync(hs.sc, run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
-      KATZ_HIP(hipStreamSynchronize(s));
-      if (!hs.sc->err && !hs.sc->done && hs.sc->need) KATZ_HIP(launch_large_sort(sa, run.w->sort, s));
+      bool sort = true;
+      if (run.k > kGatedSort) {
+        KATZ_HIP(hipMemcpyAsync(hs.sc, run.w->sc, sizeof(RunScalars), hipMemcpyDeviceToHost, s));
+        KATZ_HIP(hipStreamSynchronize(s));
+        sort = !hs.sc->err && !hs.sc->done && hs.sc->need;
+      }
+      if (sort) KATZ_HIP(launch_large_sort(sa, run.w->sort, s));
       KATZ_HIP(launch_large_finish(sa, s));
     }
   }

@@ -25,7 +25,9 @@
 // fails as well.  lk_test sorts each 2048-record tile of the (unsorted) list
 // and tests its adjacent pairs; while some tile fails, which is every iteration
 // but the last one or two (a renumbered list holds nodes of like degree side by
-// side), the device-wide sort is not launched.
+// side), the device-wide sort does not run; nor does the test while nodes outside the
+// top-k survive, which decides the iteration by itself (k = 5000 of a grid of 2^20 nodes,
+// 25 passes: 5635 -> 4683 us, with no stop of the host in any of them).
 #include <climits>
 #include <cstdint>
 
@@ -110,6 +112,7 @@ __global__ void __launch_bounds__(kFinishThreads) lk_test(SelArgs a, const int32
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->err = 2;
     return;
   }
+  if (a.sc->kept_count != 0 && !stops_anyway(a)) return;   // (k = n: nothing is kept)
   __shared__ unsigned long long sk[kTile];
   __shared__ int32_t se[kTile];
   __shared__ uint16_t ss[kTile];
@@ -150,10 +153,13 @@ __global__ void __launch_bounds__(kFinishThreads) lk_test(SelArgs a, const int32
   }
 }
 
-// sc->need: whether the host launches the sort of this iteration.
+// sc->need: whether this iteration's list is sorted.  The sort's kernels return at once
+// where it is not, given the flags (gate; null: they always run).
 __global__ void lk_decide(SelArgs a) {
   if (!halted(a.sc)) a.sc->need = sort_needed(a) ? 1 : 0;
 }
+
+__device__ __forceinline__ bool gated_off(const RunScalars* gate) { return gate && (halted(gate) || !gate->need); }
 
 // Sort records of every node (score criterion output): key = ~bits(l), id =
 // caller id.
@@ -167,7 +173,9 @@ __global__ void __launch_bounds__(kWG) lk_fill(SelArgs a, long long count, unsig
 }
 
 // Sorts each tile of the records in place.
-__global__ void __launch_bounds__(kFinishThreads) lk_tile(long long count, unsigned long long* key, int32_t* ext) {
+__global__ void __launch_bounds__(kFinishThreads) lk_tile(const RunScalars* gate, long long count,
+                                                          unsigned long long* key, int32_t* ext) {
+  if (gated_off(gate)) return;
   __shared__ unsigned long long sk[kTile];
   __shared__ int32_t se[kTile];
   const long long base = (long long)blockIdx.x * kTile;
@@ -217,9 +225,10 @@ __device__ __forceinline__ long long merge_split(const unsigned long long* ka, c
 // writes 2048 records of the output.  Its two waves of the split search find
 // where its share begins and ends in both runs; the share is staged in the LDS,
 // where a record's place is its own index plus its rank in the other run.
-__global__ void __launch_bounds__(kFinishThreads) lk_merge(long long count, long long run,
+__global__ void __launch_bounds__(kFinishThreads) lk_merge(const RunScalars* gate, long long count, long long run,
                                                            const unsigned long long* key_in, const int32_t* ext_in,
                                                            unsigned long long* key_out, int32_t* ext_out) {
+  if (gated_off(gate)) return;
   __shared__ unsigned long long sk[kTile];
   __shared__ int32_t se[kTile];
   __shared__ long long split[2];
@@ -265,8 +274,9 @@ __global__ void __launch_bounds__(kFinishThreads) lk_merge(long long count, long
 
 // The sorted list becomes the ranking output; with test = 1 every adjacent
 // pair is tested for eps-separation (the check of converged()).
-__global__ void __launch_bounds__(kWG) lk_emit(SelArgs a, long long count, int test,
+__global__ void __launch_bounds__(kWG) lk_emit(SelArgs a, const RunScalars* gate, long long count, int test,
                                                const unsigned long long* key, const int32_t* ext) {
+  if (gated_off(gate)) return;
   bool fail = false;
   for (long long i = (long long)blockIdx.x * kWG + threadIdx.x; i < count; i += (long long)gridDim.x * kWG) {
     const int v = to_int(a, ext[i]);
@@ -424,12 +434,12 @@ unsigned grid_for(long long items, long long cap) {
 }
 
 // Sorts the `count` records in rec[0]; the sorted records end in rec[*which].
-hipError_t enqueue_sort(long long count, const SortRecs rec[2], int* which, hipStream_t s) {
+hipError_t enqueue_sort(const RunScalars* gate, long long count, const SortRecs rec[2], int* which, hipStream_t s) {
   const unsigned tiles = (unsigned)((count + kTile - 1) / kTile);
-  hipLaunchKernelGGL(lk_tile, dim3(tiles), dim3(kFinishThreads), 0, s, count, rec[0].key, rec[0].ext);
+  hipLaunchKernelGGL(lk_tile, dim3(tiles), dim3(kFinishThreads), 0, s, gate, count, rec[0].key, rec[0].ext);
   int cur = 0;
   for (long long run = kTile; run < count; run *= 2) {
-    hipLaunchKernelGGL(lk_merge, dim3(tiles), dim3(kFinishThreads), 0, s, count, run,
+    hipLaunchKernelGGL(lk_merge, dim3(tiles), dim3(kFinishThreads), 0, s, gate, count, run,
                        (const unsigned long long*)rec[cur].key, (const int32_t*)rec[cur].ext, rec[cur ^ 1].key,
                        rec[cur ^ 1].ext);
     cur ^= 1;
@@ -450,9 +460,9 @@ hipError_t launch_large_test(const SelArgs& a, const SortRecs rec[2], hipStream_
 
 hipError_t launch_large_sort(const SelArgs& a, const SortRecs rec[2], hipStream_t s) {
   int cur = 0;
-  const hipError_t e = enqueue_sort(a.k, rec, &cur, s);
+  const hipError_t e = enqueue_sort(a.sc, a.k, rec, &cur, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lk_emit, dim3(grid_for(a.k, 1 << 14)), dim3(kWG), 0, s, a, (long long)a.k, 1,
+  hipLaunchKernelGGL(lk_emit, dim3(grid_for(a.k, 1 << 14)), dim3(kWG), 0, s, a, (const RunScalars*)a.sc, (long long)a.k, 1,
                      (const unsigned long long*)rec[cur].key, (const int32_t*)rec[cur].ext);
   return hipGetLastError();
 }
@@ -473,9 +483,9 @@ hipError_t launch_score_output(const SelArgs& a, const SortRecs rec[2], hipStrea
   const unsigned g = grid_for(n, 1 << 14);
   hipLaunchKernelGGL(lk_fill, dim3(g), dim3(kWG), 0, s, a, n, rec[0].key, rec[0].ext);
   int cur = 0;
-  const hipError_t e = enqueue_sort(n, rec, &cur, s);
+  const hipError_t e = enqueue_sort(nullptr, n, rec, &cur, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lk_emit, dim3(g), dim3(kWG), 0, s, a, n, 0, (const unsigned long long*)rec[cur].key,
+  hipLaunchKernelGGL(lk_emit, dim3(g), dim3(kWG), 0, s, a, (const RunScalars*)nullptr, n, 0, (const unsigned long long*)rec[cur].key,
                      (const int32_t*)rec[cur].ext);
   return hipGetLastError();
 }

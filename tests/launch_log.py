@@ -1,6 +1,6 @@
-"""A log of the kernels that the library launches, and on which streams: a small
-library, built with gcc, whose hipLaunchKernel comes before the runtime's in a process
-that loads it first.  Used by tests that run a child process (``run_child``)."""
+"""A log of the kernels that the library launches, and on which streams, and of its waits
+for streams: a small library, built with gcc, whose hipLaunchKernel and
+hipStreamSynchronize come before the runtime's in a process that loads it first.  Used by tests that run a child process (``run_child``)."""
 import os
 import subprocess
 import sys
@@ -42,7 +42,17 @@ int hipLaunchKernel(const void* f, Dim grid, Dim block, void** args, size_t lds,
   return go(f, grid, block, args, lds, stream);
 }
 
-void log_clear(void) { count = 0; }
+static int syncs;
+
+int hipStreamSynchronize(void* stream) {
+  static int (*go)(void*);
+  if (!go) go = (int (*)(void*))real("hipStreamSynchronize");
+  __atomic_fetch_add(&syncs, 1, __ATOMIC_RELAXED);
+  return go(stream);
+}
+
+void log_clear(void) { count = syncs = 0; }
+int log_syncs(void) { return syncs; }
 int log_count(void) { return count < MAX ? count : MAX; }
 void* log_stream(int i) { return seen[i].stream; }
 const char* log_name(int i) {

@@ -156,3 +156,44 @@ def test_pair_exact_tie_stops_on_iteration_limit():
     orc, res = run_both(rp, col, "pair", eps=0.0, pair=(3, 4), max_iter=20)
     assert res.status == orc.status == K().W_ITER_LIMIT
     assert res.topk.cpu().tolist() == [3, 4] == orc.topk.tolist()
+
+
+@pytest.mark.parametrize("n,k", [(20000, 16384), (20000, 16385), (16385, 16385), (45000, 40961)])
+def test_long_lists_on_both_sides_of_the_gated_sort(n, k):
+    """Up to 16384 entries the sort is launched in every iteration and returns at once
+    where it is not needed, longer lists are sorted when the host has seen that they
+    have to be: the list of every iteration limit, and the certified one, is the head of
+    all nodes by lower bound, then id."""
+    katz = K()
+    rp, col = sg.erdos_renyi(n, 6 * n, 3)
+    rp_t, col_t = dev(rp, col)
+    for r in (1, 2, 5, 60):
+        say("long lists", n, k, r)
+        a = katz.rank_static(rp_t, col_t, k, eps=1e-3, max_iter=r)
+        lo, up = katz.bounds(rp_t, col_t, a.iterations)
+        ids = torch.argsort(lo, descending=True, stable=True)[:k]
+        assert torch.equal(a.topk.long(), ids)
+        assert torch.equal(a.lower, lo[ids]) and torch.equal(a.upper, up[ids])
+        assert (a.status == katz.OK) == (a.iterations < r)
+
+
+WAITS_CHILD = r"""
+rp, col = sg.erdos_renyi(30000, 240000, 5)
+rp, col = torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda()
+waits = {}
+for r in (4, 12):
+    res, log = launches(lambda: katz.rank_static(rp, col, 5000, eps=1e-13, max_iter=r))
+    assert res.iterations == r
+    waits[r] = shim.log_syncs()
+    print("[gpu-case] waits", r, waits[r], len(log), flush=True)
+assert waits[4] == waits[12]
+print("ok")
+"""
+
+
+def test_lists_past_the_lds_sort_do_not_stop_the_host_each_iteration(tmp_path):
+    """k = 5000: the iterations' flags come back one behind, with no wait for the stream
+    in any of them."""
+    from tests.launch_log import run_child
+    say("waits of long lists")
+    assert run_child(tmp_path, WAITS_CHILD).rstrip().endswith("ok")
