@@ -1277,6 +1277,7 @@ __global__ void __launch_bounds__(kWG) sel_apply(SelArgs a, unsigned* block_prog
 // block_prog: sel_apply's words, cleared here.
 __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned* block_prog, int grid) {
   if (stopped(a.sc)) return;
+  const bool many = a.sc->cand_count[0] > kSmallCand;   // (read early: nothing waits for it at the end)
   __shared__ int s_prog;
   if (threadIdx.x == 0) s_prog = 0;
   __syncthreads();
@@ -1367,7 +1368,6 @@ __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned*
     sc->iterations = a.b.r;
     sc->cur = a.act_out_idx;
     sc->m = k + kept;
-    const bool many = sc->cand_count[0] > kSmallCand;
     sc->many = many ? 1 : 0;
     sc->top_count = 0;
     sc->kept_count = 0;
