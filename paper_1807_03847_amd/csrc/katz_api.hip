@@ -1092,9 +1092,9 @@ void poll_pause(long long spins) {
   else __builtin_ia32_pause();
 }
 
-// Waits until pass `seq` has published its flags, polling their word; when the
-// stream has drained without them (an error made the pass return early), reads
-// the device flags.
+// Waits until pass `seq` has published its flags, polling their word.  Every pass that
+// the host waits for does, a failed one too, so that other work on the stream cannot
+// hold the call up; should the stream drain without them, reads the device flags.
 int wait_flags(HostSync& hs, unsigned seq, const RunScalars* dev, PassFlags* out, hipStream_t s) {
   const unsigned long long* word = &hs.flags[seq & 1];
   for (long long spins = 1;; ++spins) {

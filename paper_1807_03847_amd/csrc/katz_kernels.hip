@@ -1276,7 +1276,11 @@ __global__ void __launch_bounds__(kWG) sel_apply(SelArgs a, unsigned* block_prog
 // every adjacent pair for eps-separation; decide whether the run stops.
 // block_prog: sel_apply's words, cleared here.
 __global__ void __launch_bounds__(kFinishThreads) sel_check(SelArgs a, unsigned* block_prog, int grid) {
-  if (stopped(a.sc)) return;
+  if (stopped(a.sc)) {
+    // An error of this pass's walk step or filter (a bad column id).
+    if (a.sc->err && threadIdx.x == 0) publish(a.pub, a.sc->err, -1, 0);
+    return;
+  }
   const bool many = a.sc->cand_count[0] > kSmallCand;   // (read early: nothing waits for it at the end)
   __shared__ int s_prog;
   if (threadIdx.x == 0) s_prog = 0;

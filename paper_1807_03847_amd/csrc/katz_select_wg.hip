@@ -448,7 +448,10 @@ __device__ __forceinline__ bool select_mid(const GraphSel& gs, const Publish& pu
 template <bool F32>
 __device__ __forceinline__ void select_graph(const GraphSel& gs, int r, const WalkMax* walk, const Publish& pub) {
   RunScalars* sc = gs.sc;
-  if (sc->done || sc->err) return;
+  if (sc->done || sc->err) {
+    if (sc->err && threadIdx.x == 0) publish(pub, sc->err, -1, 0);   // of this pass's walk step
+    return;
+  }
   if (walk) {
     // Walk step 2 of a renumbered run found a bad column id.
     if (sc->col_err) {

@@ -595,3 +595,47 @@ def test_selection_time_with_poor_floors():
     walk = ms[8]["walk_step_ms"] + ms[8]["renumber_step_ms"]
     say("selection and walk of seven passes, ms a call", round(select / 3, 3), round(walk / 3, 3))
     assert select < 3 * walk
+
+
+@pytest.mark.parametrize("n,k", [(60000, 20), (3000, 20)])
+def test_errors_come_back_from_a_busy_stream(n, k):
+    """A bad column id, found in walk step 2, is reported while another thread keeps the
+    stream busy: the failed pass tells the host, which does not wait for the stream to
+    run dry."""
+    import threading
+    import time
+    katz = K()
+    rp, col = sg.erdos_renyi(n, 8 * n, 3)
+    bad = col.copy()
+    bad[len(bad) // 2] = n
+    rp_t, bad_t = dev(rp, bad)
+    with pytest.raises(katz.KatzError):          # the workspace is there
+        katz.rank_static(rp_t, bad_t, k, eps=1e-6, flags=katz.FLAG_REORDER)
+    torch.cuda.synchronize()
+    done, started = threading.Event(), threading.Event()
+    end = [0.0]
+
+    def keep_busy():
+        t0 = time.perf_counter()
+        last = None
+        while time.perf_counter() - t0 < 3.0 and not done.is_set():
+            torch.cuda._sleep(2_000_000)         # about a millisecond
+            e = torch.cuda.Event()
+            e.record()
+            if last is not None:
+                last.synchronize()
+            last = e
+            started.set()
+        end[0] = time.perf_counter() - t0
+
+    say("error on a busy stream", n)
+    busy = threading.Thread(target=keep_busy)
+    busy.start()
+    started.wait()
+    with pytest.raises(katz.KatzError) as err:
+        katz.rank_static(rp_t, bad_t, k, eps=1e-6, flags=katz.FLAG_REORDER)
+    done.set()
+    busy.join()
+    say("reported after", round(end[0], 3), "s")
+    assert err.value.code == katz.E_CSR
+    assert end[0] < 1.5
