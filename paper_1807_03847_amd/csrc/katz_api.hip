@@ -953,6 +953,11 @@ Select select_form(const Run& run, long long m) {
   return m <= kSmallActive ? SEL_ONE : SEL_WIDE;
 }
 
+// The re-check of an update, whose list has no floor: one workgroup up to this many nodes.
+// An update that only re-checks, by histograms and by one workgroup, FP64, k = 50:
+// 16000 nodes 159 and 144 us, 30000 130 and 175, 60000 150 and 255.
+constexpr long long kCheckOne = 1 << 14;
+
 // Until a filtered pass's candidates have been counted, sets above this size go through
 // sel_refine, which costs 4 us where it has nothing to do: R-MAT of 150 K nodes would
 // lose 9 us of 330 to it, and up to here one workgroup needs 0.5 ms for a whole set.
@@ -1170,9 +1175,10 @@ int iterate(Run& run, HostSync& hs, int r_next, bool check_first, hipStream_t s,
     // enqueued before that is known.
     const unsigned seq = ++hs.seq;
     run.pub = Publish{&hs.flags[seq & 1], seq};
-    at[0] = PassAt{r - 1, run.cur ^ 1, SEL_WIDE};
+    const Select sel = m_known <= kCheckOne ? SEL_ONE : SEL_WIDE;
+    at[0] = PassAt{r - 1, run.cur ^ 1, sel};
     run.walk_max = WalkMax{nullptr, 0};
-    KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, select_form(run, m_known), m_known));
+    KATZ_TRY(enqueue_select(run, hs, r - 1, s, T, sel, m_known));
     KATZ_TRY(wait_flags(hs, seq, run.w->sc, &last, s));
     stopped = last.stopped();
     m_known = last.m;

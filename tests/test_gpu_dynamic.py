@@ -503,3 +503,29 @@ def test_small_updates_leave_the_whole_graph_unbinned(tmp_path):
     say("bins of small updates")
     out = run_child(tmp_path, BINS_CHILD)
     assert out.count("small") >= 3
+
+
+RECHECK_CHILD = r"""
+for n, wide in ((16384, 0), (16390, 1), (60000, 1)):
+    rp, col = sg.erdos_renyi(n, 3 * n, 1)
+    rp, col = torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda()
+    # eps = 1 keeps every node, so the re-check is over all of them.
+    state, res = katz.create_state(rp, col, 50, eps=1.0, max_iter=2, precision=sys.argv[2])
+    again, log = launches(lambda: state.update())
+    names = [name for name, _ in log]
+    print("[gpu-case] re-check", n, sum("sel_hist0" in m for m in names), sum("select_wg" in m for m in names), flush=True)
+    assert sum("sel_hist0" in m for m in names) == wide and sum("select_wg" in m for m in names) == 1 - wide
+    assert torch.equal(res.topk, again.topk) and torch.equal(res.lower, again.lower)
+    assert (res.active_final, res.status) == (again.active_final, again.status)
+    state.free()
+print("ok")
+"""
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_large_active_sets_are_rechecked_by_the_whole_device(tmp_path, precision):
+    """The selection of an update's re-check: one workgroup up to 16384 active nodes,
+    the device-wide one above, with the same result."""
+    from tests.launch_log import run_child
+    say("re-check of large sets", precision)
+    assert run_child(tmp_path, RECHECK_CHILD, precision).rstrip().endswith("ok")
